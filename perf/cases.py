@@ -145,16 +145,21 @@ class _Maker:
             x = x * torch.rsqrt(chi2 / nu)
         return x.clamp(-synth.FP16_MAX, synth.FP16_MAX).half()
 
-    def layer(self, d_in, d_out, rank, ws, src=0, dst=1, ln=False, lora_std=0.02, b3=False):
+    def latent(self, d_in, d_out, rank, ln=False, lora_std=0.02):
+        """One linear before it is ternarised: W, (A, B, alpha) or None, LayerNorm parameters."""
         W = self.normal(d_out, d_in) * (1.5 / math.sqrt(d_in))
-        A = B = alpha = None
+        low = None
         if rank:
-            A = (self.normal(rank, d_in) * lora_std).half()
-            B = (self.normal(d_out, rank) * lora_std).half()
-            alpha = self.normal(d_out).half()
+            low = ((self.normal(rank, d_in) * lora_std).half(), (self.normal(d_out, rank) * lora_std).half(),
+                   self.normal(d_out).half())
         norm = {}
         if ln:
             norm = {"ln_gamma": 1.0 + 0.25 * self.normal(d_in), "ln_beta": 0.2 * self.normal(d_in)}
+        return W, low, norm
+
+    def layer(self, d_in, d_out, rank, ws, src=0, dst=1, ln=False, lora_std=0.02, b3=False):
+        W, low, norm = self.latent(d_in, d_out, rank, ln, lora_std)
+        A, B, alpha = low or (None, None, None)
         if b3:
             packed, s_w = hb.hgf_quantize_pack_weights_b3(W, ws)
             return hb.Layer(packed, s_w, d_out, d_in, A, B, alpha)
@@ -356,3 +361,105 @@ def tolerance(case):
     if kind == "attention":
         return {"rel": 1e-4, "max": 4e-3}
     return {"rel": 6e-4, "max": 5e-3}
+
+
+# ------------------------------------------------------------------------------------- the same in 64 bits
+
+
+def _scale_of(W):
+    return W.double().abs().mean().clamp_min(1e-5).float()
+
+
+def _norm64(x, norm):
+    """The row that is quantised: LayerNorm by its definition (fp64 reductions, fp32 elementwise)."""
+    if not norm:
+        return x.float()
+    mean = x.double().mean(1, keepdim=True)
+    var = ((x.double() - mean) ** 2).mean(1, keepdim=True)
+    return ((x.float() - mean.float()) * (1.0 / torch.sqrt(var + 1e-5)).float()) * norm["ln_gamma"] + norm["ln_beta"]
+
+
+def _linear64(x, latent):
+    """fp64 outputs of one linear for fp16 tokens: the codes are whole numbers that the definition
+    fixes (fp32 scale, round half to even), everything behind them is in 64 bits."""
+    W, low, norm = latent
+    s_w = _scale_of(W)
+    T = torch.round(W * (1.0 / s_w)).clamp(-1, 1).double()
+    v = _norm64(x, norm)
+    amax = v.abs().amax(1, keepdim=True).clamp_min(1e-5)
+    codes = torch.round(v * (127.0 / amax)).clamp(-127, 127)
+    y = (codes.double() @ T.t()) * (amax.double() / 127.0) * s_w.double()
+    if low:
+        A, B, alpha = (t.double() for t in low)
+        y += torch.tanh(alpha) * (torch.nn.functional.silu(x.double() @ A.t()) @ B.t())
+    return y
+
+
+def _attention64(q, k, v, lens, lam):
+    """[B, H, d_h] fp64 of the differential attention step; q [B, 2H, d_h], caches [B, L, heads, d_h]."""
+    lam = float(torch.tensor(lam, dtype=torch.float32))
+    H = v.shape[2]
+    out = []
+    for b, n in enumerate(lens):
+        s = (k[b, :n].double() * q[b].double()).sum(-1) / math.sqrt(q.shape[2])
+        p = torch.softmax(s, 0)
+        out.append(0.5 * ((p[:, :H] - lam * p[:, H:]).unsqueeze(-1) * v[b, :n].double()).sum(0))
+    return torch.stack(out)
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, from torch in 64 bits: the tensors are drawn in the order
+    of prepare(), results that another entry point reads are rounded to fp16 as its interface says,
+    and the outputs themselves are not rounded."""
+    mk, kind = _Maker(seed), case["kind"]
+    if kind == "linear":
+        M, K, N, r = case["tokens"], case["d_in"], case["d_out"], case["rank"]
+        lat = mk.latent(K, N, r, case["ln"])
+        return _linear64(mk.activations(case["act"], M, K), lat)
+    if kind == "stack":
+        c, M = synth.CONFIGS[case["cfg"]], case["tokens"]
+        wiring, inputs = _wiring(case)
+        slots = {s: mk.activations(c.act, M, wiring[0][0].d_in) for s in inputs}
+        outs = []
+        for i, (p, src, dst) in enumerate(wiring):
+            if i % len(c.projections) == 0:
+                outs.append([])
+            y = _linear64(slots[src], mk.latent(p.d_in, p.d_out, c.rank, case["ln"], c.lora_std))
+            slots[dst] = y.half()
+            outs[-1].append(y.flatten())
+        return [torch.cat(b) for b in outs]
+    if kind == "mlp":
+        M, d, ffn, r = case["tokens"], case["d"], case["ffn"], case["rank"]
+        outs = []
+        for _ in range(case["blocks"]):
+            x = mk.activations("student_t3", M, d)
+            z = torch.nn.functional.silu(_linear64(x, mk.latent(d, ffn, r))) * _linear64(x, mk.latent(d, ffn, r))
+            outs += [z, _linear64(z.half(), mk.latent(ffn, d, r))]
+        return outs
+    if kind == "block":
+        B, L, H, d, hid, r = (case[k] for k in ("sequences", "context", "heads", "d", "hidden", "rank"))
+        dh = d // (2 * H)
+        lens = _lengths(case)
+        x = mk.activations("student_t4", B, d)
+        q, k, v = (_linear64(x, mk.latent(d, n, r, True)) for n in (d, d, d // 2))
+        o, gate, up, down = (mk.latent(*shape) for shape in ((d // 2, d, 0), (d, hid, r), (d, hid, r), (hid, d, r)))
+        kc, vc = mk.normal(B, L, 2 * H, dh).half(), mk.normal(B, L, H, dh).half()
+        for b, n in enumerate(lens):
+            kc[b, n - 1], vc[b, n - 1] = k[b].half().view(2 * H, dh), v[b].half().view(H, dh)
+        a = _attention64(q.half().view(B, 2 * H, dh), kc, vc, lens, 0.8).half().view(B, H * dh)
+        x1 = (x.double() + _linear64(a, o)).half()
+        z = (torch.nn.functional.silu(_linear64(x1, gate)) * _linear64(x1, up)).half()
+        return {"out": x1.double() + _linear64(z, down), "k": k, "v": v}
+    if kind == "attention":
+        B, L, H, dh = (case[k] for k in ("sequences", "context", "heads", "d_h"))
+        q, k, v = mk.normal(B, 2 * H, dh).half(), mk.normal(B, L, 2 * H, dh).half(), mk.normal(B, L, H, dh).half()
+        return _attention64(q, k, v, _lengths(case), 0.8)
+    if kind == "b3":
+        M, K, N, r = case["tokens"], case["d_in"], case["d_out"], case["rank"]
+        outs = []
+        for _ in range(case["layers"]):
+            lat = mk.latent(K, N, r)
+            outs.append(_linear64(mk.activations("student_t3", M, K), lat))
+        return outs
+    W = mk.normal(case["d_out"], case["d_in"]) * (1.5 / math.sqrt(case["d_in"]))
+    return (None, W.double().abs().mean().clamp_min(1e-5).view(1))     # (the codes: whole bytes, no rounding)
