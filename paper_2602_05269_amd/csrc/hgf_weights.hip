@@ -11,38 +11,54 @@ namespace hgf {
 
 namespace {
 
+// Sum over the workgroup (a multiple of 64 threads, at most 1024) in a fixed order: a butterfly
+// inside each wavefront, then the wavefronts' sums one after the other.  Valid in thread 0.
 __device__ inline double block_sum_f64(double v, double *sh)
 {
-    const int t = threadIdx.x;
-    sh[t] = v;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (t < s) sh[t] += sh[t + s];
-        __syncthreads();
-    }
-    return sh[0];
+    double s = 0.0;
+    if (threadIdx.x == 0)
+        for (int i = 0; i < (int)blockDim.x / 64; ++i) s += sh[i];
+    return s;
 }
 
-__global__ __launch_bounds__(256) void wsum_partial_kernel(const float *__restrict__ W, size_t n,
+// |W| summed over one contiguous chunk per workgroup, a multiple of four elements long.  Bound by
+// HBM: eight independent 16-byte requests per thread and round, where one 4-byte load per dependent
+// add reached 2.8 TB/s.
+__global__ __launch_bounds__(256) void wsum_partial_kernel(const float *__restrict__ W, size_t n, size_t chunk,
                                                            double *__restrict__ partials)
 {
-    __shared__ double sh[256];
-    const size_t chunk = (n + gridDim.x - 1) / gridDim.x;
+    __shared__ double sh[4];
+    constexpr int UN = 8;
     const size_t lo = chunk * blockIdx.x;
     const size_t hi = lo + chunk < n ? lo + chunk : n;
-    double s = 0.0;
-    for (size_t i = lo + threadIdx.x; i < hi; i += blockDim.x) s += fabs((double)W[i]);
-    s = block_sum_f64(s, sh);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
+    const size_t len = lo < hi ? hi - lo : 0;                 // (a chunk stays below 2^31 bytes: n <= HGF_MAX_DIM^2)
+    const unsigned whole = (unsigned)(len / 4);               // 16-byte pieces; beyond them the requests read as zero
+    const rsrc_t r = make_rsrc(W + (len ? lo : 0), whole * 16u);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (unsigned i = threadIdx.x; i < whole; i += 256 * UN) {
+        v4f v[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) v[u] = __builtin_bit_cast(v4f, buf_load16(r, (i + u * 256) * 16u));
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += fabs((double)v[u][e]);
+    }
+    double t = (s[0] + s[1]) + (s[2] + s[3]);
+    if (threadIdx.x < (unsigned)(len % 4)) t += fabs((double)W[lo + whole * 4 + threadIdx.x]);
+    t = block_sum_f64(t, sh);
+    if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-__global__ __launch_bounds__(256) void wsum_final_kernel(const double *__restrict__ partials, int nparts,
-                                                         size_t n, float *__restrict__ s_w)
+__global__ __launch_bounds__(kWsumBlocks) void wsum_final_kernel(const double *__restrict__ partials, size_t n,
+                                                                 float *__restrict__ s_w)
 {
-    __shared__ double sh[256];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < nparts; i += blockDim.x) s += partials[i];
-    s = block_sum_f64(s, sh);
+    __shared__ double sh[kWsumBlocks / 64];
+    const double s = block_sum_f64(partials[threadIdx.x], sh);
     if (threadIdx.x == 0) {
         float g = (float)(s / (double)n);
         *s_w = g < 1e-5f ? 1e-5f : g;
@@ -68,28 +84,62 @@ __device__ inline void word_position(size_t idx, int KT, int &row, int &kbase)
     kbase = kt * kTileCols + t * 32 + (l >> 5) * 16;
 }
 
-// One thread per packed 32-bit word: 16 codes of one row, 16 consecutive columns.
+// One wavefront per packed tile.  Bound by HBM (16 KiB read, 1 KiB written): every request takes two
+// whole 512-byte row pieces, all sixteen are in flight together, and the tile leaves as one KiB.
+// (One thread per packed word read 64 bytes per lane at a stride of a row and stored single words:
+// 147 us for 11008 x 4096; sum and packing together 233.5 us then, 67.0 us now, both passes at about
+// 5.8 TB/s because the second finds much of W in the 256 MB Infinity Cache.)
+// Lane l holds columns 4c .. 4c+3 (c = l % 32) of row 2i + l/32: codes b = 0..3 of shift s = c % 4 in
+// word t = c / 8, k-half (c / 4) % 2, so the four lanes of a quad share a word and OR their parts.
 __global__ __launch_bounds__(256) void pack_kernel(const float *__restrict__ W, int N, int K, int KT,
                                                    const float *__restrict__ s_w,
-                                                   uint32_t *__restrict__ packed, size_t nwords)
+                                                   uint32_t *__restrict__ packed, size_t ntiles)
 {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nwords) return;
-    const float inv = 1.0f / *s_w;
-    int row, kbase;
-    word_position(idx, KT, row, kbase);
-    uint32_t word = 0;
+    __shared__ __attribute__((aligned(16))) uint32_t words[4][256];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const size_t tile = (size_t)blockIdx.x * 4 + w;
+    if (tile >= ntiles) return;
+    const int rb = (int)(tile / KT), kt = (int)(tile % KT);
+    const int row0 = rb * kTileRows, rows = min(kTileRows, N - row0);
+    const int c = l & 31, k0 = kt * kTileCols + 4 * c;
+    // the rows of the block behind one descriptor (at most 32 rows of HGF_MAX_DIM floats); rows start
+    // at any multiple of four bytes, which is all a 16-byte request asks for
+    const rsrc_t r = make_rsrc(W + (size_t)row0 * K, (unsigned)rows * K * 4u);
+    v4f v[16];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int i = 0; i < 16; ++i) {
+        const int row = 2 * i + (l >> 5);
+        v[i] = __builtin_bit_cast(v4f, buf_load16(r, ((unsigned)row * K + k0) * 4u, row < rows && k0 + 3 < K));
+    }
+    if (K % 4 != 0 && kt == KT - 1) {              // the lane that holds a row's last one to three columns
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int k = kbase + 4 * s + b;
-            uint32_t c = 1;                                    // padding decodes to 0
-            if (row < N && k < K) c = ternary_code(W[(size_t)row * K + k], inv);
-            word |= c << (8 * b + 2 * s);
+        for (int i = 0; i < 16; ++i) {
+            const int row = 2 * i + (l >> 5);
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                const bool tail = row < rows && k0 + 3 >= K && k0 + e < K;
+                const float t = __builtin_bit_cast(float, buf_load4(r, ((unsigned)row * K + k0 + e) * 4u, tail));
+                v[i][e] = tail ? t : v[i][e];
+            }
         }
     }
-    packed[idx] = word;
+    const float inv = 1.0f / *s_w;
+    const int word = ((c >> 2) & 1) * kTileRows * 4 + (c >> 3);      // + 4 * row
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int row = 2 * i + (l >> 5);
+        uint32_t part = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)                // padding rows and columns decode to 0
+            part |= ((row < rows && k0 + e < K) ? ternary_code(v[i][e], inv) : 1u) << (8 * e);
+        part <<= 2 * (c & 3);
+        part |= (uint32_t)dpp_move<0xB1>((int)part);
+        part |= (uint32_t)dpp_move<0x4E>((int)part);
+        if ((c & 3) == 0) words[w][word + 4 * row] = part;
+    }
+    // (the wavefront's own words: no other wavefront reads or writes them)
+    __builtin_amdgcn_wave_barrier();
+    reinterpret_cast<v4u *>(packed)[tile * 64 + l] = reinterpret_cast<const v4u *>(words[w])[l];
 }
 
 // One thread per packed word, writing its 16 values back as int8 -1/0/+1.
@@ -138,17 +188,18 @@ hipError_t launch_zero_words(void *p, size_t n, hipStream_t st)
 
 hipError_t launch_wsum(const float *W, size_t n, double *partials, float *s_w_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(wsum_partial_kernel, dim3(kWsumBlocks), dim3(256), 0, st, W, n, partials);
-    hipLaunchKernelGGL(wsum_final_kernel, dim3(1), dim3(256), 0, st, partials, kWsumBlocks, n, s_w_out);
+    const size_t chunk = ((n + kWsumBlocks - 1) / kWsumBlocks + 3) / 4 * 4;
+    hipLaunchKernelGGL(wsum_partial_kernel, dim3(kWsumBlocks), dim3(256), 0, st, W, n, chunk, partials);
+    hipLaunchKernelGGL(wsum_final_kernel, dim3(1), dim3(kWsumBlocks), 0, st, partials, n, s_w_out);
     return hipGetLastError();
 }
 
 hipError_t launch_pack(const float *W, int N, int K, const float *s_w, uint32_t *packed, hipStream_t st)
 {
     const int KT = round_up(K, kTileCols) / kTileCols;
-    const size_t nwords = (size_t)(round_up(N, kTileRows) / kTileRows) * KT * 256;
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((nwords + 255) / 256)), dim3(256), 0, st, W, N, K, KT, s_w,
-                       packed, nwords);
+    const size_t ntiles = (size_t)(round_up(N, kTileRows) / kTileRows) * KT;
+    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)((ntiles + 3) / 4)), dim3(256), 0, st, W, N, K, KT, s_w, packed,
+                       ntiles);
     return hipGetLastError();
 }
 

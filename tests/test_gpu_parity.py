@@ -46,6 +46,22 @@ def test_pack_unpack_matches_oracle_ternariser(N, K, ws):
     g.check_weights()
 
 
+@pytest.mark.parametrize("N,K", [(1, 1), (31, 127), (33, 129), (32, 130), (65, 259), (3, 1365)])
+def test_pack_edges_of_tiles_and_odd_addresses(N, K, ws):
+    # edges of the 32 x 128 tiles, one to three columns past the last whole 16 bytes, and latents that
+    # start at any multiple of four bytes; padding rows and columns hold code 1 (bytes of 0x55)
+    W = np.random.default_rng(N * 7919 + K).standard_normal((N, K)).astype(np.float32)
+    T, s_w = orc.ternarize(W)
+    for shift in range(4):
+        flat = torch.zeros(N * K + 4, dtype=torch.float32, device="cuda")
+        flat[shift:shift + N * K] = dev(W).flatten()
+        packed, s = hb.hgf_quantize_pack_weights(flat[shift:shift + N * K].view(N, K), ws)
+        assert s.item() == float(s_w)
+        assert np.array_equal(hb.hgf_unpack_weights(packed, N, K).cpu().numpy(), T)
+        padded = hb.hgf_unpack_weights(packed, -(-N // 32) * 32, -(-K // 128) * 128).cpu().numpy()
+        assert not padded[N:].any() and not padded[:, K:].any()
+
+
 def test_pack_constructed_ties_and_zero_matrix(ws):
     W = np.array([[0.5, -0.5, 1.5, -1.5], [0.25, -0.25, 1.75, -1.75]], dtype=np.float32)
     packed, s_w = hb.hgf_quantize_pack_weights(dev(W), ws)
