@@ -11,13 +11,15 @@
 // a step streams the K and V caches once: 6 len d_h bytes per head, nothing else of size.
 // That is bandwidth-bound work with no reuse, so there are no matrix instructions here:
 // coalesced 16-byte loads, dot products in the vector ALU, cross-lane reductions.
-//   pass 1 (grid: chunks of 256 positions x heads x sequences): a workgroup loads its chunk
-//     of K1, K2 and V rows of one head in one burst, forms both branches' scores, their chunk
-//     maximum and exponentials (LDS), and both exp-weighted sums of the V rows, which it reads
-//     once for the two; it writes (max, sum, weighted V) per branch to the workspace;
+//   pass 1 (grid: heads x chunks of 256 positions x sequences): a workgroup loads its chunk
+//     of K1, K2 and V rows of one head in one burst, forms both branches' scores, maxima and
+//     exponentials, and both exp-weighted sums of the V rows, which it reads once for the two;
+//     it writes (max, sum, weighted V) per branch to the workspace;
 //   pass 2 (grid: heads x sequences): merges the chunks (rescaling by exp(max_chunk - max)),
 //     normalises, forms (a1 - lambda a2) * 0.5 and stores fp16.
 #include "hgf_internal.h"
+
+#include <type_traits>
 
 namespace hgf {
 
@@ -36,35 +38,48 @@ struct AttnParams {
     float lambda, scale;
 };
 
+// Sum over aligned groups of G lanes (G a power of two up to 16), in every lane of the group.
+template <int G>
+__device__ inline float group_sum(float v)
+{
+    auto mv = [](float x, auto ctrl) {
+        return __builtin_bit_cast(float, dpp_move<decltype(ctrl)::value>(__builtin_bit_cast(int, x)));
+    };
+    if (G > 1) v += mv(v, std::integral_constant<int, 0xB1>{});     // quad_perm [1,0,3,2]
+    if (G > 2) v += mv(v, std::integral_constant<int, 0x4E>{});     // quad_perm [2,3,0,1]
+    if (G > 4) v += mv(v, std::integral_constant<int, 0x141>{});    // row_half_mirror
+    if (G > 8) v += mv(v, std::integral_constant<int, 0x140>{});    // row_mirror
+    return v;
+}
+
 // V8: 16-byte pieces of a head row (d_h / 8).  Lane (ps = l / V8, pc = l % V8) takes piece pc of
 // the positions ps, ps + P, ... of its wavefront's 64 positions (P = 64 / V8 per instruction).
+// Bound by HBM.  Each wavefront is a softmax of its own over its 64 positions, entirely in registers:
+// K1, K2 and V are requested in one burst, and the only meeting of the workgroup is the merge of its
+// four (max, sum, weighted V) at the end.  Heads are the fastest grid dimension, so the workgroups that
+// run together read whole cache rows rather than one 128-byte head row out of every 8 KiB.  With the
+// merge below, 32 heads of 64 over 8 caches of up to 4096 positions (217 MB): 67.4 us before, with the
+// chunks fastest and four barriers per branch, 45.2 us = 4.8 TB/s now.
 template <int V8>
 __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
 {
-    constexpr int P = 64 / V8, IT = 64 / P;
-    __shared__ float sc[2][kAttnChunk];
-    __shared__ float red[2][4];
-    __shared__ float accs[4][2][V8 * 8];
+    constexpr int P = 64 / V8, IT = 64 / P, d_h = V8 * 8;
+    __shared__ float accs[4][2][d_h];
+    __shared__ float mx_s[4][2], sum_s[4][2];
     const int tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int chunk = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int h = blockIdx.x, chunk = blockIdx.y, b = blockIdx.z;
     const int len = min(max(p.lens[b], 0), p.L_max);
-    const int d_h = V8 * 8;
-    float *out = p.part + ((((size_t)b * p.n_heads + h) * p.chunks + chunk) * 2) * (d_h + 2);
     const int pos0 = chunk * kAttnChunk;
-    if (pos0 >= len) {                  // nothing cached here: an empty part (exp(-inf) weight)
-        if (tid < 2) {
-            out[tid * (d_h + 2)] = -INFINITY;
-            out[tid * (d_h + 2) + 1] = 0.f;
-        }
-        for (int e = tid; e < 2 * d_h; e += 256) out[(e / d_h) * (d_h + 2) + 2 + e % d_h] = 0.f;
-        return;
-    }
+    if (pos0 >= len) return;            // nothing cached here (the merge reads only the chunks below len)
     const int ps = l / V8, pc = l % V8;
     const size_t krow = (size_t)2 * p.n_heads * d_h, vrow = (size_t)p.n_heads * d_h;
     const rsrc_t kr = make_rsrc(p.k + (size_t)b * p.L_max * krow, (unsigned)((size_t)len * krow * 2));
     const rsrc_t vr = make_rsrc(p.v + (size_t)b * p.L_max * vrow, (unsigned)((size_t)len * vrow * 2));
-    // the burst: every K1 and K2 piece of this lane (rows past len lie beyond the descriptors: zeros)
+    const _Float16 *qb = p.q + (size_t)b * krow;
+    const v8h q1 = *reinterpret_cast<const v8h *>(qb + (size_t)h * d_h + pc * 8);
+    const v8h q2 = *reinterpret_cast<const v8h *>(qb + (size_t)(p.n_heads + h) * d_h + pc * 8);
+    // the burst (rows past len lie beyond the descriptors: zeros)
     v4u k1[IT], k2[IT], vv[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
@@ -72,124 +87,151 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
         k1[it] = buf_load16_stream(kr, (unsigned)((pos * krow + (size_t)h * d_h + pc * 8) * 2));
         k2[it] = buf_load16_stream(kr, (unsigned)((pos * krow + (size_t)(p.n_heads + h) * d_h + pc * 8) * 2));
     }
-    const _Float16 *qb = p.q + (size_t)b * krow;
-    const v8h q1 = *reinterpret_cast<const v8h *>(qb + (size_t)h * d_h + pc * 8);
-    const v8h q2 = *reinterpret_cast<const v8h *>(qb + (size_t)(p.n_heads + h) * d_h + pc * 8);
-
-    // ---- scores of both branches
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const v8h a = __builtin_bit_cast(v8h, k1[it]), c = __builtin_bit_cast(v8h, k2[it]);
-        float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            s1 += (float)q1[e] * (float)a[e];
-            s2 += (float)q2[e] * (float)c[e];
-        }
-#pragma unroll
-        for (int o = 1; o < V8; o <<= 1) {
-            s1 += __shfl_xor(s1, o, 64);
-            s2 += __shfl_xor(s2, o, 64);
-        }
-        const int idx = w * 64 + it * P + ps;
-        if (pc == 0) {
-            const bool valid = pos0 + idx < len;
-            sc[0][idx] = valid ? s1 * p.scale : -INFINITY;
-            sc[1][idx] = valid ? s2 * p.scale : -INFINITY;
-        }
-    }
-    // the V rows are requested now (the K registers are free again) and arrive during the softmax
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const unsigned pos = (unsigned)(pos0 + w * 64 + it * P + ps);
         vv[it] = buf_load16_stream(vr, (unsigned)((pos * vrow + (size_t)h * d_h + pc * 8) * 2));
     }
-    __syncthreads();
-    // ---- chunk maximum, exponentials and their sum: one position per thread
-    float m[2], lsum[2];
-#pragma unroll
-    for (int br = 0; br < 2; ++br) {
-        const float s = sc[br][tid];
-        float mx = wave_max(s);
-        if (l == 0) red[br][w] = mx;
-        __syncthreads();
-        mx = fmaxf(fmaxf(red[br][0], red[br][1]), fmaxf(red[br][2], red[br][3]));   // finite: position pos0 is valid
-        const float e = expf(s - mx);
-        sc[br][tid] = e;
-        float sum = e;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-        __syncthreads();
-        if (l == 0) red[br][w] = sum;
-        __syncthreads();
-        m[br] = mx;
-        lsum[br] = (red[br][0] + red[br][1]) + (red[br][2] + red[br][3]);
-        __syncthreads();
-    }
-    // ---- both branches' weighted sums of the V rows (read once)
-    float a1[8], a2[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) a1[e] = a2[e] = 0.f;
+    // ---- scores of both branches (each in all lanes of its position)
+    float s[2][IT], mx[2] = {-INFINITY, -INFINITY}, sum[2] = {0.f, 0.f};
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const int idx = w * 64 + it * P + ps;
-        const float p1 = sc[0][idx], p2 = sc[1][idx];
+        const v8h x1 = __builtin_bit_cast(v8h, k1[it]), x2 = __builtin_bit_cast(v8h, k2[it]);
+        float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            s1 += (float)q1[e] * (float)x1[e];
+            s2 += (float)q2[e] * (float)x2[e];
+        }
+        const bool valid = pos0 + w * 64 + it * P + ps < len;
+        s[0][it] = valid ? group_sum<V8>(s1) * p.scale : -INFINITY;
+        s[1][it] = valid ? group_sum<V8>(s2) * p.scale : -INFINITY;
+        mx[0] = fmaxf(mx[0], s[0][it]);
+        mx[1] = fmaxf(mx[1], s[1][it]);
+    }
+#pragma unroll
+    for (int br = 0; br < 2; ++br) {
+        mx[br] = wave_max(mx[br]);
+        const float m = mx[br] == -INFINITY ? 0.f : mx[br];      // (no position here: every weight is exp(-inf) = 0)
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            s[br][it] = expf(s[br][it] - m);
+            sum[br] += s[br][it];
+        }
+#pragma unroll
+        for (int o = V8; o < 64; o <<= 1) sum[br] += __shfl_xor(sum[br], o, 64);
+    }
+    // ---- both branches' weighted sums of the V rows (read once)
+    float a[2][8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) a[0][e] = a[1][e] = 0.f;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
         const v8h x = __builtin_bit_cast(v8h, vv[it]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            a1[e] += p1 * (float)x[e];
-            a2[e] += p2 * (float)x[e];
+            a[0][e] += s[0][it] * (float)x[e];
+            a[1][e] += s[1][it] * (float)x[e];
         }
     }
 #pragma unroll
     for (int o = V8; o < 64; o <<= 1) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            a1[e] += __shfl_xor(a1[e], o, 64);
-            a2[e] += __shfl_xor(a2[e], o, 64);
+            a[0][e] += __shfl_xor(a[0][e], o, 64);
+            a[1][e] += __shfl_xor(a[1][e], o, 64);
         }
     }
     if (ps == 0) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            accs[w][0][pc * 8 + e] = a1[e];
-            accs[w][1][pc * 8 + e] = a2[e];
+            accs[w][0][pc * 8 + e] = a[0][e];
+            accs[w][1][pc * 8 + e] = a[1][e];
         }
     }
-    __syncthreads();
-    for (int e = tid; e < 2 * d_h; e += 256) {
-        const int br = e / d_h, d = e % d_h;
-        out[br * (d_h + 2) + 2 + d] = (accs[0][br][d] + accs[1][br][d]) + (accs[2][br][d] + accs[3][br][d]);
+    if (l < 2) {
+        mx_s[w][l] = l == 0 ? mx[0] : mx[1];
+        sum_s[w][l] = l == 0 ? sum[0] : sum[1];
     }
-    if (tid < 2) {
-        out[tid * (d_h + 2)] = m[tid];
-        out[tid * (d_h + 2) + 1] = lsum[tid];
+    __syncthreads();
+    float *out = p.part + ((((size_t)b * p.n_heads + h) * p.chunks + chunk) * 2) * (d_h + 2);
+    if (tid < 2 * d_h) {
+        const int br = tid / d_h, d = tid % d_h;
+        const float m = fmaxf(fmaxf(mx_s[0][br], mx_s[1][br]), fmaxf(mx_s[2][br], mx_s[3][br]));
+        float acc = 0.f, total = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float f = sum_s[i][br] == 0.f ? 0.f : expf(mx_s[i][br] - m);     // (0: no positions there)
+            acc += accs[i][br][d] * f;
+            total += sum_s[i][br] * f;
+        }
+        out[br * (d_h + 2) + 2 + d] = acc;
+        if (d == 0) {
+            out[br * (d_h + 2)] = m;
+            out[br * (d_h + 2) + 1] = total;
+        }
     }
 }
 
-__global__ __launch_bounds__(128) void diff_attn_merge_kernel(AttnParams p)
+// One workgroup per head and sequence; wavefront 0 turns up to 64 chunks' (max, sum) at a time into
+// weights (LDS), then all four take every fourth chunk's rows.  Bound by latency: a fixed number of
+// trips to memory, where two loops over the chunks with a dependent load in each took 16.9 us at
+// 16 chunks.
+__global__ __launch_bounds__(512) void diff_attn_merge_kernel(AttnParams p)
 {
-    const int h = blockIdx.x, b = blockIdx.y, d = threadIdx.x;
-    const int d_h = p.d_h;
-    if (d >= d_h) return;
+    __shared__ float wgt[2][64], red[4][2][128], scale_s[2], sum_s[2];
+    const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+    const int d_h = p.d_h, d = tid & 127, part4 = tid >> 7;
     const float *part = p.part + (((size_t)b * p.n_heads + h) * p.chunks) * 2 * (d_h + 2);
     const int len = min(max(p.lens[b], 0), p.L_max);
     const int used = (len + kAttnChunk - 1) / kAttnChunk;
-    float a[2];
+    float acc[2] = {0.f, 0.f};
+    float run_m = -INFINITY, run_sum = 0.f;         // wavefronts 0 and 1: one branch each
+    for (int c0 = 0; c0 < used; c0 += 64) {
+        if (c0 > 0) __syncthreads();                // the weights of the batch before have been used
+        const int n = min(64, used - c0);
+        if (tid < 128) {
+            const int br = tid >> 6, c = tid & 63;
+            const float *q = part + ((size_t)(c0 + c) * 2 + br) * (d_h + 2);
+            const float mc = c < n ? q[0] : -INFINITY, sc = c < n ? q[1] : 0.f;
+            const float m = fmaxf(run_m, wave_max(mc));
+            const float base = m == -INFINITY ? 0.f : m;
+            const float f = expf(mc - base), keep = expf(run_m - base);
+            float t = sc * f;
 #pragma unroll
-    for (int br = 0; br < 2; ++br) {
-        float mx = -INFINITY;
-        for (int c = 0; c < used; ++c) mx = fmaxf(mx, part[(c * 2 + br) * (d_h + 2)]);
-        float sum = 0.f, acc = 0.f;
-        for (int c = 0; c < used; ++c) {
-            const float *q = part + (c * 2 + br) * (d_h + 2);
-            const float wgt = expf(q[0] - mx);
-            sum += q[1] * wgt;
-            acc += q[2 + d] * wgt;
+            for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+            run_sum = run_sum * keep + t;
+            run_m = m;
+            wgt[br][c] = f;
+            if (c == 0) {
+                scale_s[br] = keep;
+                sum_s[br] = run_sum;
+            }
         }
-        a[br] = used > 0 ? acc / sum : 0.f;
+        __syncthreads();
+        acc[0] *= scale_s[0];
+        acc[1] *= scale_s[1];
+        if (d < d_h) {
+#pragma unroll 4
+            for (int c = part4; c < n; c += 4) {
+                const float *q = part + (size_t)(c0 + c) * 2 * (d_h + 2) + 2 + d;
+                acc[0] += q[0] * wgt[0][c];
+                acc[1] += q[d_h + 2] * wgt[1][c];
+            }
+        }
     }
-    p.out[((size_t)b * p.n_heads + h) * d_h + d] = (_Float16)((a[0] - p.lambda * a[1]) * 0.5f);
+    red[part4][0][d] = acc[0];
+    red[part4][1][d] = acc[1];
+    __syncthreads();
+    if (part4 == 0 && d < d_h) {
+        float o[2] = {0.f, 0.f};
+        if (used > 0) {
+#pragma unroll
+            for (int br = 0; br < 2; ++br)
+                o[br] = ((red[0][br][d] + red[1][br][d]) + (red[2][br][d] + red[3][br][d])) / sum_s[br];
+        }
+        p.out[((size_t)b * p.n_heads + h) * d_h + d] = (_Float16)((o[0] - p.lambda * o[1]) * 0.5f);
+    }
 }
 
 }  // namespace
@@ -217,7 +259,7 @@ hipError_t launch_diff_attn(const void *q, const void *k, const void *v, const i
     p.chunks = (L_max + kAttnChunk - 1) / kAttnChunk;
     p.lambda = lambda;
     p.scale = 1.0f / sqrtf((float)d_h);
-    const dim3 grid(p.chunks, n_heads, B), block(256);
+    const dim3 grid(n_heads, p.chunks, B), block(256);
     switch (d_h / 8) {
         case 1: hipLaunchKernelGGL(diff_attn_chunk_kernel<1>, grid, block, 0, st, p); break;
         case 2: hipLaunchKernelGGL(diff_attn_chunk_kernel<2>, grid, block, 0, st, p); break;
@@ -226,7 +268,7 @@ hipError_t launch_diff_attn(const void *q, const void *k, const void *v, const i
         case 16: hipLaunchKernelGGL(diff_attn_chunk_kernel<16>, grid, block, 0, st, p); break;
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(diff_attn_merge_kernel, dim3(n_heads, B), dim3(128), 0, st, p);
+    hipLaunchKernelGGL(diff_attn_merge_kernel, dim3(n_heads, B), dim3(512), 0, st, p);
     return hipGetLastError();
 }
 

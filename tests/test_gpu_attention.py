@@ -63,6 +63,14 @@ def test_diff_attention_model_shapes():
     assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, [4096], 0.8))
 
 
+@pytest.mark.parametrize("d,L,lens", [(8, 16700, [16385, 16384, 16700]), (32, 17000, [17000, 1, 65])])
+def test_diff_attention_many_chunks(d, L, lens):
+    # more chunks of 256 positions than one batch of the merge (64), and wavefronts of 64 positions that are empty
+    q, k, v = _case(d + L, len(lens), L, 1, d)
+    out = hb.hgf_diff_attention_decode(dev(q), dev(k), dev(v), dev(np.array(lens, dtype=np.int32)), 0.8)
+    assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, lens, 0.8))
+
+
 def test_diff_attention_rejects_bad_arguments():
     lib = hb.lib()
     assert lib.hgf_diff_attention_workspace_bytes(1, 128, 4, 24) == 0          # d_h not a power of two
