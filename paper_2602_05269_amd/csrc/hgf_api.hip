@@ -26,10 +26,9 @@ Workspace carve_workspace(void *base, int M, int d_in, int d_out, int rank, int 
     ws.rowsum = reinterpret_cast<int32_t *>(take((size_t)M * 4));
     ws.h16_each = align256((size_t)M * h_stride(rank > 0 ? rank : 1) * 2);
     ws.h16 = reinterpret_cast<_Float16 *>(take(ws.h16_each * groups));
-    // two-launch decode path: per layer of a group kMaxHSplit slices of [M, h_stride] partial sums
-    const int Md = M < kMaxDecodeM ? M : kMaxDecodeM;
-    ws.hslices_each = rank > 0 ? align256((size_t)kMaxHSplit * Md * h_stride(rank) * sizeof(float)) : 0;
-    ws.hslices = reinterpret_cast<float *>(take(ws.hslices_each * groups));
+    const int Md = M < 64 ? M : 64;
+    ws.spare_bytes = rank > 0 ? groups * align256((size_t)32 * Md * h_stride(rank) * sizeof(float)) : 0;
+    ws.spare = reinterpret_cast<unsigned char *>(take(ws.spare_bytes));
     ws.wsum = reinterpret_cast<double *>(take(size_t(kWsumBlocks) * 8));
     (void)d_out;
     ws.bytes = off;
@@ -61,17 +60,24 @@ hgf_status check_layer(const hgf_layer *L, int M)
 
 hgf_status from_hip(hipError_t e) { return e == hipSuccess ? HGF_OK : HGF_ERR_DEVICE; }
 
-// Which of the two paths a group of layers takes.  Up to 40 tokens the two-launch decode path
-// always; from 41 to 64 (what its kernel handles) only groups of few rows, whose prefill grids
-// would be a handful of 256-row tiles (7B-shape FFN at 64 tokens: the down projection, 4096 rows,
-// takes 52 us on the decode path and 60 on the prefill path; up + gate, 22016 rows, 41 and 33).
-bool takes_decode_path(int M, const hgf_layer *layers, int G, bool pair)
+// Which of the two paths a group of layers takes.  The prefill kernel's tiles are 256 rows by 64 or
+// 128 tokens and walk all of d_in with one workgroup each, so a group that does not fill the chip with
+// them costs about 11 + 0.5 k-tiles microseconds whatever its size; the direct path costs by its output
+// tiles of 32 x 32.  They cross at (us, direct / prefill): 4 k-tiles, 768 tiles 12.7 / 12.8, 2048 17.1 /
+// 13.3; 16 k-tiles, 768 tiles 17.5 / 19.4, 1152 21.0 / 19.6; 24 k-tiles, 1152 tiles 22.8 / 23.4, 1728
+// 26.3 / 23.9; 32 k-tiles, 1376 tiles 30.7 / 32.4; 64 k-tiles, 1536 tiles 39.9 / 43.8; 86 k-tiles, 1024
+// tiles 39.8 / 60.0, 2048 69.0 / 61.4.  A pair (two tiles per 32 rows of z) crosses a little earlier:
+// 16 k-tiles, 1024 tiles 18.7 / 20.1; 32 k-tiles, 1376 tiles 34.9 / 33.0.  Up to 40 tokens the direct
+// path takes every group.
+bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 {
     if (M <= 40) return true;
-    if (M > kMaxDecodeM || pair) return false;
-    long long rows = 0;
-    for (int g = 0; g < G; ++g) rows += layers[g].d_out;
-    return rows <= 8192;
+    long long rbs = 0;
+    for (int g = 0; g < G; ++g) rbs += round_up(layers[g].d_out, kTileRows) / kTileRows;
+    const long long tiles = rbs * ((M + 31) / 32);
+    const int kt = round_up(layers[0].d_in, kTileCols) / kTileCols;
+    const int most = 900 + 15 * kt < 1800 ? 900 + 15 * kt : 1800;
+    return tiles <= (pair ? most * 9 / 10 : most);
 }
 
 // Profiling aid: event pairs recorded around main-kernel launches, by kind (0 decode, 1 prefill).
@@ -113,8 +119,42 @@ struct ProfileScope {
     }
 };
 
-// Decode (M <= kMaxDecodeM): `G` layers that read the same activations `x` run as two launches:
-// the fused prologue (quantiser + partial sums of every A x) and one grouped main kernel.
+// Places what the prologue of a group writes (layers, sizes and NQ are set): the first quantisation
+// in the workspace's own buffers, those of the other LayerNorms of the group and, where d_in is cut,
+// the slices of A x in its spare region; d_in stays whole where they do not fit.  False: the
+// quantisations do not fit.
+bool place_prologue(ProParams &p, const hgf_layer *layers, const Workspace &ws)
+{
+    const size_t xq_bytes = align256((size_t)p.M * round_up(p.K, kTileCols)), word_bytes = align256((size_t)p.M * 4);
+    size_t used = 0;
+    for (int i = 0; i < p.NQ; ++i) {
+        ProTokens &Q = p.Q[i];
+        Q.xq = ws.xq;
+        Q.s_x = ws.s_x;
+        Q.rowsum = ws.rowsum;
+        Q.gamma = layers[i].ln_gamma;
+        Q.beta = layers[i].ln_beta;
+        Q.eps = layers[i].ln_eps;
+        if (i == 0) continue;
+        Q.xq = reinterpret_cast<int8_t *>(ws.spare + used);
+        Q.s_x = reinterpret_cast<float *>(ws.spare + used + xq_bytes);
+        Q.rowsum = reinterpret_cast<int32_t *>(ws.spare + used + xq_bytes + word_bytes);
+        used += xq_bytes + 2 * word_bytes;
+    }
+    if (used > ws.spare_bytes) return false;
+    p.S = prologue_slices(p.K);
+    size_t each[kMaxGroup], slices = 0;
+    for (int g = 0; g < p.G; ++g) slices += each[g] = p.L[g].rank > 0 ? align256((size_t)p.S * p.M * p.L[g].hstride * 4) : 0;
+    if (used + slices > ws.spare_bytes) p.S = 1;
+    for (int g = 0; g < p.G; ++g) {
+        p.L[g].hpart = p.S > 1 ? reinterpret_cast<float *>(ws.spare + used) : nullptr;
+        used += each[g];
+    }
+    return true;
+}
+
+// Direct path: `G` layers that read the same activations `x` run as two launches: the prologue
+// (quantisers + SiLU(A x) of every layer) and one grouped main kernel.
 //
 // `pair` (G == 2): the SwiGLU pair -- layers[0] is the gate projection, layers[1] the up
 // projection; the one output ys[1] receives SiLU(y_gate) * y_up, amax_out (nullable) the
@@ -146,7 +186,6 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
             D.B = reinterpret_cast<const _Float16 *>(L.B_f16);
             D.alpha = reinterpret_cast<const _Float16 *>(L.alpha_f16);
             D.h16 = nullptr;
-            D.hpart = nullptr;
             D.y = reinterpret_cast<_Float16 *>(ys[g]);
             D.acc_debug = acc_debug;
             D.N = L.d_out;
@@ -163,37 +202,38 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
     }
     ProParams pp;
     pp.x = reinterpret_cast<const _Float16 *>(x);
-    pp.xq = ws.xq;
-    pp.s_x = ws.s_x;
-    pp.rowsum = ws.rowsum;
     pp.amax_zero = pair ? amax_out : nullptr;
-    pp.quantize = ln ? 0 : 1;
     pp.M = M;
     pp.K = K;
-    pp.Kp = round_up(K, kTileCols);
     pp.G = G;
+    pp.NQ = ln ? G : 1;
+    for (int g = 0; g < G; ++g) {
+        const hgf_layer &L = layers[g];
+        pp.L[g].A = reinterpret_cast<const _Float16 *>(L.A_f16);
+        pp.L[g].h16 = reinterpret_cast<_Float16 *>(reinterpret_cast<char *>(ws.h16) + ws.h16_each * g);
+        pp.L[g].rank = L.rank;
+        pp.L[g].hstride = h_stride(L.rank > 0 ? L.rank : 1);
+    }
+    if (!place_prologue(pp, layers, ws)) return HGF_ERR_WORKSPACE;
     DecodeParams dp;
-    dp.xq = ws.xq;
-    dp.s_x = ws.s_x;
-    dp.rowsum = ws.rowsum;
+    dp.S = pp.S;
     dp.M = M;
     dp.G = G;
     dp.pair = pair ? 1 : 0;
     dp.amax_out = pair ? amax_out : nullptr;
     for (int g = 0; g < G; ++g) {
         const hgf_layer &L = layers[g];
-        float *slices = reinterpret_cast<float *>(reinterpret_cast<char *>(ws.hslices) + ws.hslices_each * g);
-        pp.L[g].A = reinterpret_cast<const _Float16 *>(L.A_f16);
-        pp.L[g].hpart = slices;
-        pp.L[g].rank = L.rank;
-        pp.L[g].rp = h_stride(L.rank > 0 ? L.rank : 1);
         DecLayer &D = dp.L[g];
         D.packed = reinterpret_cast<const v4u *>(L.W_packed);
         D.s_w = L.s_w;
         D.B = reinterpret_cast<const _Float16 *>(L.B_f16);
         D.alpha = reinterpret_cast<const _Float16 *>(L.alpha_f16);
-        D.h16 = nullptr;
-        D.hpart = slices;                           // (the main kernel adds the slices of A x itself: no reducing launch)
+        const ProTokens &Q = pp.Q[ln ? g : 0];
+        D.h16 = pp.L[g].h16;
+        D.hpart = pp.L[g].hpart;
+        D.xq = Q.xq;
+        D.s_x = Q.s_x;
+        D.rowsum = Q.rowsum;
         D.y = reinterpret_cast<_Float16 *>(ys[g]);
         D.acc_debug = (pair && g == 1) ? acc_debug2 : acc_debug;
         D.N = L.d_out;
@@ -201,11 +241,7 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
         D.rank = L.rank;
         D.hstride = h_stride(L.rank > 0 ? L.rank : 1);
     }
-    dp.S = prologue_slices(M, K);
-    if (ln && launch_ln_quantize(pp.x, M, K, layers[0].ln_gamma, layers[0].ln_beta, layers[0].ln_eps, ws.xq, ws.s_x,
-                                 ws.rowsum, st) != hipSuccess)
-        return HGF_ERR_DEVICE;
-    if (launch_prologue(pp, nullptr, st) != hipSuccess) return HGF_ERR_DEVICE;
+    if (launch_prologue(pp, st) != hipSuccess) return HGF_ERR_DEVICE;
     ProfileScope prof(0, st);
     return from_hip(launch_decode(dp, K, st));
 }
@@ -393,7 +429,7 @@ hgf_status hgf_linear_forward(const void *x_f16, int M, const hgf_layer *L, void
     const Workspace ws = carve_workspace(workspace, M, L->d_in, L->d_out, L->rank);
     if (workspace_bytes < ws.bytes) return HGF_ERR_WORKSPACE;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (takes_decode_path(M, L, 1, false)) {
+    if (takes_direct_path(M, L, 1, false)) {
         void *ys[1] = {y_f16};
         return run_decode_group(x_f16, M, L, 1, ys, acc_debug, ws, st);
     }
@@ -425,7 +461,7 @@ hgf_status hgf_swiglu_forward(const void *x_f16, int M, const hgf_layer *gate, c
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const hgf_layer pairL[2] = {*gate, *up};
     void *ys[2] = {nullptr, z_f16};
-    if (takes_decode_path(M, pairL, 2, true))
+    if (takes_direct_path(M, pairL, 2, true))
         return run_decode_group(x_f16, M, pairL, 2, ys, acc_debug_gate, ws, st, true, amax_out, acc_debug_up);
     const PairOut po = {acc_debug_up, amax_out};
     return run_large_group(x_f16, M, pairL, 2, ys, acc_debug_gate, ws, st, &po);
@@ -502,25 +538,21 @@ hgf_status hgf_linear_forward_b3(const void *x_f16, int M, const hgf_layer *L, v
     if (workspace_bytes < ws.bytes) return HGF_ERR_WORKSPACE;
     if (L->ln_gamma || !b3_fits(M, L->d_in, L->rank)) return HGF_ERR_UNSUPPORTED;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    // steps 1, 2, 5, 6 of Algorithm 1: the decode prologue (quantiser, partial sums of A x, their sum and SiLU)
+    // steps 1, 2, 5, 6 of Algorithm 1: the prologue (quantiser, SiLU(A x))
     ProParams pp;
     pp.x = reinterpret_cast<const _Float16 *>(x_f16);
-    pp.xq = ws.xq;
-    pp.s_x = ws.s_x;
-    pp.rowsum = ws.rowsum;
     pp.amax_zero = nullptr;
-    pp.quantize = 1;
     pp.M = M;
     pp.K = L->d_in;
-    pp.Kp = round_up(L->d_in, kTileCols);
     pp.G = 1;
+    pp.NQ = 1;
     pp.L[0].A = reinterpret_cast<const _Float16 *>(L->A_f16);
-    pp.L[0].hpart = ws.hslices;
+    pp.L[0].h16 = ws.h16;
     pp.L[0].rank = L->rank;
-    pp.L[0].rp = h_stride(L->rank > 0 ? L->rank : 1);
-    _Float16 *h16[kMaxGroup] = {ws.h16, nullptr, nullptr, nullptr};
-    if (launch_prologue(pp, h16, st) != hipSuccess) return HGF_ERR_DEVICE;
-    return from_hip(launch_b3_decode(L->W_packed, ws, ws.h16, M, *L, y_f16, acc_debug, st));
+    pp.L[0].hstride = h_stride(L->rank > 0 ? L->rank : 1);
+    if (!place_prologue(pp, L, ws)) return HGF_ERR_WORKSPACE;
+    if (launch_prologue(pp, st) != hipSuccess) return HGF_ERR_DEVICE;
+    return from_hip(launch_b3_decode(L->W_packed, pp, M, *L, y_f16, acc_debug, st));
 }
 
 size_t hgf_static_scratch_bytes(void) { return kStaticScratchBytes; }
@@ -547,7 +579,7 @@ hgf_status hgf_linear_forward_static(const void *x_f16, int M, const hgf_layer *
     void *ys[1] = {y_f16};
     const bool profiling = g_profile;           // (the profiling aid creates events: not from here)
     g_profile = false;
-    const hgf_status r = takes_decode_path(M, L, 1, false) ? run_decode_group(x_f16, M, L, 1, ys, acc_debug, ws, st)
+    const hgf_status r = takes_direct_path(M, L, 1, false) ? run_decode_group(x_f16, M, L, 1, ys, acc_debug, ws, st)
                                           : run_large_group(x_f16, M, L, 1, ys, acc_debug, ws, st);
     g_profile = profiling;
     return r;
@@ -605,7 +637,7 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
 
     auto run_group = [&](const Group &gr) -> hgf_status {
         const void *x = slots[layers[gr.first].src_slot];
-        if (takes_decode_path(M, layers + gr.first, gr.G, false)) {
+        if (takes_direct_path(M, layers + gr.first, gr.G, false)) {
             void *ys[kMaxGroup];
             for (int g = 0; g < gr.G; ++g) ys[g] = slots[layers[gr.first + g].dst_slot];
             return run_decode_group(x, M, layers + gr.first, gr.G, ys, nullptr, ws, st);

@@ -71,10 +71,12 @@ __global__ __launch_bounds__(256) void unpack_b3_kernel(const unsigned char *__r
 
 struct B3Params {
     const unsigned char *packed;   // [N, Rb]
-    const int8_t *xq;              // [M, Kp]
+    const int8_t *xq;              // as in ProTokens
     const float *s_x;
     const int32_t *rowsum;
-    const _Float16 *h16;           // [M, hstride] SiLU(A x)
+    const _Float16 *h16;           // [M, hstride] SiLU(A x) ...
+    const float *hpart;            // ... or [S, M, hstride] slices of A x
+    int S;
     const float *s_w;
     const _Float16 *B, *alpha;
     _Float16 *y;
@@ -126,13 +128,22 @@ __global__ __launch_bounds__(256) void b3_decode_kernel(B3Params p)
 #pragma unroll
         for (int d = 0; d < kB3Group; ++d) {
             const int k = g * kB3Group + d;
-            v[d] = (m < p.M && k < p.K) ? (unsigned)(unsigned char)p.xq[(size_t)m * p.Kp + k] : 0u;
+            v[d] = (m < p.M && k < p.K) ? (unsigned)(unsigned char)p.xq[((size_t)(k >> 4) * p.M + m) * 16 + (k & 15)] : 0u;
         }
         xs[i] = make_uint2(v[0] | (v[1] << 8) | (v[2] << 16) | (v[3] << 24), v[4]);
     }
     for (int i = tid; i < MT * p.hstride; i += 256) {
         const int m = i / p.hstride;
-        hs[i] = (p.rank > 0 && m < p.M) ? (float)p.h16[i] : 0.0f;
+        float h = 0.f;
+        if (m < p.M && i - m * p.hstride < p.rank) {
+            if (p.S == 1) {
+                h = (float)p.h16[i];
+            } else {
+                for (int s = 0; s < p.S; ++s) h += p.hpart[(size_t)s * p.M * p.hstride + i];
+                h = (float)(_Float16)silu(h);
+            }
+        }
+        hs[i] = h;
     }
     __syncthreads();
 
@@ -247,15 +258,17 @@ bool b3_fits(int M, int K, int rank)
     return lds <= 150 * 1024;
 }
 
-hipError_t launch_b3_decode(const void *packed, const Workspace &ws, const _Float16 *h16, int M, const hgf_layer &L,
+hipError_t launch_b3_decode(const void *packed, const ProParams &pro, int M, const hgf_layer &L,
                             void *y, int32_t *acc_debug, hipStream_t st)
 {
     B3Params p;
     p.packed = reinterpret_cast<const unsigned char *>(packed);
-    p.xq = ws.xq;
-    p.s_x = ws.s_x;
-    p.rowsum = ws.rowsum;
-    p.h16 = h16;
+    p.xq = pro.Q[0].xq;
+    p.s_x = pro.Q[0].s_x;
+    p.rowsum = pro.Q[0].rowsum;
+    p.h16 = pro.L[0].h16;
+    p.hpart = pro.L[0].hpart;
+    p.S = pro.S;
     p.s_w = L.s_w;
     p.B = reinterpret_cast<const _Float16 *>(L.B_f16);
     p.alpha = reinterpret_cast<const _Float16 *>(L.alpha_f16);

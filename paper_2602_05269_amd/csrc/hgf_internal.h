@@ -13,11 +13,6 @@ namespace hgf {
 constexpr int kTileRows = 32;        // a packed tile covers 32 rows ...
 constexpr int kTileCols = 128;       // ... by 128 columns of 2-bit codes
 constexpr int kTileBytes = 1024;
-// Tokens the two-launch decode path handles (4 token tiles of 16).  It is taken up to 40 tokens
-// always and up to 64 for groups of few rows (takes_decode_path in hgf_api.hip): on the 7B-shape
-// FFN block it costs 43 us at 8 tokens, 58 at 32, 82 at 48, where the prefill path costs the same
-// 91-95 us for anything from 41 to 128.
-constexpr int kMaxDecodeM = 64;
 constexpr int kMaxGroup = 4;         // layers reading the same activations launched together
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -136,13 +131,12 @@ inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // ---- workspace layout -------------------------------------------------------------
-// [ flags | exchange buffers of the single-launch path | x_q | s_x | rowsum | h16 | h partials |
+// [ flags | exchange buffers of the single-launch path | x_q | s_x | rowsum | h16 | spare |
 //   weight-quantiser sums ]   (hgf_workspace_init zeroes the flags and fills the exchange
 //   buffers with the sentinel pattern)
 constexpr int kNumFlags = 64;                              // int32 words: launch counter, arrival count, sticky error
 constexpr size_t kZeroBytes = size_t(kNumFlags) * 4;
 constexpr int kWsumBlocks = 1024;                          // fp64 partial sums of |W|
-constexpr int kMaxHSplit = 32;                             // k-splits of the rank-r down-projection
 
 struct Workspace {
     int32_t *flags;      // zero region: [0] correction workgroups done, [1] decode workgroups done,
@@ -154,8 +148,8 @@ struct Workspace {
     int32_t *rowsum;
     _Float16 *h16;       // large M: kMaxGroup x [M, h_stride] SiLU(A x), zero padded (one per layer of a group)
     size_t h16_each;     // bytes per layer
-    float *hslices;      // decode: kMaxGroup x [S, M, h_stride] fp32 partial sums of A x
-    size_t hslices_each; // bytes per layer of a group
+    unsigned char *spare; // direct path: slices of A x; further quantisations where layers have LayerNorms of their own
+    size_t spare_bytes;
     double *wsum;        // [kWsumBlocks]
     size_t bytes;        // total bytes needed
 };
@@ -182,22 +176,28 @@ __host__ __device__ inline int h_stride(int rank)       // row stride of h16 in 
 
 struct ProLayer {
     const _Float16 *A;   // [rank, K]
-    float *hpart;        // [S, M, rp] fp32 partial sums of A x
-    int rank, rp;
+    _Float16 *h16;       // [M, hstride] SiLU(A x): whole tiles of 16 ranks are written
+    float *hpart;        // S > 1 instead: [S, M, hstride] partial sums of A x
+    int rank, hstride;
 };
-struct ProParams {
-    const _Float16 *x;
-    unsigned char *mail; // two exchange buffers of kMailBytes, sentinel-filled between launches
-    unsigned char *xchg; // two sets of kStackSetBytes for the whole-stack launch, likewise
+// One quantisation of the tokens.  xq: groups of 32 tokens (the last one smaller), 32 Kp bytes apart,
+// each [Kp / 16][tokens of the group][16]; one set per layer where LayerNorms differ.
+struct ProTokens {
     int8_t *xq;
     float *s_x;
     int32_t *rowsum;
+    const float *gamma, *beta;   // LayerNorm in front (gamma null: none; beta null: zero)
+    float eps;
+};
+struct ProParams {
+    const _Float16 *x;
     float *amax_zero;    // nullable: [M] floats the quantising workgroups set to zero (a later kernel's atomic max)
-    int quantize;        // 0: x_q, s_x and the row sums are already there (the LayerNorm quantiser wrote them)
-    int M, K, Kp, G;
+    int M, K, Kp, G, NQ; // layers; quantisations
+    int S;               // slices of d_in
+    int token_tiles;
     ProLayer L[kMaxGroup];
+    ProTokens Q[kMaxGroup];
     int job_start[kMaxGroup + 1];
-    int S, pairs, pairs_per_slice;   // slices of d_in; 64-column steps in all and per slice
 };
 
 struct DecLayer {
@@ -205,28 +205,25 @@ struct DecLayer {
     const float *s_w;
     const _Float16 *B;
     const _Float16 *alpha;
-    const _Float16 *h16;     // [M, hstride] fp16 SiLU(A x), zero padded (the base-3 path; the prefill path has its own)
-    const float *hpart;      // [S][M][hstride] fp32 slices of A x from the prologue (the decode kernel adds them itself)
+    const _Float16 *h16;     // [M, hstride] fp16 SiLU(A x)
+    const float *hpart;      // or its slices, as in ProLayer
+    const int8_t *xq;        // as in ProTokens
+    const float *s_x;
+    const int32_t *rowsum;
     _Float16 *y;
     int32_t *acc_debug;
     int N, RBn, rank, hstride;
+    int b_aligned;           // B starts at a multiple of 16 bytes
 };
 struct DecodeParams {
-    const int8_t *xq;
-    const float *s_x;
-    const int32_t *rowsum;
     int M, Kp, KT, G;
-    int S;                   // slices of A x the prologue wrote
+    int hsteps;              // 16-rank steps of the widest layer
+    int S;                   // slices of A x
     DecLayer L[kMaxGroup];
-    int wg_start[kMaxGroup + 1];
-    int RW, KW;              // row-blocks per workgroup, wavefronts per row-block (RW*KW = 4 or 8)
-    int CT, xstride;         // tiles of d_in staged in LDS at a time; bytes per staged row
-    int h_off, g_off;        // byte offsets in LDS of the SiLU(A x) rows and of the tanh(alpha) table
-    // SwiGLU pair (G == 2, both layers of one shape): a workgroup takes the SAME row-block of
-    // layer 0 (gate) and layer 1 (up), one half of its wavefronts each, and stores
-    // z = SiLU(y_gate) * y_up to L[1].y; L[0].y is unused.
+    int wg_start[kMaxGroup + 1];   // running sum of the layers' row units
+    // SwiGLU pair (G == 2, both layers of one shape): layer 0 (gate) and layer 1 (up); z = SiLU(y_gate) *
+    // y_up goes to L[1].y; L[0].y is unused.
     int pair;
-    int h_each, exch_off;    // pair: bytes per layer of the SiLU(A x) rows in LDS; offset of the y_gate exchange
     float *amax_out;         // pair, nullable: per-token max |z| (zeroed before the launch; combined with atomic max)
 };
 
@@ -306,8 +303,8 @@ hipError_t launch_ln_quantize(const _Float16 *x, int M, int K, const float *gamm
                               int8_t *xq, float *s_x, int32_t *rowsum, hipStream_t st);
 hipError_t launch_corr_down(const _Float16 *x, int M, int K, int G, const _Float16 *const *A, const int *rank,
                             _Float16 *const *h16, int8_t *xq, float *s_x, int32_t *rowsum, hipStream_t st);
-int prologue_slices(int M, int K);
-hipError_t launch_prologue(ProParams &p, _Float16 *const *h16, hipStream_t st);
+int prologue_slices(int K);
+hipError_t launch_prologue(ProParams &p, hipStream_t st);
 hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st);
 // What a plan or a launch of one of the persistent kernels came to.
 enum class Launch { kRan, kNoFit, kRefused };
@@ -334,7 +331,7 @@ size_t b3_packed_bytes(int d_out, int d_in);
 hipError_t launch_pack_b3(const float *W, int N, int K, const float *s_w, unsigned char *packed, hipStream_t st);
 hipError_t launch_unpack_b3(const unsigned char *packed, int N, int K, int8_t *T, hipStream_t st);
 bool b3_fits(int M, int K, int rank);
-hipError_t launch_b3_decode(const void *packed, const Workspace &ws, const _Float16 *h16, int M, const hgf_layer &L,
+hipError_t launch_b3_decode(const void *packed, const ProParams &pro, int M, const hgf_layer &L,
                             void *y, int32_t *acc_debug, hipStream_t st);
 
 }  // namespace hgf

@@ -1,270 +1,371 @@
-// Decode prologue (up to 64 tokens): one launch that quantises the activations and starts the
-// correction path of every layer reading them.
+// Preparation of a group of layers that read the same activations, for the direct path: one launch
+// that quantises the tokens and computes SiLU(A x) of every layer.
 //
-// Algorithm 1 of the HGF paper, steps 1-2 (per-token absmax int8 quantisation,
-// Sec. 2.2.1) and step 5 (H <- X A on the UN-quantised fp16 activations).  Workgroups
-// 0..M-1 each quantise one token; the remaining workgroups hold four wavefronts, each
-// computing one 16-rank-row tile of A x over one slice of d_in on the 16x16x32 f16 MFMA
-// (rows = rank indices, columns = tokens) and writing its fp32 partial sums.  The slices
-// are short enough that a wavefront issues all of its loads at once: the launch costs one
-// memory round trip.  The consumer adds the slices in order (deterministic) and applies
-// SiLU (step 6) while its weights are in flight.
+// Algorithm 1 of the HGF paper, steps 1-2 (per-token absmax int8 quantisation, Sec. 2.2.1, behind a
+// LayerNorm where the layer has one) and steps 5-6 (H <- SiLU(X A) on the UN-quantised fp16
+// activations).  Two roles share the grid; both only read x.
+//
+// Down-projection: a workgroup of eight wavefronts owns one tile of 16 ranks x 16 TT tokens of one
+// layer and a slice of d_in: wavefront w takes the 64-column steps w, w+8, ... on the 16x16x32 f16
+// MFMA (rows = rank indices, columns = tokens), and the eight partial tiles meet in LDS and are added
+// in order.  Up to 2048 columns are one slice, SiLU(A x) leaves as fp16; longer rows are cut, because
+// one compute unit takes in only some 0.1 MB per microsecond (all of d_in = 11008 in a workgroup: 19 us
+// for 8 tokens, 32 us for 64), their slices leave as fp32 and the consumer adds them in order.
+// Bound by latency: the launch is one or two memory round trips (6 us for a group of the 7B shape at 8
+// tokens, 8.7 at 64, where all token tiles in one wavefront took 12.7).
+//
+// Quantiser: 64, 256 or 512 threads per token by the row's length, the row in registers between the
+// passes.  x_q is stored the way the consumer's MFMA operand wants it: per group of up to 32 tokens
+// 16-byte pieces of 16 columns, [d_in / 16][token], so that a wavefront's request is contiguous.
 #include "hgf_internal.h"
 
 namespace hgf {
 
 namespace {
 
-constexpr int kRegVecs = 6;   // a token row of up to 6*256*8 = 12288 columns stays in registers
+constexpr int kProThreads = 512, kProWaves = kProThreads / 64;
 
-// One workgroup quantises one token row.  VEC: d_in % 8 == 0 (16-byte loads).
-template <bool VEC>
-__device__ void quantize_row(const ProParams &p, int m)
+// Eight (16) consecutive fp16 of a row whose address is any multiple of two bytes: the aligned dwords
+// that hold them, shifted together.  `r` starts at a multiple of four bytes; `at`: byte offset of the
+// first; the caller has checked that the dword behind the last whole one is inside as well when
+// `at` is odd in units of two bytes.
+template <int NW>      // words of two fp16
+__device__ inline void load_unaligned(rsrc_t r, unsigned at, bool ok, unsigned (&out)[NW])
 {
-    __shared__ float sh_max[4];
-    __shared__ int sh_sum[4];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const _Float16 *row = p.x + (size_t)m * p.K;
-    int8_t *out = p.xq + (size_t)m * p.Kp;
-    const int nvec = p.K / 8;
-    const bool in_regs = VEC && nvec <= kRegVecs * 256;
+    unsigned d[NW + 1];
+    const unsigned base = ok ? (at & ~3u) : kOob;
+#pragma unroll
+    for (int i = 0; i < NW; i += 4) {
+        const v4u v = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(base + i * 4), 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[i + e] = v[e];
+    }
+    const unsigned odd = at & 2u;
+    d[NW] = buf_load4(r, base + NW * 4, ok && odd);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) out[i] = __builtin_amdgcn_alignbit(d[i + 1], d[i], odd * 8u);
+}
 
-    v8h keep[kRegVecs];
-    float amax = 0.0f;
-    if (VEC) {
-        const v8h *row8 = reinterpret_cast<const v8h *>(row);
-        if (in_regs) {
-            const rsrc_t rr = make_rsrc(row, (unsigned)p.K * 2u);
+// ---------------------------------------------------------------- quantiser
+
+// T threads per token, NU 16-column units per thread kept in registers (longer rows are read again
+// for every pass).
+template <int T, int NU, bool VEC>
+__device__ inline void quantize_tokens(const ProParams &p, const ProTokens &Q, int first)
+{
+    __shared__ double sh_d[kProWaves];
+    __shared__ float sh_f[kProWaves];
+    __shared__ int sh_i[kProWaves];
+    constexpr int GW = T / 64;                      // wavefronts per token
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x % T;
+    const int w0 = w / GW * GW;
+    const int m = first + w / GW;
+    const bool live = m < p.M;                      // (a token group past the end still meets the others)
+    const _Float16 *row = p.x + (size_t)(live ? m : 0) * p.K;
+    const unsigned mis = (unsigned)(reinterpret_cast<uintptr_t>(row) & 2u);
+    const rsrc_t r = make_rsrc(reinterpret_cast<const char *>(row) - mis, live ? (unsigned)p.K * 2u + mis : 0u);
+    const int units = p.Kp / 16, chunks = (units + T * NU - 1) / (T * NU);
+
+    auto total_d = [&](double v) {
 #pragma unroll
-            for (int r = 0; r < kRegVecs; ++r)
-                keep[r] = __builtin_bit_cast(v8h, buf_load16(rr, (unsigned)(tid + r * 256) * 16u));
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (GW == 1) return v;
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) sh_d[w] = v;
+        __syncthreads();
+        v = sh_d[w0];
+        for (int i = 1; i < GW; ++i) v += sh_d[w0 + i];
+        return v;
+    };
+
+    float v[NU][16];
+    auto load = [&](int chunk) __attribute__((always_inline)) {
 #pragma unroll
-            for (int r = 0; r < kRegVecs; ++r)
+        for (int u = 0; u < NU; ++u) {
+            const int col = ((chunk * NU + u) * T + t) * 16;
+            if (VEC) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) amax = fmaxf(amax, fabsf((float)keep[r][j]));
-        } else {
-            for (int i = tid; i < nvec; i += 256) {
-                const v8h v = row8[i];
+                for (int h = 0; h < 2; ++h) {
+                    const v8h x = __builtin_bit_cast(v8h, buf_load16(r, (unsigned)(col + h * 8) * 2u));
 #pragma unroll
-                for (int j = 0; j < 8; ++j) amax = fmaxf(amax, fabsf((float)v[j]));
+                    for (int e = 0; e < 8; ++e) v[u][h * 8 + e] = (float)x[e];
+                }
+            } else {
+                unsigned wd[8];
+                const bool whole = col + 16 + (int)(mis >> 1) <= p.K;
+                load_unaligned<8>(r, (unsigned)col * 2u + mis, whole, wd);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) v[u][e] = (float)half_bits((unsigned short)(wd[e >> 1] >> (16 * (e & 1))));
+                if (!whole && col < p.K) {          // the row's last columns, one by one
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        v[u][e] = (float)half_bits(buf_load2(r, (unsigned)(col + e) * 2u + mis, col + e < p.K));
+                }
             }
         }
-    } else {
-        for (int i = tid; i < p.K; i += 256) amax = fmaxf(amax, fabsf((float)row[i]));
+    };
+    const bool ln = Q.gamma != nullptr;
+    float mu = 0.f, rstd = 0.f;
+    auto normalise = [&](int chunk) __attribute__((always_inline)) {
+        const rsrc_t gr = make_rsrc(Q.gamma, (unsigned)p.K * 4u), br = make_rsrc(Q.beta, Q.beta ? (unsigned)p.K * 4u : 0u);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int col = ((chunk * NU + u) * T + t) * 16;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                // (gamma and beta start at any multiple of four bytes, which is all the request asks for)
+                const bool whole = col + q * 4 + 4 <= p.K;
+                v4f ga = __builtin_bit_cast(v4f, buf_load16(gr, (unsigned)(col + q * 4) * 4u, whole));
+                v4f be = __builtin_bit_cast(v4f, buf_load16(br, (unsigned)(col + q * 4) * 4u, whole));
+                if (!whole && col + q * 4 < p.K) {
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) {
+                        ga[e] = __builtin_bit_cast(float, buf_load4(gr, (unsigned)(col + q * 4 + e) * 4u, col + q * 4 + e < p.K));
+                        be[e] = __builtin_bit_cast(float, buf_load4(br, (unsigned)(col + q * 4 + e) * 4u, col + q * 4 + e < p.K));
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {       // in exactly this order, one rounding each; 0 past the row
+                    float y = v[u][q * 4 + e] - mu;
+                    y = y * rstd;
+                    y = y * ga[e];
+                    y = y + be[e];
+                    v[u][q * 4 + e] = col + q * 4 + e < p.K ? y : 0.f;
+                }
+            }
+        }
+    };
+    if (chunks == 1) load(0);
+    if (ln) {
+        // mean and mean squared deviation in fp64, each rounded once
+        double s = 0.0;
+        for (int c = 0; c < chunks; ++c) {
+            if (chunks > 1) load(c);
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) s += (double)v[u][e];           // (zero past the row)
+        }
+        const double mean = total_d(s) / (double)p.K;
+        double ss = 0.0;
+        for (int c = 0; c < chunks; ++c) {
+            if (chunks > 1) load(c);
+#pragma unroll
+            for (int u = 0; u < NU; ++u)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const double d = ((c * NU + u) * T + t) * 16 + e < p.K ? (double)v[u][e] - mean : 0.0;
+                    ss += d * d;
+                }
+        }
+        const double var = total_d(ss) / (double)p.K;
+        mu = (float)mean;
+        rstd = (float)(1.0 / sqrt(var + (double)Q.eps));
+        if (chunks == 1) normalise(0);
+    }
+    float amax = 0.f;
+    for (int c = 0; c < chunks; ++c) {
+        if (chunks > 1) {
+            load(c);
+            if (ln) normalise(c);
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) amax = fmaxf(amax, fabsf(v[u][e]));
     }
     amax = wave_max(amax);
-    if (lane == 0) sh_max[wave] = amax;
-    __syncthreads();
-    amax = fmaxf(fmaxf(sh_max[0], sh_max[1]), fmaxf(sh_max[2], sh_max[3]));
+    if (GW > 1) {
+        if ((threadIdx.x & 63) == 0) sh_f[w] = amax;
+        __syncthreads();
+        for (int i = 0; i < GW; ++i) amax = fmaxf(amax, sh_f[w0 + i]);
+    }
     amax = fmaxf(amax, 1e-5f);
     const float inv = 127.0f / amax;
-
     int sum = 0;
-    if (VEC) {
-        const v8h *row8 = reinterpret_cast<const v8h *>(row);
-        uint2 *out8 = reinterpret_cast<uint2 *>(out);
-        auto quant8 = [&](const v8h v) {
-            uint32_t w[2] = {0u, 0u};
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int q = quant1((float)v[j], inv);
-                sum += q;
-                w[j >> 2] |= (uint32_t)(q & 0xff) << (8 * (j & 3));
-            }
-            return make_uint2(w[0], w[1]);
-        };
-        if (in_regs) {
-#pragma unroll
-            for (int r = 0; r < kRegVecs; ++r) {
-                const int i = tid + r * 256;
-                if (i < nvec) out8[i] = quant8(keep[r]);
-                else if (i < p.Kp / 8) out8[i] = make_uint2(0u, 0u);
-            }
-            for (int i = tid + kRegVecs * 256; i < p.Kp / 8; i += 256) out8[i] = make_uint2(0u, 0u);
-        } else {
-            for (int i = tid; i < p.Kp / 8; i += 256) out8[i] = i < nvec ? quant8(row8[i]) : make_uint2(0u, 0u);
+    const int tg = m >> 5, rows = min(32, p.M - tg * 32);        // the token's group of 32 and its size
+    int8_t *out = Q.xq + (size_t)tg * 32 * p.Kp + (m & 31) * 16;
+    for (int c = 0; c < chunks; ++c) {
+        if (chunks > 1) {
+            load(c);
+            if (ln) normalise(c);
         }
-    } else {
-        for (int i = tid; i < p.Kp; i += 256) {
-            int q = 0;
-            if (i < p.K) q = quant1((float)row[i], inv);
-            sum += q;
-            out[i] = (int8_t)q;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int unit = (c * NU + u) * T + t;
+            v4u o;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                unsigned word = 0;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int q = quant1(v[u][d * 4 + b], inv);
+                    sum += q;
+                    word |= (unsigned)(q & 0xff) << (8 * b);
+                }
+                o[d] = word;
+            }
+            if (live && unit < units) *reinterpret_cast<v4u *>(out + (size_t)unit * rows * 16) = o;
         }
     }
     sum = wave_sum(sum);
-    if (lane == 0) sh_sum[wave] = sum;
-    __syncthreads();
-    if (tid == 0) {
-        p.s_x[m] = amax / 127.0f;
-        p.rowsum[m] = sh_sum[0] + sh_sum[1] + sh_sum[2] + sh_sum[3];
+    if (GW > 1) {
+        if ((threadIdx.x & 63) == 0) sh_i[w] = sum;
+        __syncthreads();
+        sum = 0;
+        for (int i = 0; i < GW; ++i) sum += sh_i[w0 + i];
+    }
+    if (live && t == 0) {
+        Q.s_x[m] = amax / 127.0f;
+        Q.rowsum[m] = sum;
         if (p.amax_zero) p.amax_zero[m] = 0.0f;
     }
 }
 
-// One wavefront: rank tile `rt` of layer `g`, slice `sp` of d_in, every token tile.
-// Lane (i = l%16, kb = l/16) holds A[rt*16+i][k] and x[tt*16+i][k] for the same eight k per
-// MFMA: k = 64*kp + 16*kb + 0..7 and + 8..15 (two MFMAs per 64 columns), so a row is read
-// 128 contiguous bytes at a time.  All loads of the slice are issued before the first MFMA.
+// ---------------------------------------------------------------- down-projection with SiLU
+
+// Lane (i = l%16, kb = l/16) holds A[rt*16+i][k] and x[m][k], m = token tile's i-th, for the same eight
+// k per MFMA: k = 64*step + 16*kb + 0..7 and + 8..15 (two MFMAs per 64 columns), so a row is read
+// 128 contiguous bytes at a time.
 template <int TT, bool VEC>
-__device__ void corr_partial(const ProParams &p, int job)
+__device__ inline void corr_tile(const ProParams &p, int job)
 {
+    __shared__ v4f red[kProWaves][TT][64];
     int g = 0;
     while (g + 1 < p.G && job >= p.job_start[g + 1]) ++g;
     const ProLayer &L = p.L[g];
     const int local = job - p.job_start[g];
-    const int rt = local / p.S, sp = local % p.S;
+    const int sp = local % p.S, rest = local / p.S;
+    const int rt = rest / p.token_tiles, m0 = (rest % p.token_tiles) * 16 * TT;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l = threadIdx.x & 63, i = l & 15, kb = l >> 4;
     const int j = rt * 16 + i;
-    const bool j_ok = j < L.rank;
-    const rsrc_t ar = make_rsrc(L.A, (unsigned)L.rank * p.K * 2u);
-    const rsrc_t xr = make_rsrc(p.x, (unsigned)p.M * p.K * 2u);
+    const unsigned mis = (unsigned)(reinterpret_cast<uintptr_t>(L.A) & 2u);
+    const rsrc_t ar = make_rsrc(reinterpret_cast<const char *>(L.A) - mis, (unsigned)L.rank * p.K * 2u + mis);
+    // (the tokens of this tile behind a descriptor of their own: M * d_in fp16 may pass 4 GiB)
+    const _Float16 *x0 = p.x + (size_t)m0 * p.K;
+    const unsigned xmis = (unsigned)(reinterpret_cast<uintptr_t>(x0) & 2u);
+    const int mrows = min(16 * TT, p.M - m0);
+    const rsrc_t xr = make_rsrc(reinterpret_cast<const char *>(x0) - xmis, (unsigned)mrows * p.K * 2u + xmis);
+
+    auto eight = [&](rsrc_t r, unsigned m, unsigned row, int k0, bool ok) __attribute__((always_inline)) {
+        const unsigned at = (row * p.K + k0) * 2u + m;
+        if (VEC) return __builtin_bit_cast(v8h, buf_load16(r, at, ok && k0 < p.K));
+        unsigned d[4];
+        const bool whole = ok && k0 + 8 + (int)((at & 2u) >> 1) <= p.K;
+        load_unaligned<4>(r, at, whole, d);
+        v8h v = __builtin_bit_cast(v8h, (v4u){d[0], d[1], d[2], d[3]});
+        if (!whole && ok && k0 < p.K) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = half_bits(buf_load2(r, at + e * 2, k0 + e < p.K));
+        }
+        return v;
+    };
 
     v4f acc[TT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) acc[tt] = (v4f){0.f, 0.f, 0.f, 0.f};
-
-    const int kp0 = sp * p.pairs_per_slice;
-    const int kp1 = min(kp0 + p.pairs_per_slice, p.pairs);
-    constexpr int UN = 8;                      // 64-column steps issued together
-    for (int kpb = kp0; kpb < kp1; kpb += UN) {
-        v8h a[UN][2];
+    const int all = (p.K + 63) / 64, per = (all + p.S - 1) / p.S, end = min((sp + 1) * per, all);
+    constexpr int UN = 4;                           // 64-column steps requested together
+    for (int s0 = sp * per + w; s0 < end; s0 += kProWaves * UN) {
+        v8h a[UN][2], b[TT][UN][2];
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            const int k0 = (kpb + u) * 64 + kb * 16;
-            const bool ok = j_ok && (kpb + u) < kp1;
-            a[u][0] = buf_load8h<VEC>(ar, (unsigned)j * p.K + k0, p.K - k0, ok);
-            a[u][1] = buf_load8h<VEC>(ar, (unsigned)j * p.K + k0 + 8, p.K - k0 - 8, ok);
+            const int k0 = (s0 + u * kProWaves) * 64 + kb * 16;      // (past d_in: zeros)
+            const bool ok = j < L.rank && s0 + u * kProWaves < end;
+            a[u][0] = eight(ar, mis, j, k0, ok);
+            a[u][1] = eight(ar, mis, j, k0 + 8, ok);
         }
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-            const int m = tt * 16 + i;
-            const bool m_ok = m < p.M;
-            v8h b[UN][2];
+        for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
-                const int k0 = (kpb + u) * 64 + kb * 16;
-                const bool ok = m_ok && (kpb + u) < kp1;
-                b[u][0] = buf_load8h<VEC>(xr, (unsigned)m * p.K + k0, p.K - k0, ok);
-                b[u][1] = buf_load8h<VEC>(xr, (unsigned)m * p.K + k0 + 8, p.K - k0 - 8, ok);
+                const int k0 = (s0 + u * kProWaves) * 64 + kb * 16;
+                const bool ok = tt * 16 + i < mrows && s0 + u * kProWaves < end;
+                b[tt][u][0] = eight(xr, xmis, tt * 16 + i, k0, ok);
+                b[tt][u][1] = eight(xr, xmis, tt * 16 + i, k0 + 8, ok);
             }
+        __builtin_amdgcn_sched_barrier(0);          // all requests before the first product waits
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
-                acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][0], b[u][0], acc[tt], 0, 0, 0);
-                acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][1], b[u][1], acc[tt], 0, 0, 0);
+                acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][0], b[tt][u][0], acc[tt], 0, 0, 0);
+                acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][1], b[tt][u][1], acc[tt], 0, 0, 0);
             }
-        }
     }
-    // acc[tt][v]: rank index rt*16 + 4*kb + v, token tt*16 + i  ->  hpart[sp][m][rp]
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        const int m = tt * 16 + i;
-        if (m < p.M)
-            *reinterpret_cast<v4f *>(L.hpart + ((size_t)sp * p.M + m) * L.rp + rt * 16 + 4 * kb) = acc[tt];
+    for (int tt = 0; tt < TT; ++tt) red[w][tt][l] = acc[tt];
+    __syncthreads();
+    if (w >= TT) return;
+    v4f h = red[0][w][l];
+#pragma unroll
+    for (int s = 1; s < kProWaves; ++s) h += red[s][w][l];
+    // element v: rank rt*16 + 4*kb + v of token m0 + 16*w + i (ranks past the rank: zeros)
+    if (w * 16 + i >= mrows) return;
+    const size_t at = (size_t)(m0 + w * 16 + i) * L.hstride + rt * 16 + 4 * kb;
+    if (p.S > 1) {
+        *reinterpret_cast<v4f *>(L.hpart + (size_t)sp * p.M * L.hstride + at) = h;
+    } else {
+        v4h o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[v] = (_Float16)silu(h[v]);
+        *reinterpret_cast<v4h *>(L.h16 + at) = o;
     }
 }
 
-template <int TT, bool VEC>
-__global__ __launch_bounds__(256) void prologue_kernel(ProParams p)
+template <int TT, int T, int NU, bool VEC>
+__global__ __launch_bounds__(kProThreads) void prologue_kernel(ProParams p)
 {
-    const int qb = p.quantize ? p.M : 0;            // workgroups that quantise a token each
-    if ((int)blockIdx.x < qb) {
-        quantize_row<VEC>(p, blockIdx.x);
+    const int ncorr = p.job_start[p.G];
+    if ((int)blockIdx.x < ncorr) {
+        corr_tile<TT, VEC>(p, blockIdx.x);
         return;
     }
-    const int job = ((int)blockIdx.x - qb) * 4 + (threadIdx.x >> 6);
-    if (job < p.job_start[p.G]) corr_partial<TT, VEC>(p, job);
-}
-
-// Adds the slices in order (deterministic), applies SiLU (Alg. 1 step 6) and writes fp16 rows of
-// hstride (zero padded): one thread per (layer, token, rank), all its slices requested at once.
-struct ReduceParams {
-    const float *hpart[kMaxGroup];
-    _Float16 *h16[kMaxGroup];
-    int rank[kMaxGroup], rp[kMaxGroup], start[kMaxGroup + 1];
-    int M, S, G;
-};
-__global__ __launch_bounds__(256) void hreduce_kernel(ReduceParams p)
-{
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    int g = 0;
-#pragma unroll
-    for (int i = 1; i < kMaxGroup; ++i)
-        if (i < p.G && e >= p.start[i]) g = i;
-    const int idx = e - p.start[g], rp = p.rp[g];
-    const bool inside = e < p.start[p.G];
-    const int j = idx % rp;
-    const rsrc_t hr = make_rsrc(p.hpart[g], (unsigned)p.S * p.M * rp * 4u);
-    float part[kMaxHSplit];
-#pragma unroll
-    for (int sp = 0; sp < kMaxHSplit; ++sp)
-        part[sp] = __builtin_bit_cast(float, buf_load4(hr, ((unsigned)idx + (unsigned)sp * p.M * rp) * 4u,
-                                                       inside && j < p.rank[g] && sp < p.S));
-    float h = part[0];
-#pragma unroll
-    for (int sp = 1; sp < kMaxHSplit; ++sp) h += part[sp];
-    if (inside) p.h16[g][idx] = (_Float16)silu(h);
+    const int q = (int)blockIdx.x - ncorr, per_set = (p.M + kProThreads / T - 1) / (kProThreads / T);
+    quantize_tokens<T, NU, VEC>(p, p.Q[q / per_set], (q % per_set) * (kProThreads / T));
 }
 
 }  // namespace
 
-int prologue_slices(int M, int K)
-{
-    const int pairs = (K + 63) / 64;
-    int s = (pairs + 7) / 8;                   // 512 columns per slice: one batch of loads
-    (void)M;
-    if (s > kMaxHSplit) s = kMaxHSplit;
-    if (s < 1) s = 1;
-    const int per = (pairs + s - 1) / s;
-    return (pairs + per - 1) / per;
-}
+int prologue_slices(int K) { return (K + 2047) / 2048; }
 
-hipError_t launch_prologue(ProParams &p, _Float16 *const *h16, hipStream_t st)
+hipError_t launch_prologue(ProParams &p, hipStream_t st)
 {
-    p.pairs = (p.K + 63) / 64;
-    p.S = prologue_slices(p.M, p.K);
-    p.pairs_per_slice = (p.pairs + p.S - 1) / p.S;
+    p.Kp = round_up(p.K, kTileCols);
+    const int tt = p.M <= 16 ? 1 : 2;
+    p.token_tiles = (p.M + 16 * tt - 1) / (16 * tt);
     int jobs = 0;
-    bool aligned = (reinterpret_cast<uintptr_t>(p.x) % 16) == 0;
+    bool vec = p.K % 8 == 0 && (reinterpret_cast<uintptr_t>(p.x) % 16) == 0;
     for (int g = 0; g < p.G; ++g) {
         p.job_start[g] = jobs;
         if (p.L[g].rank > 0) {
-            jobs += ((p.L[g].rank + 15) / 16) * p.S;
-            aligned = aligned && (reinterpret_cast<uintptr_t>(p.L[g].A) % 16) == 0;
+            jobs += ((p.L[g].rank + 15) / 16) * p.token_tiles * p.S;
+            vec = vec && (reinterpret_cast<uintptr_t>(p.L[g].A) % 16) == 0;
         }
     }
     p.job_start[p.G] = jobs;
-    const bool vec = (p.K % 8 == 0) && aligned;
-    const dim3 grid((p.quantize ? p.M : 0) + (jobs + 3) / 4), block(256);
+    // threads per token: one 16-column unit each, a wavefront up to 1024 columns, 256 threads up to 4096;
+    // two units and 512 threads up to 16384, beyond that the row is read once per pass
+    const int T = p.Kp <= 1024 ? 64 : (p.Kp <= 4096 ? 256 : 512);
+    const int per_wg = kProThreads / T;
+    const dim3 grid(jobs + p.NQ * ((p.M + per_wg - 1) / per_wg)), block(kProThreads);
     if (grid.x == 0) return hipSuccess;             // nothing to quantise, no correction path
-    const int tt = (p.M + 15) / 16;
-#define HGF_PRO(TT_)                                                                        \
-    if (vec) hipLaunchKernelGGL((prologue_kernel<TT_, true>), grid, block, 0, st, p);       \
-    else hipLaunchKernelGGL((prologue_kernel<TT_, false>), grid, block, 0, st, p)
-    switch (tt) {
-        case 1: HGF_PRO(1); break;
-        case 2: HGF_PRO(2); break;
-        case 3: HGF_PRO(3); break;
-        default: HGF_PRO(4); break;
+#define HGF_PRO(TT_, T_, NU_)                                                                               \
+    do {                                                                                                    \
+        if (vec) hipLaunchKernelGGL((prologue_kernel<TT_, T_, NU_, true>), grid, block, 0, st, p);          \
+        else hipLaunchKernelGGL((prologue_kernel<TT_, T_, NU_, false>), grid, block, 0, st, p);             \
+    } while (0)
+    if (tt == 1) {
+        if (T == 64) HGF_PRO(1, 64, 1);
+        else if (T == 256) HGF_PRO(1, 256, 1);
+        else HGF_PRO(1, 512, 2);
+    } else {
+        if (T == 64) HGF_PRO(2, 64, 1);
+        else if (T == 256) HGF_PRO(2, 256, 1);
+        else HGF_PRO(2, 512, 2);
     }
 #undef HGF_PRO
-    if (h16 == nullptr) return hipGetLastError();   // the consumer adds the slices itself
-    ReduceParams rp;
-    rp.M = p.M;
-    rp.S = p.S;
-    rp.G = p.G;
-    int total = 0;
-    for (int g = 0; g < kMaxGroup; ++g) {
-        rp.start[g] = total;
-        rp.hpart[g] = g < p.G ? p.L[g].hpart : nullptr;
-        rp.h16[g] = g < p.G ? h16[g] : nullptr;
-        rp.rank[g] = g < p.G ? p.L[g].rank : 0;
-        rp.rp[g] = g < p.G ? p.L[g].rp : 32;
-        if (g < p.G && p.L[g].rank > 0) total += p.M * p.L[g].rp;
-    }
-    rp.start[kMaxGroup] = total;
-    for (int g = p.G; g <= kMaxGroup; ++g) rp.start[g] = total;
-    if (total > 0) hipLaunchKernelGGL(hreduce_kernel, dim3((total + 255) / 256), dim3(256), 0, st, rp);
     return hipGetLastError();
 }
 
