@@ -151,10 +151,10 @@ typedef struct {
  *   acc_debug int32 [M, d_out] or NULL: receives the exact integer accumulators
  *             sum_k T[n,k] x_q[m,k] of step 3 (for parity tests)
  *
- * M <= 40 (and up to 64 for layers of few rows) runs the bandwidth-bound decode kernels (weights streamed once); larger M
- * runs the int8 MFMA prefill kernel.  Both give the same integers.  A layer with ln_gamma set
- * takes the fused LayerNorm quantiser as its prologue (one more launch than a layer without;
- * layers with a LayerNorm of their own never share a quantisation in hgf_stack_forward). */
+ * M <= 40, and any M whose 32 x 32 output tiles are about a chipful, runs the direct kernel (weights
+ * straight from memory into the MFMA); larger M runs the int8 MFMA prefill kernel.  Both give the same integers.  A layer with ln_gamma set
+ * takes the fused LayerNorm quantiser as its prologue (layers with a LayerNorm of their own never
+ * share a quantisation in hgf_stack_forward). */
 hgf_status hgf_linear_forward(const void *x_f16, int M, const hgf_layer *L, void *y_f16,
                               int32_t *acc_debug, void *workspace, size_t workspace_bytes,
                               void *stream);

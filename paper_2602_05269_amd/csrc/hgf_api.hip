@@ -67,8 +67,9 @@ hgf_status from_hip(hipError_t e) { return e == hipSuccess ? HGF_OK : HGF_ERR_DE
 // 13.3; 16 k-tiles, 768 tiles 17.5 / 19.4, 1152 21.0 / 19.6; 24 k-tiles, 1152 tiles 22.8 / 23.4, 1728
 // 26.3 / 23.9; 32 k-tiles, 1376 tiles 30.7 / 32.4; 64 k-tiles, 1536 tiles 39.9 / 43.8; 86 k-tiles, 1024
 // tiles 39.8 / 60.0, 2048 69.0 / 61.4.  A pair (two tiles per 32 rows of z) crosses a little earlier:
-// 16 k-tiles, 1024 tiles 18.7 / 20.1; 32 k-tiles, 1376 tiles 34.9 / 33.0.  Up to 40 tokens the direct
-// path takes every group.
+// 16 k-tiles, 1024 tiles 18.7 / 20.1; 32 k-tiles, 1376 tiles 34.9 / 33.0.  With a LayerNorm the prefill
+// path has one launch more, 6 us, for which the direct path does 6000 / (3 + k-tiles / 4) tiles.  Up to
+// 40 tokens the direct path takes every group.
 bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 {
     if (M <= 40) return true;
@@ -76,7 +77,7 @@ bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
     for (int g = 0; g < G; ++g) rbs += round_up(layers[g].d_out, kTileRows) / kTileRows;
     const long long tiles = rbs * ((M + 31) / 32);
     const int kt = round_up(layers[0].d_in, kTileCols) / kTileCols;
-    const int most = 900 + 15 * kt < 1800 ? 900 + 15 * kt : 1800;
+    const int most = (900 + 15 * kt < 1800 ? 900 + 15 * kt : 1800) + (layers[0].ln_gamma ? 24000 / (12 + kt) : 0);
     return tiles <= (pair ? most * 9 / 10 : most);
 }
 
@@ -119,12 +120,19 @@ struct ProfileScope {
     }
 };
 
+// `n` quantisations of M tokens: the first has the workspace's own buffers, the others its spare region.
+bool quantisations_fit(int M, int K, int n, const Workspace &ws)
+{
+    return (n - 1) * (align256((size_t)M * round_up(K, kTileCols)) + 2 * align256((size_t)M * 4)) <= ws.spare_bytes;
+}
+
 // Places what the prologue of a group writes (layers, sizes and NQ are set): the first quantisation
 // in the workspace's own buffers, those of the other LayerNorms of the group and, where d_in is cut,
 // the slices of A x in its spare region; d_in stays whole where they do not fit.  False: the
 // quantisations do not fit.
 bool place_prologue(ProParams &p, const hgf_layer *layers, const Workspace &ws)
 {
+    if (!quantisations_fit(p.M, p.K, p.NQ, ws)) return false;
     const size_t xq_bytes = align256((size_t)p.M * round_up(p.K, kTileCols)), word_bytes = align256((size_t)p.M * 4);
     size_t used = 0;
     for (int i = 0; i < p.NQ; ++i) {
@@ -141,7 +149,6 @@ bool place_prologue(ProParams &p, const hgf_layer *layers, const Workspace &ws)
         Q.rowsum = reinterpret_cast<int32_t *>(ws.spare + used + xq_bytes + word_bytes);
         used += xq_bytes + 2 * word_bytes;
     }
-    if (used > ws.spare_bytes) return false;
     p.S = prologue_slices(p.K);
     size_t each[kMaxGroup], slices = 0;
     for (int g = 0; g < p.G; ++g) slices += each[g] = p.L[g].rank > 0 ? align256((size_t)p.S * p.M * p.L[g].hstride * 4) : 0;
@@ -164,7 +171,7 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
                             float *amax_out = nullptr, int32_t *acc_debug2 = nullptr)
 {
     const int K = layers[0].d_in;
-    const bool ln = layers[0].ln_gamma != nullptr;   // (such a layer is always a group of its own)
+    const bool ln = layers[0].ln_gamma != nullptr;   // (then every layer of the group has one)
     bool fused = !pair && !ln && g_launch_level >= 1 && M <= kMaxFusedM && K % 8 == 0 && K <= kMaxFusedK && aligned16(x);
     for (int g = 0; g < G; ++g)
         fused = fused && (layers[g].rank == 0 ||
@@ -611,14 +618,27 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
 
     // groups: consecutive layers reading the same slot with the same d_in, none of which writes
-    // that slot or a slot another member writes
+    // that slot or a slot another member writes (all with a LayerNorm of their own, or none)
+    auto apart = [M](const void *a, int da, const void *b, int db) {      // [M, d] fp16 each
+        const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+        return pa + (size_t)M * da * 2 <= pb || pb + (size_t)M * db * 2 <= pa;
+    };
     struct Group { int first, G; bool stackable; };
     std::vector<Group> groups;
     for (int i = 0; i < n_layers;) {
         int G = 1;
         while (i + G < n_layers && G < kMaxGroup) {
             const hgf_layer &C = layers[i + G];
-            bool ok = C.src_slot == layers[i].src_slot && C.d_in == layers[i].d_in && !C.ln_gamma && !layers[i].ln_gamma;
+            bool ok = C.src_slot == layers[i].src_slot && C.d_in == layers[i].d_in &&
+                      (C.ln_gamma != nullptr) == (layers[i].ln_gamma != nullptr);
+            // layers with LayerNorms need a quantisation each: the direct path's prologue makes them in one launch
+            // (and not where slots share memory: one after the other such layers see each other's outputs)
+            if (ok && C.ln_gamma) {
+                ok = takes_direct_path(M, layers + i, G + 1, false) && quantisations_fit(M, C.d_in, G + 1, ws);
+                for (int j = i; ok && j < i + G; ++j)
+                    ok = apart(slots[layers[j].dst_slot], layers[j].d_out, slots[C.src_slot], C.d_in) &&
+                         apart(slots[layers[j].dst_slot], layers[j].d_out, slots[C.dst_slot], C.d_out);
+            }
             for (int j = i; ok && j < i + G; ++j) ok = layers[j].dst_slot != C.dst_slot;
             if (!ok) break;
             ++G;

@@ -106,3 +106,30 @@ def test_layernorm_paths(M, K, N, r):
     ref = g.oracle(c["x"], dense=True)
     assert np.array_equal(acc, ref["acc"]), "int32 accumulators differ from the oracle"
     assert_close_fp16(y, ref["y"])
+
+
+@pytest.mark.parametrize("M,K,r", [(3, 100, 8), (40, 1365, 16), (500, 512, 32), (33, 3000, 24), (6, 512, 0)])
+@pytest.mark.parametrize("shared", [False, True])
+def test_layernorm_layers_of_one_input(M, K, r, shared):
+    """Three layers with LayerNorms of their own read one slot (quantised together where the workspace
+    has room: not with rank 0); with shared memory the first one's output slot is the input itself, which
+    the two others then read."""
+    ws = hb.Workspace(M, K, max(K, 520), r)
+    widths = (K if shared else 520, 96, 33)
+    slots, cases, layers = [None] * 4, [], []
+    for i, N in enumerate(widths):
+        c = synth.make_custom(8800 + M + 7 * i, M, K, N, max(r, 1), act="student_t4", lora_std=0.02, w_std=0.05)
+        if i == 0:
+            x = c["x"]
+            slots[0] = dev(x)
+        g = LnLayer(c, ws, seed=i + K, rank0=r == 0, with_beta=i != 1)
+        g.layer.c.src_slot, g.layer.c.dst_slot, g.layer.c.ln_eps = 0, i + 1, 1e-5
+        slots[i + 1] = slots[0] if shared and i == 0 else torch.zeros((M, N), dtype=torch.float16, device="cuda")
+        cases.append(g)
+        layers.append(g.layer)
+    hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
+    torch.cuda.synchronize()
+    out = [s.cpu().numpy() for s in slots]
+    assert_close_fp16(out[1], cases[0].oracle(x, dense=True)["y"], "layer 0")
+    for i in (1, 2):
+        assert_close_fp16(out[i + 1], cases[i].oracle(out[0], dense=True)["y"], f"layer {i}")
