@@ -168,11 +168,11 @@ bool place_prologue(ProParams &p, const hgf_layer *layers, const Workspace &ws)
 // per-token max of its magnitude, acc_debug2 (nullable) the up projection's accumulators.
 hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G, void *const *ys,
                             int32_t *acc_debug, const Workspace &ws, hipStream_t st, bool pair = false,
-                            float *amax_out = nullptr, int32_t *acc_debug2 = nullptr)
+                            float *amax_out = nullptr, int32_t *acc_debug2 = nullptr, bool base3 = false)
 {
     const int K = layers[0].d_in;
     const bool ln = layers[0].ln_gamma != nullptr;   // (then every layer of the group has one)
-    bool fused = !pair && !ln && g_launch_level >= 1 && M <= kMaxFusedM && K % 8 == 0 && K <= kMaxFusedK && aligned16(x);
+    bool fused = !pair && !ln && !base3 && g_launch_level >= 1 && M <= kMaxFusedM && K % 8 == 0 && K <= kMaxFusedK && aligned16(x);
     for (int g = 0; g < G; ++g)
         fused = fused && (layers[g].rank == 0 ||
                           (layers[g].rank % 8 == 0 && aligned16(layers[g].A_f16) && aligned16(layers[g].B_f16) &&
@@ -214,6 +214,7 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
     pp.K = K;
     pp.G = G;
     pp.NQ = ln ? G : 1;
+    pp.base3 = base3 ? 1 : 0;
     for (int g = 0; g < G; ++g) {
         const hgf_layer &L = layers[g];
         pp.L[g].A = reinterpret_cast<const _Float16 *>(L.A_f16);
@@ -222,8 +223,15 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
         pp.L[g].hstride = h_stride(L.rank > 0 ? L.rank : 1);
     }
     if (!place_prologue(pp, layers, ws)) return HGF_ERR_WORKSPACE;
+    if (base3) {
+        // x_q is whole units of 80 columns here, up to M * 79 bytes past the end of its region (M <= 4): over
+        // s_x and rowsum (256 bytes each), which move to the SiLU(A x) of the group's layers that there are not
+        pp.Q[0].s_x = reinterpret_cast<float *>(reinterpret_cast<char *>(ws.h16) + ws.h16_each);
+        pp.Q[0].rowsum = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(ws.h16) + 2 * ws.h16_each);
+    }
     DecodeParams dp;
     dp.S = pp.S;
+    dp.base3 = pp.base3;
     dp.M = M;
     dp.G = G;
     dp.pair = pair ? 1 : 0;
@@ -543,23 +551,10 @@ hgf_status hgf_linear_forward_b3(const void *x_f16, int M, const hgf_layer *L, v
     if (!aligned16(workspace)) return HGF_ERR_ALIGN;
     const Workspace ws = carve_workspace(workspace, M, L->d_in, L->d_out, L->rank);
     if (workspace_bytes < ws.bytes) return HGF_ERR_WORKSPACE;
-    if (L->ln_gamma || !b3_fits(M, L->d_in, L->rank)) return HGF_ERR_UNSUPPORTED;
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    // steps 1, 2, 5, 6 of Algorithm 1: the prologue (quantiser, SiLU(A x))
-    ProParams pp;
-    pp.x = reinterpret_cast<const _Float16 *>(x_f16);
-    pp.amax_zero = nullptr;
-    pp.M = M;
-    pp.K = L->d_in;
-    pp.G = 1;
-    pp.NQ = 1;
-    pp.L[0].A = reinterpret_cast<const _Float16 *>(L->A_f16);
-    pp.L[0].h16 = ws.h16;
-    pp.L[0].rank = L->rank;
-    pp.L[0].hstride = h_stride(L->rank > 0 ? L->rank : 1);
-    if (!place_prologue(pp, L, ws)) return HGF_ERR_WORKSPACE;
-    if (launch_prologue(pp, st) != hipSuccess) return HGF_ERR_DEVICE;
-    return from_hip(launch_b3_decode(L->W_packed, pp, M, *L, y_f16, acc_debug, st));
+    // up to four tokens (beyond them the 2-bit format is the faster one) of up to 20480 columns
+    if (L->ln_gamma || M > 4 || round_up(L->d_in, kB3Cols) > 20480) return HGF_ERR_UNSUPPORTED;
+    void *ys[1] = {y_f16};
+    return run_decode_group(x_f16, M, L, 1, ys, acc_debug, ws, reinterpret_cast<hipStream_t>(stream), false, nullptr, nullptr, true);
 }
 
 size_t hgf_static_scratch_bytes(void) { return kStaticScratchBytes; }

@@ -37,10 +37,47 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
 constexpr unsigned kOobStep = 0x80000000u;         // stays beyond every descriptor when step offsets are added
 
-template <int WR, int TG, int KW, int D, bool PAIR>
+// The int8 operands of five MFMAs from 16 bytes of base-3 codes, one digit of every byte each.  Bytes
+// are taken apart in pairs of 16 bits, whose products with these multipliers floor to the quotients by
+// 3, 9, 27 and 81 for every byte up to 242; digit i is quotient i - 3 quotient i+1, four at a time
+// (nothing is borrowed between bytes).  1.4 vector instructions per weight.
+typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+__device__ inline void base3_digits(v4u bytes, v4i (&digit)[5])
+{
+    auto halves = [](unsigned v) { return __builtin_bit_cast(v2us, v); };
+    auto word = [](v2us v) { return __builtin_bit_cast(unsigned, v); };
+    auto triple = [](unsigned v) {                  // (as a multiplication it would run at a quarter of the rate)
+        unsigned t;
+        asm("v_lshl_add_u32 %0, %1, 1, %1" : "=v"(t) : "v"(v));
+        return t;
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned b = bytes[i];
+        const v2us e = halves(b & 0x00ff00ffu), o = halves((b >> 8) & 0x00ff00ffu);
+        auto quotient = [&](unsigned short mul, int shift) {
+            return word((e * mul) >> (unsigned short)shift) | ((word(o * mul) >> (shift - 8)) & 0x7f007f00u);
+        };
+        const unsigned short m3 = 85;
+        const unsigned q1 = __builtin_amdgcn_perm(word(o * m3 + m3), word(e * m3 + m3), 0x07030501u);
+        const unsigned q2 = quotient(57, 9), q3 = quotient(19, 9), q4 = word((e * (unsigned short)203) >> (unsigned short)14) |
+                                                                        word((o * (unsigned short)203) >> (unsigned short)14) << 8;
+        digit[0][i] = (int)(b - triple(q1));
+        digit[1][i] = (int)(q1 - triple(q2));
+        digit[2][i] = (int)(q2 - triple(q3));
+        digit[3][i] = (int)(q3 - triple(q4));
+        digit[4][i] = (int)q4;
+    }
+}
+
+// B3: base-3 weights, rows of Kp / 5 bytes (Kp: a multiple of 80).  A k-tile is 32 bytes of every row =
+// 160 columns, a lane's 16 bytes are five MFMA operands (digit 0 of its bytes, digit 1, ...), and the
+// prologue has stored x_q to match.
+template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false>
 __global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
 {
     static_assert(!PAIR || WR == 2, "a pair is one row-block of each layer");
+    constexpr int NQ = B3 ? 5 : 4;                            // MFMAs per k-tile
     constexpr int TILES = (PAIR ? 1 : WR) * TG;               // output tiles of 32 rows x 32 tokens
     constexpr int PPW = 4 * TILES > KW ? 4 * TILES / KW : 1;  // quarter tiles a wavefront finishes (of one tile)
     static_assert(PPW <= 4, "a wavefront finishes quarters of one tile");
@@ -79,24 +116,36 @@ __global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
     for (int r = 0; r < WR; ++r) {
         const DecLayer &Lr = layer_of(r);
         const bool ok = rb_of(r) < Lr.RBn;
-        wr[r] = make_rsrc(Lr.packed + (size_t)(ok ? rb_of(r) : 0) * p.KT * 64, ok ? (unsigned)p.KT * kTileBytes : 0u);
+        if (B3) {
+            const unsigned row_bytes = (unsigned)p.Kp / 5;
+            wr[r] = make_rsrc(reinterpret_cast<const unsigned char *>(Lr.packed) + (size_t)(ok ? rb_of(r) : 0) * kTileRows * row_bytes,
+                              ok ? (unsigned)min(kTileRows, Lr.N - rb_of(r) * kTileRows) * row_bytes : 0u);
+        } else {
+            wr[r] = make_rsrc(Lr.packed + (size_t)(ok ? rb_of(r) : 0) * p.KT * 64, ok ? (unsigned)p.KT * kTileBytes : 0u);
+        }
     }
 #pragma unroll
     for (int tg = 0; tg < TG; ++tg) {
         const int rows = min(32, p.M - m0 - tg * 32);         // tokens of the group (may be <= 0)
         xr[tg] = make_rsrc(L.xq + (size_t)(rows > 0 ? m0 + tg * 32 : 0) * p.Kp, rows > 0 ? (unsigned)rows * p.Kp : 0u);
-        xstep[tg] = (unsigned)max(rows, 0) * 32u;             // bytes per 32 columns
-        xoff[tg] = jl < rows ? (unsigned)(hf * rows + jl) * 16u : kOobStep;
+        xstep[tg] = (unsigned)max(rows, 0) * (B3 ? 16u : 32u);    // bytes per MFMA (B3: of one half's tokens)
+        xoff[tg] = jl < rows ? (unsigned)(hf * (B3 ? NQ : 1) * rows + jl) * 16u : kOobStep;
     }
     v4u wq[D][WR];
-    v4u xq[D][TG][4];
+    v4u xq[D][TG][NQ];
+    const unsigned woff = B3 ? (unsigned)jl * ((unsigned)p.Kp / 5) + hf * 16u : l * 16u;
     auto request = [&](int d, int kt) __attribute__((always_inline)) {
+        // (B3: past the last k-tile lies the next row.  In the last tile the second half may be one too: its
+        // digits meet zeros, as x_q ends before)
 #pragma unroll
-        for (int r = 0; r < WR; ++r) wq[d][r] = buf_load16(wr[r], (unsigned)kt * kTileBytes + l * 16u);
+        for (int r = 0; r < WR; ++r)
+            wq[d][r] = B3 ? buf_load16(wr[r], (unsigned)kt * 32u + woff, kt < p.KT)
+                          : buf_load16(wr[r], (unsigned)kt * kTileBytes + woff);
 #pragma unroll
         for (int tg = 0; tg < TG; ++tg)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) xq[d][tg][q] = buf_load16(xr[tg], xoff[tg] + (unsigned)(kt * 4 + q) * xstep[tg]);
+            for (int q = 0; q < NQ; ++q)
+                xq[d][tg][q] = buf_load16(xr[tg], xoff[tg] + (unsigned)(kt * (B3 ? 2 * NQ : NQ) + q) * xstep[tg]);
     };
 #pragma unroll
     for (int d = 0; d < D; ++d) request(d, w + d * KW);
@@ -212,11 +261,16 @@ __global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             if (d > 0 && k0 + d * KW >= p.KT) break;
+            v4i digit[WR][5];
+            if constexpr (B3) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+                for (int r = 0; r < WR; ++r) base3_digits(wq[d][r], digit[r]);
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
 #pragma unroll
                 for (int r = 0; r < WR; ++r) {
-                    const v4i a = widen_codes(wq[d][r][q]);
+                    const v4i a = B3 ? digit[r][q] : widen_codes(wq[d][r][q & 3]);
 #pragma unroll
                     for (int tg = 0; tg < TG; ++tg)
                         acc[r][tg] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, __builtin_bit_cast(v4i, xq[d][tg][q]), acc[r][tg], 0, 0, 0);
@@ -316,7 +370,7 @@ __global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
     }
 }
 
-template <int WR, int TG, int KW, int D, bool PAIR>
+template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false>
 hipError_t launch_shape(DecodeParams &p, hipStream_t st)
 {
     int units = 0;
@@ -326,11 +380,11 @@ hipError_t launch_shape(DecodeParams &p, hipStream_t st)
     }
     for (int g = p.G; g <= kMaxGroup; ++g) p.wg_start[g] = units;
     const size_t lds = (size_t)KW * WR * TG * 4096 + (size_t)(WR + (PAIR ? 2 : 1) * TG) * p.hsteps * 1024;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<WR, TG, KW, D, PAIR>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<WR, TG, KW, D, PAIR, B3>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
     const int TU = (p.M + 32 * TG - 1) / (32 * TG);
-    hipLaunchKernelGGL((direct_kernel<WR, TG, KW, D, PAIR>), dim3((units + 7) / 8 * 8 * TU), dim3(64 * KW), lds, st, p);
+    hipLaunchKernelGGL((direct_kernel<WR, TG, KW, D, PAIR, B3>), dim3((units + 7) / 8 * 8 * TU), dim3(64 * KW), lds, st, p);
     return hipGetLastError();
 }
 
@@ -339,8 +393,8 @@ hipError_t launch_shape(DecodeParams &p, hipStream_t st)
 // Fills in the launch shape of a group whose layers, activations and outputs are set.
 hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
 {
-    p.Kp = round_up(d_in, kTileCols);
-    p.KT = p.Kp / kTileCols;
+    p.Kp = round_up(d_in, p.base3 ? kB3Cols : kTileCols);
+    p.KT = p.base3 ? (p.Kp + 2 * kB3Cols - 1) / (2 * kB3Cols) : p.Kp / kTileCols;
     p.hsteps = 0;
     int rbs = 0;
     for (int g = 0; g < p.G; ++g) {
@@ -357,6 +411,7 @@ hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
     // 35.0 for one row-block per workgroup, 30.7 for two; at 8 tokens, 688 tiles, 19.7 and 20.0; 7B-shape
     // down at 128 tokens, 512 tiles: two row-blocks with eight wavefronts 24.7, four wavefronts 27.0; at
     // 256 tokens 42.7 and 39.8).
+    if (p.base3) return launch_shape<1, 1, 4, 4, false, true>(p, st);
     const int groups = (p.M + 31) / 32, tiles = rbs * groups;
     if (p.pair) {
         if (p.G != 2 || p.L[0].N != p.L[1].N) return hipErrorInvalidValue;

@@ -181,7 +181,8 @@ struct ProLayer {
     int rank, hstride;
 };
 // One quantisation of the tokens.  xq: groups of 32 tokens (the last one smaller), 32 Kp bytes apart,
-// each [Kp / 16][tokens of the group][16]; one set per layer where LayerNorms differ.
+// each [Kp / 16][tokens of the group][16]; one set per layer where LayerNorms differ.  base3: Kp / 80
+// units, each [digit 0 .. 4][tokens][16 bytes]: byte g of digit i is column 80 unit + 5 g + i.
 struct ProTokens {
     int8_t *xq;
     float *s_x;
@@ -194,6 +195,7 @@ struct ProParams {
     float *amax_zero;    // nullable: [M] floats the quantising workgroups set to zero (a later kernel's atomic max)
     int M, K, Kp, G, NQ; // layers; quantisations
     int S;               // slices of d_in
+    int base3;           // x_q as the base-3 kernel reads it (M <= 32)
     int token_tiles;
     ProLayer L[kMaxGroup];
     ProTokens Q[kMaxGroup];
@@ -219,6 +221,7 @@ struct DecodeParams {
     int M, Kp, KT, G;
     int hsteps;              // 16-rank steps of the widest layer
     int S;                   // slices of A x
+    int base3;               // packed: base-3 rows
     DecLayer L[kMaxGroup];
     int wg_start[kMaxGroup + 1];   // running sum of the layers' row units
     // SwiGLU pair (G == 2, both layers of one shape): layer 0 (gate) and layer 1 (up); z = SiLU(y_gate) *
@@ -326,12 +329,10 @@ size_t diff_attn_workspace_bytes(int B, int L_max, int n_heads, int d_h);
 hipError_t launch_diff_attn(const void *q, const void *k, const void *v, const int32_t *lens, int B, int L_max,
                             int n_heads, int d_h, float lambda, void *out, void *workspace, hipStream_t st);
 
-// base-3 packing (five ternary weights per byte) and its few-token decode kernel
+// base-3 packing (five ternary weights per byte)
+constexpr int kB3Cols = 80;                            // columns of 16 packed bytes; rows are padded to whole ones
 size_t b3_packed_bytes(int d_out, int d_in);
 hipError_t launch_pack_b3(const float *W, int N, int K, const float *s_w, unsigned char *packed, hipStream_t st);
 hipError_t launch_unpack_b3(const unsigned char *packed, int N, int K, int8_t *T, hipStream_t st);
-bool b3_fits(int M, int K, int rank);
-hipError_t launch_b3_decode(const void *packed, const ProParams &pro, int M, const hgf_layer &L,
-                            void *y, int32_t *acc_debug, hipStream_t st);
 
 }  // namespace hgf

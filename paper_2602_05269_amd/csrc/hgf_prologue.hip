@@ -205,7 +205,15 @@ __device__ inline void quantize_tokens(const ProParams &p, const ProTokens &Q, i
                 }
                 o[d] = word;
             }
-            if (live && unit < units) *reinterpret_cast<v4u *>(out + (size_t)unit * rows * 16) = o;
+            if (p.base3) {                          // (every byte to its digit's piece)
+                if (live && unit < units) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const int col = unit * 16 + e, b = col / 5, digit = col - b * 5;
+                        Q.xq[(size_t)(((b >> 4) * 5 + digit) * p.M + m) * 16 + (b & 15)] = (int8_t)(o[e >> 2] >> (8 * (e & 3)));
+                    }
+                }
+            } else if (live && unit < units) *reinterpret_cast<v4u *>(out + (size_t)unit * rows * 16) = o;
         }
     }
     sum = wave_sum(sum);
@@ -332,7 +340,7 @@ int prologue_slices(int K) { return (K + 2047) / 2048; }
 
 hipError_t launch_prologue(ProParams &p, hipStream_t st)
 {
-    p.Kp = round_up(p.K, kTileCols);
+    p.Kp = round_up(p.K, p.base3 ? kB3Cols : kTileCols);
     const int tt = p.M <= 16 ? 1 : 2;
     p.token_tiles = (p.M + 16 * tt - 1) / (16 * tt);
     int jobs = 0;

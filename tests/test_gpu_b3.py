@@ -87,11 +87,29 @@ def test_b3_config4_full_size(proj, M, ws):
     g.check_forward(synth.make_activations(4, 0, proj, M), ws, dense=True)
 
 
+@pytest.mark.parametrize("M,K,N,r", [
+    # edges of a row's 16-byte pieces (80 columns), of a k-tile (160) and of a row-block, with a workspace of
+    # exactly this call's size (x_q in whole units of 80 columns is longer than in whole tiles of 128)
+    (4, 79, 31, 8), (3, 81, 32, 16), (4, 129, 33, 7), (1, 160, 95, 100), (2, 161, 65, 0), (4, 321, 40, 128),
+    # k-tiles per wavefront: one, five and more than are in flight; the longest row
+    (1, 640, 64, 16), (3, 3201, 33, 24), (4, 20480, 34, 128), (1, 20479, 32, 0),
+])
+def test_b3_edges(M, K, N, r):
+    c = synth.make_custom(9700 + M + K + N + r, M, K, N, max(r, 1), act="student_t3", lora_std=0.05)
+    ws = hb.Workspace(M, K, N, r)
+    B3Layer(c, ws, rank0=(r == 0)).check_forward(c["x"], ws)
+
+
 def test_b3_refuses_what_it_does_not_serve(ws):
     c = synth.make_custom(1, 5, 64, 64, 8)
     g = B3Layer(c, ws)
     with pytest.raises(hb.HgfError) as e:
         hb.hgf_linear_forward_b3(dev(c["x"]), g.layer, ws)
+    assert e.value.status == 4
+    rows = torch.full((hb.hgf_packed_weight_bytes_b3(1, 20481),), 121, dtype=torch.uint8, device="cuda")
+    long = hb.Layer(rows, g.s_w, 1, 20481)                # (more columns than it takes: refused before any launch)
+    with pytest.raises(hb.HgfError) as e:
+        hb.hgf_linear_forward_b3(torch.zeros((1, 20481), dtype=torch.float16, device="cuda"), long, hb.Workspace(1, 20481, 1, 0))
     assert e.value.status == 4
     assert hb.hgf_packed_weight_bytes_b3(11008, 4096) == 11008 * 832      # 820 bytes of digits per row, padded to 832
     assert hb.hgf_packed_weight_bytes_b3(11008, 4096) < 0.82 * hb.hgf_packed_weight_bytes(11008, 4096)
