@@ -62,23 +62,25 @@ hgf_status from_hip(hipError_t e) { return e == hipSuccess ? HGF_OK : HGF_ERR_DE
 
 // Which of the two paths a group of layers takes.  The prefill kernel's tiles are 256 rows by 64 or
 // 128 tokens and walk all of d_in with one workgroup each, so a group that does not fill the chip with
-// them costs about 11 + 0.5 k-tiles microseconds whatever its size; the direct path costs by its output
-// tiles of 32 x 32.  They cross at (us, direct / prefill): 4 k-tiles, 768 tiles 12.7 / 12.8, 2048 17.1 /
-// 13.3; 16 k-tiles, 768 tiles 17.5 / 19.4, 1152 21.0 / 19.6; 24 k-tiles, 1152 tiles 22.8 / 23.4, 1728
-// 26.3 / 23.9; 32 k-tiles, 1376 tiles 30.7 / 32.4; 64 k-tiles, 1536 tiles 39.9 / 43.8; 86 k-tiles, 1024
-// tiles 39.8 / 60.0, 2048 69.0 / 61.4.  A pair (two tiles per 32 rows of z) crosses a little earlier:
-// 16 k-tiles, 1024 tiles 18.7 / 20.1; 32 k-tiles, 1376 tiles 34.9 / 33.0.  With a LayerNorm the prefill
-// path has one launch more, 6 us, for which the direct path does 6000 / (3 + k-tiles / 4) tiles.  Up to
-// 40 tokens the direct path takes every group.
+// them costs about 10 + 0.55 k-tiles microseconds whatever its size; the direct path costs by its output
+// tiles of 32 x 32 and, for the preparation, by its tokens.  tiles + tokens at which they cross lies
+// between (us, direct / prefill): 4 k-tiles 2108 (11.5 / 12.4) and 3008 (13.1 / 12.6); 11 k-tiles 1512 (14.4
+// / 14.9) and 2252 (16.5 / 15.3); 16 k-tiles 1792 (18.0 / 19.0) and 1816 (19.5 / 18.7); 32 k-tiles 1880 (27.5 /
+// 28.4) and 2160 (31.0 / 28.7); 64 k-tiles 1816 (38.6 / 42.6) and 2400 (48.1 / 43.4); 86 k-tiles beyond 1600
+// (45.5 / 54.9).  Behind a LayerNorm the prefill path has one launch more: 4 k-tiles 4216 (18.5 / 18.7); 11
+// k-tiles beyond 3008 (22.6 / 25.5); 16, beyond 3048 (24.8 / 28.0); 64, beyond 2400 (61.0 / 74.0).  A pair
+// (two tiles per 32 rows of z) crosses between 1876 (13.2 / 14.1) and 2592 (18.9 / 14.7) at 4 k-tiles, 1632
+// (17.7 / 19.8) and 2176 (20.2 / 19.8) at 16, 1440 (28.1 / 29.5) and 2160 (36.5 / 30.5) at 32.  Up to 40
+// tokens the direct path takes every group.
 bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 {
     if (M <= 40) return true;
     long long rbs = 0;
     for (int g = 0; g < G; ++g) rbs += round_up(layers[g].d_out, kTileRows) / kTileRows;
     const long long tiles = rbs * ((M + 31) / 32);
-    const int kt = round_up(layers[0].d_in, kTileCols) / kTileCols;
-    const int most = (900 + 15 * kt < 1800 ? 900 + 15 * kt : 1800) + (layers[0].ln_gamma ? 24000 / (12 + kt) : 0);
-    return tiles <= (pair ? most * 9 / 10 : most);
+    const bool short_rows = layers[0].d_in <= 4 * kTileCols;
+    const int most = pair ? 1600 : (layers[0].ln_gamma ? (short_rows ? 4200 : 3000) : (short_rows ? 2400 : 1850));
+    return tiles + M <= most;
 }
 
 // Profiling aid: event pairs recorded around main-kernel launches, by kind (0 decode, 1 prefill).

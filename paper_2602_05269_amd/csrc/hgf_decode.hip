@@ -19,9 +19,9 @@
 //
 // Bound by HBM and, for small groups, latency.  Against a kernel that staged whole token rows in LDS
 // behind a barrier and let one wavefront finish a row-block (us per launch, 7B-shape down projection at
-// 64 tokens: 34.1 before, 12.5 with the tokens' operand from L2; 2048 -> 8192 twice at 16 tokens: 10.2
+// 64 tokens: 34.1 before, 13 with the tokens' operand from L2; 2048 -> 8192 twice at 16 tokens: 10.2
 // and 7.1).  With the prologue, per pass: 8 up-gate pairs and down projections of the 7B shape at 64
-// tokens 653 -> 449 us, 28 layers of d = 512 with LayerNorms at 500 tokens 516 -> 372 us.
+// tokens 653 -> 403 us, 28 layers of d = 512 with LayerNorms at 500 tokens 516 -> 200 us.
 //
 // SwiGLU pair: the "two row-blocks" of a workgroup are the same row-block of the gate and of the up
 // projection, so z = SiLU(y_gate) * y_up forms in registers.
@@ -73,8 +73,12 @@ __device__ inline void base3_digits(v4u bytes, v4i (&digit)[5])
 // B3: base-3 weights, rows of Kp / 5 bytes (Kp: a multiple of 80).  A k-tile is 32 bytes of every row =
 // 160 columns, a lane's 16 bytes are five MFMA operands (digit 0 of its bytes, digit 1, ...), and the
 // prologue has stored x_q to match.
+// The wavefronts per SIMD that the registers have to leave room for: grids are a few workgroups per compute
+// unit, and one more in residence can save a whole round (7B-shape up + gate at 64 tokens, 688 workgroups: 27
+// us with room for two per compute unit in registers and in LDS, 23 us with three).
+constexpr int direct_waves(int D) { return D == 1 ? 4 : 3; }
 template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false>
-__global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
+__global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(DecodeParams p)
 {
     static_assert(!PAIR || WR == 2, "a pair is one row-block of each layer");
     constexpr int NQ = B3 ? 5 : 4;                            // MFMAs per k-tile
@@ -152,11 +156,12 @@ __global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
 
     // ---- the epilogue's operands: rows of B and h as MFMA operands of 1 KiB (32 rows x 16 ranks) in LDS,
     //      dealt out over the wavefronts.  Ranks past the rank and rows past the end are zeros.
-    constexpr int kRedBytes = KW * WR * TG * 4096;
+    //      The same LDS takes the partial tiles at the end, when the corrections have been formed: what a
+    //      workgroup holds decides how many of them share a compute unit.
     constexpr int NB = WR;                                    // B blocks, then NL * TG h blocks
     const int NH = p.S > 1 ? 0 : NL * TG;
     const int JS = p.hsteps;                                  // 16-rank steps (of the wider layer of a pair)
-    unsigned char *const ops = lds + kRedBytes;
+    unsigned char *const ops = lds;
     for (int i = w; i < (NB + NH) * JS; i += KW) {
         const int blkno = i / JS, js = i - blkno * JS;
         const int j0 = js * 16 + hf * 8;
@@ -280,6 +285,32 @@ __global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
         }
     }
 
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wavefront's operands are in LDS
+    __syncthreads();
+    // ---- correction up-projection: corr[n,m] = sum_j B[n,j] h[m,j] on the f16 MFMA, of which the wavefront
+    //      keeps the quarters it finishes (a register array cannot be indexed by them: one of four is selected)
+    float cv[NL][PPW][4];
+#pragma unroll
+    for (int g = 0; g < NL; ++g) {
+        v16f corr = {};
+        const DecLayer &Lg = layer_of(g);
+        if (finishes)
+            for (int js = 0; js * 16 < Lg.rank; ++js) {
+                const v8h b = *reinterpret_cast<const v8h *>(ops + ((PAIR ? g : rt) * JS + js) * 1024 + l * 16);
+                const v8h h = *reinterpret_cast<const v8h *>(ops + ((NB + g * TG + tt) * JS + js) * 1024 + l * 16);
+                corr = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, h, corr, 0, 0, 0);
+            }
+#pragma unroll
+        for (int c = 0; c < PPW; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int q = piece0 + c;
+                cv[g][c][v] = PPW == 4 ? corr[4 * c + v]
+                                       : (q == 0 ? corr[v] : (q == 1 ? corr[4 + v] : (q == 2 ? corr[8 + v] : corr[12 + v])));
+            }
+    }
+    __syncthreads();                                          // everyone has read the operands
+
     // ---- the KW partial tiles meet in LDS (a tile as four pieces of 16 bytes per lane, piece by piece
     //      across the lanes: no bank conflicts)
     v4i *red = reinterpret_cast<v4i *>(lds);
@@ -291,22 +322,9 @@ __global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
             for (int c = 0; c < 4; ++c)
                 red[(((r * TG + tg) * KW + w) * 4 + c) * 64 + l] =
                     (v4i){acc[r][tg][4 * c], acc[r][tg][4 * c + 1], acc[r][tg][4 * c + 2], acc[r][tg][4 * c + 3]};
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wavefront's operands are in LDS
     __syncthreads();
     if (!finishes || nb >= L.N) return;
 
-    // ---- correction up-projection: corr[n,m] = sum_j B[n,j] h[m,j] on the f16 MFMA
-    v16f corr[NL];
-#pragma unroll
-    for (int g = 0; g < NL; ++g) {
-        corr[g] = (v16f){};
-        const DecLayer &Lg = layer_of(g);
-        for (int js = 0; js * 16 < Lg.rank; ++js) {
-            const v8h b = *reinterpret_cast<const v8h *>(ops + ((PAIR ? g : rt) * JS + js) * 1024 + l * 16);
-            const v8h h = *reinterpret_cast<const v8h *>(ops + ((NB + g * TG + tt) * JS + js) * 1024 + l * 16);
-            corr[g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, h, corr[g], 0, 0, 0);
-        }
-    }
     // ---- dequantise, gate, store.  Element v of quarter c is row 8c + 4hf + v of the tile, for the
     //      token of the lane.
     const int N = L.N;
@@ -324,17 +342,10 @@ __global__ __launch_bounds__(64 * KW) void direct_kernel(DecodeParams p)
 #pragma unroll
             for (int o = 1; o < KW; ++o) a[g] += part[o * 256];
             const float scale = s_x * s_w[g];
-            // (a register array cannot be indexed by the wavefront's quarter: one of four is selected)
-            float cv[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                if (PPW == 4) cv[v] = corr[g][4 * c + v];
-                else {
-                    const int q = piece0 + c;
-                    cv[v] = q == 0 ? corr[g][v] : (q == 1 ? corr[g][4 + v] : (q == 2 ? corr[g][8 + v] : corr[g][12 + v]));
-                }
                 a[g][v] -= rs;
-                y[g][v] = (float)a[g][v] * scale + tanhf(alpha[g][c][v]) * cv[v];
+                y[g][v] = (float)a[g][v] * scale + tanhf(alpha[g][c][v]) * cv[g][c][v];
             }
         }
         v4h o;
@@ -379,7 +390,8 @@ hipError_t launch_shape(DecodeParams &p, hipStream_t st)
         if (!PAIR || g == 0) units += PAIR ? p.L[g].RBn : (p.L[g].RBn + WR - 1) / WR;
     }
     for (int g = p.G; g <= kMaxGroup; ++g) p.wg_start[g] = units;
-    const size_t lds = (size_t)KW * WR * TG * 4096 + (size_t)(WR + (PAIR ? 2 : 1) * TG) * p.hsteps * 1024;
+    const size_t red = (size_t)KW * WR * TG * 4096, ops = (size_t)(WR + (PAIR ? 2 : 1) * TG) * p.hsteps * 1024;
+    const size_t lds = red > ops ? red : ops;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<WR, TG, KW, D, PAIR, B3>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
@@ -411,16 +423,21 @@ hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
     // 35.0 for one row-block per workgroup, 30.7 for two; at 8 tokens, 688 tiles, 19.7 and 20.0; 7B-shape
     // down at 128 tokens, 512 tiles: two row-blocks with eight wavefronts 24.7, four wavefronts 27.0; at
     // 256 tokens 42.7 and 39.8).
-    if (p.base3) return launch_shape<1, 1, 4, 4, false, true>(p, st);
+    // (4096 -> 11008 at one token, 344 row-blocks: two k-tiles in flight 10.6, four 11.2; eight wavefronts 11.0)
+    if (p.base3) return launch_shape<1, 1, 4, 2, false, true>(p, st);
     const int groups = (p.M + 31) / 32, tiles = rbs * groups;
     if (p.pair) {
         if (p.G != 2 || p.L[0].N != p.L[1].N) return hipErrorInvalidValue;
         // (7B-shape, 344 row-blocks at 8 tokens: four wavefronts 21.6, eight 26.4; 512 -> 1365, 43: 10.7 and 10.4)
-        return tiles > 512 ? launch_shape<2, 1, 4, 4, true>(p, st) : launch_shape<2, 1, 8, 3, true>(p, st);
+        return tiles > 512 ? launch_shape<2, 1, 4, 3, true>(p, st) : launch_shape<2, 1, 8, 3, true>(p, st);
     }
     if (groups == 1 || tiles <= 256)
-        return tiles <= 256 && p.KT >= 32 ? launch_shape<1, 1, 8, 4, false>(p, st) : launch_shape<1, 1, 4, 4, false>(p, st);
-    return tiles <= 640 ? launch_shape<2, 1, 8, 3, false>(p, st) : launch_shape<2, 1, 4, 4, false>(p, st);
+        return tiles <= 256 && p.KT >= 32 ? launch_shape<1, 1, 8, 3, false>(p, st) : launch_shape<1, 1, 4, 4, false>(p, st);
+    if (tiles <= 640) return launch_shape<2, 1, 8, 3, false>(p, st);
+    // (a wavefront with one k-tile has nothing to keep in flight behind it: registers for four workgroups
+    // per compute unit instead of two, 1024 of them in one round.  2048 tiles of four k-tiles: 8.7 us, where
+    // four in flight took 12.2)
+    return p.KT <= 4 ? launch_shape<2, 1, 4, 1, false>(p, st) : launch_shape<2, 1, 4, 3, false>(p, st);
 }
 
 }  // namespace hgf

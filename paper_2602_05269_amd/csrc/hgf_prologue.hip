@@ -12,11 +12,13 @@
 // one compute unit takes in only some 0.1 MB per microsecond (all of d_in = 11008 in a workgroup: 19 us
 // for 8 tokens, 32 us for 64), their slices leave as fp32 and the consumer adds them in order.
 // Bound by latency: the launch is one or two memory round trips (6 us for a group of the 7B shape at 8
-// tokens, 8.7 at 64, where all token tiles in one wavefront took 12.7).
+// tokens, 6.8 at 64, where all token tiles in one wavefront took 12.7).
 //
-// Quantiser: 64, 256 or 512 threads per token by the row's length, the row in registers between the
+// Quantiser: 64 to 512 threads per token by the row's length, the row in registers between the
 // passes.  x_q is stored the way the consumer's MFMA operand wants it: per group of up to 32 tokens
 // 16-byte pieces of 16 columns, [d_in / 16][token], so that a wavefront's request is contiguous.
+// (500 tokens of 1408 columns behind a LayerNorm: 13.2 us with 256 threads per token and gamma and beta
+// requested behind the reductions, 7.4 with 128 and requested with the row.)
 #include "hgf_internal.h"
 
 namespace hgf {
@@ -106,7 +108,9 @@ __device__ inline void quantize_tokens(const ProParams &p, const ProTokens &Q, i
     };
     const bool ln = Q.gamma != nullptr;
     float mu = 0.f, rstd = 0.f;
-    auto normalise = [&](int chunk) __attribute__((always_inline)) {
+    // gamma and beta of a chunk (a row in registers has them requested with it, ahead of the reductions)
+    v4f ga[NU][4], be[NU][4];
+    auto load_norm = [&](int chunk) __attribute__((always_inline)) {
         const rsrc_t gr = make_rsrc(Q.gamma, (unsigned)p.K * 4u), br = make_rsrc(Q.beta, Q.beta ? (unsigned)p.K * 4u : 0u);
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
@@ -115,27 +119,44 @@ __device__ inline void quantize_tokens(const ProParams &p, const ProTokens &Q, i
             for (int q = 0; q < 4; ++q) {
                 // (gamma and beta start at any multiple of four bytes, which is all the request asks for)
                 const bool whole = col + q * 4 + 4 <= p.K;
-                v4f ga = __builtin_bit_cast(v4f, buf_load16(gr, (unsigned)(col + q * 4) * 4u, whole));
-                v4f be = __builtin_bit_cast(v4f, buf_load16(br, (unsigned)(col + q * 4) * 4u, whole));
-                if (!whole && col + q * 4 < p.K) {
+                ga[u][q] = __builtin_bit_cast(v4f, buf_load16(gr, (unsigned)(col + q * 4) * 4u, whole));
+                be[u][q] = __builtin_bit_cast(v4f, buf_load16(br, (unsigned)(col + q * 4) * 4u, whole));
+            }
+        }
+        if (p.K % 4 == 0) return;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int col = ((chunk * NU + u) * T + t) * 16;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (col + q * 4 + 4 > p.K && col + q * 4 < p.K) {
 #pragma unroll
                     for (int e = 0; e < 3; ++e) {
-                        ga[e] = __builtin_bit_cast(float, buf_load4(gr, (unsigned)(col + q * 4 + e) * 4u, col + q * 4 + e < p.K));
-                        be[e] = __builtin_bit_cast(float, buf_load4(br, (unsigned)(col + q * 4 + e) * 4u, col + q * 4 + e < p.K));
+                        ga[u][q][e] = __builtin_bit_cast(float, buf_load4(gr, (unsigned)(col + q * 4 + e) * 4u, col + q * 4 + e < p.K));
+                        be[u][q][e] = __builtin_bit_cast(float, buf_load4(br, (unsigned)(col + q * 4 + e) * 4u, col + q * 4 + e < p.K));
                     }
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {       // in exactly this order, one rounding each; 0 past the row
-                    float y = v[u][q * 4 + e] - mu;
-                    y = y * rstd;
-                    y = y * ga[e];
-                    y = y + be[e];
-                    v[u][q * 4 + e] = col + q * 4 + e < p.K ? y : 0.f;
                 }
             }
         }
     };
-    if (chunks == 1) load(0);
+    auto normalise = [&](int chunk) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int col = ((chunk * NU + u) * T + t) * 16;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {          // in exactly this order, one rounding each; 0 past the row
+                float y = v[u][e] - mu;
+                y = y * rstd;
+                y = y * ga[u][e / 4][e % 4];
+                y = y + be[u][e / 4][e % 4];
+                v[u][e] = col + e < p.K ? y : 0.f;
+            }
+        }
+    };
+    if (chunks == 1) {
+        load(0);
+        if (ln) load_norm(0);
+    }
     if (ln) {
         // mean and mean squared deviation in fp64, each rounded once
         double s = 0.0;
@@ -167,7 +188,10 @@ __device__ inline void quantize_tokens(const ProParams &p, const ProTokens &Q, i
     for (int c = 0; c < chunks; ++c) {
         if (chunks > 1) {
             load(c);
-            if (ln) normalise(c);
+            if (ln) {
+                load_norm(c);
+                normalise(c);
+            }
         }
 #pragma unroll
         for (int u = 0; u < NU; ++u)
@@ -188,7 +212,10 @@ __device__ inline void quantize_tokens(const ProParams &p, const ProTokens &Q, i
     for (int c = 0; c < chunks; ++c) {
         if (chunks > 1) {
             load(c);
-            if (ln) normalise(c);
+            if (ln) {
+                load_norm(c);
+                normalise(c);
+            }
         }
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
@@ -341,7 +368,11 @@ int prologue_slices(int K) { return (K + 2047) / 2048; }
 hipError_t launch_prologue(ProParams &p, hipStream_t st)
 {
     p.Kp = round_up(p.K, p.base3 ? kB3Cols : kTileCols);
-    const int tt = p.M <= 16 ? 1 : 2;
+    // One token tile per workgroup while the workgroups find room side by side (a compute unit takes in 32
+    // rows instead of 48: 64 tokens of 4096 columns, 128 ranks: 6.8 us against 8.3), two where there are many
+    int tiles = 0;
+    for (int g = 0; g < p.G; ++g) tiles += (p.L[g].rank + 15) / 16;
+    const int tt = p.M <= 16 || tiles * ((p.M + 15) / 16) * p.S <= 512 ? 1 : 2;
     p.token_tiles = (p.M + 16 * tt - 1) / (16 * tt);
     int jobs = 0;
     bool vec = p.K % 8 == 0 && (reinterpret_cast<uintptr_t>(p.x) % 16) == 0;
@@ -353,9 +384,10 @@ hipError_t launch_prologue(ProParams &p, hipStream_t st)
         }
     }
     p.job_start[p.G] = jobs;
-    // threads per token: one 16-column unit each, a wavefront up to 1024 columns, 256 threads up to 4096;
-    // two units and 512 threads up to 16384, beyond that the row is read once per pass
-    const int T = p.Kp <= 1024 ? 64 : (p.Kp <= 4096 ? 256 : 512);
+    // threads per token: one 16-column unit each, a wavefront up to 1024 columns, 128 threads up to 2048, 256
+    // up to 4096; two units and 512 threads up to 16384, beyond that the row is read once per pass.  (The
+    // tokens of a workgroup lie side by side in x_q, so fewer threads per token also store longer pieces)
+    const int T = p.Kp <= 1024 ? 64 : (p.Kp <= 2048 ? 128 : (p.Kp <= 4096 ? 256 : 512));
     const int per_wg = kProThreads / T;
     const dim3 grid(jobs + p.NQ * ((p.M + per_wg - 1) / per_wg)), block(kProThreads);
     if (grid.x == 0) return hipSuccess;             // nothing to quantise, no correction path
@@ -366,10 +398,12 @@ hipError_t launch_prologue(ProParams &p, hipStream_t st)
     } while (0)
     if (tt == 1) {
         if (T == 64) HGF_PRO(1, 64, 1);
+        else if (T == 128) HGF_PRO(1, 128, 1);
         else if (T == 256) HGF_PRO(1, 256, 1);
         else HGF_PRO(1, 512, 2);
     } else {
         if (T == 64) HGF_PRO(2, 64, 1);
+        else if (T == 128) HGF_PRO(2, 128, 1);
         else if (T == 256) HGF_PRO(2, 256, 1);
         else HGF_PRO(2, 512, 2);
     }

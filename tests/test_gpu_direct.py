@@ -33,6 +33,8 @@ def _one(M, K, N, r, act="student_t3", rank0=False):
     (70, 520, 3000, 20), (130, 264, 4128, 16), (200, 2056, 2999, 64),
     # slices of d_in for A x: 2, 3, 5 and 9 of them, the last one ragged; rows at odd addresses
     (7, 2049, 64, 16), (6, 4097, 33, 32), (20, 10001, 40, 128), (5, 16500, 32, 8), (9, 1365, 512, 16), (50, 4095, 70, 15),
+    # two token tiles per workgroup of A x (more than 512 workgroups otherwise), each quantiser width
+    (1050, 130, 32, 128), (1040, 1416, 40, 128), (1040, 2056, 32, 120), (530, 4104, 33, 128),
     # a row longer than what the quantiser keeps in registers
     (6, 16640, 40, 24), (5, 33001, 32, 8),
 ])
@@ -41,8 +43,8 @@ def test_direct_path_edges(M, K, N, r):
 
 
 @pytest.mark.parametrize("M,K,N,r", [
-    (300, 1365, 4096, 32), (330, 256, 3000, 16), (1000, 4104, 2048, 8), (1000, 8200, 2048, 16), (1000, 16392, 2048, 8),
-    (700, 512, 2100, 0),
+    (600, 1365, 4096, 32), (900, 256, 3000, 16), (1000, 4104, 2048, 8), (1000, 8200, 2048, 16), (1000, 16392, 2048, 8),
+    (1000, 512, 2100, 0),
 ])
 def test_prefill_path(M, K, N, r):
     """Sizes beyond the direct path: the three register depths of the prefill quantiser, ragged row and
@@ -50,10 +52,10 @@ def test_prefill_path(M, K, N, r):
     _one(M, K, N, r, act="student_t4")
 
 
-@pytest.mark.parametrize("M", [150, 1300])
+@pytest.mark.parametrize("M", [150, 2000])
 def test_groups_of_mixed_layers(M):
     """Four layers of mixed ranks and ragged d_out read one slot, on the direct path (150 tokens) and on
-    the prefill path (1300; rank 64 pads to another width and takes a launch of its own): against the
+    the prefill path (2000; rank 64 pads to another width and takes a launch of its own): against the
     oracle."""
     K = 384
     shapes = [(300, 16), (256, 24), (40, 32), (128, 64)]
@@ -79,7 +81,7 @@ def test_groups_of_mixed_layers(M):
     # direct: eight and four wavefronts, ragged rows of the last row-block, sliced A x, one rank zero
     (33, 130, 65, 24, 8), (40, 2500, 300, 16, 40), (50, 2500, 300, 16, 24), (64, 300, 4500, 8, 0), (10, 9000, 70, 0, 128),
     # prefill
-    (300, 1365, 2050, 32, 0), (330, 384, 2100, 0, 0), (400, 4104, 2000, 16, 24),
+    (400, 1365, 2050, 32, 0), (330, 384, 2100, 0, 0), (400, 4104, 2000, 16, 24),
 ])
 def test_pair_paths(M, K, N, rg, ru):
     ws = hb.Workspace(M, K, N, max(rg, ru, 1))
@@ -94,10 +96,10 @@ def test_pair_paths(M, K, N, rg, ru):
 
 
 @pytest.mark.parametrize("M,K,N,r", [
-    # direct: a wavefront, 256 and 512 threads per token, rows read once per pass, odd rows
-    (70, 96, 40, 8), (9, 1030, 64, 16), (6, 4097, 33, 32), (5, 9001, 70, 8), (6, 16640, 40, 24), (5, 33001, 32, 0),
+    # direct: a wavefront, 128, 256 and 512 threads per token, rows read once per pass, odd rows
+    (70, 96, 40, 8), (9, 1030, 64, 16), (6, 2048, 33, 24), (6, 4097, 33, 32), (5, 9001, 70, 8), (6, 16640, 40, 24), (5, 33001, 32, 0),
     # prefill
-    (300, 1365, 4096, 32), (700, 512, 2100, 0),
+    (900, 1365, 4096, 32), (1900, 512, 2100, 0),
 ])
 def test_layernorm_paths(M, K, N, r):
     c = synth.make_custom(8600 + M + K + N + r, M, K, N, max(r, 1), act="student_t3", lora_std=0.05)
