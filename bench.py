@@ -420,8 +420,7 @@ def main() -> int:
             sm = time_steps(make_runner(wm, ws, use_graph), few, 2)
             c = hbm(wm.bytes / args.blocks, sm / args.blocks)
             c["path"] = "whole-stack launches (stack_kernel)" if M <= 4 else \
-                        "two-launch decode (prologue_kernel, decode_kernel)" if M <= 40 else \
-                        "up + gate: prefill path (prepare_kernel, prefill_kernel); down: two-launch decode"
+                        "direct path (prologue_kernel, direct_kernel)"
             cases[f"config4_block_M{M}_cold"] = c
             del wm
 
