@@ -217,6 +217,7 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
     pp.G = G;
     pp.NQ = ln ? G : 1;
     pp.base3 = base3 ? 1 : 0;
+    pp.by_rows = 0;
     for (int g = 0; g < G; ++g) {
         const hgf_layer &L = layers[g];
         pp.L[g].A = reinterpret_cast<const _Float16 *>(L.A_f16);
@@ -271,23 +272,45 @@ hgf_status run_large_group(const void *x, int M, const hgf_layer *layers, int G,
 {
     const _Float16 *xh = reinterpret_cast<const _Float16 *>(x);
     const int K = layers[0].d_in;
+    const bool ln = layers[0].ln_gamma != nullptr;   // (here such a layer is always a group of its own)
     const _Float16 *A[kMaxGroup];
     _Float16 *h16[kMaxGroup];
     int rank[kMaxGroup];
+    bool whole_rows = K % 8 == 0;                    // rows of x and A of whole 16-byte pieces
     for (int g = 0; g < G; ++g) {
         A[g] = reinterpret_cast<const _Float16 *>(layers[g].A_f16);
         rank[g] = layers[g].rank;
         h16[g] = reinterpret_cast<_Float16 *>(reinterpret_cast<char *>(ws.h16) + ws.h16_each * g);
+        whole_rows = whole_rows && (rank[g] == 0 || aligned16(A[g]));
     }
-    if (pair_out && pair_out->amax_out &&
-        launch_zero_words(pair_out->amax_out, (size_t)M, st) != hipSuccess)
-        return HGF_ERR_DEVICE;
-    const bool ln = layers[0].ln_gamma != nullptr;   // (such a layer is always a group of its own)
-    if (ln && launch_ln_quantize(xh, M, K, layers[0].ln_gamma, layers[0].ln_beta, layers[0].ln_eps, ws.xq, ws.s_x,
-                                 ws.rowsum, st) != hipSuccess)
-        return HGF_ERR_DEVICE;
-    if (launch_corr_down(xh, M, K, G, A, rank, h16, ln ? nullptr : ws.xq, ws.s_x, ws.rowsum, st) != hipSuccess)
-        return HGF_ERR_DEVICE;
+    // The direct path's prologue prepares rows that are not whole 16-byte pieces (one thread per (token, rank)
+    // before: 1365 -> 2048, 32 ranks, 1000 tokens 161 us with the main kernel, 17 now; 4097 -> 4096 744 and 40)
+    // and, as one launch instead of two, what stands behind a LayerNorm up to 2^23 elements (us, two launches /
+    // one: 512 x 4096 59.2 / 45.4, 2048 x 3072 54.7 / 51.6, 2048 x 4096 131.3 / 133.4, 2048 x 8192 115.3 / 134.9).
+    // Otherwise prepare_kernel's larger tiles of A x are the better ones (2048 x 3072: 35.4 against 44.3).
+    if (!whole_rows || (ln && (long long)M * K < (1 << 23))) {
+        ProParams pp;
+        pp.x = xh;
+        pp.amax_zero = pair_out ? pair_out->amax_out : nullptr;
+        pp.M = M;
+        pp.K = K;
+        pp.G = G;
+        pp.NQ = 1;
+        pp.S = 1;
+        pp.base3 = 0;
+        pp.by_rows = 1;
+        pp.Q[0] = {ws.xq, ws.s_x, ws.rowsum, layers[0].ln_gamma, layers[0].ln_beta, layers[0].ln_eps};
+        for (int g = 0; g < G; ++g) pp.L[g] = {A[g], h16[g], nullptr, rank[g], h_stride(rank[g] > 0 ? rank[g] : 1)};
+        if (launch_prologue(pp, st) != hipSuccess) return HGF_ERR_DEVICE;
+    } else {
+        if (pair_out && pair_out->amax_out && launch_zero_words(pair_out->amax_out, (size_t)M, st) != hipSuccess)
+            return HGF_ERR_DEVICE;
+        if (ln && launch_ln_quantize(xh, M, K, layers[0].ln_gamma, layers[0].ln_beta, layers[0].ln_eps, ws.xq, ws.s_x,
+                                     ws.rowsum, st) != hipSuccess)
+            return HGF_ERR_DEVICE;
+        if (launch_corr_down(xh, M, K, G, A, rank, h16, ln ? nullptr : ws.xq, ws.s_x, ws.rowsum, st) != hipSuccess)
+            return HGF_ERR_DEVICE;
+    }
     ProfileScope prof(1, st);
     return from_hip(launch_prefill(ws, h16, M, layers, G, ys, acc_debug, st, pair_out));
 }

@@ -22,7 +22,7 @@ namespace {
 
 struct CorrParams {
     const _Float16 *x;
-    const _Float16 *A;                          // the layer of a ragged launch; of a grouped launch: A4[g]
+    const _Float16 *A;                          // (set from A4 and so on inside a workgroup)
     _Float16 *h16;
     int M, K, rank, hstride;
     int steps;                                  // stretches of KC columns
@@ -256,27 +256,12 @@ __global__ __launch_bounds__(256) void prepare_kernel(CorrParams p, QuantParams 
     }
 }
 
-// d_in % 8 != 0 (rows not 16-byte aligned): one thread per (token, rank) pair with plain
-// loads.  Slow and simple, for odd shapes only.
-__global__ __launch_bounds__(256) void corr_down_ragged_kernel(CorrParams p)
-{
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)p.M * p.hstride) return;
-    const int m = (int)(idx / p.hstride), j = (int)(idx % p.hstride);
-    float h = 0.f;
-    if (j < p.rank) {
-        const _Float16 *xrow = p.x + (size_t)m * p.K, *arow = p.A + (size_t)j * p.K;
-        for (int k = 0; k < p.K; ++k) h += (float)arow[k] * (float)xrow[k];
-        h = silu(h);
-    }
-    p.h16[idx] = (_Float16)h;
-}
-
 }  // namespace
 
 // Layers 0..G-1 read the same x; layer g's result goes to h16[g] ([M, h_stride(rank[g])] fp16).
 // With xq != nullptr the quantised activations, their scales and sums are produced as well --
-// in the same launch where the shapes allow it, by launch_quantize before otherwise.
+// in the same launch up to 16384 columns, by launch_quantize before otherwise.  Rows are whole 16-byte
+// pieces (d_in % 8 == 0, x and A 16-byte aligned).
 hipError_t launch_corr_down(const _Float16 *x, int M, int K, int G, const _Float16 *const *A, const int *rank,
                             _Float16 *const *h16, int8_t *xq, float *s_x, int32_t *rowsum, hipStream_t st)
 {
@@ -284,24 +269,10 @@ hipError_t launch_corr_down(const _Float16 *x, int M, int K, int G, const _Float
     p.x = x;
     p.M = M;
     p.K = K;
-    bool vec = (K % 8 == 0) && (reinterpret_cast<uintptr_t>(x) % 16 == 0);
-    for (int g = 0; g < G; ++g) vec = vec && (rank[g] == 0 || reinterpret_cast<uintptr_t>(A[g]) % 16 == 0);
-    const bool together = vec && xq != nullptr && K <= 512 * 32;
+    const bool together = xq != nullptr && K <= 512 * 32;
     if (xq != nullptr && !together) {
         const hipError_t e = launch_quantize(x, M, K, xq, s_x, rowsum, st);
         if (e != hipSuccess) return e;
-    }
-    if (!vec) {
-        for (int g = 0; g < G; ++g) {
-            if (rank[g] == 0) continue;
-            p.A = A[g];
-            p.h16 = h16[g];
-            p.rank = rank[g];
-            p.hstride = h_stride(rank[g]);
-            const size_t n = (size_t)M * p.hstride;
-            hipLaunchKernelGGL(corr_down_ragged_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p);
-        }
-        return hipGetLastError();
     }
     int tiles = 0;
     p.G = G;

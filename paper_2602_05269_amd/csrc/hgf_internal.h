@@ -196,6 +196,7 @@ struct ProParams {
     int M, K, Kp, G, NQ; // layers; quantisations
     int S;               // slices of d_in
     int base3;           // x_q as the base-3 kernel reads it (M <= 32)
+    int by_rows;         // as the prefill kernel reads them: x_q [M][Kp], SiLU(A x) padded with zeros to hstride
     int token_tiles;
     ProLayer L[kMaxGroup];
     ProTokens Q[kMaxGroup];
@@ -305,7 +306,7 @@ hipError_t launch_quantize(const _Float16 *x, int M, int K, int8_t *xq, float *s
 hipError_t launch_ln_quantize(const _Float16 *x, int M, int K, const float *gamma, const float *beta, float eps,
                               int8_t *xq, float *s_x, int32_t *rowsum, hipStream_t st);
 hipError_t launch_corr_down(const _Float16 *x, int M, int K, int G, const _Float16 *const *A, const int *rank,
-                            _Float16 *const *h16, int8_t *xq, float *s_x, int32_t *rowsum, hipStream_t st);
+                            _Float16 *const *h16, int8_t *xq, float *s_x, int32_t *rowsum, hipStream_t st);   // rows of whole 16 bytes
 int prologue_slices(int K);
 hipError_t launch_prologue(ProParams &p, hipStream_t st);
 hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st);

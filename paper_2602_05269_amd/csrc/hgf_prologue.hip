@@ -1,4 +1,5 @@
-// Preparation of a group of layers that read the same activations, for the direct path: one launch
+// Preparation of a group of layers that read the same activations, for the direct path (and, where the
+// prefill path's own is slower, for that): one launch
 // that quantises the tokens and computes SiLU(A x) of every layer.
 //
 // Algorithm 1 of the HGF paper, steps 1-2 (per-token absmax int8 quantisation, Sec. 2.2.1, behind a
@@ -208,7 +209,8 @@ __device__ inline void quantize_tokens(const ProParams &p, const ProTokens &Q, i
     const float inv = 127.0f / amax;
     int sum = 0;
     const int tg = m >> 5, rows = min(32, p.M - tg * 32);        // the token's group of 32 and its size
-    int8_t *out = Q.xq + (size_t)tg * 32 * p.Kp + (m & 31) * 16;
+    int8_t *out = Q.xq + (p.by_rows ? (size_t)m * p.Kp : (size_t)tg * 32 * p.Kp + (m & 31) * 16);
+    const int step = p.by_rows ? 16 : rows * 16;
     for (int c = 0; c < chunks; ++c) {
         if (chunks > 1) {
             load(c);
@@ -240,7 +242,7 @@ __device__ inline void quantize_tokens(const ProParams &p, const ProTokens &Q, i
                         Q.xq[(size_t)(((b >> 4) * 5 + digit) * p.M + m) * 16 + (b & 15)] = (int8_t)(o[e >> 2] >> (8 * (e & 3)));
                     }
                 }
-            } else if (live && unit < units) *reinterpret_cast<v4u *>(out + (size_t)unit * rows * 16) = o;
+            } else if (live && unit < units) *reinterpret_cast<v4u *>(out + (size_t)unit * step) = o;
         }
     }
     sum = wave_sum(sum);
@@ -370,8 +372,9 @@ hipError_t launch_prologue(ProParams &p, hipStream_t st)
     p.Kp = round_up(p.K, p.base3 ? kB3Cols : kTileCols);
     // One token tile per workgroup while the workgroups find room side by side (a compute unit takes in 32
     // rows instead of 48: 64 tokens of 4096 columns, 128 ranks: 6.8 us against 8.3), two where there are many
+    auto rank_tiles = [&](const ProLayer &L) { return L.rank == 0 ? 0 : (p.by_rows ? L.hstride / 16 : (L.rank + 15) / 16); };
     int tiles = 0;
-    for (int g = 0; g < p.G; ++g) tiles += (p.L[g].rank + 15) / 16;
+    for (int g = 0; g < p.G; ++g) tiles += rank_tiles(p.L[g]);
     const int tt = p.M <= 16 || tiles * ((p.M + 15) / 16) * p.S <= 512 ? 1 : 2;
     p.token_tiles = (p.M + 16 * tt - 1) / (16 * tt);
     int jobs = 0;
@@ -379,7 +382,7 @@ hipError_t launch_prologue(ProParams &p, hipStream_t st)
     for (int g = 0; g < p.G; ++g) {
         p.job_start[g] = jobs;
         if (p.L[g].rank > 0) {
-            jobs += ((p.L[g].rank + 15) / 16) * p.token_tiles * p.S;
+            jobs += rank_tiles(p.L[g]) * p.token_tiles * p.S;
             vec = vec && (reinterpret_cast<uintptr_t>(p.L[g].A) % 16) == 0;
         }
     }

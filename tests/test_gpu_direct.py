@@ -45,6 +45,8 @@ def test_direct_path_edges(M, K, N, r):
 @pytest.mark.parametrize("M,K,N,r", [
     (600, 1365, 4096, 32), (900, 256, 3000, 16), (1000, 4104, 2048, 8), (1000, 8200, 2048, 16), (1000, 16392, 2048, 8),
     (1000, 512, 2100, 0),
+    # odd rows: ranks padded to 64 and 128 columns, rows read once per pass
+    (1000, 1365, 2100, 40), (700, 1001, 4100, 100), (700, 16401, 2100, 8),
 ])
 def test_prefill_path(M, K, N, r):
     """Sizes beyond the direct path: the three register depths of the prefill quantiser, ragged row and
@@ -98,8 +100,8 @@ def test_pair_paths(M, K, N, rg, ru):
 @pytest.mark.parametrize("M,K,N,r", [
     # direct: a wavefront, 128, 256 and 512 threads per token, rows read once per pass, odd rows
     (70, 96, 40, 8), (9, 1030, 64, 16), (6, 2048, 33, 24), (6, 4097, 33, 32), (5, 9001, 70, 8), (6, 16640, 40, 24), (5, 33001, 32, 0),
-    # prefill
-    (900, 1365, 4096, 32), (1900, 512, 2100, 0),
+    # prefill: prepared in one launch, in two
+    (900, 1365, 4096, 32), (1900, 512, 2100, 0), (1000, 2048, 2500, 40), (1100, 8192, 1800, 16),
 ])
 def test_layernorm_paths(M, K, N, r):
     c = synth.make_custom(8600 + M + K + N + r, M, K, N, max(r, 1), act="student_t3", lora_std=0.05)
