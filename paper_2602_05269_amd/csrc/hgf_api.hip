@@ -63,15 +63,15 @@ hgf_status from_hip(hipError_t e) { return e == hipSuccess ? HGF_OK : HGF_ERR_DE
 // Which of the two paths a group of layers takes.  The prefill kernel's tiles are 256 rows by 64 or
 // 128 tokens and walk all of d_in with one workgroup each, so a group that does not fill the chip with
 // them costs about 10 + 0.55 k-tiles microseconds whatever its size; the direct path costs by its output
-// tiles of 32 x 32 and, for the preparation, by its tokens.  tiles + tokens at which they cross lies
-// between (us, direct / prefill): 4 k-tiles 2108 (11.5 / 12.4) and 3008 (13.1 / 12.6); 11 k-tiles 1512 (14.4
-// / 14.9) and 2252 (16.5 / 15.3); 16 k-tiles 1792 (18.0 / 19.0) and 1816 (19.5 / 18.7); 32 k-tiles 1880 (27.5 /
-// 28.4) and 2160 (31.0 / 28.7); 64 k-tiles 1816 (38.6 / 42.6) and 2400 (48.1 / 43.4); 86 k-tiles beyond 1600
-// (45.5 / 54.9).  Behind a LayerNorm the prefill path has one launch more: 4 k-tiles 4216 (18.5 / 18.7); 11
-// k-tiles beyond 3008 (22.6 / 25.5); 16, beyond 3048 (24.8 / 28.0); 64, beyond 2400 (61.0 / 74.0).  A pair
-// (two tiles per 32 rows of z) crosses between 1876 (13.2 / 14.1) and 2592 (18.9 / 14.7) at 4 k-tiles, 1632
-// (17.7 / 19.8) and 2176 (20.2 / 19.8) at 16, 1440 (28.1 / 29.5) and 2160 (36.5 / 30.5) at 32.  Up to 40
-// tokens the direct path takes every group.
+// tiles of 32 x 32 and, for the preparation, by its tokens.  tiles + 1.5 tokens at which they cross lies
+// between (us, direct / prefill): 4 k-tiles 2458 (11.5 / 12.4) and 3548 (13.1 / 12.6); 11 k-tiles 2012 (14.4
+// / 14.9) and 3002 (16.5 / 15.3); 16 k-tiles 1920 (18.0 / 19.0) and 2116 (19.5 / 18.7); 32 k-tiles 1960 (27.5 /
+// 28.4) and 2208 (31.0 / 28.7); 64 k-tiles 2116 (38.6 / 42.6) and 2800 (48.1 / 43.4); 86 k-tiles beyond 1760
+// (45.5 / 54.9).  Behind a LayerNorm, against the prefill path's preparation in two launches: 4 k-tiles 4916
+// (18.5 / 18.7); 11 k-tiles beyond 4008 (22.6 / 25.5); 16, beyond 3548 (24.8 / 28.0); 64, beyond 2800 (61.0 /
+// 74.0); that preparation is up to 5 us shorter now.  A pair (two tiles per 32 rows of z) crosses between 2126
+// (13.2 / 14.1) and 2942 (17.2 / 14.4) at 4 k-tiles, 1680 (17.7 / 19.8) and 2240 (20.2 / 19.8) at 16, 1472
+// (28.1 / 29.5) and 2208 (36.5 / 30.5) at 32.  Up to 40 tokens the direct path takes every group.
 bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 {
     if (M <= 40) return true;
@@ -79,8 +79,8 @@ bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
     for (int g = 0; g < G; ++g) rbs += round_up(layers[g].d_out, kTileRows) / kTileRows;
     const long long tiles = rbs * ((M + 31) / 32);
     const bool short_rows = layers[0].d_in <= 4 * kTileCols;
-    const int most = pair ? 1600 : (layers[0].ln_gamma ? (short_rows ? 4200 : 3000) : (short_rows ? 2400 : 1850));
-    return tiles + M <= most;
+    const int most = pair ? 1600 : (layers[0].ln_gamma ? (short_rows ? 4200 : 2800) : (short_rows ? 2600 : 2000));
+    return tiles + M + M / 2 <= most;
 }
 
 // Profiling aid: event pairs recorded around main-kernel launches, by kind (0 decode, 1 prefill).

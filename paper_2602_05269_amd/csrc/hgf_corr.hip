@@ -22,9 +22,7 @@ namespace {
 
 struct CorrParams {
     const _Float16 *x;
-    const _Float16 *A;                          // (set from A4 and so on inside a workgroup)
-    _Float16 *h16;
-    int M, K, rank, hstride;
+    int M, K;
     int steps;                                  // stretches of KC columns
     // grouped launch: blockIdx.y walks the 32-rank tiles of up to four layers that read the same x
     int G;
