@@ -11,7 +11,7 @@
 // a step streams the K and V caches once: 6 len d_h bytes per head, nothing else of size.
 // That is bandwidth-bound work with no reuse, so there are no matrix instructions here:
 // coalesced 16-byte loads, dot products in the vector ALU, cross-lane reductions.
-//   pass 1 (grid: heads x chunks of 256 positions x sequences): a workgroup loads its chunk
+//   pass 1 (grid: chunks of 256 positions, heads, sequences): a workgroup loads its chunk
 //     of K1, K2 and V rows of one head in one burst, forms both branches' scores, maxima and
 //     exponentials, and both exp-weighted sums of the V rows, which it reads once for the two;
 //     it writes (max, sum, weighted V) per branch to the workspace;
@@ -35,6 +35,7 @@ struct AttnParams {
     float *part;                       // [B, n_heads, chunks, 2, d_h + 2]
     _Float16 *out;                     // [B, n_heads, d_h]
     int B, L_max, n_heads, d_h, chunks;
+    int heads_first;                   // grid of pass 1: heads fastest, else chunks
     float lambda, scale;
 };
 
@@ -56,10 +57,13 @@ __device__ inline float group_sum(float v)
 // the positions ps, ps + P, ... of its wavefront's 64 positions (P = 64 / V8 per instruction).
 // Bound by HBM.  Each wavefront is a softmax of its own over its 64 positions, entirely in registers:
 // K1, K2 and V are requested in one burst, and the only meeting of the workgroup is the merge of its
-// four (max, sum, weighted V) at the end.  Heads are the fastest grid dimension, so the workgroups that
-// run together read whole cache rows rather than one 128-byte head row out of every 8 KiB.  With the
-// merge below, 32 heads of 64 over 8 caches of up to 4096 positions (217 MB): 67.4 us before, with the
-// chunks fastest and four barriers per branch, 45.2 us = 4.8 TB/s now.
+// four (max, sum, weighted V) at the end.  Where heads share a cache line (128
+// bytes: d_h < 64) chunks are the fastest grid dimension, so that such heads read it on one XCD when the
+// chunks are a multiple of eight; otherwise heads are, which reads whole cache rows, except where the
+// two chunks of a head side by side do as well.  (us, chunks / heads fastest, 32 heads: 8 caches of 4096
+// positions of 16 columns 35 / 75, of 32 45 / 74, of 64 73 / 74; one cache of 16384 of 64 columns 50 / 42,
+// of 128 93 / 73; 8 caches of 512 of 64 columns 15.4 / 16.0.)  More than the 65535 chunks that a grid's
+// other dimensions take are only possible below 64 columns.
 template <int V8>
 __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
 {
@@ -68,7 +72,7 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
     __shared__ float mx_s[4][2], sum_s[4][2];
     const int tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = blockIdx.x, chunk = blockIdx.y, b = blockIdx.z;
+    const int chunk = p.heads_first ? blockIdx.y : blockIdx.x, h = p.heads_first ? blockIdx.x : blockIdx.y, b = blockIdx.z;
     const int len = min(max(p.lens[b], 0), p.L_max);
     const int pos0 = chunk * kAttnChunk;
     if (pos0 >= len) return;            // nothing cached here (the merge reads only the chunks below len)
@@ -173,8 +177,9 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
     }
 }
 
-// One workgroup per head and sequence; wavefront 0 turns up to 64 chunks' (max, sum) at a time into
-// weights (LDS), then all four take every fourth chunk's rows.  Bound by latency: a fixed number of
+// One workgroup of eight wavefronts per head and sequence; wavefronts 0 and 1, one branch each, turn up
+// to 64 chunks' (max, sum) at a time into weights (LDS), then four groups of 128 threads, one per
+// column, take every fourth chunk's rows.  Bound by latency: a fixed number of
 // trips to memory, where two loops over the chunks with a dependent load in each took 16.9 us at
 // 16 chunks.
 __global__ __launch_bounds__(512) void diff_attn_merge_kernel(AttnParams p)
@@ -259,7 +264,8 @@ hipError_t launch_diff_attn(const void *q, const void *k, const void *v, const i
     p.chunks = (L_max + kAttnChunk - 1) / kAttnChunk;
     p.lambda = lambda;
     p.scale = 1.0f / sqrtf((float)d_h);
-    const dim3 grid(n_heads, p.chunks, B), block(256);
+    p.heads_first = d_h >= 64 && p.chunks > 2;
+    const dim3 grid = p.heads_first ? dim3(n_heads, p.chunks, B) : dim3(p.chunks, n_heads, B), block(256);
     switch (d_h / 8) {
         case 1: hipLaunchKernelGGL(diff_attn_chunk_kernel<1>, grid, block, 0, st, p); break;
         case 2: hipLaunchKernelGGL(diff_attn_chunk_kernel<2>, grid, block, 0, st, p); break;

@@ -71,6 +71,17 @@ def test_diff_attention_many_chunks(d, L, lens):
     assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, lens, 0.8))
 
 
+def test_diff_attention_cache_of_more_chunks_than_a_narrow_grid_extent():
+    # a cache of 65537 chunks (one more than a grid's second extent takes), nearly all of it empty
+    L = 65536 * 256 + 1
+    q, k, v = _case(77, 1, 300, 1, 8)
+    kc = torch.zeros((1, L, 2, 8), dtype=torch.float16, device="cuda")
+    vc = torch.zeros((1, L, 1, 8), dtype=torch.float16, device="cuda")
+    kc[:, :300], vc[:, :300] = dev(k), dev(v)
+    out = hb.hgf_diff_attention_decode(dev(q), kc, vc, torch.tensor([300], dtype=torch.int32, device="cuda"), 0.8)
+    assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, [300], 0.8))
+
+
 def test_diff_attention_rejects_bad_arguments():
     lib = hb.lib()
     assert lib.hgf_diff_attention_workspace_bytes(1, 128, 4, 24) == 0          # d_h not a power of two
