@@ -12,9 +12,9 @@
 // That is bandwidth-bound work with no reuse, so there are no matrix instructions here:
 // coalesced 16-byte loads, dot products in the vector ALU, cross-lane reductions.
 //   pass 1 (grid: chunks of 256 positions, heads, sequences): a workgroup loads its chunk
-//     of K1, K2 and V rows of one head in one burst, forms both branches' scores, maxima and
-//     exponentials, and both exp-weighted sums of the V rows, which it reads once for the two;
-//     it writes (max, sum, weighted V) per branch to the workspace;
+//     of K1 and K2 rows of one head in one burst, forms both branches' scores, maxima and
+//     exponentials while the V rows arrive, and both exp-weighted sums of the V rows, which it
+//     reads once for the two; it writes (max, sum, weighted V) per branch to the workspace;
 //   pass 2 (grid: heads x sequences): merges the chunks (rescaling by exp(max_chunk - max)),
 //     normalises, forms (a1 - lambda a2) * 0.5 and stores fp16.
 #include "hgf_internal.h"
@@ -55,9 +55,12 @@ __device__ inline float group_sum(float v)
 
 // V8: 16-byte pieces of a head row (d_h / 8).  Lane (ps = l / V8, pc = l % V8) takes piece pc of
 // the positions ps, ps + P, ... of its wavefront's 64 positions (P = 64 / V8 per instruction).
-// Bound by HBM.  Each wavefront is a softmax of its own over its 64 positions, entirely in registers:
-// K1, K2 and V are requested in one burst, and the only meeting of the workgroup is the merge of its
-// four (max, sum, weighted V) at the end.  Where heads share a cache line (128
+// Bound by HBM.  Each wavefront is a softmax of its own over its 64 positions, in registers: the only
+// meeting of the workgroup is the merge of its four (max, sum, weighted V) at the end.  The V8 lanes of
+// a position hold the same score, so each of them takes the exponential of one of the lane's V8
+// positions and hands it round (all V8 in every lane: 15.5 us for 512 positions of 32 heads of 64 over 8
+// caches, 13.9 so), and V is requested when the registers of K are free again (90 instead of 124 at d_h =
+// 64, 164 instead of 226 at 128).  Where heads share a cache line (128
 // bytes: d_h < 64) chunks are the fastest grid dimension, so that such heads read it on one XCD when the
 // chunks are a multiple of eight; otherwise heads are, which reads whole cache rows, except where the
 // two chunks of a head side by side do as well.  (us, chunks / heads fastest, 32 heads: 8 caches of 4096
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
     const _Float16 *qb = p.q + (size_t)b * krow;
     const v8h q1 = *reinterpret_cast<const v8h *>(qb + (size_t)h * d_h + pc * 8);
     const v8h q2 = *reinterpret_cast<const v8h *>(qb + (size_t)(p.n_heads + h) * d_h + pc * 8);
-    // the burst (rows past len lie beyond the descriptors: zeros)
+    // (rows past len lie beyond the descriptors: zeros)
     v4u k1[IT], k2[IT], vv[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
@@ -91,13 +94,8 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
         k1[it] = buf_load16_stream(kr, (unsigned)((pos * krow + (size_t)h * d_h + pc * 8) * 2));
         k2[it] = buf_load16_stream(kr, (unsigned)((pos * krow + (size_t)(p.n_heads + h) * d_h + pc * 8) * 2));
     }
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const unsigned pos = (unsigned)(pos0 + w * 64 + it * P + ps);
-        vv[it] = buf_load16_stream(vr, (unsigned)((pos * vrow + (size_t)h * d_h + pc * 8) * 2));
-    }
     // ---- scores of both branches (each in all lanes of its position)
-    float s[2][IT], mx[2] = {-INFINITY, -INFINITY}, sum[2] = {0.f, 0.f};
+    float s[2][IT], mx[2] = {-INFINITY, -INFINITY}, sum[2];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const v8h x1 = __builtin_bit_cast(v8h, k1[it]), x2 = __builtin_bit_cast(v8h, k2[it]);
@@ -114,14 +112,23 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
         mx[1] = fmaxf(mx[1], s[1][it]);
     }
 #pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const unsigned pos = (unsigned)(pos0 + w * 64 + it * P + ps);
+        vv[it] = buf_load16_stream(vr, (unsigned)((pos * vrow + (size_t)h * d_h + pc * 8) * 2));
+    }
+#pragma unroll
     for (int br = 0; br < 2; ++br) {
         mx[br] = wave_max(mx[br]);
         const float m = mx[br] == -INFINITY ? 0.f : mx[br];      // (no position here: every weight is exp(-inf) = 0)
+        static_assert(IT == V8, "one exponential per lane");
+        float mine = s[br][0];                                   // the weight of the lane's pc-th position
 #pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            s[br][it] = expf(s[br][it] - m);
-            sum[br] += s[br][it];
-        }
+        for (int it = 1; it < IT; ++it) mine = pc == it ? s[br][it] : mine;
+        mine = expf(mine - m);
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+            s[br][it] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((ps * V8 + it) * 4, __builtin_bit_cast(int, mine)));
+        sum[br] = group_sum<V8>(mine);
 #pragma unroll
         for (int o = V8; o < 64; o <<= 1) sum[br] += __shfl_xor(sum[br], o, 64);
     }
