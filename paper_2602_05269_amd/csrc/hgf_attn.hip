@@ -16,7 +16,8 @@
 //     exponentials while the V rows arrive, and both exp-weighted sums of the V rows, which it
 //     reads once for the two; it writes (max, sum, weighted V) per branch to the workspace;
 //   pass 2 (grid: heads x sequences): merges the chunks (rescaling by exp(max_chunk - max)),
-//     normalises, forms (a1 - lambda a2) * 0.5 and stores fp16.
+//     normalises, forms (a1 - lambda a2) * 0.5 and stores fp16.  Caches of one chunk need no
+//     second launch: pass 1 does it.
 #include "hgf_internal.h"
 
 #include <type_traits>
@@ -78,7 +79,10 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
     const int chunk = p.heads_first ? blockIdx.y : blockIdx.x, h = p.heads_first ? blockIdx.x : blockIdx.y, b = blockIdx.z;
     const int len = min(max(p.lens[b], 0), p.L_max);
     const int pos0 = chunk * kAttnChunk;
-    if (pos0 >= len) return;            // nothing cached here (the merge reads only the chunks below len)
+    if (pos0 >= len) {                  // nothing cached here (the merge reads only the chunks below len)
+        if (p.chunks == 1 && tid < d_h) p.out[((size_t)b * p.n_heads + h) * d_h + tid] = (_Float16)0.f;
+        return;
+    }
     const int ps = l / V8, pc = l % V8;
     const size_t krow = (size_t)2 * p.n_heads * d_h, vrow = (size_t)p.n_heads * d_h;
     const rsrc_t kr = make_rsrc(p.k + (size_t)b * p.L_max * krow, (unsigned)((size_t)len * krow * 2));
@@ -165,21 +169,27 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
         sum_s[w][l] = l == 0 ? sum[0] : sum[1];
     }
     __syncthreads();
-    float *out = p.part + ((((size_t)b * p.n_heads + h) * p.chunks + chunk) * 2) * (d_h + 2);
-    if (tid < 2 * d_h) {
-        const int br = tid / d_h, d = tid % d_h;
-        const float m = fmaxf(fmaxf(mx_s[0][br], mx_s[1][br]), fmaxf(mx_s[2][br], mx_s[3][br]));
-        float acc = 0.f, total = 0.f;
+    const int br = tid / d_h, d = tid % d_h;
+    float acc = 0.f, total = 0.f, m = 0.f;
+    if (br < 2) {
+        m = fmaxf(fmaxf(mx_s[0][br], mx_s[1][br]), fmaxf(mx_s[2][br], mx_s[3][br]));
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float f = sum_s[i][br] == 0.f ? 0.f : expf(mx_s[i][br] - m);     // (0: no positions there)
             acc += accs[i][br][d] * f;
             total += sum_s[i][br] * f;
         }
-        out[br * (d_h + 2) + 2 + d] = acc;
+    }
+    if (p.chunks == 1) {                // no merge follows
+        if (br < 2) accs[0][br][d] = acc / total;                // (its own element: no other thread reads it before)
+        __syncthreads();
+        if (br == 0) p.out[((size_t)b * p.n_heads + h) * d_h + d] = (_Float16)((accs[0][0][d] - p.lambda * accs[0][1][d]) * 0.5f);
+    } else if (br < 2) {
+        float *out = p.part + ((((size_t)b * p.n_heads + h) * p.chunks + chunk) * 2 + br) * (d_h + 2);
+        out[2 + d] = acc;
         if (d == 0) {
-            out[br * (d_h + 2)] = m;
-            out[br * (d_h + 2) + 1] = total;
+            out[0] = m;
+            out[1] = total;
         }
     }
 }
@@ -281,7 +291,7 @@ hipError_t launch_diff_attn(const void *q, const void *k, const void *v, const i
         case 16: hipLaunchKernelGGL(diff_attn_chunk_kernel<16>, grid, block, 0, st, p); break;
         default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(diff_attn_merge_kernel, dim3(n_heads, B), dim3(512), 0, st, p);
+    if (p.chunks > 1) hipLaunchKernelGGL(diff_attn_merge_kernel, dim3(n_heads, B), dim3(512), 0, st, p);
     return hipGetLastError();
 }
 

@@ -71,6 +71,14 @@ def test_diff_attention_many_chunks(d, L, lens):
     assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, lens, 0.8))
 
 
+@pytest.mark.parametrize("d,L,lens", [(8, 256, [256, 0, 65]), (64, 200, [0, 200, 1]), (128, 257, [257, 0, 256]), (32, 1100, [769, 1024, 1025])])
+def test_diff_attention_few_chunks(d, L, lens):
+    # one chunk (no merging launch), two, five; empty sequences
+    q, k, v = _case(d + L, len(lens), L, 3, d)
+    out = hb.hgf_diff_attention_decode(dev(q), dev(k), dev(v), dev(np.array(lens, dtype=np.int32)), 0.8)
+    assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, lens, 0.8))
+
+
 def test_diff_attention_cache_of_more_chunks_than_a_narrow_grid_extent():
     # a cache of 65537 chunks (one more than a grid's second extent takes), nearly all of it empty
     L = 65536 * 256 + 1
