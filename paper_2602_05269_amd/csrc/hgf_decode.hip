@@ -76,8 +76,10 @@ __device__ inline void base3_digits(v4u bytes, v4i (&digit)[5])
 // The wavefronts per SIMD that the registers have to leave room for: grids are a few workgroups per compute
 // unit, and one more in residence can save a whole round (7B-shape up + gate at 64 tokens, 688 workgroups: 27
 // us with room for two per compute unit in registers and in LDS, 23 us with three).
+// ONCE: weights are requested as read once (non-temporal), for groups whose weights no second launch or
+// token group finds in a cache.
 constexpr int direct_waves(int D) { return D == 1 ? 4 : 3; }
-template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false>
+template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false, bool ONCE = false>
 __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(DecodeParams p)
 {
     static_assert(!PAIR || WR == 2, "a pair is one row-block of each layer");
@@ -144,6 +146,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
 #pragma unroll
         for (int r = 0; r < WR; ++r)
             wq[d][r] = B3 ? buf_load16(wr[r], (unsigned)kt * 32u + woff, kt < p.KT)
+                   : ONCE ? buf_load16_stream(wr[r], (unsigned)kt * kTileBytes + woff)
                           : buf_load16(wr[r], (unsigned)kt * kTileBytes + woff);
 #pragma unroll
         for (int tg = 0; tg < TG; ++tg)
@@ -381,7 +384,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
     }
 }
 
-template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false>
+template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false, bool ONCE = false>
 hipError_t launch_shape(DecodeParams &p, hipStream_t st)
 {
     int units = 0;
@@ -392,11 +395,11 @@ hipError_t launch_shape(DecodeParams &p, hipStream_t st)
     for (int g = p.G; g <= kMaxGroup; ++g) p.wg_start[g] = units;
     const size_t red = (size_t)KW * WR * TG * 4096, ops = (size_t)(WR + (PAIR ? 2 : 1) * TG) * p.hsteps * 1024;
     const size_t lds = red > ops ? red : ops;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<WR, TG, KW, D, PAIR, B3>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<WR, TG, KW, D, PAIR, B3, ONCE>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
     const int TU = (p.M + 32 * TG - 1) / (32 * TG);
-    hipLaunchKernelGGL((direct_kernel<WR, TG, KW, D, PAIR, B3>), dim3((units + 7) / 8 * 8 * TU), dim3(64 * KW), lds, st, p);
+    hipLaunchKernelGGL((direct_kernel<WR, TG, KW, D, PAIR, B3, ONCE>), dim3((units + 7) / 8 * 8 * TU), dim3(64 * KW), lds, st, p);
     return hipGetLastError();
 }
 
@@ -431,8 +434,23 @@ hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
         // (7B-shape, 344 row-blocks at 8 tokens: four wavefronts 21.6, eight 26.4; 512 -> 1365, 43: 10.7 and 10.4)
         return tiles > 512 ? launch_shape<2, 1, 4, 3, true>(p, st) : launch_shape<2, 1, 8, 3, true>(p, st);
     }
-    if (groups == 1 || tiles <= 256)
-        return tiles <= 256 && p.KT >= 32 ? launch_shape<1, 1, 8, 3, false>(p, st) : launch_shape<1, 1, 4, 4, false>(p, st);
+    // One token group: hardly anything but weights is read, so with many row-blocks what counts is how many
+    // wavefronts are in flight, not how deep each reads ahead, and with many bytes that they are requested as
+    // read once.  (us per pass, both launches, up to 350 MB of weights in turn, 5 .. 32 tokens; geometric mean
+    // against the best of sixteen shapes, this one / four tiles in flight: up to 8 k-tiles and 1300
+    // row-blocks 1.02 / 1.17; 9 to 24 and 257 to 800 1.01 / 1.07; longer and 513 to 800 1.02 / 1.08; up to
+    // 1050 1.01 / 1.23; beyond 1.03 / 1.33.  Up + gate of the 7B shape, 688 row-blocks, 5 tokens: 19.8 -> 18.5,
+    // without the read-once requests 19.0; three such layers 25.5 -> 22.4; 512 -> 32000 12.3 -> 9.6.)
+    if (groups == 1) {
+        if (p.KT >= 32 && tiles <= 256) return launch_shape<1, 1, 8, 3, false>(p, st);
+        if (p.KT > 8 && tiles <= (p.KT > 24 ? 512 : 256)) return launch_shape<1, 1, 4, 4, false>(p, st);
+        if (tiles <= (p.KT <= 8 ? 1300 : 800))
+            return p.KT <= 24 ? launch_shape<1, 1, 4, 1, false>(p, st) : launch_shape<1, 1, 4, 1, false, false, true>(p, st);
+        if (tiles <= 1050) return launch_shape<2, 1, 4, 2, false, false, true>(p, st);
+        return p.KT <= 4 ? launch_shape<2, 1, 4, 1, false>(p, st) : launch_shape<2, 1, 4, 1, false, false, true>(p, st);
+    }
+    if (tiles <= 256)
+        return p.KT >= 32 ? launch_shape<1, 1, 8, 3, false>(p, st) : launch_shape<1, 1, 4, 4, false>(p, st);
     if (tiles <= 640) return launch_shape<2, 1, 8, 3, false>(p, st);
     // (a wavefront with one k-tile has nothing to keep in flight behind it: registers for four workgroups
     // per compute unit instead of two, 1024 of them in one round.  2048 tiles of four k-tiles: 8.7 us, where

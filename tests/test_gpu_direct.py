@@ -43,6 +43,17 @@ def test_direct_path_edges(M, K, N, r):
 
 
 @pytest.mark.parametrize("M,K,N,r", [
+    # one token group and many row-blocks: one tile in flight up to 1300 row-blocks of 8 k-tiles, up to 800 of 24,
+    # and of longer rows with read-once requests; two row-blocks per workgroup up to 1050 and beyond (short and
+    # long rows), an odd number of them, the last one ragged
+    (9, 520, 9000, 16), (32, 1024, 41569, 8), (5, 3072, 8225, 24), (17, 3080, 16417, 8), (31, 1100, 25665, 40),
+    (6, 500, 41633, 16), (8, 1100, 33633, 0),
+])
+def test_direct_path_many_row_blocks(M, K, N, r):
+    _one(M, K, N, r)
+
+
+@pytest.mark.parametrize("M,K,N,r", [
     (600, 1365, 4096, 32), (900, 256, 3000, 16), (1000, 4104, 2048, 8), (1000, 8200, 2048, 16), (1000, 16392, 2048, 8),
     (1000, 512, 2100, 0),
     # odd rows: ranks padded to 64 and 128 columns, rows read once per pass
