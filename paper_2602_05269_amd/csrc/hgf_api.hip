@@ -130,8 +130,9 @@ bool quantisations_fit(int M, int K, int n, const Workspace &ws)
 
 // Places what the prologue of a group writes (layers, sizes and NQ are set): the first quantisation
 // in the workspace's own buffers, those of the other LayerNorms of the group and, where d_in is cut,
-// the slices of A x in its spare region; d_in stays whole where they do not fit.  False: the
-// quantisations do not fit.
+// the slices of A x in its spare region, as many of them as it holds (whole rows are slow: three layers
+// 16384 -> 512 of 64 ranks at 384 tokens 88 us, in the seven slices that fit 66).  False: the quantisations
+// do not fit.
 bool place_prologue(ProParams &p, const hgf_layer *layers, const Workspace &ws)
 {
     if (!quantisations_fit(p.M, p.K, p.NQ, ws)) return false;
@@ -151,13 +152,14 @@ bool place_prologue(ProParams &p, const hgf_layer *layers, const Workspace &ws)
         Q.rowsum = reinterpret_cast<int32_t *>(ws.spare + used + xq_bytes + word_bytes);
         used += xq_bytes + 2 * word_bytes;
     }
+    size_t slice = 0;                                // of all layers
+    for (int g = 0; g < p.G; ++g) slice += p.L[g].rank > 0 ? align256((size_t)p.M * p.L[g].hstride * 4) : 0;
     p.S = prologue_slices(p.K);
-    size_t each[kMaxGroup], slices = 0;
-    for (int g = 0; g < p.G; ++g) slices += each[g] = p.L[g].rank > 0 ? align256((size_t)p.S * p.M * p.L[g].hstride * 4) : 0;
-    if (used + slices > ws.spare_bytes) p.S = 1;
+    if (p.S * slice > ws.spare_bytes - used) p.S = (int)((ws.spare_bytes - used) / slice);
+    if (p.S < 1) p.S = 1;
     for (int g = 0; g < p.G; ++g) {
         p.L[g].hpart = p.S > 1 ? reinterpret_cast<float *>(ws.spare + used) : nullptr;
-        used += each[g];
+        if (p.L[g].rank > 0) used += align256((size_t)p.S * p.M * p.L[g].hstride * 4);
     }
     return true;
 }

@@ -90,6 +90,29 @@ def test_groups_of_mixed_layers(M):
         assert_close_fp16(slots[i + 1].cpu().numpy(), g.oracle(x, dense=True)["y"], f"layer {i}")
 
 
+@pytest.mark.parametrize("ln", [False, True])
+def test_group_with_room_for_some_slices(ln):
+    """Three layers of 9000 columns at 700 tokens: A x would be cut into five slices, the workspace holds
+    three; behind LayerNorms, where it also holds two further quantisations, 190 tokens leave room for two."""
+    M, K, r = (190, 9000, 128) if ln else (700, 9000, 32)
+    ws = hb.Workspace(M, K, 40, r)
+    layers, cases, slots = [], [], [None] * 4
+    for i, N in enumerate((40, 33, 8)):
+        c = synth.make_custom(8900 + i, M, K, N, r, act="student_t4", lora_std=0.01, w_std=0.05)
+        if i == 0:
+            x = c["x"]
+            slots[0] = dev(x)
+        g = LnLayer(c, ws, seed=i) if ln else GpuLayer(c, ws)
+        g.layer.c.src_slot, g.layer.c.dst_slot = 0, i + 1
+        slots[i + 1] = torch.zeros((M, N), dtype=torch.float16, device="cuda")
+        cases.append(g)
+        layers.append(g.layer)
+    hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
+    torch.cuda.synchronize()
+    for i, g in enumerate(cases):
+        assert_close_fp16(slots[i + 1].cpu().numpy(), g.oracle(x, dense=True)["y"], f"layer {i}")
+
+
 @pytest.mark.parametrize("M,K,N,rg,ru", [
     # direct: eight and four wavefronts, ragged rows of the last row-block, sliced A x, one rank zero
     (33, 130, 65, 24, 8), (40, 2500, 300, 16, 40), (50, 2500, 300, 16, 24), (64, 300, 4500, 8, 0), (10, 9000, 70, 0, 128),
