@@ -60,27 +60,41 @@ hgf_status check_layer(const hgf_layer *L, int M)
 
 hgf_status from_hip(hipError_t e) { return e == hipSuccess ? HGF_OK : HGF_ERR_DEVICE; }
 
-// Which of the two paths a group of layers takes.  The prefill kernel's tiles are 256 rows by 64 or
-// 128 tokens and walk all of d_in with one workgroup each, so a group that does not fill the chip with
-// them costs about 10 + 0.55 k-tiles microseconds whatever its size; the direct path costs by its output
-// tiles of 32 x 32 and, for the preparation, by its tokens.  tiles + 1.5 tokens at which they cross lies
-// between (us, direct / prefill): 4 k-tiles 2458 (11.5 / 12.4) and 3548 (13.1 / 12.6); 11 k-tiles 2012 (14.4
-// / 14.9) and 3002 (16.5 / 15.3); 16 k-tiles 1920 (18.0 / 19.0) and 2116 (19.5 / 18.7); 32 k-tiles 1960 (27.5 /
-// 28.4) and 2208 (31.0 / 28.7); 64 k-tiles 2116 (38.6 / 42.6) and 2800 (48.1 / 43.4); 86 k-tiles beyond 1760
-// (45.5 / 54.9).  Behind a LayerNorm, against the prefill path's preparation in two launches: 4 k-tiles 4916
-// (18.5 / 18.7); 11 k-tiles beyond 4008 (22.6 / 25.5); 16, beyond 3548 (24.8 / 28.0); 64, beyond 2800 (61.0 /
-// 74.0); that preparation is up to 5 us shorter now.  A pair (two tiles per 32 rows of z) crosses between 2126
-// (13.2 / 14.1) and 2942 (17.2 / 14.4) at 4 k-tiles, 1680 (17.7 / 19.8) and 2240 (20.2 / 19.8) at 16, 1472
-// (28.1 / 29.5) and 2208 (36.5 / 30.5) at 32.  Up to 40 tokens the direct path takes every group.
+// Which of the two paths a group of layers takes.  The prefill kernel's tiles are 256 rows by 64 or 128
+// tokens and walk all of d_in with one workgroup each, so a group that does not fill the chip with them
+// costs about 10 + 0.55 k-tiles microseconds whatever its size.  The direct path costs by its output tiles of
+// 32 x 32 and by its preparation.  Up to 2048 columns that leaves SiLU(A x) ready made and a token weighs
+// half a tile; longer rows are cut into slices, which the workgroups of every output tile add for themselves,
+// and a token weighs 1/4 of a tile and 0.3 for every 16 ranks of every layer.  In these units the paths cross
+// near the figures below; beyond 6144 columns the prefill workgroups' walk is what counts.  The SwiGLU pair
+// saves more on the prefill path (neither y is stored).  Layers behind LayerNorms are each a prefill group
+// of their own with a longer preparation, so they are weighed one by one, their tokens with half a tile and
+// 0.05 for every 16 ranks of sliced rows.  (2305 groups of 41 to 1536 tokens, 128 to 32768 columns, 64 to 32000
+// rows, 16 to 128 ranks, both paths timed: the choice is 0.3 % from the better path in the mean, where tiles +
+// 1.5 tokens against limits between 1600 and 4200 was 2 %.  us, direct / prefill: 512 -> 32000 behind a
+// LayerNorm, 128 tokens 18.3 / 13.4; three layers 512 -> 4096, 192 tokens 14.9 / 12.3; three 2048 -> 2048
+// behind LayerNorms, 384 tokens 31.2 / 55.6; two 4096 -> 1024, 640 tokens 31.7 / 28.2; 11008 -> 4096, 384
+// tokens 53.9 / 60.6.)  Up to 40 tokens the direct path takes every group.
 bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 {
     if (M <= 40) return true;
-    long long rbs = 0;
-    for (int g = 0; g < G; ++g) rbs += round_up(layers[g].d_out, kTileRows) / kTileRows;
-    const long long tiles = rbs * ((M + 31) / 32);
-    const bool short_rows = layers[0].d_in <= 4 * kTileCols;
-    const int most = pair ? 1600 : (layers[0].ln_gamma ? (short_rows ? 4200 : 2800) : (short_rows ? 2600 : 2000));
-    return tiles + M + M / 2 <= most;
+    const int K = layers[0].d_in;
+    const long long tokens = M, groups = (tokens + 31) / 32;
+    const bool ln = layers[0].ln_gamma != nullptr;            // (then every layer of the group has one)
+    const bool sliced = prologue_slices(K) > 1;
+    int most;
+    if (ln) most = sliced ? 2300 : (K > 512 ? 2200 : 2400);
+    else most = sliced ? (K > 6144 ? 2800 : (pair ? 1900 : 2400)) : 1750;
+    const long long each = (sliced && !ln ? 5 : 10) * tokens, rank_tile = sliced ? (ln ? 1 : 6) * tokens : 0;
+    long long cost = each;                                    // in twentieths of a tile
+    for (int g = 0; g < G; ++g) {
+        cost += 20 * groups * ((layers[g].d_out + kTileRows - 1) / kTileRows) +
+                rank_tile * (layers[g].rank > 16 ? (layers[g].rank + 15) / 16 : 1);
+        if (!ln) continue;
+        if (cost > 20 * most) return false;
+        cost = each;
+    }
+    return ln || cost <= 20 * most;
 }
 
 // Profiling aid: event pairs recorded around main-kernel launches, by kind (0 decode, 1 prefill).

@@ -2,6 +2,8 @@
 with the CPU oracle on the same seeded inputs."""
 from __future__ import annotations
 
+from contextlib import contextmanager
+
 import numpy as np
 import torch
 
@@ -29,6 +31,20 @@ def assert_close_fp16(y_gpu: np.ndarray, y_ref: np.ndarray, what: str = "y", sca
         worst = np.unravel_index(err.argmax(), err.shape)
         raise AssertionError(f"{what}: {int(bad.sum())} of {bad.size} outside tolerance ({where}); worst err "
                              f"{err.max():.3e} at {worst}: got {y_gpu[worst]!r}, reference {y_ref[worst]!r}")
+
+
+@contextmanager
+def path_taken(expected: str):
+    """Asserts that every main kernel launched inside ran on one path: "direct" (or, up to four tokens, a
+    persistent launch) or "prefill".  Does not see hgf_linear_forward_static, which takes no time stamps."""
+    hb.hgf_profile_enable(True)
+    try:
+        yield
+    finally:
+        hb.hgf_profile_enable(False)
+        (_, direct), (_, prefill) = hb.hgf_profile_collect()
+    got = {"direct": direct, "prefill": prefill}
+    assert got[expected] > 0 and sum(got.values()) == got[expected], f"expected the {expected} path, launches: {got}"
 
 
 class GpuLayer:

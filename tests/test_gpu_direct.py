@@ -8,17 +8,18 @@ import torch
 
 from paper_2602_05269_amd import binding as hb
 from paper_2602_05269_amd import synth
-from parity import GpuLayer, assert_close_fp16, dev
+from parity import GpuLayer, assert_close_fp16, dev, path_taken
 from test_gpu_layernorm import LnLayer
 from test_gpu_swiglu import _check_pair
 
 pytestmark = pytest.mark.gpu
 
 
-def _one(M, K, N, r, act="student_t3", rank0=False):
+def _one(M, K, N, r, act="student_t3", path="direct"):
     c = synth.make_custom(5000 + M + K + N + r, M, K, N, max(r, 1), act=act, lora_std=0.05)
     g = GpuLayer(c, hb.Workspace(M, K, N, max(r, 1)), rank0=r == 0)
-    y, acc = g.forward(c["x"])
+    with path_taken(path):
+        y, acc = g.forward(c["x"])
     ref = g.oracle(c["x"], dense=True)
     assert np.array_equal(acc, ref["acc"]), "int32 accumulators differ from the oracle"
     assert_close_fp16(y, ref["y"])
@@ -34,7 +35,7 @@ def _one(M, K, N, r, act="student_t3", rank0=False):
     # slices of d_in for A x: 2, 3, 5 and 9 of them, the last one ragged; rows at odd addresses
     (7, 2049, 64, 16), (6, 4097, 33, 32), (20, 10001, 40, 128), (5, 16500, 32, 8), (9, 1365, 512, 16), (50, 4095, 70, 15),
     # two token tiles per workgroup of A x (more than 512 workgroups otherwise), each quantiser width
-    (1050, 130, 32, 128), (1040, 1416, 40, 128), (1040, 2056, 32, 120), (530, 4104, 33, 128),
+    (1050, 130, 32, 128), (1040, 1416, 40, 128), (1040, 2056, 32, 64), (530, 4104, 33, 128),
     # a row longer than what the quantiser keeps in registers
     (6, 16640, 40, 24), (5, 33001, 32, 8),
 ])
@@ -54,15 +55,39 @@ def test_direct_path_many_row_blocks(M, K, N, r):
 
 
 @pytest.mark.parametrize("M,K,N,r", [
-    (600, 1365, 4096, 32), (900, 256, 3000, 16), (1000, 4104, 2048, 8), (1000, 8200, 2048, 16), (1000, 16392, 2048, 8),
-    (1000, 512, 2100, 0),
+    (600, 1365, 4096, 32), (900, 256, 3000, 16), (1000, 4104, 2048, 8), (1000, 8200, 2400, 16), (1000, 16392, 2400, 8),
+    (1000, 512, 2100, 0), (1040, 2056, 32, 120),
     # odd rows: ranks padded to 64 and 128 columns, rows read once per pass
-    (1000, 1365, 2100, 40), (700, 1001, 4100, 100), (700, 16401, 2100, 8),
+    (1000, 1365, 2100, 40), (700, 1001, 4100, 100), (700, 16401, 3600, 8),
 ])
 def test_prefill_path(M, K, N, r):
     """Sizes beyond the direct path: the three register depths of the prefill quantiser, ragged row and
     token tiles, odd rows, no correction path."""
-    _one(M, K, N, r, act="student_t4")
+    _one(M, K, N, r, act="student_t4", path="prefill")
+
+
+@pytest.mark.parametrize("M,K,N,r,path", [
+    # the line between the paths, a row-block on either side of it: up to 2048 columns, up to 6144, beyond
+    (200, 512, 7520, 16, "direct"), (200, 512, 7553, 16, "prefill"), (640, 2048, 2272, 64, "direct"), (640, 2048, 2273, 64, "prefill"),
+    (640, 2049, 2656, 48, "direct"), (640, 2049, 2657, 48, "prefill"), (640, 6152, 3904, 0, "direct"), (640, 6152, 3937, 0, "prefill"),
+])
+def test_line_between_the_paths(M, K, N, r, path):
+    _one(M, K, N, r, path=path)
+
+
+@pytest.mark.parametrize("M,K,N,path", [
+    # up to 512 columns, up to 2048, beyond
+    (320, 512, 7168, "direct"), (320, 512, 7169, "prefill"), (320, 520, 6528, "direct"), (320, 520, 6529, "prefill"),
+    (320, 2056, 6784, "direct"), (320, 2056, 6817, "prefill"),
+])
+def test_line_between_the_paths_behind_a_layernorm(M, K, N, path):
+    c = synth.make_custom(8950 + M + K + N, M, K, N, 16, act="student_t3", lora_std=0.05)
+    g = LnLayer(c, hb.Workspace(M, K, N, 16), seed=M + K)
+    with path_taken(path):
+        y, acc = g.forward(c["x"])
+    ref = g.oracle(c["x"], dense=True)
+    assert np.array_equal(acc, ref["acc"]), "int32 accumulators differ from the oracle"
+    assert_close_fp16(y, ref["y"])
 
 
 @pytest.mark.parametrize("M", [150, 2000])
@@ -84,7 +109,8 @@ def test_groups_of_mixed_layers(M):
         cases.append(g)
         layers.append(g.layer)
         slots[i + 1] = torch.zeros((M, N), dtype=torch.float16, device="cuda")
-    hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
+    with path_taken("direct" if M == 150 else "prefill"):
+        hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
     torch.cuda.synchronize()
     for i, g in enumerate(cases):
         assert_close_fp16(slots[i + 1].cpu().numpy(), g.oracle(x, dense=True)["y"], f"layer {i}")
@@ -107,19 +133,23 @@ def test_group_with_room_for_some_slices(ln):
         slots[i + 1] = torch.zeros((M, N), dtype=torch.float16, device="cuda")
         cases.append(g)
         layers.append(g.layer)
-    hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
+    with path_taken("direct"):
+        hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
     torch.cuda.synchronize()
     for i, g in enumerate(cases):
         assert_close_fp16(slots[i + 1].cpu().numpy(), g.oracle(x, dense=True)["y"], f"layer {i}")
 
 
-@pytest.mark.parametrize("M,K,N,rg,ru", [
-    # direct: eight and four wavefronts, ragged rows of the last row-block, sliced A x, one rank zero
-    (33, 130, 65, 24, 8), (40, 2500, 300, 16, 40), (50, 2500, 300, 16, 24), (64, 300, 4500, 8, 0), (10, 9000, 70, 0, 128),
-    # prefill
-    (400, 1365, 2050, 32, 0), (330, 384, 2100, 0, 0), (400, 4104, 2000, 16, 24),
+@pytest.mark.parametrize("M,K,N,rg,ru,path", [
+    # eight and four wavefronts, ragged rows of the last row-block, sliced A x, one rank zero
+    (33, 130, 65, 24, 8, "direct"), (40, 2500, 300, 16, 40, "direct"), (50, 2500, 300, 16, 24, "direct"),
+    (64, 300, 4500, 8, 0, "direct"), (10, 9000, 70, 0, 128, "direct"), (330, 384, 2100, 0, 0, "direct"),
+    (400, 1365, 2050, 32, 0, "prefill"), (450, 384, 2100, 0, 0, "prefill"), (400, 4104, 2000, 16, 24, "prefill"),
+    # a row-block on either side of the line: up to 2048 columns, up to 6144, beyond
+    (320, 1024, 2528, 16, 16, "direct"), (320, 1024, 2529, 16, 16, "prefill"), (320, 2056, 2272, 32, 32, "direct"),
+    (320, 2056, 2273, 32, 32, "prefill"), (320, 6152, 4032, 16, 0, "direct"), (320, 6152, 4033, 16, 0, "prefill"),
 ])
-def test_pair_paths(M, K, N, rg, ru):
+def test_pair_paths(M, K, N, rg, ru, path):
     ws = hb.Workspace(M, K, N, max(rg, ru, 1))
     # A x of order one: the fp16 rounding of h moves y_up by up to 2^-11 sum_j |B h|, and z by SiLU(y_gate)
     # times that; with std 0.05 at d_in = 9000, |h| ~ 5, 128 ranks and SiLU(y_gate) ~ 5 it is 8e-3, beyond
@@ -128,7 +158,8 @@ def test_pair_paths(M, K, N, rg, ru):
     cg = synth.make_custom(8400 + M + K + N + rg, M, K, N, max(rg, 1), act="student_t3", lora_std=std)
     cu = synth.make_custom(8450 + M + K + N + ru, M, K, N, max(ru, 1), act="student_t3", lora_std=std)
     gate, up = GpuLayer(cg, ws, rank0=rg == 0), GpuLayer(cu, ws, rank0=ru == 0)
-    _check_pair(gate, up, cg["x"], ws, dense=True)
+    with path_taken(path):
+        _check_pair(gate, up, cg["x"], ws, dense=True)
 
 
 @pytest.mark.parametrize("M,K,N,r", [
