@@ -432,6 +432,10 @@ hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
     if (p.pair) {
         if (p.G != 2 || p.L[0].N != p.L[1].N) return hipErrorInvalidValue;
         // (7B-shape, 344 row-blocks at 8 tokens: four wavefronts 21.6, eight 26.4; 512 -> 1365, 43: 10.7 and 10.4)
+        // (one token group: the weights are the traffic, see below.  7B-shape at 4 tokens 21.4 with three tiles in
+        // flight, 20.1 with two and read-once requests; 4096 -> 14336 at 5 tokens 20.9 and 19.6; with 256 row-blocks
+        // of 16 k-tiles 13.3 and 13.7)
+        if (groups == 1 && tiles > 512) return launch_shape<2, 1, 4, 2, true, false, true>(p, st);
         return tiles > 512 ? launch_shape<2, 1, 4, 3, true>(p, st) : launch_shape<2, 1, 8, 3, true>(p, st);
     }
     // One token group: hardly anything but weights is read, so with many row-blocks what counts is how many

@@ -141,9 +141,10 @@ def test_group_with_room_for_some_slices(ln):
 
 
 @pytest.mark.parametrize("M,K,N,rg,ru,path", [
-    # eight and four wavefronts, ragged rows of the last row-block, sliced A x, one rank zero
+    # eight and four wavefronts, ragged rows of the last row-block, sliced A x, one rank zero, many row-blocks
     (33, 130, 65, 24, 8, "direct"), (40, 2500, 300, 16, 40, "direct"), (50, 2500, 300, 16, 24, "direct"),
     (64, 300, 4500, 8, 0, "direct"), (10, 9000, 70, 0, 128, "direct"), (330, 384, 2100, 0, 0, "direct"),
+    (3, 1100, 8225, 16, 24, "direct"), (32, 2056, 8200, 0, 40, "direct"),
     (400, 1365, 2050, 32, 0, "prefill"), (450, 384, 2100, 0, 0, "prefill"), (400, 4104, 2000, 16, 24, "prefill"),
     # a row-block on either side of the line: up to 2048 columns, up to 6144, beyond
     (320, 1024, 2528, 16, 16, "direct"), (320, 1024, 2529, 16, 16, "prefill"), (320, 2056, 2272, 32, 32, "direct"),
