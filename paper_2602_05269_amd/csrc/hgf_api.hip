@@ -28,8 +28,8 @@ Workspace carve_workspace(void *base, int M, int d_in, int d_out, int rank, int 
     ws.h16 = reinterpret_cast<_Float16 *>(take(ws.h16_each * groups));
     const int Md = M < 64 ? M : 64;
     ws.spare_bytes = rank > 0 ? groups * align256((size_t)32 * Md * h_stride(rank) * sizeof(float)) : 0;
-    ws.spare = reinterpret_cast<unsigned char *>(take(ws.spare_bytes));
     ws.wsum = reinterpret_cast<double *>(take(size_t(kWsumBlocks) * 8));
+    ws.spare = reinterpret_cast<unsigned char *>(take(ws.spare_bytes));
     (void)d_out;
     ws.bytes = off;
     return ws;
@@ -353,6 +353,17 @@ Workspace carve_static(void *base, int M, const hgf_layer *L)
     return carve_workspace(base, M, L->d_in, L->d_out, L->rank, /*groups=*/1, /*with_stack=*/false);
 }
 
+// The spare region of a call of one layer: what a workspace has for it or, where less, what is left of the
+// static array (for sizes that the array serves).  Both entry points take this, so that they cut A x alike.
+size_t single_spare(int M, const hgf_layer *L)
+{
+    const size_t whole = carve_workspace(nullptr, M, L->d_in, L->d_out, L->rank).spare_bytes;
+    const Workspace s = carve_static(nullptr, M, L);
+    if (s.bytes > kStaticScratchBytes) return whole;
+    const size_t left = kStaticScratchBytes - s.bytes + s.spare_bytes;
+    return left < whole ? left : whole;
+}
+
 // The device address of `scratch` on the current device, set up on first use: the address is
 // looked up and the control words and exchange buffers are put into the state
 // hgf_workspace_init leaves them in (fill kernels on `st`, ahead of the caller's work).
@@ -482,8 +493,9 @@ hgf_status hgf_linear_forward(const void *x_f16, int M, const hgf_layer *L, void
     if (!aligned16(x_f16) || !aligned16(y_f16) || (acc_debug && !aligned16(acc_debug))) return HGF_ERR_ALIGN;
     if (!workspace) return HGF_ERR_WORKSPACE;
     if (!aligned16(workspace)) return HGF_ERR_ALIGN;
-    const Workspace ws = carve_workspace(workspace, M, L->d_in, L->d_out, L->rank);
+    Workspace ws = carve_workspace(workspace, M, L->d_in, L->d_out, L->rank);
     if (workspace_bytes < ws.bytes) return HGF_ERR_WORKSPACE;
+    ws.spare_bytes = single_spare(M, L);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (takes_direct_path(M, L, 1, false)) {
         void *ys[1] = {y_f16};
@@ -618,7 +630,8 @@ hgf_status hgf_linear_forward_static(const void *x_f16, int M, const hgf_layer *
     unsigned char *base = nullptr;
     const hgf_status ss = static_scratch(st, &base);
     if (ss != HGF_OK) return ss;
-    const Workspace ws = carve_static(base, M, L);
+    Workspace ws = carve_static(base, M, L);
+    ws.spare_bytes = single_spare(M, L);
     void *ys[1] = {y_f16};
     const bool profiling = g_profile;           // (the profiling aid creates events: not from here)
     g_profile = false;

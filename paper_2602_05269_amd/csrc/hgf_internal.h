@@ -131,8 +131,8 @@ inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // ---- workspace layout -------------------------------------------------------------
-// [ flags | exchange buffers of the single-launch path | x_q | s_x | rowsum | h16 | spare |
-//   weight-quantiser sums ]   (hgf_workspace_init zeroes the flags and fills the exchange
+// [ flags | exchange buffers of the single-launch path | x_q | s_x | rowsum | h16 |
+//   weight-quantiser sums | spare ]   (hgf_workspace_init zeroes the flags and fills the exchange
 //   buffers with the sentinel pattern)
 constexpr int kNumFlags = 64;                              // int32 words: launch counter, arrival count, sticky error
 constexpr size_t kZeroBytes = size_t(kNumFlags) * 4;
@@ -148,9 +148,9 @@ struct Workspace {
     int32_t *rowsum;
     _Float16 *h16;       // large M: kMaxGroup x [M, h_stride] SiLU(A x), zero padded (one per layer of a group)
     size_t h16_each;     // bytes per layer
+    double *wsum;        // [kWsumBlocks]
     unsigned char *spare; // direct path: slices of A x; further quantisations where layers have LayerNorms of their own
     size_t spare_bytes;
-    double *wsum;        // [kWsumBlocks]
     size_t bytes;        // total bytes needed
 };
 

@@ -32,14 +32,17 @@ def _both(g: GpuLayer, x: np.ndarray, ws: hb.Workspace):
 
 
 # (tokens, d_in, d_out, rank) of the first call and of the smaller second call, one pair per path:
-# the single persistent launch (M <= 4), the two-launch decode path, the prefill path
+# the single persistent launch (M <= 4), the direct path, few and many tokens (long rows: as many slices of d_in
+# from the array as from a workspace), the prefill path
 @pytest.mark.parametrize("first,second", [
     ((4, 4096, 1024, 64), (1, 1024, 320, 32)),
     ((32, 2048, 512, 64), (7, 1000, 130, 24)),
     ((300, 1536, 512, 64), (70, 512, 200, 16)),
+    ((1100, 4100, 64, 16), (600, 8200, 32, 24)),
+    ((1500, 256, 2000, 16), (1000, 512, 1800, 8)),
 ])
 def test_static_scratch_entry_matches_the_workspace_entry(first, second):
-    ws = hb.Workspace(512, 4096, 4096, 128)
+    ws = hb.Workspace(1500, 8200, 4096, 128)
     for i, (M, K, N, r) in enumerate((first, second, first)):
         assert hb.hgf_static_scratch_needed(M, K, N, r) <= hb.hgf_static_scratch_bytes()
         c = synth.make_custom(9100 + 10 * i + M, M, K, N, r, act="student_t3")
