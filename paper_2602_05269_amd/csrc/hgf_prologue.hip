@@ -338,8 +338,11 @@ __device__ inline void corr_tile(const ProParams &p, int job)
     v4f h = red[0][w][l];
 #pragma unroll
     for (int s = 1; s < kProWaves; ++s) h += red[s][w][l];
-    // element v: rank rt*16 + 4*kb + v of token m0 + 16*w + i (ranks past the rank: zeros)
+    // element v: rank rt*16 + 4*kb + v of token m0 + 16*w + i.  Ranks past the rank are zeros whatever x holds
+    // (their sums are not: zero times an infinity)
     if (w * 16 + i >= mrows) return;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) h[v] = rt * 16 + 4 * kb + v < L.rank ? h[v] : 0.f;
     const size_t at = (size_t)(m0 + w * 16 + i) * L.hstride + rt * 16 + 4 * kb;
     if (p.S > 1) {
         *reinterpret_cast<v4f *>(L.hpart + (size_t)sp * p.M * L.hstride + at) = h;

@@ -90,6 +90,34 @@ def test_line_between_the_paths_behind_a_layernorm(M, K, N, path):
     assert_close_fp16(y, ref["y"])
 
 
+@pytest.mark.parametrize("M,K,N,r,ln,path", [
+    (9, 130, 40, 1, False, "direct"), (50, 2500, 40, 5, False, "direct"), (600, 1365, 4096, 1, False, "prefill"),
+    (600, 1360, 4096, 17, False, "prefill"), (900, 1360, 4096, 16, True, "prefill"), (900, 1365, 4096, 3, True, "prefill"),
+])
+def test_infinite_activation_stays_out_of_padded_ranks(M, K, N, r, ln, path):
+    """One token holds +inf where every row of A is positive, so SiLU(A x) is +inf for every rank, and with
+    B and the gate positive the correction is +inf; a rank that pads the tile (a zero row of A: 0 * inf is
+    NaN) must not reach it.  The integer sum of that column's code (-127: inf * 0 is NaN, which the clip
+    turns into the lower bound) gives +inf where T is -1; behind a LayerNorm every code of the token is -127."""
+    c = synth.make_custom(5900 + M + K + r, M, K, N, r, act="normal", lora_std=0.05)
+    c["A"], c["B"], c["alpha"] = np.abs(c["A"]) + np.float16(0.01), np.abs(c["B"]) + np.float16(0.01), np.abs(c["alpha"]) + np.float16(0.1)
+    x = c["x"].copy()
+    m, k = M // 2, K // 3
+    x[m, k] = np.inf
+    ws = hb.Workspace(M, K, N, r)
+    g = LnLayer(c, ws, seed=1) if ln else GpuLayer(c, ws)
+    with path_taken(path):
+        y, acc = g.forward(x)
+    if ln:
+        # amax of an all-NaN row is the floor: a finite term beside the infinite correction
+        assert (y[m] == np.inf).all()
+    else:
+        assert np.array_equal(acc[m], -127 * g.T_ref[:, k].astype(np.int32))
+        assert (g.T_ref[:, k] == -1).any() and (y[m, g.T_ref[:, k] == -1] == np.inf).all()
+    others = np.arange(M) != m
+    assert_close_fp16(y[others], g.oracle(x[others], dense=True)["y"])
+
+
 @pytest.mark.parametrize("M", [150, 2000])
 def test_groups_of_mixed_layers(M):
     """Four layers of mixed ranks and ragged d_out read one slot, on the direct path (150 tokens) and on
