@@ -310,14 +310,20 @@ hgf_status run_large_group(const void *x, int M, const hgf_layer *layers, int G,
         pp.amax_zero = pair_out ? pair_out->amax_out : nullptr;
         pp.M = M;
         pp.K = K;
-        pp.G = G;
-        pp.NQ = 1;
         pp.S = 1;
         pp.base3 = 0;
         pp.by_rows = 1;
         pp.Q[0] = {ws.xq, ws.s_x, ws.rowsum, layers[0].ln_gamma, layers[0].ln_beta, layers[0].ln_eps};
-        for (int g = 0; g < G; ++g) pp.L[g] = {A[g], h16[g], nullptr, rank[g], h_stride(rank[g] > 0 ? rank[g] : 1)};
-        if (launch_prologue(pp, st) != hipSuccess) return HGF_ERR_DEVICE;
+        // one launch, or one per layer beyond 4 million tokens: a launch holds less than 2^32 threads (four
+        // layers of 128 ranks reach them at 7.5 million tokens)
+        const int at_once = M > (1 << 22) ? 1 : G;
+        for (int g0 = 0; g0 < G; g0 += at_once) {
+            pp.G = at_once;
+            pp.NQ = g0 == 0 ? 1 : 0;
+            for (int g = 0; g < at_once; ++g)
+                pp.L[g] = {A[g0 + g], h16[g0 + g], nullptr, rank[g0 + g], h_stride(rank[g0 + g] > 0 ? rank[g0 + g] : 1)};
+            if (launch_prologue(pp, st) != hipSuccess) return HGF_ERR_DEVICE;
+        }
     } else {
         if (pair_out && pair_out->amax_out && launch_zero_words(pair_out->amax_out, (size_t)M, st) != hipSuccess)
             return HGF_ERR_DEVICE;

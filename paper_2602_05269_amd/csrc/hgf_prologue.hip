@@ -396,7 +396,7 @@ hipError_t launch_prologue(ProParams &p, hipStream_t st)
     const int T = p.Kp <= 1024 ? 64 : (p.Kp <= 2048 ? 128 : (p.Kp <= 4096 ? 256 : 512));
     const int per_wg = kProThreads / T;
     const dim3 grid(jobs + p.NQ * ((p.M + per_wg - 1) / per_wg)), block(kProThreads);
-    if (grid.x == 0) return hipSuccess;             // nothing to quantise, no correction path
+    if (grid.x == 0) return hipSuccess;             // no quantisation (a later launch of the same tokens), no correction path
 #define HGF_PRO(TT_, T_, NU_)                                                                               \
     do {                                                                                                    \
         if (vec) hipLaunchKernelGGL((prologue_kernel<TT_, T_, NU_, true>), grid, block, 0, st, p);          \

@@ -168,6 +168,30 @@ def test_group_with_room_for_some_slices(ln):
         assert_close_fp16(slots[i + 1].cpu().numpy(), g.oracle(x, dense=True)["y"], f"layer {i}")
 
 
+def test_more_tokens_than_one_launch_prepares():
+    """Four layers of odd rows and 65 to 128 ranks read 7.6 million tokens: their preparation is more threads
+    than a launch may have, so it goes out layer by layer.  A few tokens from either end against the oracle."""
+    M, K, N = 7_600_000, 33, 8
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    x = torch.randn((M, K), generator=gen, device="cuda", dtype=torch.float16)
+    ws = hb.Workspace(M, K, N, 128)
+    layers, cases, slots = [], [], [x]
+    for i, r in enumerate((128, 65, 100, 0)):
+        c = synth.make_custom(8990 + i, 1, K, N, max(r, 1), act="normal", lora_std=0.05, w_std=0.05)
+        g = GpuLayer(c, ws, rank0=r == 0)
+        g.layer.c.src_slot, g.layer.c.dst_slot = 0, i + 1
+        slots.append(torch.zeros((M, N), dtype=torch.float16, device="cuda"))
+        cases.append(g)
+        layers.append(g.layer)
+    hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
+    torch.cuda.synchronize()
+    some = torch.cat([torch.arange(40), torch.arange(M // 2, M // 2 + 40), torch.arange(M - 40, M)])
+    xs = x[some.cuda()].cpu().numpy()
+    for i, g in enumerate(cases):
+        assert_close_fp16(slots[i + 1][some.cuda()].cpu().numpy(), g.oracle(xs)["y"], f"layer {i}")
+
+
 @pytest.mark.parametrize("M,K,N,rg,ru,path", [
     # eight and four wavefronts, ragged rows of the last row-block, sliced A x, one rank zero, many row-blocks
     (33, 130, 65, 24, 8, "direct"), (40, 2500, 300, 16, 40, "direct"), (50, 2500, 300, 16, 24, "direct"),
