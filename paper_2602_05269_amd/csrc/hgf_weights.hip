@@ -137,8 +137,11 @@ __global__ __launch_bounds__(256) void pack_kernel(const float *__restrict__ W, 
         part |= (uint32_t)dpp_move<0x4E>((int)part);
         if ((c & 3) == 0) words[w][word + 4 * row] = part;
     }
-    // (the wavefront's own words: no other wavefront reads or writes them)
+    // the wavefront's own words, from other lanes: LDS takes its requests in order, the fences keep the compiler
+    // from reordering them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     reinterpret_cast<v4u *>(packed)[tile * 64 + l] = reinterpret_cast<const v4u *>(words[w])[l];
 }
 
