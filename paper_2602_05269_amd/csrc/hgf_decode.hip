@@ -6,7 +6,7 @@
 //   y[m,n]   = acc * (s_x[m] s_w) + tanh(alpha[n]) * sum_j B[n,j] h[m,j]
 // (the prologue has left x_q, s_x, the row sums and h = SiLU(A x)).
 //
-// Work split: a workgroup owns WR row-blocks of 32 rows x TG groups of 32 tokens and all of d_in;
+// Work split: a workgroup owns WR row-blocks of 32 rows x a group of 32 tokens and all of d_in;
 // its KW wavefronts take the k-tiles round-robin and contract them on the 32x32x32 int8 MFMA (weight
 // rows = matrix rows, tokens = matrix columns).  Both operands come straight from memory into the
 // registers the MFMA reads: a tile of weights is one 16-byte request per lane (widened to int8 with
@@ -79,24 +79,25 @@ __device__ inline void base3_digits(v4u bytes, v4i (&digit)[5])
 // ONCE: weights are requested as read once (non-temporal), for groups whose weights no second launch or
 // token group finds in a cache.
 constexpr int direct_waves(int D) { return D == 1 ? 4 : 3; }
-template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false, bool ONCE = false>
+template <int WR, int KW, int D, bool PAIR, bool B3 = false, bool ONCE = false>
 __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(DecodeParams p)
 {
     static_assert(!PAIR || WR == 2, "a pair is one row-block of each layer");
     constexpr int NQ = B3 ? 5 : 4;                            // MFMAs per k-tile
-    constexpr int TILES = (PAIR ? 1 : WR) * TG;               // output tiles of 32 rows x 32 tokens
+    constexpr int TILES = PAIR ? 1 : WR;                      // output tiles of 32 rows x 32 tokens
     constexpr int PPW = 4 * TILES > KW ? 4 * TILES / KW : 1;  // quarter tiles a wavefront finishes (of one tile)
-    static_assert(PPW <= 4, "a wavefront finishes quarters of one tile");
+    static_assert(PPW <= 2, "a wavefront finishes one or two quarters of one tile");
     constexpr int NL = PAIR ? 2 : 1;                          // layers of a finished tile
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
     const int l = threadIdx.x & 63, jl = l & 31, hf = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // Token units of one row unit are eight workgroups apart, so they run on one XCD and its L2 hands
+    // Token groups of one row unit are eight workgroups apart, so they run on one XCD and its L2 hands
     // the weights to all of them.
-    const int TU = (p.M + 32 * TG - 1) / (32 * TG);
+    const int TU = (p.M + 31) / 32;
     const int blk = (int)blockIdx.x / (8 * TU), rem = (int)blockIdx.x % (8 * TU);
-    const int u = blk * 8 + rem % 8, m0 = rem / 8 * 32 * TG;
+    const int u = blk * 8 + rem % 8, m0 = rem / 8 * 32;
+    const int tokens = min(32, p.M - m0);
     if (u >= p.wg_start[p.G]) return;
     // this workgroup's layer: every candidate is read at a fixed kernel-argument offset (one batch of
     // scalar loads) and selected, instead of a dependent load at a computed offset
@@ -116,8 +117,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
     auto rb_of = [&](int r) { return PAIR ? rb0 : rb0 + r; };
 
     // ---- the main loop's operands
-    rsrc_t wr[WR], xr[TG];
-    unsigned xoff[TG], xstep[TG];
+    rsrc_t wr[WR];
 #pragma unroll
     for (int r = 0; r < WR; ++r) {
         const DecLayer &Lr = layer_of(r);
@@ -130,15 +130,11 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
             wr[r] = make_rsrc(Lr.packed + (size_t)(ok ? rb_of(r) : 0) * p.KT * 64, ok ? (unsigned)p.KT * kTileBytes : 0u);
         }
     }
-#pragma unroll
-    for (int tg = 0; tg < TG; ++tg) {
-        const int rows = min(32, p.M - m0 - tg * 32);         // tokens of the group (may be <= 0)
-        xr[tg] = make_rsrc(L.xq + (size_t)(rows > 0 ? m0 + tg * 32 : 0) * p.Kp, rows > 0 ? (unsigned)rows * p.Kp : 0u);
-        xstep[tg] = (unsigned)max(rows, 0) * (B3 ? 16u : 32u);    // bytes per MFMA (B3: of one half's tokens)
-        xoff[tg] = jl < rows ? (unsigned)(hf * (B3 ? NQ : 1) * rows + jl) * 16u : kOobStep;
-    }
+    const rsrc_t xr = make_rsrc(L.xq + (size_t)m0 * p.Kp, (unsigned)tokens * p.Kp);
+    const unsigned xstep = (unsigned)tokens * (B3 ? 16u : 32u);   // bytes per MFMA (B3: of one half's tokens)
+    const unsigned xoff = jl < tokens ? (unsigned)(hf * (B3 ? NQ : 1) * tokens + jl) * 16u : kOobStep;
     v4u wq[D][WR];
-    v4u xq[D][TG][NQ];
+    v4u xq[D][NQ];
     const unsigned woff = B3 ? (unsigned)jl * ((unsigned)p.Kp / 5) + hf * 16u : l * 16u;
     auto request = [&](int d, int kt) __attribute__((always_inline)) {
         // (B3: past the last k-tile lies the next row.  In the last tile the second half may be one too: its
@@ -149,10 +145,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
                    : ONCE ? buf_load16_stream(wr[r], (unsigned)kt * kTileBytes + woff)
                           : buf_load16(wr[r], (unsigned)kt * kTileBytes + woff);
 #pragma unroll
-        for (int tg = 0; tg < TG; ++tg)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                xq[d][tg][q] = buf_load16(xr[tg], xoff[tg] + (unsigned)(kt * (B3 ? 2 * NQ : NQ) + q) * xstep[tg]);
+        for (int q = 0; q < NQ; ++q) xq[d][q] = buf_load16(xr, xoff + (unsigned)(kt * (B3 ? 2 * NQ : NQ) + q) * xstep);
     };
 #pragma unroll
     for (int d = 0; d < D; ++d) request(d, w + d * KW);
@@ -161,8 +154,8 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
     //      dealt out over the wavefronts.  Ranks past the rank and rows past the end are zeros.
     //      The same LDS takes the partial tiles at the end, when the corrections have been formed: what a
     //      workgroup holds decides how many of them share a compute unit.
-    constexpr int NB = WR;                                    // B blocks, then NL * TG h blocks
-    const int NH = p.S > 1 ? 0 : NL * TG;
+    constexpr int NB = WR;                                    // B blocks, then NL h blocks
+    const int NH = p.S > 1 ? 0 : NL;
     const int JS = p.hsteps;                                  // 16-rank steps (of the wider layer of a pair)
     unsigned char *const ops = lds;
     for (int i = w; i < (NB + NH) * JS; i += KW) {
@@ -181,8 +174,8 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
                 *reinterpret_cast<v8h *>(dst + l * 16) = buf_load8h<false>(br, (unsigned)n * Lr.rank + j0, Lr.rank - j0, n < Lr.N);
             }
         } else {
-            const int hb = blkno - NB, lay = hb / TG, m = m0 + (hb - lay * TG) * 32 + jl;
-            const DecLayer &Lr = lay > 0 ? layer_of(1) : layer_of(0);
+            const int m = m0 + jl;
+            const DecLayer &Lr = blkno - NB > 0 ? layer_of(1) : layer_of(0);
             const rsrc_t hr = make_rsrc(Lr.h16, Lr.rank > 0 ? (unsigned)p.M * Lr.hstride * 2u : 0u);
             // (the prologue writes whole tiles of 16 ranks)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(hr, (lds_ptr_t)dst, 16,
@@ -197,7 +190,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
         for (int g = 0; g < NL; ++g) {
             const DecLayer &Lg = layer_of(g);
             const int width = (Lg.rank + 15) / 16 * 4;        // quadruples per token (whole tiles of 16 ranks)
-            const int quads = width * min(32 * TG, p.M - m0);
+            const int quads = width * tokens;
             const unsigned slice = (unsigned)p.M * Lg.hstride * 4u;
             const rsrc_t hr = make_rsrc(Lg.hpart, Lg.rank > 0 ? (unsigned)p.S * slice : 0u);
             for (int i0 = threadIdx.x; i0 < quads; i0 += 64 * KW * HV) {
@@ -225,8 +218,8 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = (_Float16)silu(h[e]);
                     if (i0 + v * 64 * KW < quads)
-                        *reinterpret_cast<v4h *>(ops + ((NB + g * TG + (tok[v] >> 5)) * JS + (j[v] >> 4)) * 1024 +
-                                                 ((j[v] >> 3 & 1) * 32 + (tok[v] & 31)) * 16 + (j[v] & 4) * 2) = o;
+                        *reinterpret_cast<v4h *>(ops + ((NB + g) * JS + (j[v] >> 4)) * 1024 +
+                                                 ((j[v] >> 3 & 1) * 32 + tok[v]) * 16 + (j[v] & 4) * 2) = o;
                 }
             }
         }
@@ -235,11 +228,10 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
     else if (p.S > 2) stage_slices(std::integral_constant<int, 4>{});
     else if (p.S > 1) stage_slices(std::integral_constant<int, 2>{});
 
-    // what this wavefront finishes: quarters piece0 .. of the tile (row-block rt, token group tt)
+    // what this wavefront finishes: quarters piece0 .. of row-block rt's tile
     const bool finishes = w * PPW < 4 * TILES;
-    const int tile = finishes ? w * PPW / 4 : 0, piece0 = finishes ? w * PPW % 4 : 0;
-    const int rt = PAIR ? 0 : tile / TG, tt = tile % TG;
-    const int m = m0 + tt * 32 + jl;
+    const int rt = finishes && !PAIR ? w * PPW / 4 : 0, piece0 = finishes ? w * PPW % 4 : 0;
+    const int m = m0 + jl;
     const bool m_ok = m < p.M;
     const int nb = (PAIR ? rb0 : rb0 + rt) * kTileRows;       // first row of the tile
     float s_w[NL], alpha[NL][PPW][4];
@@ -260,11 +252,9 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
     const int rs = (int)buf_load4(make_rsrc(L.rowsum, (unsigned)p.M * 4u), (unsigned)m * 4u, m_ok);
 
     // ---- the contraction
-    v16i acc[WR][TG];
+    v16i acc[WR];
 #pragma unroll
-    for (int r = 0; r < WR; ++r)
-#pragma unroll
-        for (int tg = 0; tg < TG; ++tg) acc[r][tg] = (v16i){};
+    for (int r = 0; r < WR; ++r) acc[r] = (v16i){};
     for (int k0 = w; k0 < p.KT; k0 += D * KW) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -279,9 +269,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
 #pragma unroll
                 for (int r = 0; r < WR; ++r) {
                     const v4i a = B3 ? digit[r][q] : widen_codes(wq[d][r][q & 3]);
-#pragma unroll
-                    for (int tg = 0; tg < TG; ++tg)
-                        acc[r][tg] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, __builtin_bit_cast(v4i, xq[d][tg][q]), acc[r][tg], 0, 0, 0);
+                    acc[r] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, __builtin_bit_cast(v4i, xq[d][q]), acc[r], 0, 0, 0);
                 }
             }
             request(d, k0 + (d + D) * KW);
@@ -300,7 +288,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
         if (finishes)
             for (int js = 0; js * 16 < Lg.rank; ++js) {
                 const v8h b = *reinterpret_cast<const v8h *>(ops + ((PAIR ? g : rt) * JS + js) * 1024 + l * 16);
-                const v8h h = *reinterpret_cast<const v8h *>(ops + ((NB + g * TG + tt) * JS + js) * 1024 + l * 16);
+                const v8h h = *reinterpret_cast<const v8h *>(ops + ((NB + g) * JS + js) * 1024 + l * 16);
                 corr = __builtin_amdgcn_mfma_f32_32x32x16_f16(b, h, corr, 0, 0, 0);
             }
 #pragma unroll
@@ -308,8 +296,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int q = piece0 + c;
-                cv[g][c][v] = PPW == 4 ? corr[4 * c + v]
-                                       : (q == 0 ? corr[v] : (q == 1 ? corr[4 + v] : (q == 2 ? corr[8 + v] : corr[12 + v])));
+                cv[g][c][v] = q == 0 ? corr[v] : (q == 1 ? corr[4 + v] : (q == 2 ? corr[8 + v] : corr[12 + v]));
             }
     }
     __syncthreads();                                          // everyone has read the operands
@@ -320,11 +307,8 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
 #pragma unroll
     for (int r = 0; r < WR; ++r)
 #pragma unroll
-        for (int tg = 0; tg < TG; ++tg)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                red[(((r * TG + tg) * KW + w) * 4 + c) * 64 + l] =
-                    (v4i){acc[r][tg][4 * c], acc[r][tg][4 * c + 1], acc[r][tg][4 * c + 2], acc[r][tg][4 * c + 3]};
+        for (int c = 0; c < 4; ++c)
+            red[((r * KW + w) * 4 + c) * 64 + l] = (v4i){acc[r][4 * c], acc[r][4 * c + 1], acc[r][4 * c + 2], acc[r][4 * c + 3]};
     __syncthreads();
     if (!finishes || nb >= L.N) return;
 
@@ -340,7 +324,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
         float y[NL][4];
 #pragma unroll
         for (int g = 0; g < NL; ++g) {
-            const v4i *part = red + (((PAIR ? g : rt) * TG + tt) * KW * 4 + piece0 + c) * 64 + l;
+            const v4i *part = red + ((PAIR ? g : rt) * KW * 4 + piece0 + c) * 64 + l;
             a[g] = part[0];
 #pragma unroll
             for (int o = 1; o < KW; ++o) a[g] += part[o * 256];
@@ -384,7 +368,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
     }
 }
 
-template <int WR, int TG, int KW, int D, bool PAIR, bool B3 = false, bool ONCE = false>
+template <int WR, int KW, int D, bool PAIR, bool B3 = false, bool ONCE = false>
 hipError_t launch_shape(DecodeParams &p, hipStream_t st)
 {
     int units = 0;
@@ -393,13 +377,13 @@ hipError_t launch_shape(DecodeParams &p, hipStream_t st)
         if (!PAIR || g == 0) units += PAIR ? p.L[g].RBn : (p.L[g].RBn + WR - 1) / WR;
     }
     for (int g = p.G; g <= kMaxGroup; ++g) p.wg_start[g] = units;
-    const size_t red = (size_t)KW * WR * TG * 4096, ops = (size_t)(WR + (PAIR ? 2 : 1) * TG) * p.hsteps * 1024;
+    const size_t red = (size_t)KW * WR * 4096, ops = (size_t)(WR + (PAIR ? 2 : 1)) * p.hsteps * 1024;
     const size_t lds = red > ops ? red : ops;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<WR, TG, KW, D, PAIR, B3, ONCE>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<WR, KW, D, PAIR, B3, ONCE>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
-    const int TU = (p.M + 32 * TG - 1) / (32 * TG);
-    hipLaunchKernelGGL((direct_kernel<WR, TG, KW, D, PAIR, B3, ONCE>), dim3((units + 7) / 8 * 8 * TU), dim3(64 * KW), lds, st, p);
+    const int TU = (p.M + 31) / 32;
+    hipLaunchKernelGGL((direct_kernel<WR, KW, D, PAIR, B3, ONCE>), dim3((units + 7) / 8 * 8 * TU), dim3(64 * KW), lds, st, p);
     return hipGetLastError();
 }
 
@@ -418,16 +402,15 @@ hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
         L.b_aligned = (reinterpret_cast<uintptr_t>(L.B) & 15u) == 0;
         if ((L.rank + 15) / 16 > p.hsteps) p.hsteps = (L.rank + 15) / 16;
     }
-    // The shape: row-blocks x token groups of a workgroup, wavefronts, tiles in flight.  `tiles` output
-    // tiles of 32 x 32 are dealt out to 256 compute units, so few tiles want many wavefronts along d_in
-    // and many tiles want a workgroup that reads its tokens (or weights) for two of them (us per group of
-    // layers, both launches: 7B-shape down, 86 k-tiles, 128 tiles: 15.9 with eight wavefronts, 16.7 with
-    // four; 2048 -> 2048, 16 k-tiles, 64 tiles: 11.9 and 11.6; 7B-shape up + gate at 64 tokens, 1376 tiles:
-    // 35.0 for one row-block per workgroup, 30.7 for two; at 8 tokens, 688 tiles, 19.7 and 20.0; 7B-shape
-    // down at 128 tokens, 512 tiles: two row-blocks with eight wavefronts 24.7, four wavefronts 27.0; at
-    // 256 tokens 42.7 and 39.8).
-    // (4096 -> 11008 at one token, 344 row-blocks: two k-tiles in flight 10.6, four 11.2; eight wavefronts 11.0)
-    if (p.base3) return launch_shape<1, 1, 4, 2, false, true>(p, st);
+    // The shape: row-blocks of a workgroup, wavefronts, tiles in flight.  `tiles` output tiles of 32 x 32 are
+    // dealt out to 256 compute units, so few tiles want many wavefronts along d_in and many tiles want a
+    // workgroup that reads its tokens for two of them (us per group of layers, both launches: 7B-shape down,
+    // 86 k-tiles, 128 tiles: 15.9 with eight wavefronts, 16.7 with four; 2048 -> 2048, 16 k-tiles, 64 tiles: 11.9
+    // and 11.6; 7B-shape up + gate at 64 tokens, 1376 tiles: 35.0 for one row-block per workgroup, 30.7 for
+    // two; 7B-shape down at 128 tokens, 512 tiles: two row-blocks with eight wavefronts 24.7, four wavefronts
+    // 27.0; at 256 tokens 42.7 and 39.8).
+    // (base-3, 4096 -> 11008 at one token, 344 row-blocks: two k-tiles in flight 10.6, four 11.2; eight wavefronts 11.0)
+    if (p.base3) return launch_shape<1, 4, 2, false, true>(p, st);
     const int groups = (p.M + 31) / 32, tiles = rbs * groups;
     if (p.pair) {
         if (p.G != 2 || p.L[0].N != p.L[1].N) return hipErrorInvalidValue;
@@ -435,8 +418,8 @@ hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
         // (one token group: the weights are the traffic, see below.  7B-shape at 4 tokens 21.4 with three tiles in
         // flight, 20.1 with two and read-once requests; 4096 -> 14336 at 5 tokens 20.9 and 19.6; with 256 row-blocks
         // of 16 k-tiles 13.3 and 13.7)
-        if (groups == 1 && tiles > 512) return launch_shape<2, 1, 4, 2, true, false, true>(p, st);
-        return tiles > 512 ? launch_shape<2, 1, 4, 3, true>(p, st) : launch_shape<2, 1, 8, 3, true>(p, st);
+        if (groups == 1 && tiles > 512) return launch_shape<2, 4, 2, true, false, true>(p, st);
+        return tiles > 512 ? launch_shape<2, 4, 3, true>(p, st) : launch_shape<2, 8, 3, true>(p, st);
     }
     // One token group: hardly anything but weights is read, so with many row-blocks what counts is how many
     // wavefronts are in flight, not how deep each reads ahead, and with many bytes that they are requested as
@@ -446,20 +429,20 @@ hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
     // 1050 1.01 / 1.23; beyond 1.03 / 1.33.  Up + gate of the 7B shape, 688 row-blocks, 5 tokens: 19.8 -> 18.5,
     // without the read-once requests 19.0; three such layers 25.5 -> 22.4; 512 -> 32000 12.3 -> 9.6.)
     if (groups == 1) {
-        if (p.KT >= 32 && tiles <= 256) return launch_shape<1, 1, 8, 3, false>(p, st);
-        if (p.KT > 8 && tiles <= (p.KT > 24 ? 512 : 256)) return launch_shape<1, 1, 4, 4, false>(p, st);
+        if (p.KT >= 32 && tiles <= 256) return launch_shape<1, 8, 3, false>(p, st);
+        if (p.KT > 8 && tiles <= (p.KT > 24 ? 512 : 256)) return launch_shape<1, 4, 4, false>(p, st);
         if (tiles <= (p.KT <= 8 ? 1300 : 800))
-            return p.KT <= 24 ? launch_shape<1, 1, 4, 1, false>(p, st) : launch_shape<1, 1, 4, 1, false, false, true>(p, st);
-        if (tiles <= 1050) return launch_shape<2, 1, 4, 2, false, false, true>(p, st);
-        return p.KT <= 4 ? launch_shape<2, 1, 4, 1, false>(p, st) : launch_shape<2, 1, 4, 1, false, false, true>(p, st);
+            return p.KT <= 24 ? launch_shape<1, 4, 1, false>(p, st) : launch_shape<1, 4, 1, false, false, true>(p, st);
+        if (tiles <= 1050) return launch_shape<2, 4, 2, false, false, true>(p, st);
+        return p.KT <= 4 ? launch_shape<2, 4, 1, false>(p, st) : launch_shape<2, 4, 1, false, false, true>(p, st);
     }
     if (tiles <= 256)
-        return p.KT >= 32 ? launch_shape<1, 1, 8, 3, false>(p, st) : launch_shape<1, 1, 4, 4, false>(p, st);
-    if (tiles <= 640) return launch_shape<2, 1, 8, 3, false>(p, st);
+        return p.KT >= 32 ? launch_shape<1, 8, 3, false>(p, st) : launch_shape<1, 4, 4, false>(p, st);
+    if (tiles <= 640) return launch_shape<2, 8, 3, false>(p, st);
     // (a wavefront with one k-tile has nothing to keep in flight behind it: registers for four workgroups
     // per compute unit instead of two, 1024 of them in one round.  2048 tiles of four k-tiles: 8.7 us, where
     // four in flight took 12.2)
-    return p.KT <= 4 ? launch_shape<2, 1, 4, 1, false>(p, st) : launch_shape<2, 1, 4, 3, false>(p, st);
+    return p.KT <= 4 ? launch_shape<2, 4, 1, false>(p, st) : launch_shape<2, 4, 3, false>(p, st);
 }
 
 }  // namespace hgf
