@@ -8,7 +8,7 @@ import torch
 from oracle import hgf_oracle as orc
 from paper_2602_05269_amd import binding as hb
 from paper_2602_05269_amd import synth
-from parity import GpuLayer, assert_close_fp16, dev
+from parity import GpuLayer, assert_close_fp16, dev, path_taken
 
 pytestmark = pytest.mark.gpu
 
@@ -125,30 +125,38 @@ def test_few_token_single_launch_parity(M, K, N, r, ws):
     assert_close_fp16(y1, y2.astype(np.float64))
 
 
-@pytest.mark.parametrize("M,K,N,r", [(65, 256, 128, 16), (130, 512, 200, 32), (256, 1365, 256, 64)])
-def test_large_m_parity(M, K, N, r, ws):
+@pytest.mark.parametrize("M,K,N,r,path", [
+    (65, 256, 128, 16, "direct"), (130, 512, 200, 32, "direct"), (256, 1365, 256, 64, "direct"),
+    (1030, 256, 1500, 16, "prefill"), (800, 520, 2000, 64, "prefill"), (200, 1365, 7700, 32, "prefill"),
+])
+def test_large_m_parity(M, K, N, r, path, ws):
     c = synth.make_custom(2000 + M + K + N + r, M, K, N, r, act="student_t4")
     g = GpuLayer(c, ws)
-    g.check_forward(c["x"])
+    with path_taken(path):
+        g.check_forward(c["x"])
 
 
 @pytest.mark.parametrize("M,K,N,r", [(70, 4104, 96, 8), (66, 8200, 64, 16), (65, 16392, 40, 8)])
 def test_large_m_long_rows_parity(M, K, N, r, ws):
-    """Rows of 4104, 8200 and 16392 columns: the prefill path's quantiser keeps 16 and 32
-    register pieces per lane for the first two (and shares the down-projections' launch);
-    the third is beyond that and takes the quantiser's own launch."""
+    """Rows of 4104, 8200 and 16392 columns beyond 64 tokens, on the direct path: three, five and nine
+    slices of d_in.  (The prefill path's quantiser at such rows, register depth by register depth:
+    test_gpu_direct.test_prefill_path.)"""
     c = synth.make_custom(2100 + M + K + N + r, M, K, N, r, act="student_t4")
     g = GpuLayer(c, ws if K <= 11008 else hb.Workspace(M, K, 64, 128))
-    g.check_forward(c["x"])
+    with path_taken("direct"):
+        g.check_forward(c["x"])
 
 
-def test_prefill_group_shares_one_launch(ws):
-    """Four layers read slot 0 at M = 150: ranks 16, 24 and 32 pad to the same 32 columns of
+@pytest.mark.parametrize("M,path", [(150, "direct"), (3500, "prefill")])
+def test_group_shares_one_launch(M, path, ws):
+    """Four layers read slot 0.  At M = 3500 ranks 16, 24 and 32 pad to the same 32 columns of
     SiLU(A x), so their tiles (d_out 300, 256 and 40: two, one and one row tiles, the first and
-    last ragged) go out as one launch of the prefill kernel; the rank-64 layer takes its own.
-    Each output is checked against the oracle and must equal, bit for bit, what the same layer
-    gives on its own."""
-    M, K = 150, 384
+    last ragged) go out as one launch of the prefill kernel; the rank-64 layer takes its own.  At
+    M = 150 the direct path takes all four in one launch.  Each output is checked against the oracle
+    and must equal, bit for bit, what the same layer gives on its own (on the same path)."""
+    K = 384
+    if M > 2048:
+        ws = hb.Workspace(M, K, 300, 64)
     shapes = [(300, 16), (256, 24), (40, 32), (128, 64)]
     cases, layers = [], []
     slots = [None] * (len(shapes) + 1)
@@ -162,13 +170,15 @@ def test_prefill_group_shares_one_launch(ws):
         cases.append(g)
         layers.append(g.layer)
         slots[i + 1] = torch.zeros((M, N), dtype=torch.float16, device="cuda")
-    hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
+    with path_taken(path):
+        hb.hgf_stack_forward(hb.Stack(layers, slots, M), ws)
     torch.cuda.synchronize()
     for i, g in enumerate(cases):
         got = slots[i + 1].cpu().numpy()
-        ref = g.oracle(x)
+        ref = g.oracle(x, dense=M > 2048)
         assert_close_fp16(got, ref["y"], f"layer {i}")
-        y1, acc1 = g.forward(x)
+        with path_taken(path):
+            y1, acc1 = g.forward(x)
         assert np.array_equal(acc1, ref["acc"])
         assert np.array_equal(got, y1), f"layer {i}: grouped launch and single layer differ"
 
@@ -176,11 +186,10 @@ def test_prefill_group_shares_one_launch(ws):
 @pytest.mark.parametrize("M", [12, 13, 33, 64])
 def test_decode_group_with_many_row_blocks(M, ws):
     """Two layers read slot 0 and have 513 row-blocks between them (d_out 8200 and 8190, the
-    second ragged; d_in 520: five k-tiles, the last ragged): the group's launch splits d_in over
-    four wavefronts up to 12 tokens and, from 13 tokens on, gives a workgroup four row-blocks with
-    two wavefronts each (the last workgroup of either layer is ragged); 33 and 64 tokens take two
-    token groups.  Every output against the oracle, accumulators bit for bit against the single
-    layer."""
+    last of either ragged; d_in 520: five k-tiles, the last ragged): one token group takes a row-block per
+    workgroup with one tile in flight, 33 and 64 tokens (two groups) two row-blocks per workgroup, the
+    last workgroup of the first layer with one.  Every output against the oracle, accumulators bit for bit
+    against the single layer."""
     K = 520
     shapes = [(8200, 16), (8190, 40)]
     cases, layers = [], []
@@ -350,17 +359,18 @@ def test_config1_stack_teacher_forced(chained, ws):
     assert rel < 0.05, rel
 
 
-@pytest.mark.parametrize("M", [1, 3, 4, 8, 16, 32, 40, 70])
+@pytest.mark.parametrize("M", [1, 3, 4, 8, 16, 32, 40, 70, 3500])
 def test_mixed_stack_teacher_forced(M, ws):
     """A short list that exercises the whole-stack launch and its fall-backs in one call: a
     group of two layers (one without correction), activations handed on inside the launch,
     ragged d_in (264), then a layer whose d_out (130) keeps it out of the whole-stack launch
     and one whose d_in (130) takes the two-launch path.  Every layer is checked against the
     oracle on the input the GPU gave it; a second run must reproduce the first bit for bit.
-    M = 8 ... 40 take the two-launch decode path, whose prologue and grouped main kernel serve
-    both layers of the group (one of them without correction) in one launch each.
-    M = 70 sends the same list down the prefill path, whose down-projection kernel serves
-    both layers of the group in one launch."""
+    M = 8 ... 70 take the direct path, whose prologue and grouped main kernel serve both layers of the
+    group (one of them without correction) in one launch each.  M = 3500 sends the same list down
+    the prefill path, whose preparation serves both layers of the group in one launch."""
+    if M > 2048:
+        ws = hb.Workspace(M, 512, 512, 32)
     shapes = [(256, 512, 16, 0, 1), (256, 384, 0, 0, 2), (512, 256, 32, 1, 3), (256, 264, 8, 3, 4),
               (264, 128, 24, 4, 5), (128, 130, 16, 5, 6), (130, 64, 8, 6, 7)]
     cases, layers = [], []
@@ -377,13 +387,14 @@ def test_mixed_stack_teacher_forced(M, ws):
     st = hb.Stack(layers, slots, M)
     flags = lambda: ws.buf[:32].view(torch.int32).cpu().numpy().copy()
     before = flags()
-    hb.hgf_stack_forward(st, ws)
+    with path_taken("prefill" if M > 2048 else "direct"):
+        hb.hgf_stack_forward(st, ws)
     torch.cuda.synchronize()
     after = flags()
     assert after[4] == before[4] + (1 if M <= 4 else 0) and after[5] == 0 and after[2] == 0, (before, after)
     host = [s.cpu().numpy() for s in slots]
     for g, (K, N, r, src, dst) in zip(cases, shapes):
-        ref = g.oracle(host[src])
+        ref = g.oracle(host[src], dense=M > 2048)
         assert_close_fp16(host[dst], ref["y"], f"slot {dst}")
         _, acc1 = g.forward(host[src])
         assert np.array_equal(acc1, ref["acc"])
