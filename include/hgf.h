@@ -151,10 +151,12 @@ typedef struct {
  *   acc_debug int32 [M, d_out] or NULL: receives the exact integer accumulators
  *             sum_k T[n,k] x_q[m,k] of step 3 (for parity tests)
  *
- * M <= 40, and any M whose 32 x 32 output tiles are about a chipful, runs the direct kernel (weights
- * straight from memory into the MFMA); larger M runs the int8 MFMA prefill kernel.  Both give the same integers.  A layer with ln_gamma set
- * takes the fused LayerNorm quantiser as its prologue (layers with a LayerNorm of their own never
- * share a quantisation in hgf_stack_forward). */
+ * Up to 40 tokens always, and beyond as long as the 32 x 32 output tiles and the tokens of the layer
+ * (or of the group of layers that share an input) stay below a limit of some 1750 to 2800 tiles, a call
+ * runs the direct kernel (weights straight from memory into the MFMA; up to 4 tokens as one persistent
+ * launch); larger ones run the int8 MFMA prefill kernel.  Both give the same integers.  A layer with
+ * ln_gamma set is quantised behind the fused LayerNorm.  In hgf_stack_forward layers with LayerNorms of
+ * their own never share a quantisation; on the direct path those that read one slot share the launches. */
 hgf_status hgf_linear_forward(const void *x_f16, int M, const hgf_layer *L, void *y_f16,
                               int32_t *acc_debug, void *workspace, size_t workspace_bytes,
                               void *stream);
@@ -303,7 +305,7 @@ hgf_status hgf_probe_mfma_rate(int operand_kind, int iters, double *tops_out, do
  * d_in <= 12288.  level 2 (default): hgf_stack_forward runs whole runs of groups of layers as
  * one persistent launch (activations handed from layer to layer inside the launch), and
  * single groups as level 1; level 1: each group of layers is one persistent launch;
- * level 0: the two-launch path that serves 5..64 tokens.  Results agree bit for bit in the
+ * level 0: the direct path's two launches, as for more tokens.  Results agree bit for bit in the
  * integers; the fp16 outputs may differ in the last place (different split of A x). */
 void hgf_set_single_launch(int level);
 

@@ -146,7 +146,7 @@ struct Workspace {
     int8_t *xq;
     float *s_x;
     int32_t *rowsum;
-    _Float16 *h16;       // large M: kMaxGroup x [M, h_stride] SiLU(A x), zero padded (one per layer of a group)
+    _Float16 *h16;       // kMaxGroup x [M, h_stride] SiLU(A x), zero padded (one per layer of a group)
     size_t h16_each;     // bytes per layer
     double *wsum;        // [kWsumBlocks]
     unsigned char *spare; // direct path: slices of A x; further quantisations where layers have LayerNorms of their own
