@@ -105,13 +105,28 @@ __global__ __launch_bounds__(256) void pack_kernel(const float *__restrict__ W, 
     // the rows of the block behind one descriptor (at most 32 rows of HGF_MAX_DIM floats); rows start
     // at any multiple of four bytes, which is all a 16-byte request asks for
     const rsrc_t r = make_rsrc(W + (size_t)row0 * K, (unsigned)rows * K * 4u);
+    // (the lane that holds a row's last one to three columns asks for the row's last four, in the same burst, and
+    // moves them down: three more requests per row behind the first cost 0.4 us, 65 x 65 9.5 against 9.1)
+    const bool last = K >= 4 && k0 < K && k0 + 3 >= K;
+    const int from = last ? K - 4 : k0;
     v4f v[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int row = 2 * i + (l >> 5);
-        v[i] = __builtin_bit_cast(v4f, buf_load16(r, ((unsigned)row * K + k0) * 4u, row < rows && k0 + 3 < K));
+        v[i] = __builtin_bit_cast(v4f, buf_load16(r, ((unsigned)row * K + from) * 4u, row < rows && from + 3 < K));
     }
-    if (K % 4 != 0 && kt == KT - 1) {              // the lane that holds a row's last one to three columns
+    if (K % 4 != 0 && kt == KT - 1 && K >= 4) {
+        const int down = 4 - K % 4;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const v4f u = v[i];
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                const float t = down == 1 ? u[e + 1] : (down == 2 ? u[e < 2 ? e + 2 : 3] : u[3]);
+                v[i][e] = last ? t : u[e];
+            }
+        }
+    } else if (K < 4) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int row = 2 * i + (l >> 5);

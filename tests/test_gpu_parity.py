@@ -46,7 +46,7 @@ def test_pack_unpack_matches_oracle_ternariser(N, K, ws):
     g.check_weights()
 
 
-@pytest.mark.parametrize("N,K", [(1, 1), (31, 127), (33, 129), (32, 130), (65, 259), (3, 1365)])
+@pytest.mark.parametrize("N,K", [(1, 1), (2, 3), (35, 4), (3, 5), (34, 6), (5, 7), (31, 127), (33, 129), (32, 130), (65, 259), (3, 1365)])
 def test_pack_edges_of_tiles_and_odd_addresses(N, K, ws):
     # edges of the 32 x 128 tiles, one to three columns past the last whole 16 bytes, and latents that
     # start at any multiple of four bytes; padding rows and columns hold code 1 (bytes of 0x55)
