@@ -36,7 +36,7 @@ struct AttnParams {
     float *part;                       // [B, n_heads, chunks, 2, d_h + 2]
     _Float16 *out;                     // [B, n_heads, d_h]
     int B, L_max, n_heads, d_h, chunks;
-    int heads_first;                   // grid of pass 1: heads fastest, else chunks
+    int heads_first, rotate;           // grid of pass 1: heads fastest, else chunks; see launch_diff_attn
     float lambda, scale;
 };
 
@@ -61,13 +61,7 @@ __device__ inline float group_sum(float v)
 // a position hold the same score, so each of them takes the exponential of one of the lane's V8
 // positions and hands it round (all V8 in every lane: 15.5 us for 512 positions of 32 heads of 64 over 8
 // caches, 13.9 so), and V is requested when the registers of K are free again (90 instead of 124 at d_h =
-// 64, 164 instead of 226 at 128).  Where heads share a cache line (128
-// bytes: d_h < 64) chunks are the fastest grid dimension, so that such heads read it on one XCD when the
-// chunks are a multiple of eight; otherwise heads are, which reads whole cache rows, except where the
-// two chunks of a head side by side do as well.  (us, chunks / heads fastest, 32 heads: 8 caches of 4096
-// positions of 16 columns 35 / 75, of 32 45 / 74, of 64 73 / 74; one cache of 16384 of 64 columns 50 / 42,
-// of 128 93 / 73; 8 caches of 512 of 64 columns 15.4 / 16.0.)  More than the 65535 chunks that a grid's
-// other dimensions take are only possible below 64 columns.
+// 64, 164 instead of 226 at 128).
 template <int V8>
 __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
 {
@@ -76,7 +70,9 @@ __global__ __launch_bounds__(256) void diff_attn_chunk_kernel(AttnParams p)
     __shared__ float mx_s[4][2], sum_s[4][2];
     const int tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int chunk = p.heads_first ? blockIdx.y : blockIdx.x, h = p.heads_first ? blockIdx.x : blockIdx.y, b = blockIdx.z;
+    const int h = p.heads_first ? blockIdx.x : blockIdx.y, b = blockIdx.z;
+    int chunk = p.heads_first ? blockIdx.y : blockIdx.x;
+    if (p.rotate) chunk = (chunk + (V8 < 8 ? h * V8 / 8 : h) + b) % p.chunks;      // (by cache lines of heads, and by sequences)
     const int len = min(max(p.lens[b], 0), p.L_max);
     const int pos0 = chunk * kAttnChunk;
     if (pos0 >= len) {                  // nothing cached here (the merge reads only the chunks below len)
@@ -281,7 +277,21 @@ hipError_t launch_diff_attn(const void *q, const void *k, const void *v, const i
     p.chunks = (L_max + kAttnChunk - 1) / kAttnChunk;
     p.lambda = lambda;
     p.scale = 1.0f / sqrtf((float)d_h);
-    p.heads_first = d_h >= 64 && p.chunks > 2;
+    // Heads or chunks fastest.  Where heads share a cache line (128 bytes: d_h < 64), chunks: such heads then read
+    // it on one XCD when the chunks are a multiple of eight.  From 128 columns on heads, which reads whole cache
+    // rows; between, chunks for many workgroups, heads for few, for four chunks, and for long caches, whose
+    // chunks alone fill the chip.  With chunks fastest an XCD would always get the same chunks, and caches that
+    // are not full have only the first ones: the chunks are rotated from line to line and sequence to sequence.
+    // (us, chunks rotated / heads fastest, caches read in turn that the Infinity Cache does not hold.  Full:
+    // 8 of 4096 positions, 32 heads of 16 columns 39 / 77, of 32 47 / 75; 64 of 4096, 8 heads of 64 131 / 143; one of
+    // 4096, 32 heads of 64 18.6 / 15.8; 4 of 8192, 16 heads of 128 75 / 68.  8 ragged caches of up to 4096, 32
+    // heads, chunks not rotated / rotated / heads: 16 columns 34 / 28 / 46, 32 38 / 33 / 45, 64 52 / 44 / 44.  Of 802
+    // sizes and fillings 12 are more than 3 % slower than the better of the two orders, taken throughout and
+    // not rotated: at worst 4 caches of 8192, 30 % full, 16 heads of 32, 24.5 instead of 21.3.)
+    // Only chunks can be more than the 65535 that a grid's other dimensions take, and only below 64 columns.
+    p.heads_first = d_h >= 64 && p.chunks > 3 &&
+                    (d_h > 64 || p.chunks == 4 || p.chunks >= 32 || (long long)B * n_heads * p.chunks < 2048);
+    p.rotate = !p.heads_first;
     const dim3 grid = p.heads_first ? dim3(n_heads, p.chunks, B) : dim3(p.chunks, n_heads, B), block(256);
     switch (d_h / 8) {
         case 1: hipLaunchKernelGGL(diff_attn_chunk_kernel<1>, grid, block, 0, st, p); break;

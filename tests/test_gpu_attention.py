@@ -71,9 +71,10 @@ def test_diff_attention_many_chunks(d, L, lens):
     assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, lens, 0.8))
 
 
-@pytest.mark.parametrize("d,L,lens", [(8, 256, [256, 0, 65]), (64, 200, [0, 200, 1]), (128, 257, [257, 0, 256]), (32, 1100, [769, 1024, 1025])])
+@pytest.mark.parametrize("d,L,lens", [(8, 256, [256, 0, 65]), (64, 200, [0, 200, 1]), (128, 257, [257, 0, 256]), (32, 1100, [769, 1024, 1025]),
+                                      (128, 900, [900, 768, 1]), (64, 900, [3, 900, 513])])
 def test_diff_attention_few_chunks(d, L, lens):
-    # one chunk (no merging launch), two, five; empty sequences
+    # one chunk (no merging launch), two, five, four (heads fastest); empty sequences
     q, k, v = _case(d + L, len(lens), L, 3, d)
     out = hb.hgf_diff_attention_decode(dev(q), dev(k), dev(v), dev(np.array(lens, dtype=np.int32)), 0.8)
     assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, lens, 0.8))
@@ -88,6 +89,16 @@ def test_diff_attention_cache_of_more_chunks_than_a_narrow_grid_extent():
     kc[:, :300], vc[:, :300] = dev(k), dev(v)
     out = hb.hgf_diff_attention_decode(dev(q), kc, vc, torch.tensor([300], dtype=torch.int32, device="cuda"), 0.8)
     assert_close_fp16(out.cpu().numpy(), orc.diff_attention_decode(q, k, v, [300], 0.8))
+
+
+def test_diff_attention_many_workgroups():
+    # 64 columns, five chunks, more than 2048 workgroups: chunks fastest; few of them: heads fastest
+    q, k, v = _case(78, 26, 1030, 16, 64)
+    lens = [1030, 1024, 1025, 1, 0, 700] * 4 + [255, 256]
+    out = hb.hgf_diff_attention_decode(dev(q), dev(k), dev(v), dev(np.array(lens, dtype=np.int32)), 0.8).cpu().numpy()
+    assert_close_fp16(out, orc.diff_attention_decode(q, k, v, lens, 0.8))
+    few = hb.hgf_diff_attention_decode(dev(q[:2]), dev(k[:2]), dev(v[:2]), dev(np.array(lens[:2], dtype=np.int32)), 0.8)
+    assert np.array_equal(few.cpu().numpy(), out[:2])
 
 
 def test_diff_attention_rejects_bad_arguments():
