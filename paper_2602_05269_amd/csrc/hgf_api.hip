@@ -74,7 +74,9 @@ hgf_status from_hip(hipError_t e) { return e == hipSuccess ? HGF_OK : HGF_ERR_DE
 // 1.5 tokens against limits between 1600 and 4200 was 2 %.  us, direct / prefill: 512 -> 32000 behind a
 // LayerNorm, 128 tokens 18.3 / 13.4; three layers 512 -> 4096, 192 tokens 14.9 / 12.3; three 2048 -> 2048
 // behind LayerNorms, 384 tokens 31.2 / 55.6; two 4096 -> 1024, 640 tokens 31.7 / 28.2; 11008 -> 4096, 384
-// tokens 53.9 / 60.6.)  Up to 40 tokens the direct path takes every group.
+// tokens 53.9 / 60.6.)  Up to 40 tokens the direct path takes every group.  Layers without ranks on short rows
+// (run_large_group) cost less on the prefill path: 142 x 456 -> 15616 behind a LayerNorm 14.1 / 10.9, 627 x 51 ->
+// 2304 9.1 / 7.6, but 1258 x 56 -> 1152 behind one 10.6 / 11.4, 193 x 146 -> 3744 8.2 / 9.1.
 bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 {
     if (M <= 40) return true;
@@ -82,9 +84,12 @@ bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
     const long long tokens = M, groups = (tokens + 31) / 32;
     const bool ln = layers[0].ln_gamma != nullptr;            // (then every layer of the group has one)
     const bool sliced = prologue_slices(K) > 1;
+    bool ranks = false;
+    for (int g = 0; g < G; ++g) ranks = ranks || layers[g].rank > 0;
     int most;
     if (ln) most = sliced ? 2300 : (K > 512 ? 2200 : 2400);
     else most = sliced ? (K > 6144 ? 2800 : (pair ? 1900 : 2400)) : 1750;
+    if (!ranks && K <= 512) most = K % 8 ? 1300 : (ln ? 2100 : most);
     const long long each = (sliced && !ln ? 5 : 10) * tokens, rank_tile = sliced ? (ln ? 1 : 6) * tokens : 0;
     long long cost = each;                                    // in twentieths of a tile
     for (int g = 0; g < G; ++g) {
@@ -293,18 +298,24 @@ hgf_status run_large_group(const void *x, int M, const hgf_layer *layers, int G,
     _Float16 *h16[kMaxGroup];
     int rank[kMaxGroup];
     bool whole_rows = K % 8 == 0;                    // rows of x and A of whole 16-byte pieces
+    bool ranks = false;
     for (int g = 0; g < G; ++g) {
         A[g] = reinterpret_cast<const _Float16 *>(layers[g].A_f16);
         rank[g] = layers[g].rank;
         h16[g] = reinterpret_cast<_Float16 *>(reinterpret_cast<char *>(ws.h16) + ws.h16_each * g);
         whole_rows = whole_rows && (rank[g] == 0 || aligned16(A[g]));
+        ranks = ranks || rank[g] > 0;
     }
     // The direct path's prologue prepares rows that are not whole 16-byte pieces (one thread per (token, rank)
     // before: 1365 -> 2048, 32 ranks, 1000 tokens 161 us with the main kernel, 17 now; 4097 -> 4096 744 and 40)
     // and, as one launch instead of two, what stands behind a LayerNorm up to 2^23 elements (us, two launches /
     // one: 512 x 4096 59.2 / 45.4, 2048 x 3072 54.7 / 51.6, 2048 x 4096 131.3 / 133.4, 2048 x 8192 115.3 / 134.9).
     // Otherwise prepare_kernel's larger tiles of A x are the better ones (2048 x 3072: 35.4 against 44.3).
-    if (!whole_rows || (ln && (long long)M * K < (1 << 23))) {
+    // Without ranks there is one launch either way, and short rows are quantised faster by a workgroup per
+    // token (us, that / the prologue: odd rows 131 x 158 -> 8192 7.8 / 8.9, 4 x 307 x 947 -> 6192 19.2 / 19.1, 109 x
+    // 4316 -> 6136 25.4 / 20.4; behind a LayerNorm 137 x 192 -> 8832 10.2 / 11.6, 1015 x 688 -> 1120 14.9 / 13.9).
+    const bool short_rows = !ranks && K <= 512;
+    if (!short_rows && (!whole_rows || (ln && (long long)M * K < (1 << 23)))) {
         ProParams pp;
         pp.x = xh;
         pp.amax_zero = pair_out ? pair_out->amax_out : nullptr;
@@ -330,7 +341,10 @@ hgf_status run_large_group(const void *x, int M, const hgf_layer *layers, int G,
         if (ln && launch_ln_quantize(xh, M, K, layers[0].ln_gamma, layers[0].ln_beta, layers[0].ln_eps, ws.xq, ws.s_x,
                                      ws.rowsum, st) != hipSuccess)
             return HGF_ERR_DEVICE;
-        if (launch_corr_down(xh, M, K, G, A, rank, h16, ln ? nullptr : ws.xq, ws.s_x, ws.rowsum, st) != hipSuccess)
+        if (!ln && !whole_rows && launch_quantize(xh, M, K, ws.xq, ws.s_x, ws.rowsum, st) != hipSuccess)
+            return HGF_ERR_DEVICE;
+        if (launch_corr_down(xh, M, K, G, A, rank, h16, ln || !whole_rows ? nullptr : ws.xq, ws.s_x, ws.rowsum, st) !=
+            hipSuccess)
             return HGF_ERR_DEVICE;
     }
     ProfileScope prof(1, st);

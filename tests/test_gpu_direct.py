@@ -69,6 +69,8 @@ def test_prefill_path(M, K, N, r):
 @pytest.mark.parametrize("M,K,N,r,path", [
     # the line between the paths, a row-block on either side of it: up to 2048 columns, up to 6144, beyond
     (200, 512, 7520, 16, "direct"), (200, 512, 7553, 16, "prefill"), (640, 2048, 2272, 64, "direct"), (640, 2048, 2273, 64, "prefill"),
+    # no ranks: odd rows of up to 512 columns, longer ones
+    (320, 137, 3648, 0, "direct"), (320, 137, 3649, 0, "prefill"), (320, 511, 3649, 0, "prefill"), (320, 513, 3649, 0, "direct"),
     (640, 2049, 2656, 48, "direct"), (640, 2049, 2657, 48, "prefill"), (640, 6152, 3904, 0, "direct"), (640, 6152, 3937, 0, "prefill"),
 ])
 def test_line_between_the_paths(M, K, N, r, path):
@@ -83,6 +85,21 @@ def test_line_between_the_paths(M, K, N, r, path):
 def test_line_between_the_paths_behind_a_layernorm(M, K, N, path):
     c = synth.make_custom(8950 + M + K + N, M, K, N, 16, act="student_t3", lora_std=0.05)
     g = LnLayer(c, hb.Workspace(M, K, N, 16), seed=M + K)
+    with path_taken(path):
+        y, acc = g.forward(c["x"])
+    ref = g.oracle(c["x"], dense=True)
+    assert np.array_equal(acc, ref["acc"]), "int32 accumulators differ from the oracle"
+    assert_close_fp16(y, ref["y"])
+
+
+@pytest.mark.parametrize("M,K,N,path", [
+    # up to 512 columns, where a workgroup per token prepares, and beyond, where the prologue does
+    (320, 512, 6208, "direct"), (320, 512, 6209, "prefill"), (320, 520, 6209, "direct"), (320, 137, 3648, "direct"),
+    (320, 137, 3649, "prefill"), (320, 511, 3649, "prefill"), (600, 1025, 4100, "prefill"),
+])
+def test_line_between_the_paths_behind_a_layernorm_without_ranks(M, K, N, path):
+    c = synth.make_custom(8990 + M + K + N, M, K, N, 1, act="student_t3", lora_std=0.05)
+    g = LnLayer(c, hb.Workspace(M, K, N, 1), seed=M + K, rank0=True)
     with path_taken(path):
         y, acc = g.forward(c["x"])
     ref = g.oracle(c["x"], dense=True)
