@@ -60,6 +60,10 @@ hgf_status check_layer(const hgf_layer *L, int M)
 
 hgf_status from_hip(hipError_t e) { return e == hipSuccess ? HGF_OK : HGF_ERR_DEVICE; }
 
+// Beyond 4096 columns, more tokens than a fifth of the columns: what stands behind a LayerNorm is prepared for the
+// prefill kernel in two launches (run_large_group).
+bool many_tokens_for_long_rows(int K, int M) { return K > 4096 && K < 5 * (long long)M; }
+
 // Which of the two paths a group of layers takes.  The prefill kernel's tiles are 256 rows by 64 or 128
 // tokens and walk all of d_in with one workgroup each, so a group that does not fill the chip with them
 // costs about 10 + 0.55 k-tiles microseconds whatever its size.  The direct path costs by its output tiles of
@@ -69,7 +73,8 @@ hgf_status from_hip(hipError_t e) { return e == hipSuccess ? HGF_OK : HGF_ERR_DE
 // near the figures below; beyond 6144 columns the prefill workgroups' walk is what counts.  The SwiGLU pair
 // saves more on the prefill path (neither y is stored).  Layers behind LayerNorms are each a prefill group
 // of their own with a longer preparation, so they are weighed one by one, their tokens with half a tile and
-// 0.05 for every 16 ranks of sliced rows.  (2305 groups of 41 to 1536 tokens, 128 to 32768 columns, 64 to 32000
+// 0.05 for every 16 ranks of sliced rows; where that preparation is two launches, 0.1, and tokens beyond 512
+// a tile more (1385 x 5952 -> 728, 128 ranks 88 / 76; 1409 x 4984 -> 72, three of 16 ranks 161 / 174).  (2305 groups of 41 to 1536 tokens, 128 to 32768 columns, 64 to 32000
 // rows, 16 to 128 ranks, both paths timed: the choice is 0.3 % from the better path in the mean, where tiles +
 // 1.5 tokens against limits between 1600 and 4200 was 2 %.  us, direct / prefill: 512 -> 32000 behind a
 // LayerNorm, 128 tokens 18.3 / 13.4; three layers 512 -> 4096, 192 tokens 14.9 / 12.3; three 2048 -> 2048
@@ -87,10 +92,12 @@ bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
     bool ranks = false;
     for (int g = 0; g < G; ++g) ranks = ranks || layers[g].rank > 0;
     int most;
-    if (ln) most = sliced ? 2300 : (K > 512 ? 2200 : 2400);
+    const bool two = ln && many_tokens_for_long_rows(K, M);
+    if (ln) most = sliced ? (two ? 2200 : 2300) : (K > 512 ? 2200 : 2400);
     else most = sliced ? (K > 6144 ? 2800 : (pair ? 1900 : 2400)) : 1750;
     if (!ranks && K <= 512) most = K % 8 ? 1300 : (ln ? 2100 : most);
-    const long long each = (sliced && !ln ? 5 : 10) * tokens, rank_tile = sliced ? (ln ? 1 : 6) * tokens : 0;
+    const long long beyond = two && tokens > 512 ? 20 * (tokens - 512) : 0;
+    const long long each = (sliced && !ln ? 5 : 10) * tokens + beyond, rank_tile = sliced ? (two ? 2 : (ln ? 1 : 6)) * tokens : 0;
     long long cost = each;                                    // in twentieths of a tile
     for (int g = 0; g < G; ++g) {
         cost += 20 * groups * ((layers[g].d_out + kTileRows - 1) / kTileRows) +
@@ -310,12 +317,16 @@ hgf_status run_large_group(const void *x, int M, const hgf_layer *layers, int G,
     // before: 1365 -> 2048, 32 ranks, 1000 tokens 161 us with the main kernel, 17 now; 4097 -> 4096 744 and 40)
     // and, as one launch instead of two, what stands behind a LayerNorm up to 2^23 elements (us, two launches /
     // one: 512 x 4096 59.2 / 45.4, 2048 x 3072 54.7 / 51.6, 2048 x 4096 131.3 / 133.4, 2048 x 8192 115.3 / 134.9).
-    // Otherwise prepare_kernel's larger tiles of A x are the better ones (2048 x 3072: 35.4 against 44.3).
+    // Otherwise prepare_kernel's larger tiles of A x are the better ones (2048 x 3072: 35.4 against 44.3), and
+    // beyond 4096 columns corr_down_kernel's are, unless the rows are much longer than there are tokens (1503 x 4472
+    // 56.5 / 63.2, 1072 x 4496 for three layers of 128 ranks 158 / 182, 1030 x 4256 49.1 / 48.9, 964 x 5128 52.8 / 50.2,
+    // 1093 x 6544 69.9 / 56.7).
     // Without ranks there is one launch either way, and short rows are quantised faster by a workgroup per
     // token (us, that / the prologue: odd rows 131 x 158 -> 8192 7.8 / 8.9, 4 x 307 x 947 -> 6192 19.2 / 19.1, 109 x
     // 4316 -> 6136 25.4 / 20.4; behind a LayerNorm 137 x 192 -> 8832 10.2 / 11.6, 1015 x 688 -> 1120 14.9 / 13.9).
     const bool short_rows = !ranks && K <= 512;
-    if (!short_rows && (!whole_rows || (ln && (long long)M * K < (1 << 23)))) {
+    const bool one_launch = ln && (long long)M * K < (1 << 23) && !many_tokens_for_long_rows(K, M);
+    if (!short_rows && (!whole_rows || one_launch)) {
         ProParams pp;
         pp.x = xh;
         pp.amax_zero = pair_out ? pair_out->amax_out : nullptr;

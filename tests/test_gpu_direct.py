@@ -81,6 +81,10 @@ def test_line_between_the_paths(M, K, N, r, path):
     # up to 512 columns, up to 2048, beyond
     (320, 512, 7168, "direct"), (320, 512, 7169, "prefill"), (320, 520, 6528, "direct"), (320, 520, 6529, "prefill"),
     (320, 2056, 6784, "direct"), (320, 2056, 6817, "prefill"),
+    # prefill of more than 4096 columns: prepared in one launch, in two
+    (900, 4504, 2400, "prefill"), (1000, 4496, 2200, "prefill"),
+    # ... and the line where it is two
+    (1000, 4992, 1088, "direct"), (1000, 4992, 1089, "prefill"), (998, 4992, 1089, "direct"),
 ])
 def test_line_between_the_paths_behind_a_layernorm(M, K, N, path):
     c = synth.make_custom(8950 + M + K + N, M, K, N, 16, act="student_t3", lora_std=0.05)
