@@ -69,19 +69,24 @@ bool many_tokens_for_long_rows(int K, int M) { return K > 4096 && K < 5 * (long 
 // costs about 10 + 0.55 k-tiles microseconds whatever its size.  The direct path costs by its output tiles of
 // 32 x 32 and by its preparation.  Up to 2048 columns that leaves SiLU(A x) ready made and a token weighs
 // half a tile; longer rows are cut into slices, which the workgroups of every output tile add for themselves,
-// and a token weighs 1/4 of a tile and 0.3 for every 16 ranks of every layer.  In these units the paths cross
-// near the figures below; beyond 6144 columns the prefill workgroups' walk is what counts.  The SwiGLU pair
-// saves more on the prefill path (neither y is stored).  Layers behind LayerNorms are each a prefill group
-// of their own with a longer preparation, so they are weighed one by one, their tokens with half a tile and
-// 0.05 for every 16 ranks of sliced rows; where that preparation is two launches, 0.1, and tokens beyond 512
-// a tile more (1385 x 5952 -> 728, 128 ranks 88 / 76; 1409 x 4984 -> 72, three of 16 ranks 161 / 174).  (2305 groups of 41 to 1536 tokens, 128 to 32768 columns, 64 to 32000
-// rows, 16 to 128 ranks, both paths timed: the choice is 0.3 % from the better path in the mean, where tiles +
-// 1.5 tokens against limits between 1600 and 4200 was 2 %.  us, direct / prefill: 512 -> 32000 behind a
-// LayerNorm, 128 tokens 18.3 / 13.4; three layers 512 -> 4096, 192 tokens 14.9 / 12.3; three 2048 -> 2048
-// behind LayerNorms, 384 tokens 31.2 / 55.6; two 4096 -> 1024, 640 tokens 31.7 / 28.2; 11008 -> 4096, 384
-// tokens 53.9 / 60.6.)  Up to 40 tokens the direct path takes every group.  Layers without ranks on short rows
-// (run_large_group) cost less on the prefill path: 142 x 456 -> 15616 behind a LayerNorm 14.1 / 10.9, 627 x 51 ->
-// 2304 9.1 / 7.6, but 1258 x 56 -> 1152 behind one 10.6 / 11.4, 193 x 146 -> 3744 8.2 / 9.1.
+// and a token weighs 1/4 of a tile and 0.3 for every 16 ranks of every layer.  Beyond 512 tokens, where the
+// prefill kernel fills the chip with few rows, each weighs 1/4 more, of sliced rows 1 more.  In these units the
+// paths cross near the figures below; beyond 6144 columns the prefill workgroups' walk is what counts.  The
+// SwiGLU pair saves more on the prefill path (neither y is stored).  Layers behind LayerNorms are each a prefill
+// group of their own with a longer preparation, so they are weighed one by one, their tokens with half a tile
+// and 0.05 for every 16 ranks of sliced rows; where that preparation is two launches, 0.1, and tokens beyond 512
+// a tile more (up to 6144 columns).  Layers without ranks on short rows (run_large_group) cost less on the prefill path.  Up to 40
+// tokens the direct path takes every group.
+// (2514 groups of 41 to 5000 tokens, 40 to 32768 columns, 32 to 32000 rows, 8 to 128 ranks, both paths timed: the
+// choice is 0.2 % from the better path in the mean, where tiles + 1.5 tokens against limits between 1600 and 4200
+// was 2 %.  us, direct / prefill: 512 -> 32000 behind a LayerNorm, 128 tokens 18.3 / 13.4; three layers 512 -> 4096,
+// 192 tokens 14.9 / 12.3; three 2048 -> 2048 behind LayerNorms, 384 tokens 31.2 / 55.6; two 4096 -> 1024, 640 tokens
+// 31.7 / 28.2; 11008 -> 4096, 384 tokens 53.9 / 60.6; many tokens: 1543 x 8368 -> 192 78.1 / 63.3, 1087 x 2480 -> 888
+// as a pair 31.9 / 23.6, 2446 x 440 -> 592 19.9 / 15.8, but 1299 x 3248 -> 608 23.9 / 25.8; prepared in two launches:
+// 1385 x 5952 -> 728, 128 ranks 88 / 76, three 1409 x 4984 -> 72, 16 ranks 161 / 174, three 1741 x 7144 -> 32
+// 198 / 249; without ranks: 142 x 456 ->
+// 15616 behind a LayerNorm 14.1 / 10.9, 627 x 51 -> 2304 9.1 / 7.6, but 1258 x 56 -> 1152 behind one 10.6 / 11.4,
+// 193 x 146 -> 3744 8.2 / 9.1.)
 bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 {
     if (M <= 40) return true;
@@ -92,12 +97,14 @@ bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
     bool ranks = false;
     for (int g = 0; g < G; ++g) ranks = ranks || layers[g].rank > 0;
     int most;
-    const bool two = ln && many_tokens_for_long_rows(K, M);
+    const bool two = ln && K <= 6144 && many_tokens_for_long_rows(K, M);
     if (ln) most = sliced ? (two ? 2200 : 2300) : (K > 512 ? 2200 : 2400);
     else most = sliced ? (K > 6144 ? 2800 : (pair ? 1900 : 2400)) : 1750;
     if (!ranks && K <= 512) most = K % 8 ? 1300 : (ln ? 2100 : most);
-    const long long beyond = two && tokens > 512 ? 20 * (tokens - 512) : 0;
-    const long long each = (sliced && !ln ? 5 : 10) * tokens + beyond, rank_tile = sliced ? (two ? 2 : (ln ? 1 : 6)) * tokens : 0;
+    const int more = ln ? (two ? 20 : (K > 512 && !sliced ? 5 : 0)) : (sliced ? 20 : 5);
+    const long long beyond = tokens > 512 ? more * (tokens - 512) : 0;
+    const long long each = (sliced && !ln ? 5 : 10) * tokens + beyond;
+    const long long rank_tile = sliced ? (two ? 2 : (ln ? 1 : 6)) * tokens : 0;
     long long cost = each;                                    // in twentieths of a tile
     for (int g = 0; g < G; ++g) {
         cost += 20 * groups * ((layers[g].d_out + kTileRows - 1) / kTileRows) +

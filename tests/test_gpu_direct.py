@@ -68,10 +68,12 @@ def test_prefill_path(M, K, N, r):
 
 @pytest.mark.parametrize("M,K,N,r,path", [
     # the line between the paths, a row-block on either side of it: up to 2048 columns, up to 6144, beyond
-    (200, 512, 7520, 16, "direct"), (200, 512, 7553, 16, "prefill"), (640, 2048, 2272, 64, "direct"), (640, 2048, 2273, 64, "prefill"),
+    (200, 512, 7520, 16, "direct"), (200, 512, 7553, 16, "prefill"), (640, 2048, 2208, 64, "direct"), (640, 2048, 2209, 64, "prefill"),
     # no ranks: odd rows of up to 512 columns, longer ones
     (320, 137, 3648, 0, "direct"), (320, 137, 3649, 0, "prefill"), (320, 511, 3649, 0, "prefill"), (320, 513, 3649, 0, "direct"),
-    (640, 2049, 2656, 48, "direct"), (640, 2049, 2657, 48, "prefill"), (640, 6152, 3904, 0, "direct"), (640, 6152, 3937, 0, "prefill"),
+    (640, 2049, 2432, 48, "direct"), (640, 2049, 2433, 48, "prefill"), (640, 6152, 3712, 0, "direct"), (640, 6152, 3713, 0, "prefill"),
+    # many tokens, few rows: 2000 x (1/2 + 1/4) - 512/4 = 1372 and 6 tiles of 63 rows
+    (2000, 264, 192, 8, "direct"), (2000, 264, 193, 8, "prefill"), (1300, 2056, 512, 8, "direct"), (1300, 2056, 1248, 8, "prefill"),
 ])
 def test_line_between_the_paths(M, K, N, r, path):
     _one(M, K, N, r, path=path)
