@@ -81,8 +81,8 @@ bool many_tokens_for_long_rows(int K, int M) { return K > 4096 && K < 5 * (long 
 // choice is 0.2 % from the better path in the mean, where tiles + 1.5 tokens against limits between 1600 and 4200
 // was 2 %.  us, direct / prefill: 512 -> 32000 behind a LayerNorm, 128 tokens 18.3 / 13.4; three layers 512 -> 4096,
 // 192 tokens 14.9 / 12.3; three 2048 -> 2048 behind LayerNorms, 384 tokens 31.2 / 55.6; two 4096 -> 1024, 640 tokens
-// 31.7 / 28.2; 11008 -> 4096, 384 tokens 53.9 / 60.6; many tokens: 1543 x 8368 -> 192 78.1 / 63.3, 1087 x 2480 -> 888
-// as a pair 31.9 / 23.6, 2446 x 440 -> 592 19.9 / 15.8, but 1299 x 3248 -> 608 23.9 / 25.8; prepared in two launches:
+// 31.7 / 28.2; 11008 -> 4096, 384 tokens 53.9 / 60.6; many tokens: 3343 x 2880 -> 88 35.8 / 26.9, 1633 x 6760 -> 368
+// as a pair 58.6 / 44.1, 3583 x 800 -> 72 behind a LayerNorm 33.7 / 28.2, but 2401 x 304 -> 392 12.5 / 14.1; prepared in two launches:
 // 1385 x 5952 -> 728, 128 ranks 88 / 76, three 1409 x 4984 -> 72, 16 ranks 161 / 174, three 1741 x 7144 -> 32
 // 198 / 249; without ranks: 142 x 456 ->
 // 15616 behind a LayerNorm 14.1 / 10.9, 627 x 51 -> 2304 9.1 / 7.6, but 1258 x 56 -> 1152 behind one 10.6 / 11.4,
