@@ -216,7 +216,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
                                                                 i0 + v * 64 * KW < quads));
                     v4h o;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (_Float16)silu(h[e]);
+                    for (int e = 0; e < 4; ++e) o[e] = round_half(silu_hw(h[e]));
                     if (i0 + v * 64 * KW < quads)
                         *reinterpret_cast<v4h *>(ops + ((NB + g) * JS + (j[v] >> 4)) * 1024 +
                                                  ((j[v] >> 3 & 1) * 32 + tok[v]) * 16 + (j[v] & 4) * 2) = o;
@@ -332,13 +332,13 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 a[g][v] -= rs;
-                y[g][v] = (float)a[g][v] * scale + tanhf(alpha[g][c][v]) * cv[g][c][v];
+                y[g][v] = (float)a[g][v] * scale + tanh_hw(alpha[g][c][v]) * cv[g][c][v];
             }
         }
         v4h o;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            o[v] = (_Float16)(PAIR ? silu(y[0][v]) * y[NL - 1][v] : y[0][v]);
+            o[v] = round_half(PAIR ? silu_hw(y[0][v]) * y[NL - 1][v] : y[0][v]);
             if (n + v < N) zmax = fmaxf(zmax, fabsf((float)o[v]));
         }
         if (!m_ok) continue;

@@ -87,6 +87,27 @@ __device__ inline v4i widen_codes(uint32_t w)
     return a;
 }
 __device__ inline float silu(float h) { return h / (1.0f + expf(-h)); }
+// SiLU and tanh from the hardware's exponential and reciprocal (about one unit in the last place each); near
+// zero tanh by its series, where 1 - t would cancel
+__device__ inline float silu_hw(float h)
+{
+    return h * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(h * -1.44269504088896340736f));
+}
+__device__ inline float tanh_hw(float a)
+{
+    const float t = __builtin_amdgcn_exp2f(fabsf(a) * -2.88539008177792681472f);
+    const float big = copysignf((1.0f - t) * __builtin_amdgcn_rcpf(1.0f + t), a);
+    const float s = a * a;
+    const float small = a + a * s * (-1.0f / 3 + s * (2.0f / 15 + s * (-17.0f / 315 + s * (62.0f / 2835))));
+    return fabsf(a) < 0.3f ? small : big;
+}
+// fp32 to fp16.  (The compiler joins a product and its conversion into one instruction, which rounds once, in
+// some places and not in others; kernels that have to give the same bits keep the product's own rounding.)
+__device__ inline _Float16 round_half(float v)
+{
+    asm("" : "+v"(v));
+    return (_Float16)v;
+}
 // Wave-wide reductions with the result in every lane.  The lanes of a row of 16 exchange
 // through the data-parallel-primitive modifiers of the vector ALU (xor 1, xor 2, mirror within
 // 8, mirror within 16: four dependent instructions); the four rows are then combined from
