@@ -154,7 +154,7 @@ typedef struct {
  * Up to 40 tokens always, and beyond as long as the 32 x 32 output tiles and the tokens of the layer
  * (or of the group of layers that share an input) stay below a limit of some 1750 to 2800 tiles, a call
  * runs the direct kernel (weights straight from memory into the MFMA; up to 4 tokens as one persistent
- * launch); larger ones run the int8 MFMA prefill kernel.  Both give the same integers.  A layer with
+ * launch; short rows as one launch whose workgroups prepare their tokens themselves); larger ones run the int8 MFMA prefill kernel.  Both give the same integers.  A layer with
  * ln_gamma set is quantised behind the fused LayerNorm.  In hgf_stack_forward layers with LayerNorms of
  * their own never share a quantisation; on the direct path those that read one slot share the launches. */
 hgf_status hgf_linear_forward(const void *x_f16, int M, const hgf_layer *L, void *y_f16,

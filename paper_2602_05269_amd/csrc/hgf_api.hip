@@ -214,6 +214,39 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
         fused = fused && (layers[g].rank == 0 ||
                           (layers[g].rank % 8 == 0 && aligned16(layers[g].A_f16) && aligned16(layers[g].B_f16) &&
                            (reinterpret_cast<uintptr_t>(layers[g].alpha_f16) & 3u) == 0));
+    // short rows: one launch, every workgroup prepares its tokens itself
+    if (!base3 && !fused) {
+        ShortParams sp;
+        sp.x = reinterpret_cast<const _Float16 *>(x);
+        sp.M = M;
+        sp.K = K;
+        sp.G = G;
+        sp.pair = pair ? 1 : 0;
+        sp.amax_out = pair ? amax_out : nullptr;
+        for (int g = 0; g < G; ++g) {
+            const hgf_layer &L = layers[g];
+            ShortLayer &S = sp.L[g];
+            S.packed = reinterpret_cast<const v4u *>(L.W_packed);
+            S.s_w = L.s_w;
+            S.A = reinterpret_cast<const _Float16 *>(L.A_f16);
+            S.B = reinterpret_cast<const _Float16 *>(L.B_f16);
+            S.alpha = reinterpret_cast<const _Float16 *>(L.alpha_f16);
+            S.gamma = L.ln_gamma;
+            S.beta = L.ln_beta;
+            S.eps = L.ln_eps;
+            S.y = reinterpret_cast<_Float16 *>(ys[g]);
+            S.acc_debug = (pair && g == 1) ? acc_debug2 : acc_debug;
+            S.N = L.d_out;
+            S.RBn = round_up(L.d_out, kTileRows) / kTileRows;
+            S.rank = L.rank;
+        }
+        size_t lds_bytes = 0;
+        if (plan_short(sp, &lds_bytes)) {
+            if (sp.amax_out && launch_zero_words(sp.amax_out, (size_t)M, st) != hipSuccess) return HGF_ERR_DEVICE;
+            ProfileScope prof(0, st);
+            return from_hip(launch_short(sp, lds_bytes, st));
+        }
+    }
     if (fused) {
         FusedParams fp;
         fp.x = reinterpret_cast<const _Float16 *>(x);

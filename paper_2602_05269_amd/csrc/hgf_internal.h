@@ -252,6 +252,31 @@ struct DecodeParams {
     float *amax_out;         // pair, nullable: per-token max |z| (zeroed before the launch; combined with atomic max)
 };
 
+// Short rows: one launch per group, every workgroup prepares its tokens itself.
+struct ShortLayer {
+    const v4u *packed;
+    const float *s_w;
+    const _Float16 *A, *B, *alpha;
+    const float *gamma, *beta;   // as in ProTokens
+    _Float16 *y;
+    int32_t *acc_debug;
+    float eps;
+    int N, RBn, rank;
+    int b_aligned;               // rows of B are whole aligned pieces of 8 ranks
+};
+struct ShortParams {
+    const _Float16 *x;
+    int M, K, Kp, KT, G, pair;   // pair: as in DecodeParams
+    int plog, token_groups;      // log2 of a workgroup's tokens
+    int KS;                      // wavefronts that share a row-block's k-tiles
+    int vec;                     // rows of x and of every A are whole aligned pieces of 16 bytes
+    int ustride, part_off, h_off, red_off;   // LDS: bytes between units of 16 columns; A x in parts; SiLU(A x); partial tiles
+    float *amax_out;
+    int wg_start[kMaxGroup + 1]; // running sum of the layers' row units
+    ShortLayer L[kMaxGroup];
+};
+constexpr size_t kShortLdsMax = 150 * 1024;
+
 // Single persistent launch for a handful of tokens: every workgroup quantises the tokens
 // itself, streams its share of the row-blocks ("units") and exchanges the partial sums of
 // A x with the others through a sentinel-filled buffer in the workspace.
@@ -331,6 +356,8 @@ hipError_t launch_corr_down(const _Float16 *x, int M, int K, int G, const _Float
 int prologue_slices(int K);
 hipError_t launch_prologue(ProParams &p, hipStream_t st);
 hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st);
+bool plan_short(ShortParams &p, size_t *lds_bytes);
+hipError_t launch_short(const ShortParams &p, size_t lds_bytes, hipStream_t st);
 // What a plan or a launch of one of the persistent kernels came to.
 enum class Launch { kRan, kNoFit, kRefused };
 bool plan_fused(FusedParams &p, size_t *lds_bytes);
