@@ -267,6 +267,10 @@ hgf_status hgf_linear_forward_static(const void *x_f16, int M, const hgf_layer *
  *   layers  host array of n_layers descriptions
  *   slots   host array of n_slots device pointers
  *
+ * For 5 <= M <= 16 runs of five groups or more (without LayerNorms, rows of whole 16-byte pieces, no slot written
+ * twice or over one that is read) execute as one launch each, a queue of tasks; its workgroups wait for each other
+ * but make progress however few of them the device holds at a time, so it needs nothing to itself.
+ *
  * For M <= 4 runs of layers execute as persistent launches whose workgroups hand activations
  * to each other inside the launch.  Such a launch is sized to what an occupancy query says
  * the device holds at once, and needs the device to itself while it runs: kernels of other
@@ -305,7 +309,8 @@ hgf_status hgf_probe_mfma_rate(int operand_kind, int iters, double *tops_out, do
  * d_in <= 12288.  level 2 (default): hgf_stack_forward runs whole runs of groups of layers as
  * one persistent launch (activations handed from layer to layer inside the launch), and
  * single groups as level 1; level 1: each group of layers is one persistent launch;
- * level 0: the direct path's two launches, as for more tokens.  Results agree bit for bit in the
+ * level 0: the direct path's two launches, as for more tokens.  (At level 0 hgf_stack_forward has no queue of
+ * tasks for more tokens either: two launches per group, the same bits.)  Results agree bit for bit in the
  * integers; the fp16 outputs may differ in the last place (different split of A x). */
 void hgf_set_single_launch(int level);
 

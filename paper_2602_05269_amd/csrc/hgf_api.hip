@@ -20,6 +20,9 @@ Workspace carve_workspace(void *base, int M, int d_in, int d_out, int rank, int 
     ws.flags = reinterpret_cast<int32_t *>(take(kZeroBytes));
     ws.mail = reinterpret_cast<unsigned char *>(take(2 * kMailBytes));
     ws.xchg = with_stack ? reinterpret_cast<unsigned char *>(take(2 * kStackSetBytes)) : nullptr;
+    ws.bmail = with_stack ? reinterpret_cast<unsigned char *>(take(2 * kBatchMailBytes)) : nullptr;
+    ws.bwords = with_stack ? reinterpret_cast<int32_t *>(take(size_t(kBatchMaxPhases) * kBatchWords * 4)) : nullptr;
+    ws.bact = with_stack ? reinterpret_cast<unsigned char *>(take(kBatchActBytes)) : nullptr;
     const int Kp = round_up(d_in, kTileCols);
     ws.xq = reinterpret_cast<int8_t *>(take((size_t)M * Kp));
     ws.s_x = reinterpret_cast<float *>(take((size_t)M * 4));
@@ -197,6 +200,76 @@ bool place_prologue(ProParams &p, const hgf_layer *layers, const Workspace &ws)
     return true;
 }
 
+// Two [M, d] fp16 matrices that share no memory.
+bool apart(int M, const void *a, int da, const void *b, int db)
+{
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return pa + (size_t)M * da * 2 <= pb || pb + (size_t)M * db * 2 <= pa;
+}
+
+// A group that the task queue takes as a phase: up to 16 tokens, rows of whole aligned 16-byte pieces.
+bool batchable(int M, const hgf_layer *layers, int G)
+{
+    if (M > kBatchTokens || g_launch_level < 1) return false;
+    const int K = layers[0].d_in;
+    int rank = 0;
+    for (int g = 0; g < G; ++g) rank = layers[g].rank > rank ? layers[g].rank : rank;
+    if (K % 8 != 0 || !batch_fits(M, K, G, rank)) return false;
+    for (int g = 0; g < G; ++g) {
+        const hgf_layer &L = layers[g];
+        if (L.ln_gamma) return false;
+        if (L.rank > 0 && (L.rank % 8 != 0 || !aligned16(L.A_f16) || !aligned16(L.B_f16))) return false;
+    }
+    return true;
+}
+void set_batch_layer(BatchLayer &D, const hgf_layer &L, void *y)
+{
+    D.packed = reinterpret_cast<const v4u *>(L.W_packed);
+    D.s_w = L.s_w;
+    D.A = reinterpret_cast<const _Float16 *>(L.A_f16);
+    D.B = reinterpret_cast<const _Float16 *>(L.B_f16);
+    D.alpha = reinterpret_cast<const _Float16 *>(L.alpha_f16);
+    D.y = reinterpret_cast<_Float16 *>(y);
+    D.N = L.d_out;
+    D.rank = L.rank;
+}
+void set_batch_workspace(BatchParams &bp, const Workspace &ws)
+{
+    bp.flags = ws.flags;
+    bp.mail = ws.bmail;
+    bp.act = ws.bact;
+    bp.words = ws.bwords;
+}
+
+// Fills in what the launch for short rows reads of a group.
+void set_short(ShortParams &sp, const void *x, int M, const hgf_layer *layers, int G, void *const *ys, int32_t *acc_debug, bool pair,
+               float *amax_out, int32_t *acc_debug2)
+{
+    sp.x = reinterpret_cast<const _Float16 *>(x);
+    sp.M = M;
+    sp.K = layers[0].d_in;
+    sp.G = G;
+    sp.pair = pair ? 1 : 0;
+    sp.amax_out = pair ? amax_out : nullptr;
+    for (int g = 0; g < G; ++g) {
+        const hgf_layer &L = layers[g];
+        ShortLayer &S = sp.L[g];
+        S.packed = reinterpret_cast<const v4u *>(L.W_packed);
+        S.s_w = L.s_w;
+        S.A = reinterpret_cast<const _Float16 *>(L.A_f16);
+        S.B = reinterpret_cast<const _Float16 *>(L.B_f16);
+        S.alpha = reinterpret_cast<const _Float16 *>(L.alpha_f16);
+        S.gamma = L.ln_gamma;
+        S.beta = L.ln_beta;
+        S.eps = L.ln_eps;
+        S.y = reinterpret_cast<_Float16 *>(ys[g]);
+        S.acc_debug = (pair && g == 1) ? acc_debug2 : acc_debug;
+        S.N = L.d_out;
+        S.RBn = round_up(L.d_out, kTileRows) / kTileRows;
+        S.rank = L.rank;
+    }
+}
+
 // Direct path: `G` layers that read the same activations `x` run as two launches: the prologue
 // (quantisers + SiLU(A x) of every layer) and one grouped main kernel.
 //
@@ -214,32 +287,13 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
         fused = fused && (layers[g].rank == 0 ||
                           (layers[g].rank % 8 == 0 && aligned16(layers[g].A_f16) && aligned16(layers[g].B_f16) &&
                            (reinterpret_cast<uintptr_t>(layers[g].alpha_f16) & 3u) == 0));
-    // short rows: one launch, every workgroup prepares its tokens itself
-    if (!base3 && !fused) {
+    // Short rows: one launch, every workgroup prepares its tokens itself (where no output lies over the tokens, as the
+    // workgroups read and write at their own pace)
+    bool free_tokens = !fused && !base3;
+    for (int g = 0; g < G; ++g) free_tokens = free_tokens && (!ys[g] || apart(M, x, K, ys[g], layers[g].d_out));
+    if (free_tokens) {
         ShortParams sp;
-        sp.x = reinterpret_cast<const _Float16 *>(x);
-        sp.M = M;
-        sp.K = K;
-        sp.G = G;
-        sp.pair = pair ? 1 : 0;
-        sp.amax_out = pair ? amax_out : nullptr;
-        for (int g = 0; g < G; ++g) {
-            const hgf_layer &L = layers[g];
-            ShortLayer &S = sp.L[g];
-            S.packed = reinterpret_cast<const v4u *>(L.W_packed);
-            S.s_w = L.s_w;
-            S.A = reinterpret_cast<const _Float16 *>(L.A_f16);
-            S.B = reinterpret_cast<const _Float16 *>(L.B_f16);
-            S.alpha = reinterpret_cast<const _Float16 *>(L.alpha_f16);
-            S.gamma = L.ln_gamma;
-            S.beta = L.ln_beta;
-            S.eps = L.ln_eps;
-            S.y = reinterpret_cast<_Float16 *>(ys[g]);
-            S.acc_debug = (pair && g == 1) ? acc_debug2 : acc_debug;
-            S.N = L.d_out;
-            S.RBn = round_up(L.d_out, kTileRows) / kTileRows;
-            S.rank = L.rank;
-        }
+        set_short(sp, x, M, layers, G, ys, acc_debug, pair, amax_out, acc_debug2);
         size_t lds_bytes = 0;
         if (plan_short(sp, &lds_bytes)) {
             if (sp.amax_out && launch_zero_words(sp.amax_out, (size_t)M, st) != hipSuccess) return HGF_ERR_DEVICE;
@@ -508,7 +562,8 @@ hgf_status hgf_workspace_init(void *workspace, size_t workspace_bytes, void *str
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (launch_fill(ws.flags, align256(kZeroBytes), 0u, st) != hipSuccess) return HGF_ERR_DEVICE;
     if (launch_fill(ws.mail, 2 * kMailBytes, 0xFFFFFFFFu, st) != hipSuccess) return HGF_ERR_DEVICE;
-    return from_hip(launch_fill(ws.xchg, 2 * kStackSetBytes, 0xFFFFFFFFu, st));
+    if (launch_fill(ws.xchg, 2 * kStackSetBytes, 0xFFFFFFFFu, st) != hipSuccess) return HGF_ERR_DEVICE;
+    return from_hip(launch_fill(ws.bmail, 2 * kBatchMailBytes + size_t(kBatchMaxPhases) * kBatchWords * 4, 0xFFFFFFFFu, st));
 }
 
 hgf_status hgf_quantize_pack_weights(const float *W, int d_out, int d_in, void *packed_out, float *s_w_out,
@@ -739,11 +794,7 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
 
     // groups: consecutive layers reading the same slot with the same d_in, none of which writes
     // that slot or a slot another member writes (all with a LayerNorm of their own, or none)
-    auto apart = [M](const void *a, int da, const void *b, int db) {      // [M, d] fp16 each
-        const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
-        return pa + (size_t)M * da * 2 <= pb || pb + (size_t)M * db * 2 <= pa;
-    };
-    struct Group { int first, G; bool stackable; };
+    struct Group { int first, G; bool stackable, batch; };
     std::vector<Group> groups;
     for (int i = 0; i < n_layers;) {
         int G = 1;
@@ -756,8 +807,8 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
             if (ok && C.ln_gamma) {
                 ok = takes_direct_path(M, layers + i, G + 1, false) && quantisations_fit(M, C.d_in, G + 1, ws);
                 for (int j = i; ok && j < i + G; ++j)
-                    ok = apart(slots[layers[j].dst_slot], layers[j].d_out, slots[C.src_slot], C.d_in) &&
-                         apart(slots[layers[j].dst_slot], layers[j].d_out, slots[C.dst_slot], C.d_out);
+                    ok = apart(M, slots[layers[j].dst_slot], layers[j].d_out, slots[C.src_slot], C.d_in) &&
+                         apart(M, slots[layers[j].dst_slot], layers[j].d_out, slots[C.dst_slot], C.d_out);
             }
             for (int j = i; ok && j < i + G; ++j) ok = layers[j].dst_slot != C.dst_slot;
             if (!ok) break;
@@ -771,7 +822,17 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
                         (L.rank == 0 || (L.rank % 8 == 0 && aligned16(L.A_f16) && aligned16(L.B_f16) &&
                                          (reinterpret_cast<uintptr_t>(L.alpha_f16) & 3u) == 0));
         }
-        groups.push_back({i, G, stackable});
+        // a phase of the task queue, unless its rows are short
+        bool batch = M > kMaxFusedM && batchable(M, layers + i, G);
+        if (batch) {
+            void *ys[kMaxGroup];
+            for (int g = 0; g < G; ++g) ys[g] = slots[layers[i + g].dst_slot];
+            ShortParams sp;
+            set_short(sp, slots[layers[i].src_slot], M, layers + i, G, ys, nullptr, false, nullptr, nullptr);
+            size_t lds_bytes = 0;
+            batch = !plan_short(sp, &lds_bytes);
+        }
+        groups.push_back({i, G, stackable, batch});
         i += G;
     }
 
@@ -837,8 +898,81 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
         return launch_stack(sp, lds_bytes, st) == hipSuccess ? Launch::kRan : Launch::kRefused;
     };
 
+    // Runs groups [a, b') as one launch of the task queue, b' <= b as far as they fit: every slot that is written
+    // in it shares no memory with another that is written or with one that is read as it was before the launch.
+    auto run_batch = [&](size_t a, size_t b, size_t &ran) -> Launch {
+        BatchParams bp;
+        set_batch_workspace(bp, ws);
+        bp.M = M;
+        struct Range { const void *p; int d; bool written; } ranges[2 * kBatchMaxLayers];
+        int nr = 0, nl = 0, np = 0;
+        size_t act = 0, mail = 0;
+        const int Mp = M + (M & 1);
+        for (size_t gi = a; gi < b && np < kBatchMaxPhases; ++gi) {
+            const Group &gr = groups[gi];
+            if (nl + gr.G > kBatchMaxLayers) break;
+            const int K = layers[gr.first].d_in, src = layers[gr.first].src_slot;
+            BatchPhase &P = bp.ph[np];
+            P.x_ext = reinterpret_cast<const _Float16 *>(slots[src]);
+            P.K = K;
+            P.first_layer = (unsigned char)nl;
+            P.G = (unsigned char)gr.G;
+            P.src_phase = P.src_layer = -1;
+            for (int q = 0; q < np; ++q)            // the latest earlier layer of this launch that writes the slot
+                for (int j = 0; j < bp.ph[q].G; ++j) {
+                    const int i = bp.ph[q].first_layer + j;
+                    if (layers[groups[a].first + i].dst_slot == src) {
+                        P.src_phase = (short)q;
+                        P.src_layer = (short)i;
+                    }
+                }
+            bool ok = P.src_phase < 0 || bp.L[P.src_layer].N == K;
+            const int nr0 = nr;
+            auto add = [&](const void *p, int d, bool written) {
+                for (int i = 0; i < nr && ok; ++i) ok = (!written && !ranges[i].written) || apart(M, p, d, ranges[i].p, ranges[i].d);
+                ranges[nr++] = {p, d, written};
+            };
+            if (P.src_phase < 0) add(slots[src], K, false);
+            size_t act1 = act, mail1 = mail;
+            for (int g = 0; g < gr.G; ++g) {
+                const hgf_layer &L = layers[gr.first + g];
+                add(slots[L.dst_slot], L.d_out, true);
+                set_batch_layer(bp.L[nl + g], L, slots[L.dst_slot]);
+                act1 += align256((size_t)((L.d_out + kTileRows - 1) / kTileRows) * Mp * 64);
+                if (L.rank > 0) mail1 += (size_t)prologue_slices(K) * M * h_stride(L.rank) * 4;
+            }
+            if (!ok || act1 > kBatchActBytes || mail1 > kBatchMailBytes) {
+                nr = nr0;
+                break;
+            }
+            act = act1;
+            mail = mail1;
+            nl += gr.G;
+            ++np;
+        }
+        ran = np;
+        // (a launch begins with some 8 us that no earlier phase hides: four phases of the 1.2B shape 51.8 us in two
+        // launches each, 55.0 so at 16 tokens, eight 107 and 88; of the 7B shape four 64.8 and 61.0 at 8 tokens)
+        if (np < kBatchMinPhases) return Launch::kNoFit;
+        bp.nphases = np;
+        size_t lds_bytes = 0;
+        if (!plan_batch(bp, &lds_bytes)) return Launch::kNoFit;
+        ProfileScope prof(0, st);
+        return launch_batch(bp, lds_bytes, st) == hipSuccess ? Launch::kRan : Launch::kRefused;
+    };
+
     size_t gi = 0;
     while (gi < groups.size()) {
+        if (groups[gi].batch) {
+            size_t ge = gi, ran = 0;
+            while (ge < groups.size() && groups[ge].batch) ++ge;
+            const Launch r = ge - gi >= (size_t)kBatchMinPhases ? run_batch(gi, ge, ran) : Launch::kNoFit;
+            if (r == Launch::kRefused) return HGF_ERR_DEVICE;
+            if (r == Launch::kRan) {
+                gi += ran;
+                continue;
+            }
+        }
         // the longest run of stackable groups that fits one launch's description
         size_t ge = gi;
         int nl = 0;

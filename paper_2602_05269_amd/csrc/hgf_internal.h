@@ -164,6 +164,9 @@ struct Workspace {
                          // [2] sticky: a bounded wait ran out
     unsigned char *mail; // two exchange buffers of kMailBytes, sentinel-filled between launches
     unsigned char *xchg; // two sets of kStackSetBytes for the whole-stack launch, likewise
+    unsigned char *bmail; // two exchange regions of kBatchMailBytes for the task queue, likewise
+    int32_t *bwords;     // its tasks' words
+    unsigned char *bact; // its copies of outputs
     int8_t *xq;
     float *s_x;
     int32_t *rowsum;
@@ -341,6 +344,46 @@ struct StackParams {
 };
 static_assert(sizeof(StackParams) <= 4096, "kernel arguments");
 
+// A list of phases for 5 to 16 tokens as a queue of tasks, see hgf_batch.hip.
+constexpr int kBatchTokens = 16;
+constexpr int kBatchMinPhases = 5;
+constexpr int kBatchMaxLayers = 40, kBatchMaxPhases = 16;
+constexpr int kBatchSlices = 6;                        // slices of A x at most: d_in <= 12288
+constexpr int kBatchWords = 512;                       // unit tasks of a phase at most
+constexpr size_t kBatchActBytes = size_t(8) << 20;     // copies of the layers' outputs
+constexpr size_t kBatchMailBytes = size_t(2) << 20;    // sums of A x; the workspace holds two, sentinel-filled between launches
+struct BatchLayer {                                    // 64 bytes
+    const v4u *packed;
+    const float *s_w;
+    const _Float16 *A, *B, *alpha;
+    _Float16 *y;
+    int N, rank;
+    unsigned act_off, mail_off;                        // bytes: its copy, its sums of A x ([slice][token][h_stride] fp32)
+};
+struct BatchPhase {                                    // 80 bytes
+    const _Float16 *x_ext;                             // the tokens, when they were written before the launch (src_phase < 0)
+    unsigned src_off;                                  // else: their copy
+    int K, task0;                                      // its first task; job tasks come first
+    int unit_end[3], job_end[3];                       // ends of its first layers' units and jobs (2^30 past the last)
+    int units, jobs;                                   // row-blocks; tiles of A x
+    int h_off, red_off;                                // LDS: SiLU(A x); partial tiles (0: in the tokens' place)
+    unsigned char first_layer, G, upt, S;              // upt: units of a task at most
+    short src_phase, src_layer;
+    int unit_tasks;
+};
+struct BatchParams {
+    int32_t *flags;               // [2] sticky error, [8] launch counter, [9] workgroups done, [10] extent used, [11] next task
+    unsigned char *mail, *act;
+    int32_t *words;               // [phase][kBatchWords]: the launch's number, once the task is done
+    int M, nphases, tasks, cus;   // (two phases at least)
+    unsigned mail_used;
+    int polls;
+    int h_layer;                  // LDS: bytes of SiLU(A x) per layer
+    BatchPhase ph[kBatchMaxPhases];
+    BatchLayer L[kBatchMaxLayers];
+};
+static_assert(sizeof(BatchParams) <= 4096, "kernel arguments");
+
 // ---- kernel launchers (each validates nothing: the ABI layer has done it) -----------
 hipError_t launch_wsum(const float *W, size_t n, double *partials, float *s_w_out, hipStream_t st);
 hipError_t launch_pack(const float *W, int N, int K, const float *s_w, uint32_t *packed, hipStream_t st);
@@ -358,6 +401,9 @@ hipError_t launch_prologue(ProParams &p, hipStream_t st);
 hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st);
 bool plan_short(ShortParams &p, size_t *lds_bytes);
 hipError_t launch_short(const ShortParams &p, size_t lds_bytes, hipStream_t st);
+bool batch_fits(int M, int K, int G, int rank);        // one phase, in LDS
+bool plan_batch(BatchParams &p, size_t *lds_bytes);
+hipError_t launch_batch(const BatchParams &p, size_t lds_bytes, hipStream_t st);
 // What a plan or a launch of one of the persistent kernels came to.
 enum class Launch { kRan, kNoFit, kRefused };
 bool plan_fused(FusedParams &p, size_t *lds_bytes);
