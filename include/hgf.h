@@ -308,7 +308,8 @@ hgf_status hgf_probe_mfma_rate(int operand_kind, int iters, double *tops_out, do
 /* Tuning hook (host state, not thread-safe) for calls with at most 4 tokens, d_in % 8 == 0 and
  * d_in <= 12288.  level 2 (default): hgf_stack_forward runs whole runs of groups of layers as
  * one persistent launch (activations handed from layer to layer inside the launch), and
- * single groups as level 1; level 1: each group of layers is one persistent launch;
+ * single groups as level 1; level 1: each group of layers is one persistent launch, a
+ * base-3 layer of one token and 768 columns or of two and 1536, up to 2^27 weights, too;
  * level 0: the direct path's two launches, as for more tokens.  (At level 0 hgf_stack_forward has no queue of
  * tasks for more tokens either: two launches per group, the same bits.)  Results agree bit for bit in the
  * integers; the fp16 outputs may differ in the last place (different split of A x). */
@@ -320,7 +321,8 @@ void hgf_set_single_launch(int level);
  * (byte offset 8, cleared by hgf_workspace_init), turns the affected outputs into NaN and lets
  * the kernel run to its end.  tries > 0 replaces the bound of every wait by that many tries, so
  * that a test can see the give-up path without anything having to go wrong; 0 restores the
- * default.  Never needed in production. */
+ * default.  (In the persistent launch of a base-3 layer it is after how many reads of the exchange
+ * a workgroup computes the sums it waits for itself: the outputs are the same.)  Never needed in production. */
 void hgf_set_wait_limit(int tries);
 
 /* Measurement aid (host state, not thread-safe): time stamps from inside the whole-stack launch

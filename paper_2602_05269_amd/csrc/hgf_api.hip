@@ -282,16 +282,23 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
 {
     const int K = layers[0].d_in;
     const bool ln = layers[0].ln_gamma != nullptr;   // (then every layer of the group has one)
-    bool fused = !pair && !ln && !base3 && g_launch_level >= 1 && M <= kMaxFusedM && K % 8 == 0 && K <= kMaxFusedK && aligned16(x);
+    // Workgroups of a single launch read the tokens and write the outputs at their own pace: an output that lies over
+    // the tokens takes two launches.
+    bool free_tokens = true;
+    for (int g = 0; g < G; ++g) free_tokens = free_tokens && (!ys[g] || apart(M, x, K, ys[g], layers[g].d_out));
+    // The persistent launch.  Base-3 weights take it for one token from 768 columns on and for two from 1536 (one token:
+    // 4096 -> 11008 rank 128 15.6 us in two launches, 12.4 in one; 11008 x 11008 23.1, 20.6; 2048 -> 8192 11.3, 10.7;
+    // 1024 -> 4096 8.5, 8.4; 256 -> 1024 7.1, 7.6; two: 11008 -> 4096 20.2, 16.2; 1536 -> 4096 9.8, 9.1; 1024 -> 4096
+    // 8.6, 9.3), up to 2^27 weights (4096 -> 32000 20.7, 19.5; 8192 -> 28672 28.5, 29.8).  For three and four the tokens' conversion, which every workgroup repeats, takes what the launch saves
+    // (2048 -> 8192 11.6, 12.3; 4096 -> 11008 15.9, 15.3; 5504 -> 28672 23.7, 25.1).
+    bool fused = !pair && !ln && free_tokens && g_launch_level >= 1 && M <= kMaxFusedM && K % 8 == 0 && K <= kMaxFusedK &&
+                 aligned16(x) && (!base3 || (M <= kMaxFusedB3M && K >= 768 * M && (size_t)K * layers[0].d_out <= (size_t)1 << 27));
     for (int g = 0; g < G; ++g)
         fused = fused && (layers[g].rank == 0 ||
                           (layers[g].rank % 8 == 0 && aligned16(layers[g].A_f16) && aligned16(layers[g].B_f16) &&
                            (reinterpret_cast<uintptr_t>(layers[g].alpha_f16) & 3u) == 0));
-    // Short rows: one launch, every workgroup prepares its tokens itself (where no output lies over the tokens, as the
-    // workgroups read and write at their own pace)
-    bool free_tokens = !fused && !base3;
-    for (int g = 0; g < G; ++g) free_tokens = free_tokens && (!ys[g] || apart(M, x, K, ys[g], layers[g].d_out));
-    if (free_tokens) {
+    // Short rows: one launch, every workgroup prepares its tokens itself
+    if (free_tokens && !fused && !base3) {
         ShortParams sp;
         set_short(sp, x, M, layers, G, ys, acc_debug, pair, amax_out, acc_debug2);
         size_t lds_bytes = 0;
@@ -307,6 +314,7 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
         fp.M = M;
         fp.K = K;
         fp.G = G;
+        fp.base3 = base3 ? 1 : 0;
         fp.flags = ws.flags;
         fp.mail = ws.mail;
         for (int g = 0; g < G; ++g) {

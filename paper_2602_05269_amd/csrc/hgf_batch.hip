@@ -74,15 +74,6 @@ __device__ __forceinline__ bool has_sentinel(v4u v)
 {
     return v[0] == kSentinel || v[1] == kSentinel || v[2] == kSentinel || v[3] == kSentinel;
 }
-template <int H>
-__device__ __forceinline__ float scaled_half(uint32_t packed, float scale)
-{
-    float r;
-    if (H == 0) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(scale));
-    else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(scale));
-    return r;
-}
-
 // Where the tokens of a phase are: the caller's rows, or the copy that earlier tasks have made of their
 // outputs, [row-block][tokens, padded to even][32 rows].
 struct Source {
@@ -111,8 +102,6 @@ __device__ __forceinline__ void quantise_tokens(const Source &S, int tx, int M, 
             x[u] = buf_load16(S.r, S.at(tok, col), tok < M && col < K);
         }
     };
-    // (magnitudes of fp16 order like their bits, two at a time; a wavefront that sees an infinity or what is not a
-    // number goes the long way round, where the latter counts for nothing)
     bool odd = false;
     float amax = 0.f;
 #pragma unroll
@@ -120,17 +109,13 @@ __device__ __forceinline__ void quantise_tokens(const Source &S, int tx, int M, 
         load(c);
         uint32_t mx = 0u;
 #pragma unroll
-        for (int u = 0; u < NP; ++u)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) asm("v_pk_max_u16 %0, %1, %2" : "=v"(mx) : "v"(mx), "v"(x[u][d] & 0x7fff7fffu));
-        if (__builtin_amdgcn_ballot_w64((mx & 0xffffu) >= 0x7c00u || mx >= 0x7c000000u) != 0) {
+        for (int u = 0; u < NP; ++u) mx = max_magnitudes(x[u], mx);
+        if (__builtin_amdgcn_ballot_w64(odd_magnitudes(mx)) != 0) {
             odd = true;
 #pragma unroll
-            for (int u = 0; u < NP; ++u)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)half_bits((unsigned short)(x[u][e >> 1] >> (16 * (e & 1))))));
+            for (int u = 0; u < NP; ++u) amax = max_odd(x[u], amax);
         } else {
-            amax = fmaxf(amax, fmaxf((float)half_bits((unsigned short)mx), (float)half_bits((unsigned short)(mx >> 16))));
+            amax = fmaxf(amax, larger_magnitude(mx));
         }
     }
     auto fmax_dpp = [&](int moved) { amax = fmaxf(amax, __builtin_bit_cast(float, moved)); };
@@ -152,29 +137,11 @@ __device__ __forceinline__ void quantise_tokens(const Source &S, int tx, int M, 
     for (int c = 0; c < CH; ++c) {
         if (c > 0) load(c);
 #pragma unroll
-    for (int u = 0; u < NP; ++u) {
-        // round(x * inv), half to even, by adding 1.5 * 2^23 to the product: the code is the sum's low byte.
-        // (|x| is at most the token's maximum, so there is nothing to clip; the median makes -127 of what is not a
-        // number, as clipping by minimum and maximum does)
-        float f[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = e & 1 ? scaled_half<1>(x[u][e >> 1], inv) : scaled_half<0>(x[u][e >> 1], inv);
-        if (odd) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) f[e] = __builtin_amdgcn_fmed3f(f[e], -127.0f, 127.0f);
+        for (int u = 0; u < NP; ++u) {
+            const uint2 q = eight_codes(x[u], inv, odd, sum);
+            const int col = (t + (c * NP + u) * T) * 8;
+            if (col < Kp) *reinterpret_cast<uint2 *>(xq + (col >> 4) * ustride + tok * 16 + (col & 8)) = q;
         }
-        uint32_t q[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            uint32_t b[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) b[e] = __builtin_bit_cast(uint32_t, f[4 * h + e] + 12582912.0f);
-            q[h] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
-            sum = __builtin_amdgcn_sdot4((int)q[h], 0x01010101, sum, false);
-        }
-        const int col = (t + (c * NP + u) * T) * 8;
-        if (col < Kp) *reinterpret_cast<uint2 *>(xq + (col >> 4) * ustride + tok * 16 + (col & 8)) = make_uint2(q[0], q[1]);
-    }
     }
     sum += dpp_move<0xB1>(sum);
     sum += dpp_move<0x4E>(sum);

@@ -37,39 +37,6 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
 constexpr unsigned kOobStep = 0x80000000u;         // stays beyond every descriptor when step offsets are added
 
-// The int8 operands of five MFMAs from 16 bytes of base-3 codes, one digit of every byte each.  Bytes
-// are taken apart in pairs of 16 bits, whose products with these multipliers floor to the quotients by
-// 3, 9, 27 and 81 for every byte up to 242; digit i is quotient i - 3 quotient i+1, four at a time
-// (nothing is borrowed between bytes).  1.4 vector instructions per weight.
-typedef unsigned short v2us __attribute__((ext_vector_type(2)));
-__device__ inline void base3_digits(v4u bytes, v4i (&digit)[5])
-{
-    auto halves = [](unsigned v) { return __builtin_bit_cast(v2us, v); };
-    auto word = [](v2us v) { return __builtin_bit_cast(unsigned, v); };
-    auto triple = [](unsigned v) {                  // (as a multiplication it would run at a quarter of the rate)
-        unsigned t;
-        asm("v_lshl_add_u32 %0, %1, 1, %1" : "=v"(t) : "v"(v));
-        return t;
-    };
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const unsigned b = bytes[i];
-        const v2us e = halves(b & 0x00ff00ffu), o = halves((b >> 8) & 0x00ff00ffu);
-        auto quotient = [&](unsigned short mul, int shift) {
-            return word((e * mul) >> (unsigned short)shift) | ((word(o * mul) >> (shift - 8)) & 0x7f007f00u);
-        };
-        const unsigned short m3 = 85;
-        const unsigned q1 = __builtin_amdgcn_perm(word(o * m3 + m3), word(e * m3 + m3), 0x07030501u);
-        const unsigned q2 = quotient(57, 9), q3 = quotient(19, 9), q4 = word((e * (unsigned short)203) >> (unsigned short)14) |
-                                                                        word((o * (unsigned short)203) >> (unsigned short)14) << 8;
-        digit[0][i] = (int)(b - triple(q1));
-        digit[1][i] = (int)(q1 - triple(q2));
-        digit[2][i] = (int)(q2 - triple(q3));
-        digit[3][i] = (int)(q3 - triple(q4));
-        digit[4][i] = (int)q4;
-    }
-}
-
 // B3: base-3 weights, rows of Kp / 5 bytes (Kp: a multiple of 80).  A k-tile is 32 bytes of every row =
 // 160 columns, a lane's 16 bytes are five MFMA operands (digit 0 of its bytes, digit 1, ...), and the
 // prologue has stored x_q to match.

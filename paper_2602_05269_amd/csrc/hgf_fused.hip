@@ -9,10 +9,10 @@
 //
 // A workgroup has seven streaming wavefronts and one service wavefront.
 //   streaming: request the token rows and the first ring of weight tiles; quantise the
-//     tokens into LDS (steps 1-2; the int8 row never goes to memory); then per unit,
-//     contract tiles w, w+7, ... of d_in on the int8 MFMA over 2-bit codes (step 3),
-//     refilling each ring slot as it is consumed, and post the partial int32 tile to an
-//     LDS mailbox.
+//     tokens into LDS (steps 1-2; the int8 row never goes to memory), all between two
+//     barriers; then per unit, contract tiles w, w+7, ... of d_in on the int8 MFMA over
+//     2-bit codes or base-3 digits (step 3), refilling each ring slot as it is consumed,
+//     and post the partial int32 tile to an LDS mailbox.
 //   service: computes one slice of A x (step 5) on the f16 MFMA and writes its fp32
 //     partial sums to a device-wide exchange buffer; collects every slice of the group,
 //     adds them in order and applies SiLU (step 6); then per unit adds the seven posted
@@ -26,7 +26,23 @@
 // buffers alternate by a launch counter kept in the workspace: each launch fills the one
 // the next launch will use with sentinels, and the last workgroup to finish advances the
 // counter.  Every wait is bounded; on expiry a sticky word is set in the workspace and the
-// affected outputs are NaN.
+// affected outputs are NaN.  In the base-3 launch a workgroup that has waited for a while
+// computes the missing slices itself (the same bits), so that the launch ends however few of its
+// workgroups the device holds at a time, beside other streams' launches too.  (The 2-bit launch
+// goes without: the registers of that branch cost it up to 4 %.)
+//
+// What bounds it: one token's layer is a chain (token row, slice of A x, exchange, epilogue)
+// of instruction issue and round trips beside the weights' stream.  So the service wavefront
+// goes first on its SIMD, and the ring is no deeper than the stream needs: in flight beyond
+// that, weights lengthen the queues that the exchange's round trips wait in (six tiles -> four
+// and the priority: three layers 4096 -> 4096 of rank 128 13.8 -> 13.1 us; base-3 4096 -> 11008
+// 13.9 -> 12.4 with three; three for 2-bit weights takes 8192 -> 28672 from 19.2 to 20.0).
+// Four tokens quantised between two barriers, and codes taken from the low byte of an addition:
+// 4096 -> 11008 17.0 -> 14.7 us against one token after the other, 2048 -> 8192 13.3 -> 12.1.
+//
+// Base-3: a k-tile is 32 bytes of each of 32 rows, a lane's sixteen bytes are one row's 80
+// columns, and the tokens lie in LDS digit by digit, so that each of the five digits of a byte
+// is one MFMA.  The decode (a multiply and a shift a digit) is what its large layers wait for.
 #include "hgf_internal.h"
 
 namespace hgf {
@@ -35,11 +51,9 @@ namespace {
 
 constexpr int kStream = 7;             // streaming wavefronts per workgroup (wavefront 7 is the service one)
 constexpr int kXV = 4;                 // 16-byte pieces of a token row per streaming thread: 448*4*8 >= kMaxFusedK
-constexpr int kPF = 6;                 // weight tiles in flight per streaming wavefront.  More than the
-                                       // bandwidth-delay product needs only lengthens every queue, and with
-                                       // it the round trips of the exchange below.
 constexpr int kMaxUnits = 16;          // units per workgroup at most: each has a mailbox slot of its own
 constexpr int kLdsPolls = 1 << 22;     // bound of a wait on LDS (about a second)
+constexpr int kOwnPolls = 128;         // reads of the exchange buffer (1 to 2 us each) before a workgroup helps itself
 constexpr int kMemPolls = 1 << 18;     // bound of a wait on the exchange buffer (about a second)
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
 constexpr int kHsStride = HGF_MAX_RANK;  // halves per (layer, token) row of SiLU(A x) in LDS
@@ -76,6 +90,8 @@ __device__ __forceinline__ int layer_of(const FusedParams &p, int u)
 }
 
 // ------------------------------------------------------------------ streaming side
+// MT: tokens kept in registers (1, 2 or 4, at least M).  B3: base-3 weights.
+template <int MT, bool B3>
 __device__ __forceinline__ void streaming_wave(const FusedParams &p, unsigned char *lds, Control *ctl, float *sh_max, int *sh_sum,
                                float *sh_sx, int *sh_rs, int c, int nunits)
 {
@@ -83,21 +99,24 @@ __device__ __forceinline__ void streaming_wave(const FusedParams &p, unsigned ch
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int jl = l & 31, hf = l >> 5;
     constexpr int nthreads = kStream * 64;
+    constexpr int kPF = B3 ? 3 : 4;    // weight tiles in flight
 
-    // ---- (1) the first token row
+    // ---- (1) the token rows
     const rsrc_t xr = make_rsrc(p.x, (unsigned)p.M * p.K * 2u);
-    v8h keep[kXV];
+    v4u keep[MT][kXV];
 #pragma unroll
-    for (int r = 0; r < kXV; ++r) {
-        const int i = tid + r * nthreads;
-        keep[r] = __builtin_bit_cast(v8h, buf_load16(xr, (unsigned)i * 16u, i * 8 < p.K));
-    }
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r = 0; r < kXV; ++r) {
+            const int i = tid + r * nthreads;
+            keep[m][r] = buf_load16(xr, ((unsigned)m * p.K + (unsigned)i * 8u) * 2u, m < p.M && i * 8 < p.K);
+        }
 
     // ---- (2) the ring of weight tiles.  The load cursor (li, lj) runs kPF tiles ahead of
     //      the MFMA cursor; tile j of a unit is column tile 7*j + w of its row-block.
     //      The layers' bases and extents sit in scalar registers: the cursor selects, it never loads.
     const void *pk0 = p.L[0].packed, *pk1 = p.L[1].packed, *pk2 = p.L[2].packed, *pk3 = p.L[3].packed;
-    const unsigned by0 = (unsigned)p.L[0].RBn * p.KT * kTileBytes, by1 = (unsigned)p.L[1].RBn * p.KT * kTileBytes,
+    const unsigned by0 = B3 ? (unsigned)p.L[0].N * p.row_bytes : (unsigned)p.L[0].RBn * p.KT * kTileBytes, by1 = (unsigned)p.L[1].RBn * p.KT * kTileBytes,
                    by2 = (unsigned)p.L[2].RBn * p.KT * kTileBytes, by3 = (unsigned)p.L[3].RBn * p.KT * kTileBytes;
     const int us1 = p.G > 1 ? p.ustart[1] : 0x7fffffff, us2 = p.G > 2 ? p.ustart[2] : 0x7fffffff,
               us3 = p.G > 3 ? p.ustart[3] : 0x7fffffff;
@@ -114,14 +133,17 @@ __device__ __forceinline__ void streaming_wave(const FusedParams &p, unsigned ch
         if (u >= us2) { lbase = pk2; lbytes = by2; first = us2; }
         if (u >= us3) { lbase = pk3; lbytes = by3; first = us3; }
         if (!valid) lbytes = 0;
-        lrow = (unsigned)(u - first) * p.KT;
+        lrow = B3 ? (unsigned)(u - first) * kTileRows * p.row_bytes : (unsigned)(u - first) * p.KT;
     };
     load_unit();
     v4u wq[kPF];
     auto issue = [&](v4u &dst) {
         const int kt = lj * kStream + w;
         const rsrc_t wr = make_rsrc(lbase, lbytes);
-        dst = buf_load16_stream(wr, kt < p.KT ? (lrow + kt) * kTileBytes + l * 16 : kOob);
+        // (base-3: past the last k-tile lies the next row, in the last one the second half may be one too: its digits
+        // meet zeros; rows past the end read as zero)
+        if (B3) dst = buf_load16_stream(wr, kt < p.KT ? lrow + (unsigned)jl * p.row_bytes + kt * 32u + hf * 16u : kOob);
+        else dst = buf_load16_stream(wr, kt < p.KT ? (lrow + kt) * kTileBytes + l * 16u : kOob);
         if (++lj == p.TPW) {
             lj = 0;
             ++li;
@@ -131,21 +153,34 @@ __device__ __forceinline__ void streaming_wave(const FusedParams &p, unsigned ch
 #pragma unroll
     for (int t = 0; t < kPF; ++t) issue(wq[t]);
 
-    // ---- per-token absmax int8 quantisation into LDS (Sec. 2.2.1), one token after the other
+    // ---- per-token absmax int8 quantisation into LDS (Sec. 2.2.1), all tokens between two barriers (one after
+    //      the other they took 1.8 us each)
     const int nvec_p = p.Kp / 8;
-    auto quantise_row = [&](int m) {
+    bool odd = false;                   // this wavefront has seen an infinity or what is not a number
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        uint32_t mx = 0u;
         float amax = 0.0f;
 #pragma unroll
-        for (int r = 0; r < kXV; ++r)
-            if (r * nthreads < nvec_p)  // (compute only: the loads themselves are unconditional)
+        for (int r = 0; r < kXV; ++r)   // (compute only: the loads themselves are unconditional)
+            if (r * nthreads < nvec_p) mx = max_magnitudes(keep[m][r], mx);
+        if (__builtin_amdgcn_ballot_w64(odd_magnitudes(mx)) != 0) {
+            odd = true;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)keep[r][e]));
+            for (int r = 0; r < kXV; ++r) amax = max_odd(keep[m][r], amax);
+        } else {
+            amax = larger_magnitude(mx);
+        }
         amax = wave_max(amax);
-        if (l == 0) sh_max[w] = amax;
-        __syncthreads();
-        amax = sh_max[0];
+        if (l == 0) sh_max[w * kMaxFusedM + m] = amax;
+    }
+    __syncthreads();
 #pragma unroll
-        for (int i = 1; i < kStream; ++i) amax = fmaxf(amax, sh_max[i]);
+    for (int m = 0; m < MT; ++m) {
+        if (m >= p.M) break;
+        float amax = sh_max[m];
+#pragma unroll
+        for (int i = 1; i < kStream; ++i) amax = fmaxf(amax, sh_max[i * kMaxFusedM + m]);
         amax = fmaxf(amax, 1e-5f);
         const float inv = 127.0f / amax;
         int sum = 0;
@@ -153,36 +188,33 @@ __device__ __forceinline__ void streaming_wave(const FusedParams &p, unsigned ch
         for (int r = 0; r < kXV; ++r) {
             if (r * nthreads >= nvec_p) continue;
             const int i = tid + r * nthreads;
-            uint32_t q2[2] = {0u, 0u};
+            const uint2 q = eight_codes(keep[m][r], inv, odd, sum);
+            if (i >= nvec_p) continue;
+            if (B3) {                   // every byte to its digit's sixteen: column 80 unit + 5 byte + digit
+                const int unit = i / (kB3Cols / 8), at = (i - unit * (kB3Cols / 8)) * 8, byte = at / 5;
+                int digit = at - byte * 5, off = m * p.xstride + unit * kB3Cols + digit * 16 + byte;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int q = quant1((float)keep[r][e], inv);
-                sum += q;
-                q2[e >> 2] |= (uint32_t)(q & 0xff) << (8 * (e & 3));
+                for (int e = 0; e < 8; ++e) {
+                    lds[off] = (unsigned char)((e < 4 ? q.x : q.y) >> (8 * (e & 3)));
+                    off += digit == 4 ? 1 - 64 : 16;
+                    digit = digit == 4 ? 0 : digit + 1;
+                }
+            } else {
+                *reinterpret_cast<uint2 *>(lds + m * p.xstride + i * 8) = q;
             }
-            if (i < nvec_p) *reinterpret_cast<uint2 *>(lds + m * p.xstride + i * 8) = make_uint2(q2[0], q2[1]);
         }
         sum = wave_sum(sum);
-        if (l == 0) sh_sum[w] = sum;
-        __syncthreads();
-        if (tid == 0) {
-            int s = sh_sum[0];
-#pragma unroll
-            for (int i = 1; i < kStream; ++i) s += sh_sum[i];
-            sh_sx[m] = amax / 127.0f;
-            sh_rs[m] = s;
-        }
-    };
-    quantise_row(0);                    // outside the loop: its wait must not cover the loads behind it
-    for (int m = 1; m < p.M; ++m) {
-#pragma unroll
-        for (int r = 0; r < kXV; ++r) {
-            const int i = tid + r * nthreads;
-            keep[r] = __builtin_bit_cast(v8h, buf_load16(xr, ((unsigned)m * p.K + (unsigned)i * 8u) * 2u, i * 8 < p.K));
-        }
-        quantise_row(m);
+        if (l == 0) sh_sum[w * kMaxFusedM + m] = sum;
+        if (tid == 0) sh_sx[m] = amax / 127.0f;
     }
-    // the token scales written by thread 0 after the last barrier reach the service side
+    __syncthreads();
+    if (tid < p.M) {
+        int s = sh_sum[tid];
+#pragma unroll
+        for (int i = 1; i < kStream; ++i) s += sh_sum[i * kMaxFusedM + tid];
+        sh_rs[tid] = s;
+    }
+    // the token scales written by the first wavefront reach the service side
     // through the release/acquire pair on `arrived`
 
     // ---- contraction: one ring slot per step
@@ -198,12 +230,14 @@ __device__ __forceinline__ void streaming_wave(const FusedParams &p, unsigned ch
             if (kt < p.KT && ci < nunits) {
                 // tokens are the matrix rows (lane jl < M holds 16 int8 of token jl), the 32 weight
                 // rows the matrix columns: lane n < 32 ends up with acc[m] for tokens m = 0..3
-                const unsigned char *xrow = lds + kt * kTileCols + hf * 16;
+                const unsigned char *xrow = B3 ? lds + kt * 2 * kB3Cols + hf * kB3Cols : lds + kt * kTileCols + hf * 16;
+                v4i digit[5];
+                if (B3) base3_digits(wq[t], digit);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const v4i wcodes = widen_codes(wq[t][q]);
+                for (int q = 0; q < (B3 ? 5 : 4); ++q) {
+                    const v4i wcodes = B3 ? digit[q] : widen_codes(wq[t][q & 3]);
                     v4i xv = (v4i){0, 0, 0, 0};
-                    if (jl < p.M) xv = *reinterpret_cast<const v4i *>(xrow + jl * p.xstride + q * 32);
+                    if (jl < p.M) xv = *reinterpret_cast<const v4i *>(xrow + jl * p.xstride + q * (B3 ? 16 : 32));
                     acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(xv, wcodes, acc, 0, 0, 0);
                 }
             }
@@ -321,6 +355,7 @@ __device__ __forceinline__ v16f corr_unit(const _Float16 *hrow, const unsigned c
     return c0 + c1;
 }
 
+template <bool B3>
 __device__ __forceinline__ void service_wave(const FusedParams &p, unsigned char *lds, Control *ctl, const float *sh_sx,
                              const int *sh_rs, int c, int nunits)
 {
@@ -397,11 +432,9 @@ __device__ __forceinline__ void service_wave(const FusedParams &p, unsigned char
         }
     }
     if (nunits > 0) {
-        for (int b = 1; b < 2 * p.M; ++b) {
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
     }
     while (job < njobs) {
         job_decode(p, job, g, rt, sp);
@@ -466,6 +499,15 @@ __device__ __forceinline__ void service_wave(const FusedParams &p, unsigned char
                 if (++polls >= kMemPolls) {
                     failed = true;
                     break;
+                }
+                if (B3 && polls == p.own_polls) {   // whoever owes a slice may have no compute unit yet
+                    for (job = 0; job < njobs; ++job) {
+                        job_decode(p, job, g, rt, sp);
+                        kp0 = sp * p.pairs_per_slice;
+                        kp1 = min(kp0 + p.pairs_per_slice, p.pairs);
+                        job_load(p, jr, g, rt, kp0, kp1);
+                        job_store(job_compute());
+                    }
                 }
                 __builtin_amdgcn_s_sleep(2);
             }
@@ -552,12 +594,13 @@ __device__ __forceinline__ void service_wave(const FusedParams &p, unsigned char
     }
 }
 
+template <int MT, bool B3>
 __global__ __launch_bounds__(512) void fused_kernel(FusedParams p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     __shared__ Control ctl;
-    __shared__ float sh_max[8], sh_sx[kMaxFusedM];
-    __shared__ int sh_sum[8], sh_rs[kMaxFusedM];
+    __shared__ float sh_max[kStream * kMaxFusedM], sh_sx[kMaxFusedM];
+    __shared__ int sh_sum[kStream * kMaxFusedM], sh_rs[kMaxFusedM];
 
     const int c = blockIdx.x;
     const int total = p.ustart[p.G];
@@ -568,14 +611,24 @@ __global__ __launch_bounds__(512) void fused_kernel(FusedParams p)
 #pragma unroll
             for (int i = 0; i < kMaxUnits; ++i) ctl.arrived[i] = 0;
         }
-        service_wave(p, lds, &ctl, sh_sx, sh_rs, c, nunits);
+        __builtin_amdgcn_s_setprio(3);  // its latency is the launch's
+        service_wave<B3>(p, lds, &ctl, sh_sx, sh_rs, c, nunits);
     } else if (nunits > 0) {
-        streaming_wave(p, lds, &ctl, sh_max, sh_sum, sh_sx, sh_rs, c, nunits);
+        streaming_wave<MT, B3>(p, lds, &ctl, sh_max, sh_sum, sh_sx, sh_rs, c, nunits);
     }
 }
 
 int g_num_cus = 0, g_device = -1;
 constexpr size_t kFusedLdsMax = 144 * 1024;
+
+// A compute unit holds a workgroup of the kernel at its largest LDS request.
+bool resident(void (*kernel)(FusedParams))
+{
+    int per_cu = 0;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsMax) ==
+               hipSuccess &&
+           hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 512, kFusedLdsMax) == hipSuccess && per_cu >= 1;
+}
 
 }  // namespace
 
@@ -585,7 +638,7 @@ constexpr size_t kFusedLdsMax = 144 * 1024;
 // False: the group does not fit this path (too many units per workgroup, or LDS).
 bool plan_fused(FusedParams &p, size_t *lds_bytes)
 {
-    // The workgroups exchange partial sums within the launch, so all of them must be resident
+    // The workgroups exchange partial sums within the launch, so all of them should be resident
     // at once: at most one per compute unit, and only if the occupancy query confirms that a
     // unit holds this kernel at its largest LDS request (asked once per device).
     int dev = 0;
@@ -594,21 +647,22 @@ bool plan_fused(FusedParams &p, size_t *lds_bytes)
         return false;
     }
     if (g_num_cus == 0 || dev != g_device) {
-        int n = 0, per_cu = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(fused_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsMax) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fused_kernel, 512, kFusedLdsMax) != hipSuccess ||
-            per_cu < 1) {
+        int n = 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || !resident(&fused_kernel<1, false>) ||
+            !resident(&fused_kernel<2, false>) || !resident(&fused_kernel<4, false>) || !resident(&fused_kernel<1, true>) ||
+            !resident(&fused_kernel<2, true>)) {
             (void)hipGetLastError();
             return false;
         }
         g_num_cus = n > 0 ? n : 1;
         g_device = dev;
     }
+    p.own_polls = stack_wait_limit() > 0 ? stack_wait_limit() : kOwnPolls;
     const int M = p.M;
-    p.Kp = round_up(p.K, kTileCols);
-    p.KT = p.Kp / kTileCols;
+    const int cols = p.base3 ? 2 * kB3Cols : kTileCols;     // of a k-tile
+    p.Kp = round_up(p.K, cols);
+    p.KT = p.Kp / cols;
+    p.row_bytes = (unsigned)round_up(p.K, kB3Cols) / 5;
     p.TPW = (p.KT + kStream - 1) / kStream;
     int units = 0, hstride_max = 32;
     for (int g = 0; g < p.G; ++g) {
@@ -654,7 +708,9 @@ bool plan_fused(FusedParams &p, size_t *lds_bytes)
 
 hipError_t launch_fused(const FusedParams &p, size_t lds_bytes, hipStream_t st)
 {
-    hipLaunchKernelGGL(fused_kernel, dim3(p.nwg), dim3(512), lds_bytes, st, p);
+    void (*const kernel)(FusedParams) = p.base3 ? (p.M == 1 ? &fused_kernel<1, true> : &fused_kernel<2, true>)
+                                                : (p.M == 1 ? &fused_kernel<1, false> : (p.M == 2 ? &fused_kernel<2, false> : &fused_kernel<4, false>));
+    hipLaunchKernelGGL(kernel, dim3(p.nwg), dim3(512), lds_bytes, st, p);
     return hipGetLastError();
 }
 

@@ -87,6 +87,39 @@ __device__ inline v4i widen_codes(uint32_t w)
     return a;
 }
 __device__ inline float silu(float h) { return h / (1.0f + expf(-h)); }
+// The int8 operands of five MFMAs from 16 bytes of base-3 codes, one digit of every byte each.  Bytes
+// are taken apart in pairs of 16 bits, whose products with these multipliers floor to the quotients by
+// 3, 9, 27 and 81 for every byte up to 242; digit i is quotient i - 3 quotient i+1, four at a time
+// (nothing is borrowed between bytes).  1.4 vector instructions per weight.
+typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+__device__ inline void base3_digits(v4u bytes, v4i (&digit)[5])
+{
+    auto halves = [](unsigned v) { return __builtin_bit_cast(v2us, v); };
+    auto word = [](v2us v) { return __builtin_bit_cast(unsigned, v); };
+    auto triple = [](unsigned v) {                  // (as a multiplication it would run at a quarter of the rate)
+        unsigned t;
+        asm("v_lshl_add_u32 %0, %1, 1, %1" : "=v"(t) : "v"(v));
+        return t;
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned b = bytes[i];
+        const v2us e = halves(b & 0x00ff00ffu), o = halves((b >> 8) & 0x00ff00ffu);
+        auto quotient = [&](unsigned short mul, int shift) {
+            return word((e * mul) >> (unsigned short)shift) | ((word(o * mul) >> (shift - 8)) & 0x7f007f00u);
+        };
+        const unsigned short m3 = 85;
+        const unsigned q1 = __builtin_amdgcn_perm(word(o * m3 + m3), word(e * m3 + m3), 0x07030501u);
+        const unsigned q2 = quotient(57, 9), q3 = quotient(19, 9), q4 = word((e * (unsigned short)203) >> (unsigned short)14) |
+                                                                        word((o * (unsigned short)203) >> (unsigned short)14) << 8;
+        digit[0][i] = (int)(b - triple(q1));
+        digit[1][i] = (int)(q1 - triple(q2));
+        digit[2][i] = (int)(q2 - triple(q3));
+        digit[3][i] = (int)(q3 - triple(q4));
+        digit[4][i] = (int)q4;
+    }
+}
+
 // SiLU and tanh from the hardware's exponential and reciprocal (about one unit in the last place each); near
 // zero tanh by its series, where 1 - t would cancel
 __device__ inline float silu_hw(float h)
@@ -107,6 +140,61 @@ __device__ inline _Float16 round_half(float v)
 {
     asm("" : "+v"(v));
     return (_Float16)v;
+}
+// fp32 product of fp16 half H (0: low, 1: high) of `packed` and the fp32 `scale`, rounded once
+// (an FMA whose addend is zero), without a conversion instruction of its own
+template <int H>
+__device__ inline float scaled_half(uint32_t packed, float scale)
+{
+    float r;
+    if (H == 0) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(scale));
+    else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(scale));
+    return r;
+}
+// Eight int8 codes round(x * inv), half to even, of the fp16 in x, by adding 1.5 * 2^23 to the products: a code is
+// its sum's low byte.  |x| is at most the token's maximum, so there is nothing to clip, unless the token is `odd`
+// (it holds an infinity or what is not a number): the median makes -127 of what is not a number, as clipping by
+// minimum and maximum does.  The codes are added to `sum`.
+__device__ inline uint2 eight_codes(v4u x, float inv, bool odd, int &sum)
+{
+    float f[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = e & 1 ? scaled_half<1>(x[e >> 1], inv) : scaled_half<0>(x[e >> 1], inv);
+    if (odd) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = __builtin_amdgcn_fmed3f(f[e], -127.0f, 127.0f);
+    }
+    uint32_t q[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b[e] = __builtin_bit_cast(uint32_t, f[4 * h + e] + 12582912.0f);
+        q[h] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
+        sum = __builtin_amdgcn_sdot4((int)q[h], 0x01010101, sum, false);
+    }
+    return make_uint2(q[0], q[1]);
+}
+// Running maximum of fp16 magnitudes, two at a time (they order like their bits); kOddBits and above: an infinity or
+// what is not a number.
+constexpr uint32_t kOddBits = 0x7c00u;
+__device__ inline uint32_t max_magnitudes(v4u x, uint32_t mx)
+{
+#pragma unroll
+    for (int d = 0; d < 4; ++d) asm("v_pk_max_u16 %0, %1, %2" : "=v"(mx) : "v"(mx), "v"(x[d] & 0x7fff7fffu));
+    return mx;
+}
+__device__ inline bool odd_magnitudes(uint32_t mx) { return (mx & 0xffffu) >= kOddBits || mx >= kOddBits << 16; }
+__device__ inline float larger_magnitude(uint32_t mx)
+{
+    return fmaxf((float)half_bits((unsigned short)mx), (float)half_bits((unsigned short)(mx >> 16)));
+}
+// The same where some are odd: what is not a number counts for nothing.
+__device__ inline float max_odd(v4u x, float amax)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)half_bits((unsigned short)(x[e >> 1] >> (16 * (e & 1))))));
+    return amax;
 }
 // Wave-wide reductions with the result in every lane.  The lanes of a row of 16 exchange
 // through the data-parallel-primitive modifiers of the vector ALU (xor 1, xor 2, mirror within
@@ -283,14 +371,17 @@ constexpr size_t kShortLdsMax = 150 * 1024;
 // Single persistent launch for a handful of tokens: every workgroup quantises the tokens
 // itself, streams its share of the row-blocks ("units") and exchanges the partial sums of
 // A x with the others through a sentinel-filled buffer in the workspace.
-constexpr int kMaxFusedM = 4;
+constexpr int kMaxFusedM = 4, kMaxFusedB3M = 2;
 constexpr int kMaxFusedK = 12288;
 constexpr int kFusedSplit = 24;                               // slices of d_in at most (512 columns each)
 constexpr size_t kMailLayerBytes = size_t(64) * HGF_MAX_RANK * 4;   // 64 (slice, token) rows of fp32 per layer
 constexpr size_t kMailBytes = kMailLayerBytes * kMaxGroup;    // one exchange buffer; the workspace holds two
 struct FusedParams {
     const _Float16 *x;            // [M, K] fp16
-    int M, K, Kp, KT, TPW, G;     // TPW: tiles of a unit per streaming wavefront
+    int M, K, Kp, KT, TPW, G;     // TPW: tiles of a unit per streaming wavefront; Kp: whole k-tiles
+    int base3;                    // packed: base-3 rows; a k-tile is 32 bytes of every row = 160 columns (G == 1)
+    unsigned row_bytes;
+    int own_polls;           // of them
     DecLayer L[kMaxGroup];        // h16 unused
     const _Float16 *A[kMaxGroup];
     int ustart[kMaxGroup + 1];    // running sum of the layers' row-blocks
@@ -410,6 +501,7 @@ bool plan_fused(FusedParams &p, size_t *lds_bytes);
 hipError_t launch_fused(const FusedParams &p, size_t lds_bytes, hipStream_t st);
 bool plan_stack(StackParams &p, size_t *lds_bytes);
 void set_stack_wait_limit(int tries);
+int stack_wait_limit();
 void set_stack_trace(unsigned long long *buf, size_t bytes, int first_phase);
 hipError_t launch_stack(const StackParams &p, size_t lds_bytes, hipStream_t st);
 struct PairOut {                 // extra outputs of a SwiGLU pair launch (both nullable)

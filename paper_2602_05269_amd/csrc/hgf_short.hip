@@ -30,17 +30,6 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// fp32 product of fp16 half H (0: low, 1: high) of `packed` and the fp32 `scale`, rounded once
-// (an FMA whose addend is zero), without a conversion instruction of its own
-template <int H>
-__device__ __forceinline__ float scaled_half(uint32_t packed, float scale)
-{
-    float r;
-    if (H == 0) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(scale));
-    else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(scale));
-    return r;
-}
-
 struct TokenWords {
     float s_x[32];
     int rowsum[32];
@@ -177,7 +166,7 @@ struct Tokens {
     {
         float v[LN ? NP : 1][8];
         float amax;
-        bool odd = LN;                  // codes are clipped: products may pass 127, or be what is not a number
+        bool odd = false;
         if (LN) {
             // mean and mean squared deviation in fp64, each rounded once; then fp32 in exactly this order, one
             // rounding each
@@ -210,22 +199,16 @@ struct Tokens {
                     amax = fmaxf(amax, fabsf(v[u][e]));
                 }
         } else {
-            // (magnitudes of fp16 order like their bits, two at a time; a token with an infinity or what is not a
-            // number goes the long way round, where the latter counts for nothing)
             uint32_t mx = 0u;
 #pragma unroll
-            for (int u = 0; u < NP; ++u)
-#pragma unroll
-                for (int d = 0; d < 4; ++d) asm("v_pk_max_u16 %0, %1, %2" : "=v"(mx) : "v"(mx), "v"(x[u][d] & 0x7fff7fffu));
-            odd = __builtin_amdgcn_ballot_w64((mx & 0xffffu) >= 0x7c00u || mx >= 0x7c000000u) != 0;
+            for (int u = 0; u < NP; ++u) mx = max_magnitudes(x[u], mx);
+            odd = __builtin_amdgcn_ballot_w64(odd_magnitudes(mx)) != 0;
             if (odd) {
                 amax = 0.f;
 #pragma unroll
-                for (int u = 0; u < NP; ++u)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(half_at(u, e)));
+                for (int u = 0; u < NP; ++u) amax = max_odd(x[u], amax);
             } else {
-                amax = fmaxf((float)half_bits((unsigned short)mx), (float)half_bits((unsigned short)(mx >> 16)));
+                amax = larger_magnitude(mx);
             }
         }
         amax = lanes_max(amax, tlog);
@@ -234,33 +217,24 @@ struct Tokens {
         int sum = 0;
 #pragma unroll
         for (int u = 0; u < NP; ++u) {
-            // round(x * inv), half to even, by adding 1.5 * 2^23 to the product: the code is the sum's low byte.
-            // (|x| is at most the token's maximum, so there is nothing to clip.  For the odd token the median
-            // makes -127 of what is not a number, as clipping by minimum and maximum does.)
-            uint32_t b[8];
+            uint2 q;
+            if (LN) {                               // (the same, of fp32 values, which may pass 127 by a rounding)
+                uint32_t w2[2];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float f;
-                if (LN) f = v[u][e] * inv;
-                else f = e & 1 ? scaled_half<1>(x[u][e >> 1], inv) : scaled_half<0>(x[u][e >> 1], inv);
-                b[e] = __builtin_bit_cast(uint32_t, f);
-            }
-            if (odd) {
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t b[4];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) b[e] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(__builtin_bit_cast(float, b[e]), -127.0f, 127.0f));
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) b[e] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, b[e]) + 12582912.0f);
-            uint32_t q[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint32_t lo = __builtin_amdgcn_perm(b[4 * h + 1], b[4 * h + 0], 0x0c0c0400u);
-                const uint32_t hi = __builtin_amdgcn_perm(b[4 * h + 3], b[4 * h + 2], 0x0c0c0400u);
-                q[h] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-                sum = __builtin_amdgcn_sdot4((int)q[h], 0x01010101, sum, false);
+                    for (int e = 0; e < 4; ++e)
+                        b[e] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(v[u][4 * h + e] * inv, -127.0f, 127.0f) + 12582912.0f);
+                    w2[h] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u), 0x05040100u);
+                    sum = __builtin_amdgcn_sdot4((int)w2[h], 0x01010101, sum, false);
+                }
+                q = make_uint2(w2[0], w2[1]);
+            } else {
+                q = eight_codes(x[u], inv, odd, sum);
             }
             const int col = column(u);
-            if (col < p.Kp) *reinterpret_cast<uint2 *>(xq + (col >> 4) * p.ustride + tok * 16 + (col & 8)) = make_uint2(q[0], q[1]);
+            if (col < p.Kp) *reinterpret_cast<uint2 *>(xq + (col >> 4) * p.ustride + tok * 16 + (col & 8)) = q;
         }
         sum = lanes_sum(sum, tlog);
         if (t == 0) {

@@ -1243,6 +1243,7 @@ bool plan_stack(StackParams &p, size_t *lds_bytes)
 }
 
 void set_stack_wait_limit(int tries) { g_wait_limit = tries > 0 ? tries : 0; }
+int stack_wait_limit() { return g_wait_limit; }
 
 void set_stack_trace(unsigned long long *buf, size_t bytes, int first_phase)
 {
