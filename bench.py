@@ -420,7 +420,7 @@ def main() -> int:
             sm = time_steps(make_runner(wm, ws, use_graph), few, 2)
             c = hbm(wm.bytes / args.blocks, sm / args.blocks)
             c["path"] = "whole-stack launches (stack_kernel)" if M <= 4 else \
-                        "direct path (prologue_kernel, direct_kernel)"
+                        "queue of tasks (batch_kernel)" if M <= 16 else "direct path (prologue_kernel, direct_kernel)"
             cases[f"config4_block_M{M}_cold"] = c
             del wm
 
@@ -465,9 +465,9 @@ def main() -> int:
         torch.cuda.empty_cache()
 
         # ---- base-3 packing (1.6 bits per weight) against the 2-bit layout: 16 distinct `up`
-        #      layers (4096 -> 11008, r=128) at M=1, one call per layer.  "same_path": the 2-bit
-        #      layer through the launch-per-step path as well (prologue, main kernel; the base-3 path has
-        #      the slice reduction as a third launch).
+        #      layers (4096 -> 11008, r=128) at M=1, one call per layer: both in the persistent
+        #      launch.  "same_path": the 2-bit layer through the two launches (prologue, main kernel) that base-3 layers
+        #      of more tokens take.
         def b3_cases():
             gen = torch.Generator(device="cuda")
             gen.manual_seed(4500)
@@ -530,7 +530,7 @@ def main() -> int:
         w0 = Workload(0, 8, 1, seed=0, ws=ws)
         s0 = time_steps(make_runner(w0, ws, use_graph), max(20, args.steps), args.warmup)
         cases["config0_single_M8_hot"] = hbm(w0.bytes, s0)
-        cases["config0_single_M8_hot"]["note"] = "0.03 MB of parameters: the latency of two launches, not bandwidth"
+        cases["config0_single_M8_hot"]["note"] = "0.03 MB of parameters: the latency of one launch, not bandwidth"
         del w0
         # 8-layer d=512 stack at M=1: 14.7 MB of parameters, cache-resident ("hot"), launch bound
         w1 = Workload(1, 1, 8, seed=1000, ws=ws)

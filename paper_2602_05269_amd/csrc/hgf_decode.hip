@@ -21,7 +21,7 @@
 // behind a barrier and let one wavefront finish a row-block (us per launch, 7B-shape down projection at
 // 64 tokens: 34.1 before, 13 with the tokens' operand from L2; 2048 -> 8192 twice at 16 tokens: 10.2
 // and 7.1).  With the prologue, per pass: 8 up-gate pairs and down projections of the 7B shape at 64
-// tokens 653 -> 403 us, 28 layers of d = 512 with LayerNorms at 500 tokens 516 -> 200 us.
+// tokens 653 -> 386 us, 28 layers of d = 512 with LayerNorms at 500 tokens 516 -> 176 us (short rows in one launch).
 //
 // SwiGLU pair: the "two row-blocks" of a workgroup are the same row-block of the gate and of the up
 // projection, so z = SiLU(y_gate) * y_up forms in registers.
@@ -376,7 +376,7 @@ hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st)
     // and 11.6; 7B-shape up + gate at 64 tokens, 1376 tiles: 35.0 for one row-block per workgroup, 30.7 for
     // two; 7B-shape down at 128 tokens, 512 tiles: two row-blocks with eight wavefronts 24.7, four wavefronts
     // 27.0; at 256 tokens 42.7 and 39.8).
-    // (base-3, 4096 -> 11008 at one token, 344 row-blocks: two k-tiles in flight 10.6, four 11.2; eight wavefronts 11.0)
+    // (base-3, 344 row-blocks of 4096 columns: two k-tiles in flight 10.6, four 11.2; eight wavefronts 11.0)
     if (p.base3) return launch_shape<1, 4, 2, false, true>(p, st);
     const int groups = (p.M + 31) / 32, tiles = rbs * groups;
     if (p.pair) {

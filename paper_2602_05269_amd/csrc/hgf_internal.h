@@ -380,8 +380,8 @@ struct FusedParams {
     const _Float16 *x;            // [M, K] fp16
     int M, K, Kp, KT, TPW, G;     // TPW: tiles of a unit per streaming wavefront; Kp: whole k-tiles
     int base3;                    // packed: base-3 rows; a k-tile is 32 bytes of every row = 160 columns (G == 1)
-    unsigned row_bytes;
-    int own_polls;           // of them
+    unsigned row_bytes;           // of them
+    int own_polls;                // reads of the exchange before a workgroup of the base-3 launch helps itself
     DecLayer L[kMaxGroup];        // h16 unused
     const _Float16 *A[kMaxGroup];
     int ustart[kMaxGroup + 1];    // running sum of the layers' row-blocks
