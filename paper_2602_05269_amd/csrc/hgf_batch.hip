@@ -196,7 +196,7 @@ __device__ __forceinline__ bool gather_layer(const BatchLayer &LL, int first, in
         for (int s = 1; s < kBatchSlices; ++s) h += part[s];
         v4h o;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = round_half(silu_hw(j + v < rank ? h[v] : 0.f));
+        for (int v = 0; v < 4; ++v) o[v] = (_Float16)silu(j + v < rank ? h[v] : 0.f);
         *reinterpret_cast<v4h *>(hl + (j >> 4) * 1024 + ((j >> 3 & 1) * 32 + tok) * 16 + (j & 4) * 2) = o;
     }
     return !late;
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
                 const int gx = tx - CW * 64, i = gx >> 5, u = u0 + min(i, n - 1), gg = layer_of(u), row = block_of(u, gg) * kTileRows + (gx & 31);
                 const BatchLayer &L = D.L[first + gg];
                 float gate = 0.f;
-                if (L.rank > 0 && row < L.N) gate = tanh_hw((float)L.alpha[row]);
+                if (L.rank > 0 && row < L.N) gate = tanhf((float)L.alpha[row]);
                 sh.gate[gx] = gate;
                 if ((gx & 31) == 0) sh.s_w[i] = *L.s_w;
             }
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const float cv = fq == 0 ? corr[v] : (fq == 1 ? corr[4 + v] : (fq == 2 ? corr[8 + v] : corr[12 + v]));
-                    o[v] = round_half((float)(a[v] - rs) * scale + gate[v] * cv);
+                    o[v] = (_Float16)((float)(a[v] - rs) * scale + gate[v] * cv);
                     if (failed) o[v] = __builtin_bit_cast(_Float16, (unsigned short)0x7e00);
                 }
                 if (m_ok && nn < N) {

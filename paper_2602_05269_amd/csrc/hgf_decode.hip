@@ -21,7 +21,7 @@
 // behind a barrier and let one wavefront finish a row-block (us per launch, 7B-shape down projection at
 // 64 tokens: 34.1 before, 13 with the tokens' operand from L2; 2048 -> 8192 twice at 16 tokens: 10.2
 // and 7.1).  With the prologue, per pass: 8 up-gate pairs and down projections of the 7B shape at 64
-// tokens 653 -> 386 us, 28 layers of d = 512 with LayerNorms at 500 tokens 516 -> 176 us (short rows in one launch).
+// tokens 653 -> 404 us, 28 layers of d = 512 with LayerNorms at 500 tokens 516 -> 181 us (short rows in one launch).
 //
 // SwiGLU pair: the "two row-blocks" of a workgroup are the same row-block of the gate and of the up
 // projection, so z = SiLU(y_gate) * y_up forms in registers.
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
                                                                 i0 + v * 64 * KW < quads));
                     v4h o;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = round_half(silu_hw(h[e]));
+                    for (int e = 0; e < 4; ++e) o[e] = (_Float16)silu(h[e]);
                     if (i0 + v * 64 * KW < quads)
                         *reinterpret_cast<v4h *>(ops + ((NB + g) * JS + (j[v] >> 4)) * 1024 +
                                                  ((j[v] >> 3 & 1) * 32 + tok[v]) * 16 + (j[v] & 4) * 2) = o;
@@ -299,13 +299,13 @@ __global__ __launch_bounds__(64 * KW, direct_waves(D)) void direct_kernel(Decode
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 a[g][v] -= rs;
-                y[g][v] = (float)a[g][v] * scale + tanh_hw(alpha[g][c][v]) * cv[g][c][v];
+                y[g][v] = (float)a[g][v] * scale + tanhf(alpha[g][c][v]) * cv[g][c][v];
             }
         }
         v4h o;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            o[v] = round_half(PAIR ? silu_hw(y[0][v]) * y[NL - 1][v] : y[0][v]);
+            o[v] = PAIR ? product_half(silu(y[0][v]), y[NL - 1][v]) : (_Float16)y[0][v];
             if (n + v < N) zmax = fmaxf(zmax, fabsf((float)o[v]));
         }
         if (!m_ok) continue;

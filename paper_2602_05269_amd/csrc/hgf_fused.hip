@@ -72,9 +72,10 @@ __device__ __forceinline__ v4u buf_load16_agent(rsrc_t r, unsigned off, bool ok 
     return __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(ok ? off : kOob), 0, 16));
 }
 
-// Cheap transcendental forms for the service wavefront, whose latency is the tail of the
-// launch (hardware exp2 and reciprocal, about 1 ulp each; the results are rounded to fp16
-// or multiply an fp16-bound term).
+// Cheap transcendental forms for the service wavefront of the 2-bit launch, whose latency is its tail
+// (hardware exp2 and reciprocal, about 1 ulp each; the results are rounded to fp16 or multiply an
+// fp16-bound term).  Base-3 layers have the library's, as in their two launches: this tanh cancels near zero
+// (relative error 1e-4 at 1e-3), and they cost the launch 0.1 us of 12.
 __device__ __forceinline__ float exp_fast(float v) { return __builtin_amdgcn_exp2f(v * 1.44269504088896340736f); }
 __device__ __forceinline__ float silu_fast(float h) { return h * __builtin_amdgcn_rcpf(1.0f + exp_fast(-h)); }
 __device__ __forceinline__ float tanh_fast(float a) { return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + exp_fast(2.0f * a)); }
@@ -517,7 +518,7 @@ __device__ __forceinline__ void service_wave(const FusedParams &p, unsigned char
             if (inside) {
                 v4h o;
 #pragma unroll
-                for (int v = 0; v < 4; ++v) o[v] = (j + v < rank) ? (_Float16)silu_fast(h[v]) : (_Float16)0.0f;
+                for (int v = 0; v < 4; ++v) o[v] = (j + v < rank) ? (_Float16)(B3 ? silu(h[v]) : silu_fast(h[v])) : (_Float16)0.0f;
                 *reinterpret_cast<v4h *>(hs + (gg * p.M + idx * 4 / hstride) * kHsStride + j) = o;
             }
         }
@@ -557,7 +558,8 @@ __device__ __forceinline__ void service_wave(const FusedParams &p, unsigned char
             v16f corr = (v16f){};
             float gate = 0.f;
             if (Lrank > 0) {
-                gate = tanh_fast((float)*reinterpret_cast<const _Float16 *>(op + p.unit_alpha + jl * 2));
+                const float al = (float)*reinterpret_cast<const _Float16 *>(op + p.unit_alpha + jl * 2);
+                gate = B3 ? tanhf(al) : tanh_fast(al);
                 const _Float16 *hrow = hs + (gg * p.M + jl) * kHsStride + hf * 8;
                 const unsigned char *brow = op + (hf * 32 + jl) * 16;
                 switch (Lhstride / 16) {

@@ -120,26 +120,13 @@ __device__ inline void base3_digits(v4u bytes, v4i (&digit)[5])
     }
 }
 
-// SiLU and tanh from the hardware's exponential and reciprocal (about one unit in the last place each); near
-// zero tanh by its series, where 1 - t would cancel
-__device__ inline float silu_hw(float h)
+// fp16 of the exact product, rounded once.  (The compiler joins a product and its conversion into this instruction
+// in some places and not in others; kernels that have to give the same bits say it.)
+__device__ inline _Float16 product_half(float a, float b)
 {
-    return h * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(h * -1.44269504088896340736f));
-}
-__device__ inline float tanh_hw(float a)
-{
-    const float t = __builtin_amdgcn_exp2f(fabsf(a) * -2.88539008177792681472f);
-    const float big = copysignf((1.0f - t) * __builtin_amdgcn_rcpf(1.0f + t), a);
-    const float s = a * a;
-    const float small = a + a * s * (-1.0f / 3 + s * (2.0f / 15 + s * (-17.0f / 315 + s * (62.0f / 2835))));
-    return fabsf(a) < 0.3f ? small : big;
-}
-// fp32 to fp16.  (The compiler joins a product and its conversion into one instruction, which rounds once, in
-// some places and not in others; kernels that have to give the same bits keep the product's own rounding.)
-__device__ inline _Float16 round_half(float v)
-{
-    asm("" : "+v"(v));
-    return (_Float16)v;
+    uint32_t r;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b));
+    return half_bits((unsigned short)r);
 }
 // fp32 product of fp16 half H (0: low, 1: high) of `packed` and the fp32 `scale`, rounded once
 // (an FMA whose addend is zero), without a conversion instruction of its own

@@ -349,7 +349,7 @@ __device__ inline void corr_tile(const ProParams &p, int job)
     } else {
         v4h o;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = round_half(silu_hw(h[v]));
+        for (int v = 0; v < 4; ++v) o[v] = (_Float16)silu(h[v]);
         *reinterpret_cast<v4h *>(L.h16 + at) = o;
     }
 }

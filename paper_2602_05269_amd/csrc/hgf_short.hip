@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kThreads) void short_kernel(ShortParams p)
         const int j = (r - (second ? rt0 : 0)) * 16 + 4 * (le >> 4), rank = second ? L2.rank : L.rank;
         v4h o;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) o[v] = round_half(silu_hw(j + v < rank ? h[v] : 0.f));
+        for (int v = 0; v < 4; ++v) o[v] = (_Float16)silu(j + v < rank ? h[v] : 0.f);
         *reinterpret_cast<v4h *>(hl + r * 1024 + ((j >> 3 & 1) * 32 + 16 * tt + (le & 15)) * 16 + (j & 4) * 2) = o;
     }
 
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kThreads) void short_kernel(ShortParams p)
 #pragma unroll
         for (int c = 0; c < PPW; ++c)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) gate[g][c][v] = tanh_hw(alpha[g][c][v]);
+            for (int v = 0; v < 4; ++v) gate[g][c][v] = tanhf(alpha[g][c][v]);
     v4i *red = reinterpret_cast<v4i *>(lds + p.red_off);
     if (KS > 1) {
 #pragma unroll
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(kThreads) void short_kernel(ShortParams p)
         v4h o;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            o[v] = round_half(PAIR ? silu_hw(y[0][v]) * y[NL - 1][v] : y[0][v]);
+            o[v] = PAIR ? product_half(silu(y[0][v]), y[NL - 1][v]) : (_Float16)y[0][v];
             if (n + v < N) zmax = fmaxf(zmax, fabsf((float)o[v]));
         }
         if (!m_ok) continue;
