@@ -22,7 +22,7 @@ Workspace carve_workspace(void *base, int M, int d_in, int d_out, int rank, int 
     ws.xchg = with_stack ? reinterpret_cast<unsigned char *>(take(2 * kStackSetBytes)) : nullptr;
     ws.bmail = with_stack ? reinterpret_cast<unsigned char *>(take(2 * kBatchMailBytes)) : nullptr;
     ws.bwords = with_stack ? reinterpret_cast<int32_t *>(take(size_t(kBatchMaxPhases) * kBatchWords * 4)) : nullptr;
-    ws.bact = with_stack ? reinterpret_cast<unsigned char *>(take(kBatchActBytes)) : nullptr;
+    ws.bact = with_stack ? reinterpret_cast<unsigned char *>(take(kBatchActRegion)) : nullptr;
     const int Kp = round_up(d_in, kTileCols);
     ws.xq = reinterpret_cast<int8_t *>(take((size_t)M * Kp));
     ws.s_x = reinterpret_cast<float *>(take((size_t)M * 4));
@@ -237,7 +237,9 @@ void set_batch_workspace(BatchParams &bp, const Workspace &ws)
 {
     bp.flags = ws.flags;
     bp.mail = ws.bmail;
-    bp.act = ws.bact;
+    // (a workspace is aligned to 16 bytes; the region has room for the rest)
+    const uintptr_t act = reinterpret_cast<uintptr_t>(ws.bact);
+    bp.act = ws.bact + ((act + kBatchActAlign - 1) / kBatchActAlign * kBatchActAlign - act);
     bp.words = ws.bwords;
 }
 

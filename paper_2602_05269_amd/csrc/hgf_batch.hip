@@ -29,8 +29,8 @@
 // refills what the one before it used of the other.  Outputs of a layer: besides the caller's slot they go, with
 // device scope, to a copy in the workspace, then the task's word is set to the launch's number; readers wait for
 // the words of all tasks of the phase and then read the copy through their L2, as often as they like: its lines are
-// written once in a launch, each by one workgroup (a row-block's outputs are whole lines), and nobody has read
-// them before.
+// written once in a launch, each by one workgroup (a row-block's outputs are whole lines: the copies begin at a
+// multiple of 256 bytes wherever the workspace does), and nobody has read them before.
 #include "hgf_internal.h"
 
 #include <type_traits>

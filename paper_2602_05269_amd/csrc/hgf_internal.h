@@ -428,7 +428,9 @@ constexpr int kBatchMinPhases = 5;
 constexpr int kBatchMaxLayers = 40, kBatchMaxPhases = 16;
 constexpr int kBatchSlices = 6;                        // slices of A x at most: d_in <= 12288
 constexpr int kBatchWords = 512;                       // unit tasks of a phase at most
-constexpr size_t kBatchActBytes = size_t(8) << 20;     // copies of the layers' outputs
+constexpr size_t kBatchActRegion = size_t(8) << 20;    // copies of the layers' outputs, from its first address ...
+constexpr size_t kBatchActAlign = 256;                 // ... that is a multiple of this: no line holds two row-blocks' outputs
+constexpr size_t kBatchActBytes = kBatchActRegion - kBatchActAlign;
 constexpr size_t kBatchMailBytes = size_t(2) << 20;    // sums of A x; the workspace holds two, sentinel-filled between launches
 struct BatchLayer {                                    // 64 bytes
     const v4u *packed;

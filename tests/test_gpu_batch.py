@@ -146,3 +146,31 @@ def test_queue_shares_a_workspace_and_a_graph():
         assert all(np.array_equal(a, b) for a, b in zip(_run(st4, s4, ws, 2), want4))
         assert all(np.array_equal(a.view(np.uint16), b.view(np.uint16)) for a, b in zip(_run(st16, s16, ws, 2), want16))
     assert _flags(ws)[2] == 0
+
+
+class _ShiftedWorkspace:
+    """A workspace that starts 16 bytes (all that is asked of it) past a multiple of 256."""
+
+    def __init__(self, shift, *dims):
+        self.bytes = hb.hgf_workspace_bytes(*dims)
+        whole = torch.zeros(self.bytes + 512, dtype=torch.uint8, device="cuda")
+        start = -whole.data_ptr() % 256 + shift
+        self.buf = whole[start:start + self.bytes]
+        hb.hgf_workspace_init(self)
+
+
+@pytest.mark.parametrize("shift", [16, 112, 240])
+def test_queue_in_a_workspace_between_two_lines(shift):
+    """Other tokens in every pass over one workspace: nothing of a pass before is taken for a token of this one."""
+    M, d = 8, 2304
+    ws = _ShiftedWorkspace(shift, M, d, d, 48)
+    _, st, slots = _list([(d, d, 48, i, i + 1) for i in range(8)], M, ws)
+    x = slots[0].clone()
+    for seed in range(3):
+        slots[0].copy_(x.roll(seed, 0) * (1.0 - 0.25 * seed))
+        two = _run(st, slots, ws, 0)
+        before = _flags(ws)
+        one = _run(st, slots, ws, 2)
+        assert _flags(ws)[8] == before[8] + 1
+        for i, (a, b) in enumerate(zip(one, two)):
+            assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), f"slot {i}"
