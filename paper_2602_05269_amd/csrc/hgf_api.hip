@@ -20,9 +20,6 @@ Workspace carve_workspace(void *base, int M, int d_in, int d_out, int rank, int 
     ws.flags = reinterpret_cast<int32_t *>(take(kZeroBytes));
     ws.mail = reinterpret_cast<unsigned char *>(take(2 * kMailBytes));
     ws.xchg = with_stack ? reinterpret_cast<unsigned char *>(take(2 * kStackSetBytes)) : nullptr;
-    ws.bmail = with_stack ? reinterpret_cast<unsigned char *>(take(2 * kBatchMailBytes)) : nullptr;
-    ws.bwords = with_stack ? reinterpret_cast<int32_t *>(take(size_t(kBatchMaxPhases) * kBatchWords * 4)) : nullptr;
-    ws.bact = with_stack ? reinterpret_cast<unsigned char *>(take(kBatchActRegion)) : nullptr;
     const int Kp = round_up(d_in, kTileCols);
     ws.xq = reinterpret_cast<int8_t *>(take((size_t)M * Kp));
     ws.s_x = reinterpret_cast<float *>(take((size_t)M * 4));
@@ -236,11 +233,9 @@ void set_batch_layer(BatchLayer &D, const hgf_layer &L, void *y)
 void set_batch_workspace(BatchParams &bp, const Workspace &ws)
 {
     bp.flags = ws.flags;
-    bp.mail = ws.bmail;
-    // (a workspace is aligned to 16 bytes; the region has room for the rest)
-    const uintptr_t act = reinterpret_cast<uintptr_t>(ws.bact);
-    bp.act = ws.bact + ((act + kBatchActAlign - 1) / kBatchActAlign * kBatchActAlign - act);
-    bp.words = ws.bwords;
+    bp.xchg = ws.xchg;
+    // (a workspace is aligned to 16 bytes)
+    bp.act_shift = (unsigned)((0 - reinterpret_cast<uintptr_t>(ws.xchg)) % kBatchActAlign);
 }
 
 // Fills in what the launch for short rows reads of a group.
@@ -572,8 +567,7 @@ hgf_status hgf_workspace_init(void *workspace, size_t workspace_bytes, void *str
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (launch_fill(ws.flags, align256(kZeroBytes), 0u, st) != hipSuccess) return HGF_ERR_DEVICE;
     if (launch_fill(ws.mail, 2 * kMailBytes, 0xFFFFFFFFu, st) != hipSuccess) return HGF_ERR_DEVICE;
-    if (launch_fill(ws.xchg, 2 * kStackSetBytes, 0xFFFFFFFFu, st) != hipSuccess) return HGF_ERR_DEVICE;
-    return from_hip(launch_fill(ws.bmail, 2 * kBatchMailBytes + size_t(kBatchMaxPhases) * kBatchWords * 4, 0xFFFFFFFFu, st));
+    return from_hip(launch_fill(ws.xchg, 2 * kStackSetBytes, 0xFFFFFFFFu, st));
 }
 
 hgf_status hgf_quantize_pack_weights(const float *W, int d_out, int d_in, void *packed_out, float *s_w_out,
@@ -951,7 +945,7 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
                 act1 += align256((size_t)((L.d_out + kTileRows - 1) / kTileRows) * Mp * 64);
                 if (L.rank > 0) mail1 += (size_t)prologue_slices(K) * M * h_stride(L.rank) * 4;
             }
-            if (!ok || act1 > kBatchActBytes || mail1 > kBatchMailBytes) {
+            if (!ok || act1 > kBatchActBytes || mail1 + (np + 1) * kBatchPhaseWords > kBatchMailBytes) {
                 nr = nr0;
                 break;
             }

@@ -25,9 +25,10 @@
 // 2048 at 16 tokens 11.8 / 15.6).
 //
 // Hand-over.  Sums of A x: the region holds a sentinel (all ones) wherever nothing has been written; readers
-// re-read with device scope until no word is the sentinel.  Two regions alternate by a launch counter; each launch
-// refills what the one before it used of the other.  Outputs of a layer: besides the caller's slot they go, with
-// device scope, to a copy in the workspace, then the task's word is set to the launch's number; readers wait for
+// re-read with device scope until no word is the sentinel.  The two sets of regions are those of the whole-stack
+// launch (lists of up to 4 tokens), under its protocol: they alternate by one launch counter, and each launch refills
+// what the one before it used of the other.  Outputs of a layer: besides the caller's slot they go, with
+// device scope, to a copy in the workspace, then the task's word is set; readers wait for
 // the words of all tasks of the phase and then read the copy through their L2, as often as they like: its lines are
 // written once in a launch, each by one workgroup (a row-block's outputs are whole lines: the copies begin at a
 // multiple of 256 bytes wherever the workspace does), and nobody has read them before.
@@ -41,6 +42,7 @@ namespace {
 
 constexpr int kWaves = 16, kThreads = 64 * kWaves;
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
+constexpr unsigned kDone = 1;          // a task's word
 constexpr int kPolls = 1 << 18;        // bound of a wait for another workgroup (about a second)
 constexpr int kD = 8;                  // weight tiles in flight per wavefront
 constexpr size_t kLdsMax = 154 * 1024;   // (of 160 KiB; the words and the launch's description are static)
@@ -52,6 +54,7 @@ __host__ __device__ constexpr int unit_stride(int slots) { return slots * 16 + (
 
 struct Words {                         // LDS
     int ticket, epoch, failed;
+    unsigned act_used, mail_used;      // of the other set
     float amax[kWaves];
     int sum[kWaves];
     float s_x[32];
@@ -219,13 +222,27 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
             ((const __attribute__((address_space(4))) uint32_t *)__builtin_amdgcn_kernarg_segment_ptr())[e];
     if (threadIdx.x == 0) {
         sh.ticket = __hip_atomic_fetch_add(p.flags + 11, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sh.epoch = __hip_atomic_load(p.flags + 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh.epoch = __hip_atomic_load(p.flags + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh.act_used = (unsigned)__hip_atomic_load(p.flags + 6, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh.mail_used = (unsigned)__hip_atomic_load(p.flags + 7, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sh.failed = 0;
     }
     lds_barrier();
-    const unsigned epoch = (unsigned)uniform(sh.epoch), tag = epoch + 1u;
-    unsigned char *const mine = p.mail + (size_t)(epoch & 1u) * kBatchMailBytes;
-    const rsrc_t mail = make_rsrc(mine, (unsigned)kBatchMailBytes), act = make_rsrc(p.act, (unsigned)kBatchActBytes);
+    const unsigned epoch = (unsigned)uniform(sh.epoch);
+    unsigned char *const mine = p.xchg + (size_t)(epoch & 1u) * kStackSetBytes, *const words = mine + kStackActBytes;
+    const rsrc_t mail = make_rsrc(mine + kStackActBytes, (unsigned)kBatchMailBytes),
+                 act = make_rsrc(mine + p.act_shift, (unsigned)kBatchActBytes);
+    {   // this workgroup's share of what the launch before used of the other set
+        unsigned char *const other = p.xchg + (size_t)((epoch & 1u) ^ 1u) * kStackSetBytes;
+        const unsigned used[2] = {(unsigned)uniform((int)sh.act_used), (unsigned)uniform((int)sh.mail_used)};
+        const v4u s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const rsrc_t r = make_rsrc(other + i * kStackActBytes, used[i]);
+            for (unsigned v = blockIdx.x * kThreads + threadIdx.x; v < used[i] / 16u; v += gridDim.x * kThreads)
+                __builtin_amdgcn_raw_buffer_store_b128(s4, r, (int)(v * 16u), 0, 16);
+        }
+    }
     int ph = 0;
     bool failed = false;
 
@@ -245,16 +262,6 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
         const int KT = (K + kTileCols - 1) / kTileCols, Kp = KT * kTileCols;
         const int local = ticket - uniform(P.task0), jtasks = (jobs + 1) / 2;
 
-        // every task of the first phase refills its share of what the launch before used of the other region
-        if (ph == 0) {
-            const unsigned used = (unsigned)__hip_atomic_load(p.flags + 10, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const rsrc_t other = make_rsrc(p.mail + (size_t)((epoch & 1u) ^ 1u) * kBatchMailBytes, used);
-            const v4u s4 = {kSentinel, kSentinel, kSentinel, kSentinel};
-            const unsigned tasks0 = (unsigned)uniform(D.ph[1].task0);
-            for (unsigned v = (unsigned)local * kThreads + tx; v < used / 16u; v += tasks0 * kThreads)
-                __builtin_amdgcn_raw_buffer_store_b128(s4, other, (int)(v * 16u), 0, 16);
-        }
-
         Source src;
         if (src_phase < 0) {
             src.r = make_rsrc(uniform(P.x_ext), (unsigned)M * K * 2u);
@@ -272,16 +279,16 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
             if (src_phase < 0) return;
             if (w == 0) {
                 const int n = uniform(D.ph[src_phase].unit_tasks);
-                const rsrc_t words = make_rsrc(p.words + src_phase * kBatchWords, (unsigned)n * 4u);
+                const rsrc_t wd = make_rsrc(words + src_phase * kBatchPhaseWords, (unsigned)n * 4u);
                 int polls = 0;
 #pragma clang loop unroll(disable)
                 while (!failed) {
-                    const v4u a = load16_agent(words, (unsigned)l * 16u), b = n > 256 ? load16_agent(words, 1024u + (unsigned)l * 16u) : a;
+                    const v4u a = load16_agent(wd, (unsigned)l * 16u), b = n > 256 ? load16_agent(wd, 1024u + (unsigned)l * 16u) : a;
                     bool ready = true;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        ready = ready && (4 * l + e >= n || a[e] == tag);
-                        ready = ready && (256 + 4 * l + e >= n || b[e] == tag);
+                        ready = ready && (4 * l + e >= n || a[e] == kDone);
+                        ready = ready && (256 + 4 * l + e >= n || b[e] == kDone);
                     }
                     if (__builtin_amdgcn_ballot_w64(!ready) == 0) break;
                     if (++polls >= p.polls) failed = true;
@@ -514,7 +521,8 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
             // ---- the task's word, once all of its outputs are where every workgroup sees them
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             lds_barrier();
-            if (tx == 0) __hip_atomic_store(p.words + ph * kBatchWords + t, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tx == 0)
+                __hip_atomic_store(reinterpret_cast<unsigned *>(words + ph * kBatchPhaseWords) + t, kDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (tx == 0) sh.ticket = next;
         lds_barrier();
@@ -526,8 +534,10 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
         if (done == (int)gridDim.x - 1) {
             __hip_atomic_store(p.flags + 9, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(p.flags + 11, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(p.flags + 10, (int)p.mail_used, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(p.flags + 8, (int)(epoch + 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(p.flags + 6, (int)p.act_used, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(p.flags + 7, (int)p.mail_used, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(p.flags + 8, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(p.flags + 4, (int)(epoch + 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -581,7 +591,7 @@ bool plan_batch(BatchParams &p, size_t *lds_bytes)
     }
     const int Mp = p.M + (p.M & 1);
     p.polls = kPolls;
-    size_t act = 0, mail = 0;
+    size_t act = 0, mail = p.nphases * kBatchPhaseWords;
     int tasks = 0, rank_max = 0;
     for (int i = 0; i < p.ph[p.nphases - 1].first_layer + p.ph[p.nphases - 1].G; ++i) rank_max = p.L[i].rank > rank_max ? p.L[i].rank : rank_max;
     p.h_layer = (rank_max + 15) / 16 * 1024;
@@ -626,6 +636,7 @@ bool plan_batch(BatchParams &p, size_t *lds_bytes)
     }
     if (act > kBatchActBytes || mail > kBatchMailBytes) return false;
     p.tasks = tasks;
+    p.act_used = (unsigned)(p.act_shift + act);
     p.mail_used = (unsigned)mail;
     p.cus = cus;
     *lds_bytes = lds;

@@ -238,10 +238,7 @@ struct Workspace {
     int32_t *flags;      // zero region: [0] correction workgroups done, [1] decode workgroups done,
                          // [2] sticky: a bounded wait ran out
     unsigned char *mail; // two exchange buffers of kMailBytes, sentinel-filled between launches
-    unsigned char *xchg; // two sets of kStackSetBytes for the whole-stack launch, likewise
-    unsigned char *bmail; // two exchange regions of kBatchMailBytes for the task queue, likewise
-    int32_t *bwords;     // its tasks' words
-    unsigned char *bact; // its copies of outputs
+    unsigned char *xchg; // two sets of kStackSetBytes for the whole-stack launch and the task queue, likewise
     int8_t *xq;
     float *s_x;
     int32_t *rowsum;
@@ -428,17 +425,21 @@ constexpr int kBatchMinPhases = 5;
 constexpr int kBatchMaxLayers = 40, kBatchMaxPhases = 16;
 constexpr int kBatchSlices = 6;                        // slices of A x at most: d_in <= 12288
 constexpr int kBatchWords = 512;                       // unit tasks of a phase at most
-constexpr size_t kBatchActRegion = size_t(8) << 20;    // copies of the layers' outputs, from its first address ...
-constexpr size_t kBatchActAlign = 256;                 // ... that is a multiple of this: no line holds two row-blocks' outputs
-constexpr size_t kBatchActBytes = kBatchActRegion - kBatchActAlign;
-constexpr size_t kBatchMailBytes = size_t(2) << 20;    // sums of A x; the workspace holds two, sentinel-filled between launches
+// A launch takes the whole-stack launch's set whose turn it is: copies of the layers' outputs in the place of its
+// copies, from the first address that is a multiple of kBatchActAlign (no line holds two row-blocks' outputs); in the
+// place of its sums of A x the tasks' words, [phase][kBatchWords], and this launch's sums.
+constexpr size_t kBatchActAlign = 256;
+constexpr size_t kBatchActBytes = kStackActBytes - kBatchActAlign;
+constexpr size_t kBatchMailBytes = kStackSetBytes - kStackActBytes;
+constexpr size_t kBatchPhaseWords = size_t(kBatchWords) * 4;   // bytes
 struct BatchLayer {                                    // 64 bytes
     const v4u *packed;
     const float *s_w;
     const _Float16 *A, *B, *alpha;
     _Float16 *y;
     int N, rank;
-    unsigned act_off, mail_off;                        // bytes: its copy, its sums of A x ([slice][token][h_stride] fp32)
+    unsigned act_off, mail_off;                        // bytes: its copy; its sums of A x ([slice][token][h_stride] fp32) behind
+                                                       // the set's copies
 };
 struct BatchPhase {                                    // 80 bytes
     const _Float16 *x_ext;                             // the tokens, when they were written before the launch (src_phase < 0)
@@ -452,11 +453,12 @@ struct BatchPhase {                                    // 80 bytes
     int unit_tasks;
 };
 struct BatchParams {
-    int32_t *flags;               // [2] sticky error, [8] launch counter, [9] workgroups done, [10] extent used, [11] next task
-    unsigned char *mail, *act;
-    int32_t *words;               // [phase][kBatchWords]: the launch's number, once the task is done
-    int M, nphases, tasks, cus;   // (two phases at least)
-    unsigned mail_used;
+    int32_t *flags;               // [2] sticky error, [4], [6], [7] as in StackParams, [8] launches of this kind, [9] workgroups
+                                  // done, [11] next task
+    unsigned char *xchg;          // two sets of kStackSetBytes
+    unsigned act_shift;           // bytes from a set's begin to its copies
+    int M, nphases, tasks, cus;
+    unsigned act_used, mail_used;
     int polls;
     int h_layer;                  // LDS: bytes of SiLU(A x) per layer
     BatchPhase ph[kBatchMaxPhases];

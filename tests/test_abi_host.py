@@ -38,6 +38,8 @@ def test_sizes():
     b = hb.hgf_workspace_bytes(64, 11008, 11008, 128)
     c = hb.hgf_workspace_bytes(2048, 8192, 8192, 64)
     assert 0 < a < b < c
+    # the exchange sets of the layer lists (16 MiB) and, for one token of one column, next to nothing else
+    assert hb.hgf_workspace_bytes(1, 1, 1, 0) <= (16 << 20) + (1 << 19)
     assert hb.hgf_workspace_bytes(1, 512, 512, 129) == 0
     assert hb.hgf_workspace_bytes(0, 512, 512, 8) == 0
 
