@@ -315,8 +315,8 @@ hgf_status hgf_probe_mfma_rate(int operand_kind, int iters, double *tops_out, do
  * integers; the fp16 outputs may differ in the last place (different split of A x). */
 void hgf_set_single_launch(int level);
 
-/* Test hook (host state, not thread-safe) for the whole-stack launch of hgf_stack_forward, in
- * which workgroups wait for each other's results: every such wait gives up after a bounded
+/* Test hook (host state, not thread-safe) for the whole-stack launch of hgf_stack_forward and its queue of
+ * tasks, in which workgroups wait for each other's results: every such wait gives up after a bounded
  * number of tries (by default about a second), sets the sticky error word of the workspace
  * (byte offset 8, cleared by hgf_workspace_init), turns the affected outputs into NaN and lets
  * the kernel run to its end.  tries > 0 replaces the bound of every wait by that many tries, so

@@ -10,8 +10,9 @@
 //
 // A workgroup takes the next task from a counter, so tasks begin in order, and a task waits only for tasks
 // before it, which by then run or are done: the launch comes to its end however few of its workgroups the
-// device holds at a time, whatever else runs.  (Every wait is bounded all the same; on expiry the sticky word of
-// the workspace is set and outputs are NaN.)
+// device holds at a time, whatever else runs.  (Every wait is bounded all the same.  On expiry the sticky word of
+// the workspace is set, the workgroup's outputs from there on are NaN, its sums of A x too, and its tasks' words say
+// so: who reads them gives up as well, as a NaN among the tokens alone would be lost in the quantiser.)
 //
 // Bound by latency and instruction issue: a phase is a hop through memory (the last store to the next phase's
 // tokens, 2 us), the tokens' trip and quantiser (2.5; its 4.5 instructions per element are the same in every
@@ -42,8 +43,8 @@ namespace {
 
 constexpr int kWaves = 16, kThreads = 64 * kWaves;
 constexpr unsigned kSentinel = 0xFFFFFFFFu;
-constexpr unsigned kDone = 1;          // a task's word
-constexpr int kPolls = 1 << 18;        // bound of a wait for another workgroup (about a second)
+constexpr unsigned kDone = 1, kVoid = 2;   // a task's word: outputs are there; a wait has expired before them
+constexpr int kPolls = 1 << 18;        // bound of a wait for another workgroup (about a second; hgf_set_wait_limit)
 constexpr int kD = 8;                  // weight tiles in flight per wavefront
 constexpr size_t kLdsMax = 154 * 1024;   // (of 160 KiB; the words and the launch's description are static)
 
@@ -284,13 +285,13 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
 #pragma clang loop unroll(disable)
                 while (!failed) {
                     const v4u a = load16_agent(wd, (unsigned)l * 16u), b = n > 256 ? load16_agent(wd, 1024u + (unsigned)l * 16u) : a;
-                    bool ready = true;
+                    unsigned worst = 0u;                      // (past the last word lie zeros; the sentinel is the largest)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        ready = ready && (4 * l + e >= n || a[e] == kDone);
-                        ready = ready && (256 + 4 * l + e >= n || b[e] == kDone);
+                    for (int e = 0; e < 4; ++e) worst = max(worst, max(a[e], b[e]));
+                    if (__builtin_amdgcn_ballot_w64(worst > kVoid) == 0) {
+                        failed = __builtin_amdgcn_ballot_w64(worst == kVoid) != 0;
+                        break;
                     }
-                    if (__builtin_amdgcn_ballot_w64(!ready) == 0) break;
                     if (++polls >= p.polls) failed = true;
                     __builtin_amdgcn_s_sleep(1);
                 }
@@ -351,6 +352,7 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
                 v4f h = part[w * 64 + l];
 #pragma unroll
                 for (int s = 1; s < 8; ++s) h += part[(w + s) * 64 + l];
+                if (sh.failed != 0) h = (v4f){NAN, NAN, NAN, NAN};    // (not the sentinel)
                 // element v: rank 16 rt + 4 kb + v of token m
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, h), mail,
                                                        (int)(m < M ? L.mail_off + (unsigned)((sp * M + m) * hs + rt * 16 + 4 * kb) * 4u : kOob), 0, 16);
@@ -522,7 +524,7 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             lds_barrier();
             if (tx == 0)
-                __hip_atomic_store(reinterpret_cast<unsigned *>(words + ph * kBatchPhaseWords) + t, kDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(reinterpret_cast<unsigned *>(words + ph * kBatchPhaseWords) + t, failed ? kVoid : kDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         if (tx == 0) sh.ticket = next;
         lds_barrier();
@@ -590,7 +592,7 @@ bool plan_batch(BatchParams &p, size_t *lds_bytes)
         device = dev;
     }
     const int Mp = p.M + (p.M & 1);
-    p.polls = kPolls;
+    p.polls = stack_wait_limit() > 0 ? stack_wait_limit() : kPolls;
     size_t act = 0, mail = p.nphases * kBatchPhaseWords;
     int tasks = 0, rank_max = 0;
     for (int i = 0; i < p.ph[p.nphases - 1].first_layer + p.ph[p.nphases - 1].G; ++i) rank_max = p.L[i].rank > rank_max ? p.L[i].rank : rank_max;

@@ -174,3 +174,29 @@ def test_queue_in_a_workspace_between_two_lines(shift):
         assert _flags(ws)[8] == before[8] + 1
         for i, (a, b) in enumerate(zip(one, two)):
             assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), f"slot {i}"
+
+
+@pytest.mark.parametrize("M", [8, 16])
+def test_queue_gives_up_without_a_wrong_number(M):
+    """Every wait bounded by one try, set from the host: the launch ends, the sticky word is set, and an output is
+    what it should be or NaN, layers without ranks (whose quantiser passes over a NaN) among them."""
+    ws = hb.Workspace(M, 8184, 8184, 128)
+    shapes = CHAIN[:8] + [(8184, 2304, 0, 8, 9), (2304, 2080, 48, 9, 10)]
+    _, st, slots = _list(shapes, M, ws)
+    want = _run(st, slots, ws, 2)
+    assert _flags(ws)[2] == 0
+    try:
+        hb.hgf_set_wait_limit(1)
+        got = _run(st, slots, ws, 2)
+    finally:
+        hb.hgf_set_wait_limit(0)
+    after = _flags(ws)
+    assert after[2] != 0 and after[9] == 0 and after[11] == 0, after
+    for i, (a, b) in enumerate(zip(got, want)):
+        fine = ~np.isnan(a)
+        assert np.array_equal(a[fine].view(np.uint16), b[fine].view(np.uint16)), f"slot {i}"
+    assert np.isnan(got[-1]).all()
+    hb.hgf_workspace_init(ws)
+    for a, b in zip(_run(st, slots, ws, 2), want):
+        assert np.array_equal(a.view(np.uint16), b.view(np.uint16))
+    assert _flags(ws)[2] == 0
