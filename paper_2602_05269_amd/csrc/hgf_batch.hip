@@ -576,20 +576,10 @@ bool batch_fits(int M, int K, int G, int rank)
 // first_layer, G) and layers (pointers, N, rank) are set.  False: does not fit.
 bool plan_batch(BatchParams &p, size_t *lds_bytes)
 {
-    static int cus = 0, device = -1;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
         (void)hipGetLastError();
         return false;
-    }
-    if (cus == 0 || dev != device) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) {
-            (void)hipGetLastError();
-            return false;
-        }
-        cus = n;
-        device = dev;
     }
     const int Mp = p.M + (p.M & 1);
     p.polls = stack_wait_limit() > 0 ? stack_wait_limit() : kPolls;
@@ -648,8 +638,8 @@ bool plan_batch(BatchParams &p, size_t *lds_bytes)
 template <int SL>
 static hipError_t launch_slots(const BatchParams &p, size_t lds_bytes, hipStream_t st)
 {
-    static const hipError_t attr =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(&batch_kernel<SL>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
+    static OncePerDevice once;
+    const hipError_t attr = allow_lds(once, reinterpret_cast<const void *>(&batch_kernel<SL>), kLdsMax);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL((batch_kernel<SL>), dim3(p.tasks < p.cus ? p.tasks : p.cus), dim3(kThreads), lds_bytes, st, p);
     return hipGetLastError();

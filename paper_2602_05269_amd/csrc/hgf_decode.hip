@@ -346,8 +346,8 @@ hipError_t launch_shape(DecodeParams &p, hipStream_t st)
     for (int g = p.G; g <= kMaxGroup; ++g) p.wg_start[g] = units;
     const size_t red = (size_t)KW * WR * 4096, ops = (size_t)(WR + (PAIR ? 2 : 1)) * p.hsteps * 1024;
     const size_t lds = red > ops ? red : ops;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&direct_kernel<WR, KW, D, PAIR, B3, ONCE>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    static OncePerDevice once;
+    const hipError_t attr = allow_lds(once, reinterpret_cast<const void *>(&direct_kernel<WR, KW, D, PAIR, B3, ONCE>), 160 * 1024);
     if (attr != hipSuccess) return attr;
     const int TU = (p.M + 31) / 32;
     hipLaunchKernelGGL((direct_kernel<WR, KW, D, PAIR, B3, ONCE>), dim3((units + 7) / 8 * 8 * TU), dim3(64 * KW), lds, st, p);

@@ -7,6 +7,7 @@
 #include <stddef.h>
 
 #include "../../include/hgf.h"
+#include "hgf_once.h"
 
 namespace hgf {
 
@@ -486,6 +487,14 @@ hipError_t launch_short(const ShortParams &p, size_t lds_bytes, hipStream_t st);
 bool batch_fits(int M, int K, int G, int rank);        // one phase, in LDS
 bool plan_batch(BatchParams &p, size_t *lds_bytes);
 hipError_t launch_batch(const BatchParams &p, size_t lds_bytes, hipStream_t st);
+// Lets `kernel` be launched with up to `bytes` of dynamic LDS on the current device (the runtime keeps that per device).
+inline hipError_t allow_lds(OncePerDevice &once, const void *kernel, size_t bytes)
+{
+    int dev = -1;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    return (hipError_t)once(dev, [&] { return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); });
+}
 // What a plan or a launch of one of the persistent kernels came to.
 enum class Launch { kRan, kNoFit, kRefused };
 bool plan_fused(FusedParams &p, size_t *lds_bytes);

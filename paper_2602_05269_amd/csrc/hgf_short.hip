@@ -534,8 +534,8 @@ __global__ __launch_bounds__(kThreads) void short_kernel(ShortParams p)
 template <int KS, int NP, int UN, bool PAIR, bool LN, bool VEC>
 hipError_t launch_one(const ShortParams &p, size_t lds, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&short_kernel<KS, NP, UN, PAIR, LN, VEC>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kShortLdsMax);
+    static OncePerDevice once;
+    const hipError_t attr = allow_lds(once, reinterpret_cast<const void *>(&short_kernel<KS, NP, UN, PAIR, LN, VEC>), kShortLdsMax);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL((short_kernel<KS, NP, UN, PAIR, LN, VEC>), dim3(p.wg_start[p.G] * p.token_groups), dim3(kThreads), lds,
                        st, p);
