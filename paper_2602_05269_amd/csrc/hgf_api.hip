@@ -210,8 +210,12 @@ bool batchable(int M, const hgf_layer *layers, int G)
     if (M > kBatchTokens || g_launch_level < 1) return false;
     const int K = layers[0].d_in;
     int rank = 0;
-    for (int g = 0; g < G; ++g) rank = layers[g].rank > rank ? layers[g].rank : rank;
-    if (K % 8 != 0 || !batch_fits(M, K, G, rank)) return false;
+    long long row_blocks = 0;
+    for (int g = 0; g < G; ++g) {
+        rank = layers[g].rank > rank ? layers[g].rank : rank;
+        row_blocks += (layers[g].d_out + kTileRows - 1) / kTileRows;
+    }
+    if (K % 8 != 0 || !batch_fits(M, K, G, rank, row_blocks)) return false;
     for (int g = 0; g < G; ++g) {
         const hgf_layer &L = layers[g];
         if (L.ln_gamma) return false;

@@ -382,6 +382,7 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
                 sh.gate[gx] = gate;
                 if ((gx & 31) == 0) sh.s_w[i] = *L.s_w;
             }
+            const int red_off = uniform(P.red_off), h_off = uniform(P.h_off), h_layer = uniform(P.h_layer);
             tokens_ready();
             unsigned char *const xq = lds;
             const int np = (Kp * SL + kThreads * 8 - 1) / (kThreads * 8);
@@ -391,13 +392,12 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
             else quantise_tokens<SL, 8, 2>(src, tx, M, K, Kp, ustride, xq, sh);
             lds_barrier();
 
-            const int red_off = uniform(P.red_off), h_off = uniform(P.h_off);
             const int g0 = layer_of(u0), g1 = layer_of(u0 + n - 1);
             if (w >= CW) {
                 // ---- SiLU(A x) of the units' layers
 #pragma clang loop unroll(disable)
                 for (int gg = g0; gg <= g1; ++gg)
-                    if (!gather_layer(D.L[first + gg], tx - CW * 64, kThreads - CW * 64, mail, S, M, p.polls, failed, lds + h_off + (gg - g0) * p.h_layer)) {
+                    if (!gather_layer(D.L[first + gg], tx - CW * 64, kThreads - CW * 64, mail, S, M, p.polls, failed, lds + h_off + (gg - g0) * h_layer)) {
                         sh.failed = 1;
                         __hip_atomic_store(p.flags + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(kThreads) void batch_kernel(const BatchParams p)
                     s_x = sh.s_x[jl];
                     rs = SL == 8 ? sh.sum[2 * jl] + sh.sum[2 * jl + 1] : sh.rowsum[jl];
                 }
-                const unsigned char *const hl = lds + h_off + (fg - g0) * p.h_layer + l * 16;
+                const unsigned char *const hl = lds + h_off + (fg - g0) * h_layer + l * 16;
                 v16f corr = (v16f){};
 #pragma unroll
                 for (int js = 0; js < 8; ++js)
@@ -564,16 +564,17 @@ static size_t phase_lds(int M, int K, int layers, int h_layer, int *h_off, int *
     *h_off = (int)off;
     return off + h;
 }
-bool batch_fits(int M, int K, int G, int rank)
+bool batch_fits(int M, int K, int G, int rank, long long row_blocks)
 {
     int h, r;
-    return M <= kBatchTokens && prologue_slices(K) <= kBatchSlices &&
+    return M <= kBatchTokens && prologue_slices(K) <= kBatchSlices && row_blocks <= 4 * kBatchWords &&
            (size_t)round_up(K, kTileCols) * token_slots(M) <= size_t(16) * 8 * kThreads &&       // pieces of a thread
            phase_lds(M, K, G, (rank + 15) / 16 * 1024, &h, &r) <= kLdsMax;
 }
 
 // Fills in tasks, exchange offsets and LDS layout of a launch whose M, phases (x_ext or src_phase, K,
-// first_layer, G) and layers (pointers, N, rank) are set.  False: does not fit.
+// first_layer, G) and layers (pointers, N, rank) are set.  False: does not fit (not where every phase does by itself and
+// the exchange sets hold them all).
 bool plan_batch(BatchParams &p, size_t *lds_bytes)
 {
     int dev = 0, cus = 0;
@@ -584,16 +585,14 @@ bool plan_batch(BatchParams &p, size_t *lds_bytes)
     const int Mp = p.M + (p.M & 1);
     p.polls = stack_wait_limit() > 0 ? stack_wait_limit() : kPolls;
     size_t act = 0, mail = p.nphases * kBatchPhaseWords;
-    int tasks = 0, rank_max = 0;
-    for (int i = 0; i < p.ph[p.nphases - 1].first_layer + p.ph[p.nphases - 1].G; ++i) rank_max = p.L[i].rank > rank_max ? p.L[i].rank : rank_max;
-    p.h_layer = (rank_max + 15) / 16 * 1024;
+    int tasks = 0;
     size_t lds = 0;
     for (int i = 0; i < p.nphases; ++i) {
         BatchPhase &P = p.ph[i];
         const int S = prologue_slices(P.K);
         if (S > kBatchSlices) return false;
         P.S = (unsigned char)S;
-        int units = 0, jobs = 0;
+        int units = 0, jobs = 0, rank_max = 0;
         for (int g = 0; g < P.G; ++g) {
             BatchLayer &L = p.L[P.first_layer + g];
             const int rbs = (L.N + kTileRows - 1) / kTileRows;
@@ -601,6 +600,7 @@ bool plan_batch(BatchParams &p, size_t *lds_bytes)
             L.act_off = (unsigned)act;
             L.mail_off = (unsigned)mail;
             act += align256((size_t)rbs * Mp * 64);
+            rank_max = L.rank > rank_max ? L.rank : rank_max;
             if (L.rank > 0) {
                 jobs += (L.rank + 15) / 16 * S;
                 mail += (size_t)S * p.M * h_stride(L.rank) * 4;
@@ -623,7 +623,8 @@ bool plan_batch(BatchParams &p, size_t *lds_bytes)
         if (P.unit_tasks > kBatchWords) return false;
         P.task0 = tasks;
         tasks += jt + P.unit_tasks;
-        const size_t need = phase_lds(p.M, P.K, P.G < upt ? P.G : upt, p.h_layer, &P.h_off, &P.red_off);
+        P.h_layer = (rank_max + 15) / 16 * 1024;
+        const size_t need = phase_lds(p.M, P.K, P.G < upt ? P.G : upt, P.h_layer, &P.h_off, &P.red_off);
         if (need > lds) lds = need;
     }
     if (act > kBatchActBytes || mail > kBatchMailBytes) return false;

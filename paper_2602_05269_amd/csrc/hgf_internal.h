@@ -448,7 +448,7 @@ struct BatchPhase {                                    // 80 bytes
     int K, task0;                                      // its first task; job tasks come first
     int unit_end[3], job_end[3];                       // ends of its first layers' units and jobs (2^30 past the last)
     int units, jobs;                                   // row-blocks; tiles of A x
-    int h_off, red_off;                                // LDS: SiLU(A x); partial tiles (0: in the tokens' place)
+    int h_off, h_layer, red_off;                       // LDS: SiLU(A x), bytes of it per layer; partial tiles (0: in the tokens' place)
     unsigned char first_layer, G, upt, S;              // upt: units of a task at most
     short src_phase, src_layer;
     int unit_tasks;
@@ -461,7 +461,6 @@ struct BatchParams {
     int M, nphases, tasks, cus;
     unsigned act_used, mail_used;
     int polls;
-    int h_layer;                  // LDS: bytes of SiLU(A x) per layer
     BatchPhase ph[kBatchMaxPhases];
     BatchLayer L[kBatchMaxLayers];
 };
@@ -484,7 +483,7 @@ hipError_t launch_prologue(ProParams &p, hipStream_t st);
 hipError_t launch_decode(DecodeParams &p, int d_in, hipStream_t st);
 bool plan_short(ShortParams &p, size_t *lds_bytes);
 hipError_t launch_short(const ShortParams &p, size_t lds_bytes, hipStream_t st);
-bool batch_fits(int M, int K, int G, int rank);        // one phase, in LDS
+bool batch_fits(int M, int K, int G, int rank, long long row_blocks);   // one phase: its largest rank, all its rows
 bool plan_batch(BatchParams &p, size_t *lds_bytes);
 hipError_t launch_batch(const BatchParams &p, size_t lds_bytes, hipStream_t st);
 // Lets `kernel` be launched with up to `bytes` of dynamic LDS on the current device (the runtime keeps that per device).

@@ -200,3 +200,21 @@ def test_queue_gives_up_without_a_wrong_number(M):
     for a, b in zip(_run(st, slots, ws, 2), want):
         assert np.array_equal(a.view(np.uint16), b.view(np.uint16))
     assert _flags(ws)[2] == 0
+
+
+@pytest.mark.parametrize("M,shapes", [
+    # rows of 8192 columns at 16 tokens have room for two layers of 64 ranks, not of 128: each phase for itself
+    (16, [(2056, 8192, 64, 0, 1), (8192, 4200, 64, 1, 2), (8192, 4200, 64, 1, 3), (4200, 2056, 128, 2, 4), (2056, 2056, 40, 4, 5),
+          (2056, 2056, 40, 5, 6)]),
+    # a group of more rows than a phase has words for ends a run, it does not undo it
+    (5, [(2056, 2056, 48, i, i + 1) for i in range(5)] + [(2056, 40000, 8, 5, 6), (2056, 40000, 8, 5, 7)]),
+])
+def test_one_phase_does_not_cost_a_list_its_queue(M, shapes):
+    ws = hb.Workspace(M, 8192, 40000, 128)
+    _, st, slots = _list(shapes, M, ws)
+    two = _run(st, slots, ws, 0)
+    before = _flags(ws)
+    one = _run(st, slots, ws, 2)
+    assert _flags(ws)[8] == before[8] + 1
+    for i, (a, b) in enumerate(zip(one, two)):
+        assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), f"slot {i}"
