@@ -305,14 +305,15 @@ hgf_status hgf_profile_collect(double *ms_out, long long *launches_out);
  * HGF_ERR_SHAPE for a kind outside 0..2 or iters outside 1..2^20. */
 hgf_status hgf_probe_mfma_rate(int operand_kind, int iters, double *tops_out, double *ghz_out, void *stream);
 
-/* Tuning hook (host state, not thread-safe) for calls with at most 4 tokens, d_in % 8 == 0 and
- * d_in <= 12288.  level 2 (default): hgf_stack_forward runs whole runs of groups of layers as
- * one persistent launch (activations handed from layer to layer inside the launch), and
+/* Tuning hook (host state, not thread-safe) for calls that the direct path could take.  At most 4 tokens,
+ * d_in % 8 == 0 and d_in <= 12288: level 2 (default): hgf_stack_forward runs whole runs of groups of
+ * layers as one persistent launch (activations handed from layer to layer inside the launch), and
  * single groups as level 1; level 1: each group of layers is one persistent launch, a
  * base-3 layer of one token and 768 columns or of two and 1536, up to 2^27 weights, too;
- * level 0: the direct path's two launches, as for more tokens.  (At level 0 hgf_stack_forward has no queue of
- * tasks for more tokens either: two launches per group, the same bits.)  Results agree bit for bit in the
- * integers; the fp16 outputs may differ in the last place (different split of A x). */
+ * level 0: the direct path's two launches, as for more tokens.  Results agree bit for bit in the
+ * integers; the fp16 outputs may differ in the last place (different split of A x).
+ * Groups of short rows and the queue of tasks of hgf_stack_forward: one launch at levels 1 and 2, two launches
+ * per group at level 0, with the same bits. */
 void hgf_set_single_launch(int level);
 
 /* Test hook (host state, not thread-safe) for the whole-stack launch of hgf_stack_forward and its queue of

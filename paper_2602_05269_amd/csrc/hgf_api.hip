@@ -118,7 +118,7 @@ bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 
 // Profiling aid: event pairs recorded around main-kernel launches, by kind (0 decode, 1 prefill).
 bool g_profile = false;
-int g_launch_level = 2;      // 0: two launches per group, 1: one persistent launch per group, 2: per stack
+int g_launch_level = 2;      // 0: two launches per group, 1: one where a group has such a path, 2: one per stack
 std::vector<std::pair<hipEvent_t, hipEvent_t>> g_events[2];
 std::vector<hipEvent_t> g_event_pool;
 
@@ -299,7 +299,7 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
                           (layers[g].rank % 8 == 0 && aligned16(layers[g].A_f16) && aligned16(layers[g].B_f16) &&
                            (reinterpret_cast<uintptr_t>(layers[g].alpha_f16) & 3u) == 0));
     // Short rows: one launch, every workgroup prepares its tokens itself
-    if (free_tokens && !fused && !base3) {
+    if (free_tokens && !fused && !base3 && g_launch_level >= 1) {
         ShortParams sp;
         set_short(sp, x, M, layers, G, ys, acc_debug, pair, amax_out, acc_debug2);
         size_t lds_bytes = 0;

@@ -2,6 +2,8 @@
 (tokens per workgroup, wavefronts per row-block, pieces per thread), ragged tokens, rows, ranks and columns,
 with and without LayerNorm, single, grouped and as a SwiGLU pair.  Accumulators bit for bit, outputs within
 2e-3 + 1e-2 |y| (fp16 rounding of h and y)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -76,3 +78,87 @@ def test_short_rows_give_the_bits_of_two_launches(M, bad):
         two = slots[i + 2].cpu().numpy()
         assert np.array_equal(np.isnan(y), np.isnan(two))
         assert np.array_equal(y[~np.isnan(y)].view(np.uint16), two[~np.isnan(y)].view(np.uint16))
+
+
+class _KernelNode(ctypes.Structure):           # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def _launches(call):
+    """(threads, workgroups) of every kernel that `call` launches, from a capture of it."""
+    hip = ctypes.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    raw = ctypes.c_void_p(graph.raw_cuda_graph())
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        k = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0
+        out.append((k.block[0] * k.block[1] * k.block[2], k.grid[0] * k.grid[1] * k.grid[2]))
+    return out
+
+
+@pytest.mark.parametrize("bad", [None, np.inf, np.nan])
+@pytest.mark.parametrize("kind,M,K,N,r,tokens,ks", [
+    # tokens of a workgroup and wavefronts per row-block that the rule chooses; with the columns they give the pieces
+    # per thread (1, 2 or 4) and, beyond 512, two steps of A x
+    ("plain", 8, 512, 33, 16, 8, 8), ("plain", 7, 1024, 95, 32, 8, 8), ("plain", 9, 2048, 64, 16, 8, 8), ("plain", 48, 512, 1400, 24, 16, 8),
+    ("plain", 40, 256, 2000, 16, 16, 8), ("plain", 100, 512, 1333, 16, 16, 4), ("plain", 100, 256, 1333, 16, 16, 4),
+    ("plain", 64, 1000, 3200, 16, 16, 4), ("plain", 250, 512, 1060, 32, 32, 4), ("plain", 255, 512, 2100, 8, 32, 2),
+    ("plain", 255, 256, 2100, 8, 32, 2), ("plain", 255, 128, 2100, 8, 32, 2), ("plain", 500, 264, 2050, 16, 32, 1),
+    ("plain", 500, 256, 2050, 16, 32, 1), ("plain", 500, 72, 2050, 16, 32, 1),
+    ("plain", 13, 65, 100, 17, 8, 8), ("plain", 50, 511, 1300, 16, 16, 8), ("plain", 300, 333, 640, 3, 16, 4), ("plain", 300, 201, 640, 3, 16, 4),
+    ("plain", 300, 333, 1280, 3, 32, 4), ("plain", 300, 511, 2400, 3, 32, 2), ("plain", 300, 250, 2400, 3, 32, 2),
+    ("plain", 300, 100, 2400, 3, 32, 2), ("plain", 300, 131, 4000, 3, 32, 1), ("plain", 300, 99, 4000, 3, 32, 1),
+    ("ln", 40, 512, 1500, 16, 8, 8), ("ln", 120, 512, 1061, 16, 8, 4), ("ln", 100, 1024, 960, 16, 8, 4), ("ln", 24, 1024, 400, 16, 8, 8),
+    ("ln", 300, 512, 700, 16, 16, 4), ("ln", 300, 512, 1280, 16, 16, 2), ("ln", 500, 512, 1500, 16, 16, 1), ("ln", 300, 200, 1280, 16, 16, 2),
+    ("ln", 500, 128, 1500, 16, 16, 1), ("ln", 24, 255, 300, 16, 8, 8), ("ln", 120, 251, 1000, 5, 8, 4), ("ln", 300, 201, 1280, 16, 16, 2), ("ln", 500, 250, 1500, 5, 16, 1),
+    ("pair", 24, 512, 1365, 16, 8, 8), ("pair", 60, 504, 1400, 16, 16, 8), ("pair", 130, 256, 1100, 16, 16, 4), ("pair", 400, 128, 1000, 8, 32, 4),
+    ("pair", 400, 120, 1700, 8, 32, 2), ("pair", 40, 304, 20000, 8, 32, 1), ("pair", 33, 77, 320, 5, 8, 8), ("pair", 40, 511, 20000, 8, 32, 1),
+])
+def test_shape_and_bits_of_two_launches(kind, M, K, N, r, tokens, ks, bad):
+    """The rule's choice, seen in the captured launch, and the same bits as the two launches of level 0, also for tokens
+    that hold an infinity or what is not a number."""
+    ws = hb.Workspace(M, K, N, r)
+    cases = [synth.make_custom(6700 + i, M, K, N, r, act="student_t4", lora_std=0.05, w_std=0.05) for i in range(2 if kind == "pair" else 1)]
+    gs = [LnLayer(c, ws, seed=M + K) if kind == "ln" else GpuLayer(c, ws) for c in cases]
+    x = cases[0]["x"].copy()
+    if bad is not None:
+        x[M // 2, K // 3] = bad
+        x[0, K - 1] = -bad
+    xd = dev(x)
+    out = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    accs = [torch.empty((M, N), dtype=torch.int32, device="cuda") for _ in gs]
+
+    def call():
+        if kind == "pair":
+            hb.hgf_swiglu_forward(xd, gs[0].layer, gs[1].layer, ws, z=out, acc_debug_gate=accs[0], acc_debug_up=accs[1])
+        else:
+            hb.hgf_linear_forward(xd, gs[0].layer, ws, y=out, acc_debug=accs[0])
+
+    got = []
+    for level in (2, 0):
+        hb.hgf_set_single_launch(level)
+        try:
+            call()
+            got.append([out.cpu().numpy().copy()] + [a.cpu().numpy().copy() for a in accs])
+            if bad is None:
+                seen = _launches(call)
+                if level == 2:
+                    assert seen == [(512, -(-M // tokens) * -(-(-(-N // 32)) * ks // 8))], seen
+                else:
+                    assert len(seen) == 2, seen
+        finally:
+            hb.hgf_set_single_launch(2)
+    one, two = got
+    assert np.array_equal(np.isnan(one[0]), np.isnan(two[0]))
+    fine = ~np.isnan(one[0])
+    assert np.array_equal(one[0][fine].view(np.uint16), two[0][fine].view(np.uint16))
+    for a, b in zip(one[1:], two[1:]):
+        assert np.array_equal(a, b)
