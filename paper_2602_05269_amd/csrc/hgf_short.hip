@@ -531,34 +531,44 @@ __global__ __launch_bounds__(kThreads) void short_kernel(ShortParams p)
     }
 }
 
+// Which instantiations plan_short's shapes lead to.  Pieces: the columns of all token slots by 4096.  UN 2: rows beyond
+// 512 columns, which are aligned and, behind a LayerNorm, have eight slots and two pieces at most; eight wavefronts
+// per row-block have 16 slots at most.
+constexpr bool reached(int KS, int NP, int UN, bool ln, bool vec)
+{
+    if (UN == 2) return vec && (ln ? NP == 2 && KS >= 4 : (KS == 8 && NP >= 2) || (KS == 4 && NP == 4));
+    if (ln) return NP == 1 || (NP == 2 && vec && KS < 8);
+    return KS < 8 || NP < 4;
+}
+
 template <int KS, int NP, int UN, bool PAIR, bool LN, bool VEC>
 hipError_t launch_one(const ShortParams &p, size_t lds, hipStream_t st)
 {
-    static OncePerDevice once;
-    const hipError_t attr = allow_lds(once, reinterpret_cast<const void *>(&short_kernel<KS, NP, UN, PAIR, LN, VEC>), kShortLdsMax);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((short_kernel<KS, NP, UN, PAIR, LN, VEC>), dim3(p.wg_start[p.G] * p.token_groups), dim3(kThreads), lds,
-                       st, p);
-    return hipGetLastError();
+    if constexpr (reached(KS, NP, UN, LN, VEC)) {
+        static OncePerDevice once;
+        const hipError_t attr = allow_lds(once, reinterpret_cast<const void *>(&short_kernel<KS, NP, UN, PAIR, LN, VEC>), kShortLdsMax);
+        if (attr != hipSuccess) return attr;
+        hipLaunchKernelGGL((short_kernel<KS, NP, UN, PAIR, LN, VEC>), dim3(p.wg_start[p.G] * p.token_groups), dim3(kThreads), lds, st, p);
+        return hipGetLastError();
+    } else {
+        return hipErrorInvalidConfiguration;
+    }
 }
 
 template <int KS, int NP, int UN>
-hipError_t launch_kind(const ShortParams &p, bool vec, size_t lds, hipStream_t st)
+hipError_t launch_kind(const ShortParams &p, size_t lds, hipStream_t st)
 {
-    if (p.pair) return vec ? launch_one<KS, NP, UN, true, false, true>(p, lds, st) : launch_one<KS, NP, UN, true, false, false>(p, lds, st);
-    if (p.L[0].gamma) {
-        constexpr int NPL = NP > 2 ? 2 : NP;        // (plan_short takes no more behind a LayerNorm)
-        return vec ? launch_one<KS, NPL, UN, false, true, true>(p, lds, st) : launch_one<KS, NPL, UN, false, true, false>(p, lds, st);
-    }
-    return vec ? launch_one<KS, NP, UN, false, false, true>(p, lds, st) : launch_one<KS, NP, UN, false, false, false>(p, lds, st);
+    if (p.pair) return p.vec ? launch_one<KS, NP, UN, true, false, true>(p, lds, st) : launch_one<KS, NP, UN, true, false, false>(p, lds, st);
+    if (p.L[0].gamma) return p.vec ? launch_one<KS, NP, UN, false, true, true>(p, lds, st) : launch_one<KS, NP, UN, false, true, false>(p, lds, st);
+    return p.vec ? launch_one<KS, NP, UN, false, false, true>(p, lds, st) : launch_one<KS, NP, UN, false, false, false>(p, lds, st);
 }
 template <int KS, int UN>
-hipError_t launch_pieces(const ShortParams &p, bool vec, size_t lds, hipStream_t st)
+hipError_t launch_pieces(const ShortParams &p, size_t lds, hipStream_t st)
 {
     const int columns = p.Kp << p.plog;             // of all token slots: 4096 per piece
-    if (columns <= 4096) return launch_kind<KS, 1, UN>(p, vec, lds, st);
-    if (columns <= 8192) return launch_kind<KS, 2, UN>(p, vec, lds, st);
-    return launch_kind<KS, 4, UN>(p, vec, lds, st);
+    if (columns <= 4096) return launch_kind<KS, 1, UN>(p, lds, st);
+    if (columns <= 8192) return launch_kind<KS, 2, UN>(p, lds, st);
+    return launch_kind<KS, 4, UN>(p, lds, st);
 }
 
 }  // namespace
@@ -626,10 +636,10 @@ hipError_t launch_short(const ShortParams &p, size_t lds_bytes, hipStream_t st)
 {
     const bool one_step = p.K <= 512;               // 64 columns of A x for each of the eight wavefronts
     switch (p.KS) {
-        case 1: return launch_pieces<1, 1>(p, p.vec, lds_bytes, st);
-        case 2: return one_step ? launch_pieces<2, 1>(p, p.vec, lds_bytes, st) : launch_pieces<2, 2>(p, p.vec, lds_bytes, st);
-        case 4: return one_step ? launch_pieces<4, 1>(p, p.vec, lds_bytes, st) : launch_pieces<4, 2>(p, p.vec, lds_bytes, st);
-        default: return one_step ? launch_pieces<8, 1>(p, p.vec, lds_bytes, st) : launch_pieces<8, 2>(p, p.vec, lds_bytes, st);
+        case 1: return launch_pieces<1, 1>(p, lds_bytes, st);      // (four k-tiles and less)
+        case 2: return launch_pieces<2, 1>(p, lds_bytes, st);      // (its 32 slots, or 16 behind a LayerNorm, are full at 512)
+        case 4: return one_step ? launch_pieces<4, 1>(p, lds_bytes, st) : launch_pieces<4, 2>(p, lds_bytes, st);
+        default: return one_step ? launch_pieces<8, 1>(p, lds_bytes, st) : launch_pieces<8, 2>(p, lds_bytes, st);
     }
 }
 
