@@ -322,8 +322,8 @@ void hgf_set_single_launch(int level);
  * (byte offset 8, cleared by hgf_workspace_init), turns the affected outputs into NaN and lets
  * the kernel run to its end.  tries > 0 replaces the bound of every wait by that many tries, so
  * that a test can see the give-up path without anything having to go wrong; 0 restores the
- * default.  (In the persistent launch of a base-3 layer it is after how many reads of the exchange
- * a workgroup computes the sums it waits for itself: the outputs are the same.)  Never needed in production. */
+ * default.  (In the persistent launch of a base-3 layer it is after how many reads of the exchange,
+ * 128 at most, a workgroup computes the sums it waits for itself: the outputs are the same.)  Never needed in production. */
 void hgf_set_wait_limit(int tries);
 
 /* Measurement aid (host state, not thread-safe): time stamps from inside the whole-stack launch

@@ -659,7 +659,7 @@ bool plan_fused(FusedParams &p, size_t *lds_bytes)
         g_num_cus = n > 0 ? n : 1;
         g_device = dev;
     }
-    p.own_polls = stack_wait_limit() > 0 ? stack_wait_limit() : kOwnPolls;
+    p.own_polls = stack_wait_limit() > 0 && stack_wait_limit() < kOwnPolls ? stack_wait_limit() : kOwnPolls;
     const int M = p.M;
     const int cols = p.base3 ? 2 * kB3Cols : kTileCols;     // of a k-tile
     p.Kp = round_up(p.K, cols);
