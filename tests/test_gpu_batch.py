@@ -218,3 +218,19 @@ def test_one_phase_does_not_cost_a_list_its_queue(M, shapes):
     assert _flags(ws)[8] == before[8] + 1
     for i, (a, b) in enumerate(zip(one, two)):
         assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), f"slot {i}"
+
+
+def test_blocks_that_reuse_their_slots():
+    """Every block writes the same q, k, v, o, up, gate and down slots: no run is long enough for the queue, and every
+    output is that of level 0."""
+    M, d, f = 8, 2304, 2400
+    ws = hb.Workspace(M, f, f, 48)
+    block = [(d, d, 48, 0, 1), (d, d, 48, 0, 2), (d, d, 48, 0, 3), (d, d, 48, 1, 4), (d, f, 48, 4, 5), (d, f, 48, 4, 6), (f, d, 48, 5, 0)]
+    _, st, slots = _list(block * 3, M, ws)
+    x = slots[0].clone()
+    two = _run(st, slots, ws, 0)
+    for _ in range(2):
+        slots[0].copy_(x)
+        for i, (a, b) in enumerate(zip(_run(st, slots, ws, 2), two)):
+            assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), f"slot {i}"
+    assert _flags(ws)[8] == 0 and _flags(ws)[2] == 0
