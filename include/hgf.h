@@ -309,7 +309,8 @@ hgf_status hgf_probe_mfma_rate(int operand_kind, int iters, double *tops_out, do
  * d_in % 8 == 0 and d_in <= 12288: level 2 (default): hgf_stack_forward runs whole runs of groups of
  * layers as one persistent launch (activations handed from layer to layer inside the launch), and
  * single groups as level 1; level 1: each group of layers is one persistent launch, a
- * base-3 layer of one token and 768 columns or of two and 1536, up to 2^27 weights, too;
+ * base-3 layer of one token and 768 columns or of two and 1536 (beyond 2048 rows 1536 and 1600), up to 2^27
+ * weights, too;
  * level 0: the direct path's two launches, as for more tokens.  Results agree bit for bit in the
  * integers; the fp16 outputs may differ in the last place (different split of A x).
  * Groups of short rows and the queue of tasks of hgf_stack_forward: one launch at levels 1 and 2, two launches

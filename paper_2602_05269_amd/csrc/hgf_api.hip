@@ -287,13 +287,18 @@ hgf_status run_decode_group(const void *x, int M, const hgf_layer *layers, int G
     // the tokens takes two launches.
     bool free_tokens = true;
     for (int g = 0; g < G; ++g) free_tokens = free_tokens && (!ys[g] || apart(M, x, K, ys[g], layers[g].d_out));
-    // The persistent launch.  Base-3 weights take it for one token from 768 columns on and for two from 1536 (one token:
-    // 4096 -> 11008 rank 128 15.6 us in two launches, 12.4 in one; 11008 x 11008 23.1, 20.6; 2048 -> 8192 11.3, 10.7;
-    // 1024 -> 4096 8.5, 8.4; 256 -> 1024 7.1, 7.6; two: 11008 -> 4096 20.2, 16.2; 1536 -> 4096 9.8, 9.1; 1024 -> 4096
-    // 8.6, 9.3), up to 2^27 weights (4096 -> 32000 20.7, 19.5; 8192 -> 28672 28.5, 29.8).  For three and four the tokens' conversion, which every workgroup repeats, takes what the launch saves
+    // The persistent launch.  Base-3 weights take it for one token from 768 columns on and for two from 1536, of more
+    // than 2048 rows from 1536 and 1600 on (us in two launches and in one, weights from memory; one token: 4096 -> 11008
+    // rank 128 16.3, 12.8; 11008 x 11008 24.9, 21.2; 2048 -> 8192 11.8, 11.3; rank 16: 768 -> 32 8.0, 7.8; 768 -> 2048
+    // 8.7, 8.65; 768 -> 4096 8.5, 9.4; 1024 -> 8192 9.8, 11.1; 1536 -> 8192 10.9, 11.0; 256 -> 1024 7.6, 8.5; two tokens:
+    // 11008 -> 4096 20.0, 16.4; rank 16: 1536 -> 1024 9.7, 9.1; 1536 -> 8192 11.05, 11.8; 1792 -> 8192 11.2, 11.9; 3072 ->
+    // 8192 12.5, 12.1), up to 2^27 weights (8192 -> 28672 32.4, 29.2, but 28.5, 29.8 where layers are met again).
+    // For three and four the tokens' conversion, which every workgroup repeats, takes what the launch saves
     // (2048 -> 8192 11.6, 12.3; 4096 -> 11008 15.9, 15.3; 5504 -> 28672 23.7, 25.1).
+    const bool b3_in_one = base3 && M <= kMaxFusedB3M && K >= 768 * M && (layers[0].d_out <= 2048 || K >= (M == 1 ? 1536 : 1600)) &&
+                           (size_t)K * layers[0].d_out <= (size_t)1 << 27;
     bool fused = !pair && !ln && free_tokens && g_launch_level >= 1 && M <= kMaxFusedM && K % 8 == 0 && K <= kMaxFusedK &&
-                 aligned16(x) && (!base3 || (M <= kMaxFusedB3M && K >= 768 * M && (size_t)K * layers[0].d_out <= (size_t)1 << 27));
+                 aligned16(x) && (!base3 || b3_in_one);
     for (int g = 0; g < G; ++g)
         fused = fused && (layers[g].rank == 0 ||
                           (layers[g].rank % 8 == 0 && aligned16(layers[g].A_f16) && aligned16(layers[g].B_f16) &&

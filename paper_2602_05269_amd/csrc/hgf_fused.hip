@@ -545,16 +545,8 @@ __device__ __forceinline__ void service_wave(const FusedParams &p, unsigned char
             if (u >= us2) { gg = 2; ufirst = us2; LN = N2; Lrank = rk2; Lhstride = hs2; Ly = y2; Ldbg = d2; swb = swb2; }
             if (u >= us3) { gg = 3; ufirst = us3; LN = N3; Lrank = rk3; Lhstride = hs3; Ly = y3; Ldbg = d3; swb = swb3; }
             const int n0 = (u - ufirst) * kTileRows;
-            int polls = 0;
-            while (!failed && lds_load(&ctl->arrived[i]) < kStream) {
-                if (++polls >= kLdsPolls) {
-                    failed = true;
-                    if (l == 0) __hip_atomic_store(p.flags + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            // corr[m] of lane n: sum_j h[m][j] B[n0+n][j]  (tokens as matrix rows, as in the streaming side)
+            // corr[m] of lane n: sum_j h[m][j] B[n0+n][j]  (tokens as matrix rows, as in the streaming side); it and
+            // the gate do not wait for the unit's sums
             v16f corr = (v16f){};
             float gate = 0.f;
             if (Lrank > 0) {
@@ -567,6 +559,15 @@ __device__ __forceinline__ void service_wave(const FusedParams &p, unsigned char
                     case 4: corr = corr_unit<4>(hrow, brow, jl < p.M); break;
                     default: corr = corr_unit<8>(hrow, brow, jl < p.M); break;
                 }
+            }
+            int polls = 0;
+            while (!failed && lds_load(&ctl->arrived[i]) < kStream) {
+                if (++polls >= kLdsPolls) {
+                    failed = true;
+                    if (l == 0) __hip_atomic_store(p.flags + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
             }
             const int n = n0 + l;
             if (l < 32 && n < LN) {
@@ -687,7 +688,11 @@ bool plan_fused(FusedParams &p, size_t *lds_bytes)
         if (p.L[g].rank > 0) jobs += ((p.L[g].rank + 15) / 16) * p.S;
     }
     p.job_start[p.G] = jobs;
+    // One workgroup per unit or slice at least, and 64, as they share the refill of the other exchange buffer: two
+    // or three take 2 us for it (one token, 16 ranks: base-3 768 -> 32 10.4 and 7.8, two launches 8.0; 2048 -> 32 9.6 and
+    // 7.9; 2-bit 1536 -> 32 9.2 and 7.2)
     int nwg = units > jobs ? units : jobs;
+    if (nwg < 64) nwg = 64;
     if (nwg > g_num_cus) nwg = g_num_cus;      // one resident workgroup per compute unit
     p.nwg = nwg;
     const int per_wg = (units + nwg - 1) / nwg;

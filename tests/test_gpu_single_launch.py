@@ -27,6 +27,8 @@ def launches(ws):
     (1, 1120, 64, 24, True), (2, 4008, 65, 40, True), (1, 1048, 1, 0, True), (2, 2000, 257, 0, True),
     # two units of rows per workgroup
     (2, 1600, 8300, 16, True),
+    # more than 2048 rows
+    (1, 1528, 2049, 16, False), (1, 1528, 2048, 16, True), (1, 1536, 2049, 16, True), (2, 1592, 2049, 16, False), (2, 1536, 2048, 16, True),
 ])
 def test_base3_in_the_persistent_launch(M, K, N, r, one):
     c = synth.make_custom(9800 + M + K + N + r, M, K, N, max(r, 1), act="student_t3", lora_std=0.05)
@@ -66,7 +68,7 @@ def test_tokens_quantised_together(M, K, N, r, bad):
     assert_close_fp16(y[fine], y2[fine])
 
 
-@pytest.mark.parametrize("M,K,N,r", [(2, 11008, 64, 100), (1, 4096, 300, 128), (1, 1000, 9000, 24)])
+@pytest.mark.parametrize("M,K,N,r", [(2, 11008, 64, 100), (1, 4096, 300, 128), (1, 1000, 9000, 24), (1, 1600, 9000, 24)])
 def test_base3_workgroups_that_wait_help_themselves(M, K, N, r):
     c = synth.make_custom(9950 + M + K, M, K, N, r, act="student_t3", lora_std=0.05)
     ws = hb.Workspace(M, K, N, r)
