@@ -533,18 +533,18 @@ __global__ __launch_bounds__(kThreads) void short_kernel(ShortParams p)
 
 // Which instantiations plan_short's shapes lead to.  Pieces: the columns of all token slots by 4096.  UN 2: rows beyond
 // 512 columns, which are aligned and, behind a LayerNorm, have eight slots and two pieces at most; eight wavefronts
-// per row-block have 16 slots at most.
-constexpr bool reached(int KS, int NP, int UN, bool ln, bool vec)
+// per row-block have 16 slots at most, one wavefront stands behind a LayerNorm, pairs have two for 256 columns at most.
+constexpr bool reached(int KS, int NP, int UN, bool pair, bool ln, bool vec)
 {
     if (UN == 2) return vec && (ln ? NP == 2 && KS >= 4 : (KS == 8 && NP >= 2) || (KS == 4 && NP == 4));
     if (ln) return NP == 1 || (NP == 2 && vec && KS < 8);
-    return KS < 8 || NP < 4;
+    return KS == 8 ? NP < 4 : (KS == 4 || (KS == 2 && !(pair && NP == 4)));
 }
 
 template <int KS, int NP, int UN, bool PAIR, bool LN, bool VEC>
 hipError_t launch_one(const ShortParams &p, size_t lds, hipStream_t st)
 {
-    if constexpr (reached(KS, NP, UN, LN, VEC)) {
+    if constexpr (reached(KS, NP, UN, PAIR, LN, VEC)) {
         static OncePerDevice once;
         const hipError_t attr = allow_lds(once, reinterpret_cast<const void *>(&short_kernel<KS, NP, UN, PAIR, LN, VEC>), kShortLdsMax);
         if (attr != hipSuccess) return attr;
@@ -581,14 +581,13 @@ bool plan_short(ShortParams &p, size_t *lds_bytes)
     p.KT = p.Kp / kTileCols;
     const bool ln = p.L[0].gamma != nullptr;
     p.vec = p.K % 8 == 0 && (reinterpret_cast<uintptr_t>(p.x) & 15u) == 0;
-    int rt = 0, rbs = 0;                            // rank tiles of a workgroup; row-blocks
+    int rt = 0;                                     // rank tiles of a workgroup
     for (int g = 0; g < p.G; ++g) {
         ShortLayer &L = p.L[g];
         const int r = (L.rank + 15) / 16;
         rt = p.pair ? rt + r : (r > rt ? r : rt);
         L.b_aligned = L.rank % 8 == 0 && (reinterpret_cast<uintptr_t>(L.B) & 15u) == 0;
         p.vec = p.vec && (L.rank == 0 || (reinterpret_cast<uintptr_t>(L.A) & 15u) == 0);
-        rbs += p.pair && g == 1 ? 0 : L.RBn;
     }
     // Every workgroup reads all of A and takes two rank tiles at a time, so more ranks or columns are prepared
     // faster by workgroups of their own (us, two launches / one, 24 tokens, 512 rows: 2048 columns 16 ranks 10.2 / 9.1,
@@ -598,17 +597,31 @@ bool plan_short(ShortParams &p, size_t *lds_bytes)
     if (rt > 2 || (rt > 0 ? rt : 1) * p.K > 2048 || (!p.vec && p.K > (ln ? 256 : 512))) return false;
     // What a workgroup prepares and finishes is what it takes, so it has eight tokens of one row-block while that
     // needs no more than a workgroup per compute unit; then 16 tokens, then more row-blocks (512 -> 512, 32 ranks:
-    // the six shapes 6.2, 6.3, 6.7, 7.1, 8.0 and 9.4 us at one workgroup per compute unit; with 384 workgroups the first
+    // the shapes 6.2, 6.3, 6.7, 7.1 and 8.0 us at one workgroup per compute unit; with 384 workgroups the first
     // takes 8.6).  Behind a LayerNorm tokens are dear (6.7 with 8, 7.4 with 16, 10.2 with 32).
-    static const signed char plain[][2] = {{3, 8}, {4, 8}, {4, 4}, {5, 4}, {5, 2}, {5, 1}}, norm[][2] = {{3, 8}, {3, 4}, {4, 4}, {4, 2}, {4, 1}};
-    const int shapes = ln ? 5 : 6;
+    // Two launches are as fast or faster (us, they / one) where a workgroup would have eight row-blocks of 32 tokens
+    // (129 tokens, two 487 -> 3541 14.7 / 17.5; in the mean 1.01), for pairs of more than 256 columns with four (169 x
+    // 286 -> 3674 14.6 / 16.5), behind a LayerNorm of more than 256 columns with eight below 256 tokens (88 x 472 -> 7523
+    // 12.6 / 13.5, but three 500 x 512 -> 512 14.8 / 11.9), and where rows of B are read element by element for several
+    // row-blocks (17 ranks: 32 tokens, two 536 -> 2940 9.3 / 10.3; 128 x 448 -> 5285 behind a LayerNorm 12.9 / 14.6).
+    // (19 000 groups that the rule takes, of 5 to 3000 tokens, timed both ways: 0.80 in the mean, 1.09 at worst.)
+    static const signed char plain[][2] = {{3, 8}, {4, 8}, {4, 4}, {5, 4}, {5, 2}}, norm[][2] = {{3, 8}, {3, 4}, {4, 4}, {4, 2}, {4, 1}};
+    bool pieces = true;                             // rows of B of more than 16 ranks are whole aligned pieces
+    for (int g = 0; g < p.G; ++g) pieces = pieces && (p.L[g].rank <= 16 || p.L[g].b_aligned);
+    const bool several = p.K <= 256 || pieces;
+    auto row_units = [&]() {                        // workgroups per token group
+        int n = 0;
+        for (int g = 0; g < (p.pair ? 1 : p.G); ++g) n += (p.L[g].RBn * p.KS + 7) / 8;
+        return n;
+    };
     bool fits = false;
-    for (int i = 0; i < shapes && !fits; ++i) {
+    for (int i = 0; i < 5 && !fits; ++i) {
         p.plog = ln ? norm[i][0] : plain[i][0];
         p.KS = ln ? norm[i][1] : plain[i][1];
         p.token_groups = (p.M + (1 << p.plog) - 1) >> p.plog;
         fits = p.KT <= 4 * p.KS && (long long)p.Kp << p.plog <= (ln ? 8192 : 16384) &&
-               (long long)p.token_groups * ((rbs * p.KS + 7) / 8) <= 256;
+               (long long)p.token_groups * row_units() <= 256 && (p.KS == 8 || several) && !(p.pair && p.KS == 2 && p.Kp > 256) &&
+               !(ln && p.KS == 1 && p.Kp > 256 && p.M < 256);
     }
     if (!fits) return false;
     const int tt = p.plog > 4 ? 2 : 1, per = 8 / p.KS;
