@@ -267,8 +267,9 @@ hgf_status hgf_linear_forward_static(const void *x_f16, int M, const hgf_layer *
  *   layers  host array of n_layers descriptions
  *   slots   host array of n_slots device pointers
  *
- * For 5 <= M <= 16 runs of five groups or more (without LayerNorms, rows of whole 16-byte pieces, no slot written
- * twice or over one that is read) execute as one launch each, a queue of tasks; its workgroups wait for each other
+ * For 5 <= M <= 16 runs of five groups or more (without LayerNorms, rows and ranks of whole 16-byte pieces, none of
+ * them short rows, no slot written twice or over one that is read: a list whose blocks reuse their slots takes two
+ * launches per group) execute as one launch each, a queue of tasks; its workgroups wait for each other
  * but make progress however few of them the device holds at a time, so it needs nothing to itself.
  *
  * For M <= 4 runs of layers execute as persistent launches whose workgroups hand activations

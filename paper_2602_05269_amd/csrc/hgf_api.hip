@@ -86,7 +86,9 @@ bool many_tokens_for_long_rows(int K, int M) { return K > 4096 && K < 5 * (long 
 // 1385 x 5952 -> 728, 128 ranks 88 / 76, three 1409 x 4984 -> 72, 16 ranks 161 / 174, three 1741 x 7144 -> 32
 // 198 / 249; without ranks: 142 x 456 ->
 // 15616 behind a LayerNorm 14.1 / 10.9, 627 x 51 -> 2304 9.1 / 7.6, but 1258 x 56 -> 1152 behind one 10.6 / 11.4,
-// 193 x 146 -> 3744 8.2 / 9.1.)
+// 193 x 146 -> 3744 8.2 / 9.1.  All of these with the direct path's two launches: where short rows take one
+// (plan_short), the line lies too low for many tokens, 1536 x 512 -> 512 7.9 / 10.8, 4096 x 512 -> 256 8.0 / 14.4,
+// 8192 x 512 -> 64 7.0 / 21.0; below it the choice is right, three 768 x 512 -> 512 10.6 / 11.3.)
 bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 {
     if (M <= 40) return true;
@@ -835,7 +837,8 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
                         (L.rank == 0 || (L.rank % 8 == 0 && aligned16(L.A_f16) && aligned16(L.B_f16) &&
                                          (reinterpret_cast<uintptr_t>(L.alpha_f16) & 3u) == 0));
         }
-        // a phase of the task queue, unless its rows are short
+        // a phase of the task queue, unless its rows are short.  (Such lists would gain from it too, which is left: us, d = 512
+        // blocks of 16 ranks at 16 tokens, one launch a group / the queue: 8 groups 51.9 / 43.9, 32 groups 192.6 / 128.4.)
         bool batch = M > kMaxFusedM && batchable(M, layers + i, G);
         if (batch) {
             void *ys[kMaxGroup];
@@ -964,8 +967,9 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
             ++np;
         }
         ran = np;
-        // (a launch begins with some 8 us that no earlier phase hides: four phases of the 1.2B shape 51.8 us in two
-        // launches each, 55.0 so at 16 tokens, eight 107 and 88; of the 7B shape four 64.8 and 61.0 at 8 tokens)
+        // (a launch begins with some 8 us that no earlier phase hides: us, two launches each / so, four phases of the
+        // 1.2B shape at 16 tokens 47.2 / 55.0 where the weights are met again, 57.9 / 54.9 from memory, eight 102 / 86 and
+        // 116 / 86; of the 7B shape at 8 tokens four 64.6 / 61.1 and 72.2 / 62.3)
         if (np < kBatchMinPhases) return Launch::kNoFit;
         bp.nphases = np;
         size_t lds_bytes = 0;

@@ -14,13 +14,16 @@
 // the workspace is set, the workgroup's outputs from there on are NaN, its sums of A x too, and its tasks' words say
 // so: who reads them gives up as well, as a NaN among the tokens alone would be lost in the quantiser.)
 //
-// Bound by latency and instruction issue: a phase is a hop through memory (the last store to the next phase's
-// tokens, 2 us), the tokens' trip and quantiser (2.5; its 4.5 instructions per element are the same in every
-// workgroup, 5 to 7 for rows of 8192 and 11008 columns), contraction (0.5 to 1.5), and, beside these, A x and its
-// exchange (5), then the finish (1.5).  Weights, gates and rows of A are asked for before the tokens are there.
+// Bound by latency: wavefronts spend 65 % (7B shape, 8 tokens) to 75 % (1.2B shape, 16) of their time at waits and
+// barriers, 21 and 13 % ready and waiting to issue, 14 and 12 % issuing (shader counters).  A phase is a hop through
+// memory (the last store to the next phase's tokens, 2 us), the tokens' trip and quantiser (2.5; its 4.5 instructions
+// per element are the same in every workgroup, 5 to 7 for rows of 8192 and 11008 columns), contraction (0.5 to 1.5),
+// and, beside these, A x and its exchange (5), then the finish (1.5).  Weights, gates and rows of A are asked for
+// before the tokens are there.
 // Two launches per group were bound by the launches (2.7 us each in a chain) and the same trips.  us per pass,
-// before / now: twelve 1.2B-shape layers (48 groups) at 16 tokens 684 / 452, eight 7B-shape FFN blocks (16 groups) at
-// 8 tokens 287 / 218; one such layer alone 51.8 / 55.0: a launch begins with 8 us that nothing hides (kBatchMinPhases).
+// before / now: twelve 1.2B-shape layers (48 groups) at 16 tokens 694 / 453, eight 7B-shape FFN blocks (16 groups) at
+// 8 tokens 288 / 221; one such layer alone, its weights in cache, 47.2 / 55.0: a launch begins with
+// 8 us that nothing hides (kBatchMinPhases).
 // Beyond 16 tokens rows of 8192 columns do not fit LDS, and quantising them in every workgroup costs more than the
 // launch (24 tokens, 2048 columns and up: 318 / 355), so there it stays two launches; so does a single group (2048 ->
 // 2048 at 16 tokens 11.8 / 15.6).

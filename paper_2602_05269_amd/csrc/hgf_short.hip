@@ -10,8 +10,9 @@
 // wavefront in between, some 2 ns each.  So a workgroup has as few tokens and row-blocks as leave one workgroup
 // per compute unit (plan_short), the tokens and A x are requested before everything else, and what does not
 // depend on them (gates) is computed while others wait.  us per call, two launches of the direct path before /
-// this one: 256 -> 256 at 8 tokens 6.7 / 5.4; three 512 -> 512 at 24 tokens 7.8 / 5.8, behind LayerNorms 8.9 / 7.2,
-// at 500 tokens 14.4 / 11.3; pair 512 -> 1365 at 24 tokens 9.8 / 7.5; 512 -> 64 at 2048 tokens 12.1 / 6.8.
+// this one (in a chain of the same call): 256 -> 256 at 8 tokens 6.5 / 5.1; three 512 -> 512 at 24 tokens 7.7 / 5.6,
+// behind LayerNorms 8.7 / 6.7, at 500 tokens 13.0 / 10.2; pair 512 -> 1365 at 24 tokens 9.6 / 7.6; 512 -> 64 at 2048
+// tokens 10.9 / 5.8.
 //
 // A x is added up in the order of the direct path's prologue (eight wavefronts, 64 columns each in turn), the
 // rest in that of its main kernel: both give the same bits, so a layer's result does not depend on what else is
