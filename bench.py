@@ -505,7 +505,7 @@ def main() -> int:
             try:
                 res["config4_up_M1_2bit_same_path_cold"] = hbm(b2, timed(lambda: [hb.hgf_linear_forward(x, l, ws, y=y) for l in l2]))
             finally:
-                hb.hgf_set_single_launch(2)
+                hb.hgf_set_single_launch(3)
             res["config4_up_M1_base3_cold"] = hbm(b3, timed(lambda: [hb.hgf_linear_forward_b3(x, l, ws, y=y) for l in l3]))
             return res
         cases.update(b3_cases())

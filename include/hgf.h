@@ -269,7 +269,8 @@ hgf_status hgf_linear_forward_static(const void *x_f16, int M, const hgf_layer *
  *
  * For 5 <= M <= 16 runs of five groups or more (without LayerNorms, rows and ranks of whole 16-byte pieces, none of
  * them short rows, no slot written twice or over one that is read: a list whose blocks reuse their slots takes two
- * launches per group) execute as one launch each, a queue of tasks; its workgroups wait for each other
+ * launches per group; two groups or more beside the longest chain of groups that read each other, or 256 MiB of
+ * weights in the list) execute as one launch each, a queue of tasks; its workgroups wait for each other
  * but make progress however few of them the device holds at a time, so it needs nothing to itself.
  *
  * For M <= 4 runs of layers execute as persistent launches whose workgroups hand activations
@@ -307,15 +308,16 @@ hgf_status hgf_profile_collect(double *ms_out, long long *launches_out);
 hgf_status hgf_probe_mfma_rate(int operand_kind, int iters, double *tops_out, double *ghz_out, void *stream);
 
 /* Tuning hook (host state, not thread-safe) for calls that the direct path could take.  At most 4 tokens,
- * d_in % 8 == 0 and d_in <= 12288: level 2 (default): hgf_stack_forward runs whole runs of groups of
+ * d_in % 8 == 0 and d_in <= 12288: levels 2 and 3 (default): hgf_stack_forward runs whole runs of groups of
  * layers as one persistent launch (activations handed from layer to layer inside the launch), and
  * single groups as level 1; level 1: each group of layers is one persistent launch, a
  * base-3 layer of one token and 768 columns or of two and 1536 (beyond 2048 rows 1536 and 1600), up to 2^27
  * weights, too;
  * level 0: the direct path's two launches, as for more tokens.  Results agree bit for bit in the
  * integers; the fp16 outputs may differ in the last place (different split of A x).
- * Groups of short rows and the queue of tasks of hgf_stack_forward: one launch at levels 1 and 2, two launches
- * per group at level 0, with the same bits. */
+ * Groups of short rows and the queue of tasks of hgf_stack_forward: one launch from level 1 on, two launches
+ * per group at level 0, with the same bits.  Level 3 leaves a chain of groups to two launches each where that is
+ * faster (see hgf_stack_forward), levels 1 and 2 take the queue for every run that fits it. */
 void hgf_set_single_launch(int level);
 
 /* Test hook (host state, not thread-safe) for the whole-stack launch of hgf_stack_forward and its queue of

@@ -159,7 +159,8 @@ def hgf_workspace_init(ws: Workspace, stream=None) -> None:
 
 
 def hgf_set_single_launch(level) -> None:
-    """0: two launches per group; 1 (or True): one persistent launch per group; 2: per stack."""
+    """0: two launches per group; 1 (or True): one persistent launch per group; 2: per stack; 3 (default): as 2, but
+    chains of groups for 5 to 16 tokens take two launches each where that is faster."""
     lib().hgf_set_single_launch(int(level))
 
 

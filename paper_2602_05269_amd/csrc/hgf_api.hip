@@ -2,6 +2,7 @@
 // Every check happens before the first HIP call, so the error paths run without a GPU.
 #include "hgf_internal.h"
 
+#include <algorithm>
 #include <utility>
 #include <vector>
 
@@ -120,7 +121,7 @@ bool takes_direct_path(int M, const hgf_layer *layers, int G, bool pair)
 
 // Profiling aid: event pairs recorded around main-kernel launches, by kind (0 decode, 1 prefill).
 bool g_profile = false;
-int g_launch_level = 2;      // 0: two launches per group, 1: one where a group has such a path, 2: one per stack
+int g_launch_level = 3;      // 0: two launches per group, 1: one where a group has such a path, 2: one per stack, 3: the faster
 std::vector<std::pair<hipEvent_t, hipEvent_t>> g_events[2];
 std::vector<hipEvent_t> g_event_pool;
 
@@ -914,14 +915,27 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
         return launch_stack(sp, lds_bytes, st) == hipSuccess ? Launch::kRan : Launch::kRefused;
     };
 
+    // The list's weights are more than the last-level cache holds (those that several layers share counted once).
+    auto from_memory = [&]() {
+        std::vector<std::pair<const void *, size_t>> w;
+        for (int i = 0; i < n_layers; ++i) w.emplace_back(layers[i].W_packed, (size_t)layers[i].d_in * layers[i].d_out / 4);
+        std::sort(w.begin(), w.end());
+        size_t bytes = 0;
+        for (size_t i = 0; i < w.size(); ++i)
+            if (i == 0 || w[i].first != w[i - 1].first) bytes += w[i].second;
+        return bytes >= kLastLevelCache;
+    };
+
     // Runs groups [a, b') as one launch of the task queue, b' <= b as far as they fit: every slot that is written
     // in it shares no memory with another that is written or with one that is read as it was before the launch.
+    // Without a launch: `ran` groups are not worth another attempt.
     auto run_batch = [&](size_t a, size_t b, size_t &ran) -> Launch {
         BatchParams bp;
         set_batch_workspace(bp, ws);
         bp.M = M;
         struct Range { const void *p; int d; bool written; } ranges[2 * kBatchMaxLayers];
         int nr = 0, nl = 0, np = 0;
+        int depth[kBatchMaxPhases], deepest = 0, fresh = 0;     // phases that wait for each other; the first later one that does not
         size_t act = 0, mail = 0;
         const int Mp = M + (M & 1);
         for (size_t gi = a; gi < b && np < kBatchMaxPhases; ++gi) {
@@ -964,24 +978,37 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
             act = act1;
             mail = mail1;
             nl += gr.G;
+            depth[np] = P.src_phase < 0 ? 1 : depth[P.src_phase] + 1;
+            deepest = depth[np] > deepest ? depth[np] : deepest;
+            if (P.src_phase < 0 && fresh == 0) fresh = np;
             ++np;
         }
-        ran = np;
         // (a launch begins with some 8 us that no earlier phase hides: us, two launches each / so, four phases of the
         // 1.2B shape at 16 tokens 47.2 / 55.0 where the weights are met again, 57.9 / 54.9 from memory, eight 102 / 86 and
         // 116 / 86; of the 7B shape at 8 tokens four 64.6 / 61.1 and 72.2 / 62.3)
+        ran = 1;
         if (np < kBatchMinPhases) return Launch::kNoFit;
+        // A run that is one chain has nothing to do while a phase waits: its two launches per group, whose tokens are
+        // quantised once, are faster unless the weights come from memory, which the queue asks for ahead.  (us in the queue /
+        // in two launches each, 196 lists of 6 to 16 phases repeated / behind flushed caches, in the mean: one chain 1.07
+        // (1.33 at most) / 0.87, two phases beside the chain 0.92 / 0.74, four 0.78 / 0.66, eight 0.66 / 0.56; a chain of 64
+        // phases of the 7B shape, 1.4 GB, at 8 tokens 0.79.)
+        if (g_launch_level >= 3 && np - deepest < 2 && !from_memory()) {
+            ran = fresh > 0 ? fresh : np;
+            return Launch::kNoFit;
+        }
         bp.nphases = np;
         size_t lds_bytes = 0;
         if (!plan_batch(bp, &lds_bytes)) return Launch::kNoFit;
+        ran = np;
         ProfileScope prof(0, st);
         return launch_batch(bp, lds_bytes, st) == hipSuccess ? Launch::kRan : Launch::kRefused;
     };
 
-    size_t gi = 0;
+    size_t gi = 0, queue_from = 0;
     while (gi < groups.size()) {
-        if (groups[gi].batch) {
-            size_t ge = gi, ran = 0;
+        if (groups[gi].batch && gi >= queue_from) {
+            size_t ge = gi, ran = 1;
             while (ge < groups.size() && groups[ge].batch) ++ge;
             const Launch r = ge - gi >= (size_t)kBatchMinPhases ? run_batch(gi, ge, ran) : Launch::kNoFit;
             if (r == Launch::kRefused) return HGF_ERR_DEVICE;
@@ -989,6 +1016,7 @@ hgf_status hgf_stack_forward(const hgf_layer *layers, int n_layers, void *const 
                 gi += ran;
                 continue;
             }
+            queue_from = gi + ran;
         }
         // the longest run of stackable groups that fits one launch's description
         size_t ge = gi;
@@ -1044,7 +1072,7 @@ hgf_status hgf_profile_collect(double *ms_out, long long *launches_out)
     return HGF_OK;
 }
 
-void hgf_set_single_launch(int level) { g_launch_level = level < 0 ? 0 : (level > 2 ? 2 : level); }
+void hgf_set_single_launch(int level) { g_launch_level = level < 0 ? 0 : (level > 3 ? 3 : level); }
 
 void hgf_set_wait_limit(int tries) { set_stack_wait_limit(tries); }
 

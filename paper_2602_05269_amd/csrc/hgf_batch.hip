@@ -23,7 +23,8 @@
 // Two launches per group were bound by the launches (2.7 us each in a chain) and the same trips.  us per pass,
 // before / now: twelve 1.2B-shape layers (48 groups) at 16 tokens 694 / 453, eight 7B-shape FFN blocks (16 groups) at
 // 8 tokens 288 / 221; one such layer alone, its weights in cache, 47.2 / 55.0: a launch begins with
-// 8 us that nothing hides (kBatchMinPhases).
+// 8 us that nothing hides (kBatchMinPhases).  The gain is the weights' trip from memory and phases that do not wait for
+// each other; a chain of groups whose weights caches hold is left to two launches each (hgf_stack_forward).
 // Beyond 16 tokens rows of 8192 columns do not fit LDS, and quantising them in every workgroup costs more than the
 // launch (24 tokens, 2048 columns and up: 318 / 355), so there it stays two launches; so does a single group (2048 ->
 // 2048 at 16 tokens 11.8 / 15.6).

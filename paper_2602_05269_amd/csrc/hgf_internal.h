@@ -423,6 +423,7 @@ static_assert(sizeof(StackParams) <= 4096, "kernel arguments");
 // A list of phases for 5 to 16 tokens as a queue of tasks, see hgf_batch.hip.
 constexpr int kBatchTokens = 16;
 constexpr int kBatchMinPhases = 5;
+constexpr size_t kLastLevelCache = size_t(256) << 20;  // the Infinity Cache: a list of more weights finds none of them there
 constexpr int kBatchMaxLayers = 40, kBatchMaxPhases = 16;
 constexpr int kBatchSlices = 6;                        // slices of A x at most: d_in <= 12288
 constexpr int kBatchWords = 512;                       // unit tasks of a phase at most

@@ -234,3 +234,50 @@ def test_blocks_that_reuse_their_slots():
         for i, (a, b) in enumerate(zip(_run(st, slots, ws, 2), two)):
             assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), f"slot {i}"
     assert _flags(ws)[8] == 0 and _flags(ws)[2] == 0
+
+
+def _chain(n, d, r, slot=0, first=1):
+    """n groups, each of which reads the one before, from `slot` on; outputs in slots from `first` on."""
+    return [(d, d, r, slot if i == 0 else first + i - 1, first + i) for i in range(n)]
+
+
+@pytest.mark.parametrize("shapes,queues", [
+    (_chain(6, 2304, 48), 0),
+    (_chain(5, 2304, 48) + [(2304, 2304, 48, 1, 6)], 0),
+    (_chain(5, 2304, 48) + [(2304, 2304, 48, 1, 6), (2304, 2304, 48, 2, 7)], 1),
+    (_chain(5, 2304, 48) + _chain(2, 2304, 48, 0, 6), 1),
+    (_chain(17, 2304, 48), 0),
+    (_chain(16, 2304, 48) + [(2304, 2304, 48, 0, 17), (2304, 2304, 48, 1, 18), (2304, 2304, 48, 2, 19), (2304, 2304, 48, 3, 20),
+                             (2304, 2304, 48, 4, 21)], 1),
+])
+def test_chains_take_two_launches_per_group(shapes, queues):
+    """A run that is one chain of groups is left to two launches each, with the bits of the queue; one with two groups
+    beside the chain is not, also where it begins behind a longer chain."""
+    M = 8
+    ws = hb.Workspace(M, 2304, 2304, 48)
+    _, st, slots = _list(shapes, M, ws)
+    queue = _run(st, slots, ws, 2)
+    before = _flags(ws)
+    got = _run(st, slots, ws, 3)
+    assert _flags(ws)[8] == before[8] + queues
+    for i, (a, b) in enumerate(zip(got, queue)):       # (a long chain may grow past the largest fp16)
+        assert np.array_equal(a, b, equal_nan=True), f"slot {i}"
+
+
+def test_a_chain_of_more_weights_than_caches_hold_takes_the_queue():
+    """256 MiB of distinct weights; the same chain over one layer's weights takes two launches per group."""
+    M, d, n = 5, 8192, 16
+    ws = hb.Workspace(M, d, d, 0)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    packed = [hb.hgf_quantize_pack_weights(torch.randn((d, d), generator=gen, device="cuda") * 0.02, ws) for _ in range(n)]
+    x = torch.randn((M, d), generator=gen, device="cuda").half()
+    for same in (False, True):
+        slots = [x] + [torch.empty((M, d), dtype=torch.float16, device="cuda") for _ in range(n)]
+        layers = [hb.Layer(*packed[0 if same else i], d, d, src_slot=i, dst_slot=i + 1) for i in range(n)]
+        st = hb.Stack(layers, slots, M)
+        want = _run(st, slots, ws, 0)
+        before = _flags(ws)
+        got = _run(st, slots, ws, 3)
+        assert _flags(ws)[8] == before[8] + (0 if same else 1)
+        for i, (a, b) in enumerate(zip(got, want)):
+            assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), f"slot {i}"
